@@ -364,7 +364,8 @@ def problem_run(mesh, opts, steps, warmup, objective="compliance", with_grad=Tru
             "rel_residual": float(np.max(rec["resid"])),
             "status": "converged" if all(v == sso.SSO_OK for v in rec["status"]) else
                       "stopped above rtol",
-            "solver": "fused single-reduction" if st["solver"] == sso.SOLVER_FUSED else
+            "solver": "direct" if st["solver"] == sso.SOLVER_AUTO else
+                      "fused single-reduction" if st["solver"] == sso.SOLVER_FUSED else
                       "standard",
             "n_blocks": n_blocks, "n_nodes": mesh.n_nodes,
             "iteration": {"kernels": "k_cg1_iter1" if st["solver"] == sso.SOLVER_FUSED else
@@ -450,16 +451,17 @@ def _public(run):
 
 
 def large_leg(args):
-    """The 300 x 300 shell at rtol 1e-10: FP64 (whose iteration gives the roofline; AUTO's choice
-    at this size and tolerance) and mixed precision with AUTO's inner cap of 30 iterations, with
-    the mixed result's error against the FP64 one."""
+    """The 300 x 300 shell at rtol 1e-10: FP64 (AUTO's choice at this size and tolerance), the
+    standard PCG recurrences beside it (whose iteration gives the roofline) and mixed precision
+    with AUTO's inner cap of 30 iterations, with the mixed result's error against the FP64 one."""
     import paper_2407_20026_amd as sso
     mesh = meshgen.shell_300()
     out = {}
     runs = {}
-    for prec in ("fp64", "mixed"):
+    for prec in ("fp64", "fp64_pcg", "mixed"):
         opts = sso.Options(rtol=1e-10, max_it=400000, profile_every=args.profile_every,
                            precision=sso.PREC_MIXED if prec == "mixed" else sso.PREC_FP64,
+                           solver=sso.SOLVER_STANDARD if prec == "fp64_pcg" else sso.SOLVER_AUTO,
                            refine_steps=20000, inner_max_it=30 if prec == "mixed" else 0)
         runs[prec] = problem_run(mesh, opts, steps=2, warmup=1)
         log(f"300x300 shell {prec}: {runs[prec]['ms_per_step']:.1f} ms per forward + adjoint, "
@@ -479,7 +481,7 @@ def large_leg(args):
                             "precision for rtol 1e-9 or tighter)"
     if out["mixed"].get("outer_steps", 0) == 0:
         raise RuntimeError("mixed precision ran no outer steps on the 300 x 300 shell")
-    return out, runs["fp64"]
+    return out, runs["fp64_pcg"]
 
 
 def out_of_cache_leg(args):
@@ -490,7 +492,8 @@ def out_of_cache_leg(args):
     iterations), the solve stopping at that limit."""
     import paper_2407_20026_amd as sso
     mesh = meshgen.shell(500, seed=5)
-    opts = sso.Options(precision=sso.PREC_FP64, rtol=1e-10, max_it=3000, profile_every=16)
+    opts = sso.Options(precision=sso.PREC_FP64, rtol=1e-10, max_it=3000, profile_every=16,
+                       solver=sso.SOLVER_STANDARD)
     with sso.Problem(mesh, opts) as prob:
         for _ in range(2):   # the first solve pays the pattern, the second is the one kept
             prob.solve(check=False)
@@ -512,13 +515,17 @@ def shell60_leg(args):
     run = problem_run(mesh, opts, steps=20, warmup=3)
     log(f"60x60 shell: {run['ms_per_step']:.2f} ms per forward + adjoint")
     out = _public(run)
+    # the single-reduction iteration, for its roofline
+    opts.solver = sso.SOLVER_FUSED
+    run = problem_run(mesh, opts, steps=5, warmup=2)
+    out["fused_pcg"] = _public(run)
     out["workload"] = "60x60 continuous shell, 22,326 DOF, FP64, compliance, rtol 1e-8, seed 1"
     return out, run
 
 
 def general_leg(args):
     """The 60 x 60 shell with a linear objective g = u_z at the centre node: its adjoint is a
-    second PCG solve (K lambda = a), unlike compliance where lambda = u."""
+    second solve (K lambda = a), unlike compliance where lambda = u."""
     import paper_2407_20026_amd as sso
     run = problem_run(meshgen.shell_60(), sso.Options(rtol=1e-8, max_it=400000), steps=5,
                       warmup=1, objective="linear")

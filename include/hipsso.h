@@ -87,7 +87,14 @@ enum { SSO_PREC_FP64 = 0, SSO_PREC_MIXED = 1, SSO_PREC_AUTO = 2 };
 /* PCG recurrences.  STANDARD: Hestenes-Stiefel CG, two kernels and two reductions per
  * iteration.  FUSED: the single-reduction form of Chronopoulos & Gear (one kernel and one
  * reduction per iteration; keeps B = K M, M the block-Jacobi inverse, beside K: one more array
- * of K's size).  AUTO: sso_solve takes WG for FP64 problems resident in one workgroup's LDS
+ * of K's size).  AUTO: sso_solve in FP64 solves
+ * directly (multifrontal elimination in a nested dissection order, refined on the true residual
+ * until rtol is met; no PCG iterations) where the solver's arrays stay within what a surface
+ * structure fills, some 2 KB per node and doubling of the node count.  Measured against the
+ * recurrences named below, one design step: 11 x 11 grid-shell 0.55 against 3.3 ms, 60 x 60 shell
+ * 1.9 against 16 ms, 300 x 300 shell 20 against 510 ms.  A structure that fills more, a K that is
+ * not positive definite to working precision, or a target below what refinement reaches runs PCG:
+ * sso_solve takes WG for FP64 problems resident in one workgroup's LDS
  * (at most 144 nodes; measured 3.07 against 4.39 ms on the 121-node grid-shell), FUSED up to
  * 8,192 nodes (latency-bound sizes; 13.4 against 20.2 ms on a 60 x 60 shell, equal on 90 x 90,
  * 88 against 63 ms on 120 x 120) and STANDARD above; sso_solve_begin (multi-problem launches)
@@ -143,7 +150,8 @@ typedef struct {
 } sso_options;
 
 typedef struct {
-  int32_t iters;              /* PCG iterations of the last solve (all inner solves)         */
+  int32_t iters;              /* PCG iterations of the last solve (all inner solves; 0 for a
+                                 direct solve)                                               */
   double rel_residual;        /* ||f - K u||_2 / ||f||_2 recomputed after the solve, the row
                                  sums of K u in double-double (compensated) arithmetic       */
   double t_elem_us;           /* element stiffness + loads                                   */
@@ -159,7 +167,8 @@ typedef struct {
   int32_t spmv_samples;       /* number of sampled iterations                                */
   double spmv_bytes;          /* algorithmic bytes of one iteration                          */
   int32_t refine_steps;       /* mixed precision: outer steps (FP32 inner solves) run        */
-  int32_t solver;             /* SSO_SOLVER_STANDARD, _FUSED or _WG: recurrences that ran    */
+  int32_t solver;             /* SSO_SOLVER_STANDARD, _FUSED or _WG: recurrences that ran;
+                                 SSO_SOLVER_AUTO: solved directly                            */
   int32_t sym_products;       /* 1: the standard recurrences' products read only K's upper
                                  triangle, each block below the diagonal as the transpose of
                                  its mirror (single FP64 solves of a K of 128 MiB or more; the

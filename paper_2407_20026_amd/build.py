@@ -14,8 +14,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhipsso.so")
-SOURCES = ["api.hip", "pattern.hip", "elements.hip", "assemble.hip", "pcg.hip", "extras.hip",
-           "ceiling.hip", "validate.cpp"]
+SOURCES = ["api.hip", "pattern.hip", "elements.hip", "assemble.hip", "pcg.hip", "direct.hip",
+           "extras.hip", "ceiling.hip", "validate.cpp", "direct_plan.cpp"]
 ARCH = os.environ.get("HIPSSO_ARCH", "gfx950")
 
 # Kernel arguments preloaded into SGPRs (gfx950), up to 16 dwords: a kernel's first loads need

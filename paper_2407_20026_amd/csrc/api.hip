@@ -27,6 +27,13 @@ static_assert(SSO_NOALLOC_MAX_QUADS * 15 + 2 * 1024 <=
 struct SharedPattern {
   Pattern pat;
   std::atomic<int> refs{1};
+  // the direct solver's plan, built by the first solve that may use it (under the mutex; read-only
+  // afterwards); its device tables live in the pattern's arena
+  std::mutex direct_mutex;
+  enum { DIRECT_UNKNOWN, DIRECT_READY, DIRECT_REFUSED };
+  int direct_state = DIRECT_UNKNOWN;
+  DirectPlan plan;
+  DirectArgs tables{};
 };
 
 struct sso_problem {
@@ -64,6 +71,9 @@ struct sso_problem {
   int32_t* col = nullptr;
   int32_t* perm = nullptr;
   int32_t* seg = nullptr;
+  bool direct = false;          // the last solve chose the direct solver
+  bool factored = false;        // its factor is that of the current K
+  DirectArgs da{};              // its arrays (allocated on first use)
   bool solved = false;
   bool in_batch = false;        // started with sso_solve_begin, not yet finished
   bool batch_pending = false;   // listed in a multi-problem launch not yet waited for
@@ -93,6 +103,17 @@ struct sso_batch {
 };
 
 namespace {
+
+// Most device memory that the direct solver's numeric arrays may take: what the fill of a surface
+// structure (grid-shell or shell of any outline) or of a chain needs, which grows as n log n.  A
+// structure that fills more (members joined in space; a solid lattice of 20 x 20 x 20 nodes takes
+// three times this) also costs more operations than PCG's few hundred iterations there, and PCG
+// keeps it.  The serving loops' admission bounds a request's memory by the same formula.
+double direct_max_bytes(const Mesh& m) {
+  const double n = m.n_nodes;
+  return 288.0 * (std::log2(n + 1.0) + 1.0) * (1.3 * n + 2.6 * m.n_beams + 7.0 * m.n_quads) +
+         1048576.0;
+}
 
 sso_options default_options() {
   sso_options o;
@@ -463,10 +484,170 @@ MixedParams mixed_params(const sso_problem* p) {
   return mp;
 }
 
+// The direct solver's plan and tables for the problem's topology, built on first use; false: the
+// direct solver is not for this structure.
+int direct_tables(sso_problem* p, bool* ready) {
+  SharedPattern* sh = p->shared;
+  std::lock_guard<std::mutex> lock(sh->direct_mutex);
+  if (sh->direct_state == SharedPattern::DIRECT_UNKNOWN) {
+    const int n = p->m.n_nodes;
+    hipStream_t s = p->s;
+    DirectPlan& pl = sh->plan;
+    bool ok = false;
+    try {
+      std::vector<int32_t> rp(n + 1), col(p->pat.n_blocks);
+      TRY_HIP(hipMemcpyAsync(rp.data(), p->pat.brow_ptr, sizeof(int32_t) * rp.size(),
+                             hipMemcpyDeviceToHost, s));
+      TRY_HIP(hipMemcpyAsync(col.data(), p->pat.bcol, sizeof(int32_t) * col.size(),
+                             hipMemcpyDeviceToHost, s));
+      TRY_HIP(hipStreamSynchronize(s));
+      ok = build_direct_plan(n, rp.data(), col.data(), direct_max_bytes(p->m), pl);
+      if (ok && debug_mode()) {
+        char msg[256];
+        if (check_direct_plan(n, rp.data(), col.data(), pl, msg, sizeof msg) != 0) {
+          std::fprintf(stderr, "hipsso debug: %s\n", msg);
+          return SSO_EINVAL;
+        }
+      }
+    } catch (...) {   // out of host memory
+      ok = false;
+    }
+    if (ok) {
+      AllocScope ts(&p->bytes, &sh->pat.mem);
+      DirectArgs& t = sh->tables;
+      auto put = [&](auto** dst, const auto& v) {
+        using V = typename std::decay_t<decltype(v)>::value_type;
+        V* d = nullptr;
+        hipError_t e = dev_alloc(&d, (int64_t)v.size(), s);
+        if (e == hipSuccess && !v.empty())
+          e = hipMemcpyAsync(d, v.data(), sizeof(V) * v.size(), hipMemcpyHostToDevice, s);
+        *dst = d;
+        return e;
+      };
+      TRY_HIP(put(&t.fronts, pl.fronts));
+      TRY_HIP(put(&t.nodes, pl.nodes));
+      TRY_HIP(put(&t.maps, pl.maps));
+      TRY_HIP(put(&t.entries, pl.entries));
+      TRY_HIP(put(&t.items, pl.items));
+      TRY_HIP(put(&t.steps, pl.steps));
+      TRY_HIP(put(&t.level_off, pl.level_off));
+      TRY_HIP(put(&t.level_np, pl.level_np));
+      TRY_HIP(hipStreamSynchronize(s));
+      t.n_levels = pl.levels();
+      t.bdiag = p->pat.bdiag;
+      pl.drop_tables();
+    } else {
+      pl = DirectPlan();
+    }
+    sh->direct_state = ok ? SharedPattern::DIRECT_READY : SharedPattern::DIRECT_REFUSED;
+  }
+  *ready = sh->direct_state == SharedPattern::DIRECT_READY;
+  return SSO_OK;
+}
+
+// Whether the direct solver takes the coming solve, with its arrays in place if so.
+int choose_direct(sso_problem* p) {
+  p->factored = false;
+  p->direct = false;
+  if (p->opt.solver != SSO_SOLVER_AUTO || mixed(p)) return SSO_OK;
+  bool ready = false;
+  const int st = direct_tables(p, &ready);
+  if (st != SSO_OK || !ready) return st;
+  if (!p->da.fact) {
+    const DirectPlan& pl = p->shared->plan;
+    const int64_t n = 6 * (int64_t)p->m.n_nodes;
+    DirectArgs a = p->shared->tables;
+    double* d = nullptr;
+    const hipError_t e = dev_alloc(&d, pl.values() + 2, p->s);   // one buffer, cut below
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      return SSO_OK;               // PCG needs less
+    }
+    TRY_HIP(e);
+    auto cut = [&](int64_t len) {
+      double* q = d;
+      d += len;
+      return q;
+    };
+    a.f0 = cut(pl.work_len);       // the panels first: their lengths are even (16-byte loads)
+    a.x1 = cut(pl.again_len);
+    a.w = cut(pl.w_len);
+    a.u = cut(pl.u_len);
+    a.fact = cut(pl.fact_len);
+    a.b = cut(n);
+    a.sol = cut(n);
+    a.v = cut(pl.v_len);
+    a.flag = reinterpret_cast<unsigned*>(cut(1));
+    a.K = p->K;
+    p->da = a;
+  }
+  p->direct = true;
+  return SSO_OK;
+}
+
+// K x = b with the direct solver: factor K if the current one is not yet factored, substitute,
+// and refine on the true residual (row sums in double-double) until it meets rtol, as long as a
+// step gains a factor of two.  *done: met; otherwise x is the best so far.  A K that is not
+// positive definite to working precision leaves *done false and x = 0.
+int run_direct(sso_problem* p, const double* b, double* x, bool* done) {
+  hipStream_t s = p->s;
+  const DirectPlan& pl = p->shared->plan;
+  DirectArgs& a = p->da;
+  const int64_t n = 6 * (int64_t)p->m.n_nodes;
+  *done = false;
+  if (!p->factored) {
+    TRY_HIP(hipMemsetAsync(a.flag, 0, sizeof(unsigned), s));
+    TRY_HIP(launch_direct_factor(pl, a, s));
+  }
+  DirectArgs q = a;
+  q.rhs = b;
+  q.sol = x;
+  TRY_HIP(launch_direct_solve(pl, q, s));
+  double prev = -1.0;
+  constexpr int MAX_STEPS = 6;
+  for (int step = 0;; ++step) {
+    TRY_HIP(launch_true_residual(p->m, p->pat, p->K, x, b, p->w.r, p->w, p->d_scal, s));
+    unsigned flag = 0;
+    TRY_HIP(hipMemcpyAsync(p->h_scal, p->d_scal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+    if (!p->factored)
+      TRY_HIP(hipMemcpyAsync(&flag, a.flag, sizeof(unsigned), hipMemcpyDeviceToHost, s));
+    TRY_HIP(hipStreamSynchronize(s));
+    const double rn = std::sqrt(p->h_scal[0]), bn = std::sqrt(p->h_scal[1]);
+    if (flag || !std::isfinite(rn)) {
+      TRY_HIP(hipMemsetAsync(x, 0, sizeof(double) * n, s));
+      p->direct = false;
+      return SSO_OK;
+    }
+    p->factored = true;
+    // a first solution that only just meets the target takes one more step: a refined one is
+    // orders of magnitude below it
+    if (rn <= (step == 0 ? 0.5 : 1.0) * p->opt.rtol * bn) {
+      *done = true;
+      return SSO_OK;
+    }
+    if (step == MAX_STEPS || (prev >= 0.0 && rn > 0.5 * prev)) return SSO_OK;
+    prev = rn;
+    q.rhs = p->w.r;
+    q.sol = a.sol;
+    TRY_HIP(launch_direct_solve(pl, q, s));
+    TRY_HIP(launch_axpy(1.0, a.sol, x, n, s));
+  }
+}
+
 // Solve K x = b (b masked) in the problem's precision mode.
 int run_solver(sso_problem* p, const double* b, double* x, int* iters, int* outer) {
   int status = SSO_OK;
   *outer = 0;
+  if (p->direct) {
+    bool done = false;
+    const int st = run_direct(p, b, x, &done);
+    if (st != SSO_OK || done) return st;
+    if (p->direct) {   // the target lies below what refinement reaches: corrections by PCG
+      TRY_HIP(pcg_correct(p->m, p->pat, p->K, p->Dinv, b, x, p->opt.rtol, p->opt.max_it, p->w,
+                          p->s, iters, &status));
+      return status;
+    }
+  }
   if (one_wg(p)) {
     TRY_HIP(pcg_solve_wg(p->m, p->pat, p->K, p->Dinv, b, x, p->opt.rtol, p->opt.max_it, p->w,
                          p->s, iters, &status, p->opt.profile_every));
@@ -495,6 +676,12 @@ int prepare(sso_problem* p, bool batch) {
   // median latency 14.5 -> 5.1 ms at the same capacity).
   if (batch && p->opt.solver == SSO_SOLVER_AUTO && p->solver_used != SSO_SOLVER_WG)
     p->solver_used = SSO_SOLVER_STANDARD;
+  p->direct = p->factored = false;
+  if (!batch) {
+    const int st = choose_direct(p);
+    if (st != SSO_OK) return st;
+    if (p->direct) p->solver_used = SSO_SOLVER_STANDARD;   // should it go back to PCG
+  }
   const bool mx = mixed(p), fu = fused(p);
   const int64_t nk = 36 * p->pat.n_blocks;
   const int64_t nb = 36 * right_precondition_blocks(p->pat, p->m.n_nodes);
@@ -729,8 +916,8 @@ int sso_solve(sso_problem* p, double* u_out, sso_stats* stats) {
         fused_used(p) ? fused_bytes_per_iteration(p->m.n_nodes, p->pat.n_blocks, mixed(p))
                       : pcg_bytes_per_iteration(p->m.n_nodes, p->pat.n_blocks, mixed(p),
                                                 sym_used(p, true));
-    stats->solver = p->solver_used;
-    stats->sym_products = sym_used(p, true) ? 1 : 0;
+    stats->solver = p->direct ? SSO_SOLVER_AUTO : p->solver_used;
+    stats->sym_products = !p->direct && sym_used(p, true) ? 1 : 0;
   }
   // after SSO_ENOTCONV u holds the last iterate; objective and adjoint stay available
   p->solved = (status == SSO_OK || status == SSO_ENOTCONV);

@@ -1,0 +1,664 @@
+// Plan of the sparse direct solver (host): nested dissection, fronts, work lists.
+//
+// Sec. 2.2.2 of the paper solves K u = f with direct solvers.  Here the node graph of K (one
+// vertex per node, an edge where two nodes share an element) is split by vertex separators,
+// recursively, and every separator is eliminated after the two parts that it separates.  A
+// surface structure of n nodes then fills about n log n blocks and takes about n^1.5 operations.
+//
+// Splitting uses graph distances only.  Four landmarks far from each other (breadth-first
+// search, farthest point next) give every node four distances; sums and differences of them are
+// integer coordinates, and on a grid numbered in any way (members along grid lines, or quads)
+// with its corners as landmarks they are the grid's own x and y.  A part is cut at the median of
+// each candidate coordinate, the nodes of one side that touch the other form the separator, and
+// the candidate with the smallest one is taken.
+#include "direct_plan.h"
+
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <exception>
+#include <map>
+#include <memory>
+#include <system_error>
+#include <thread>
+
+namespace sso {
+namespace {
+
+// Parts of at most this many nodes are eliminated whole.
+constexpr int LEAF_NODES = 10;
+// Parts of fewer nodes keep the coordinates of the part they were cut from.
+constexpr int LANDMARK_NODES = 120;
+// Parts of at least this many nodes hand one half to another thread, up to MAX_THREADS at once.
+constexpr int MAX_THREADS = 8;
+constexpr int THREAD_NODES = 4000;
+
+// A part of the node graph, renumbered 0 .. n - 1 (no self edges).
+struct Part {
+  std::vector<int32_t> id;      // global node numbers
+  std::vector<int32_t> rp, col;
+  std::vector<int32_t> coord[4];
+  int n() const { return (int)id.size(); }
+};
+
+struct Tree {                   // a front of the elimination: own nodes, then up to two subtrees
+  std::vector<int32_t> own;
+  std::unique_ptr<Tree> child[2];
+};
+
+// Breadth-first distances from src (d: -1 everywhere on entry); queue: the nodes reached, in order.
+void bfs(const Part& g, int src, std::vector<int32_t>& d, std::vector<int32_t>& queue) {
+  queue.clear();
+  queue.push_back(src);
+  d[src] = 0;
+  for (size_t h = 0; h < queue.size(); ++h) {
+    const int v = queue[h], dv = d[v] + 1;
+    for (int e = g.rp[v]; e < g.rp[v + 1]; ++e) {
+      const int w = g.col[e];
+      if (d[w] < 0) {
+        d[w] = dv;
+        queue.push_back(w);
+      }
+    }
+  }
+}
+
+// The part's coordinates.  Landmark 0 is a node farthest from the first node, each next one the
+// node farthest from those before (largest smallest distance, then largest sum of distances, so
+// that on a grid the corners come before the middles of its edges); ties go to the lower degree,
+// then to the lower number.  A node that a landmark does not reach counts as farther than any
+// other (a part may fall into pieces).
+void coordinates(Part& g) {
+  const int n = g.n();
+  std::vector<int32_t> dist[4], queue;
+  queue.reserve(n);
+  auto distances = [&](int src, std::vector<int32_t>& d) {
+    d.assign(n, -1);
+    bfs(g, src, d, queue);
+    if ((int)queue.size() < n)
+      for (int32_t& v : d)
+        if (v < 0) v = n;
+  };
+  auto farthest = [&](int k) {      // from landmarks 0 .. k - 1
+    int best = 0;
+    int64_t kb = -1;
+    for (int v = 0; v < n; ++v) {
+      int64_t lo = dist[0][v], sum = lo;
+      for (int q = 1; q < k; ++q) {
+        lo = std::min<int64_t>(lo, dist[q][v]);
+        sum += dist[q][v];
+      }
+      const int64_t key = lo * (4 * (int64_t)n + 1) + sum;
+      const int dv = g.rp[v + 1] - g.rp[v], db = g.rp[best + 1] - g.rp[best];
+      if (key > kb || (key == kb && dv < db)) {
+        best = v;
+        kb = key;
+      }
+    }
+    return best;
+  };
+  distances(0, dist[0]);
+  const int first = farthest(1);
+  distances(first, dist[0]);
+  for (int k = 1; k < 4; ++k) distances(farthest(k), dist[k]);
+  for (auto& c : g.coord) c.resize(n);
+  for (int v = 0; v < n; ++v) {
+    const int a = dist[0][v], b = dist[1][v], c = dist[2][v], d = dist[3][v];
+    g.coord[0][v] = (a + b) - (c + d);
+    g.coord[1][v] = (a + c) - (b + d);
+    g.coord[2][v] = (a + d) - (b + c);
+    g.coord[3][v] = a - b;
+  }
+}
+
+// Cuts the part at the median of a coordinate.  side: 0, 1, or 2 in the separator (the nodes of
+// one side that touch the other).  Returns the separator's size; n0, n1: the sides without it.
+int try_split(const Part& g, const std::vector<int32_t>& c, std::vector<int8_t>& side,
+              std::vector<int32_t>& hist, int& n0, int& n1) {
+  const int n = g.n();
+  const auto range = std::minmax_element(c.begin(), c.end());
+  const int lo = *range.first, hi = *range.second;
+  int left = 0, cut_at = 0;        // side 0: c < cut_at
+  if (lo < hi) {
+    hist.assign(hi - lo + 2, 0);
+    for (int v : c) ++hist[v - lo + 1];
+    int below = 0, best = n + 1;
+    for (int k = 1; k <= hi - lo; ++k) {       // side 0 = values below lo + k
+      below += hist[k];
+      const int off = std::abs(n - 2 * below);
+      if (off < best) {
+        best = off;
+        left = below;
+        cut_at = lo + k;
+      }
+    }
+    for (int v = 0; v < n; ++v) side[v] = c[v] >= cut_at;
+  } else {                          // one value: cut the list where it lies
+    left = n / 2;
+    for (int v = 0; v < n; ++v) side[v] = v >= left;
+  }
+  int touch[2] = {0, 0};
+  for (int v = 0; v < n; ++v) {
+    const int s = side[v] & 1;
+    for (int e = g.rp[v]; e < g.rp[v + 1]; ++e)
+      if ((side[g.col[e]] & 1) != s) {
+        ++touch[s];
+        side[v] = (int8_t)(s | 4);
+        break;
+      }
+  }
+  const int from = touch[1] < touch[0] || (touch[1] == touch[0] && left <= n - left) ? 1 : 0;
+  for (int v = 0; v < n; ++v) {
+    const int s = side[v] & 1;
+    side[v] = (int8_t)((side[v] & 4) && s == from ? 2 : s);
+  }
+  n0 = left - (from == 0 ? touch[0] : 0);
+  n1 = n - left - (from == 1 ? touch[1] : 0);
+  return touch[from];
+}
+
+Part sub_part(const Part& g, const std::vector<int8_t>& side, int which, int n,
+              std::vector<int32_t>& local) {
+  Part s;
+  s.id.reserve(n);
+  const bool keep = g.n() >= LANDMARK_NODES ? n < LANDMARK_NODES : true;
+  size_t edges = 0;
+  for (int v = 0; v < g.n(); ++v) {
+    local[v] = -1;
+    if (side[v] != which) continue;
+    local[v] = (int32_t)s.id.size();
+    s.id.push_back(g.id[v]);
+    edges += g.rp[v + 1] - g.rp[v];
+  }
+  s.rp.reserve(n + 1);
+  s.col.reserve(edges);
+  s.rp.push_back(0);
+  for (int v = 0; v < g.n(); ++v) {
+    if (side[v] != which) continue;
+    for (int e = g.rp[v]; e < g.rp[v + 1]; ++e)
+      if (local[g.col[e]] >= 0) s.col.push_back(local[g.col[e]]);
+    s.rp.push_back((int32_t)s.col.size());
+  }
+  if (keep && n > LEAF_NODES)
+    for (int k = 0; k < 4; ++k) {
+      s.coord[k].reserve(n);
+      for (int v = 0; v < g.n(); ++v)
+        if (side[v] == which) s.coord[k].push_back(g.coord[k][v]);
+    }
+  return s;
+}
+
+// threads: how many this call may use, itself included
+std::unique_ptr<Tree> dissect(Part g, int threads) {
+  const int n = g.n();
+  if (n == 0) return nullptr;
+  auto t = std::make_unique<Tree>();
+  if (n <= LEAF_NODES) {
+    t->own = std::move(g.id);
+    return t;
+  }
+  if (g.coord[0].empty()) coordinates(g);
+  std::vector<int8_t> side(n), best_side;
+  std::vector<int32_t> hist;
+  double cost = 0.0;
+  int n0 = 0, n1 = 0;
+  for (int k = 0; k < 4; ++k) {
+    int a, b;
+    const int s = try_split(g, g.coord[k], side, hist, a, b);
+    const double balance = (double)std::max(a, b) / n;
+    const double ck = s * (1.0 + 2.0 * std::max(0.0, balance - 0.55)) + 1e-6 * balance;
+    if (k == 0 || ck < cost) {
+      cost = ck;
+      n0 = a;
+      n1 = b;
+      best_side = side;
+    }
+  }
+  std::vector<int32_t>& local = hist;
+  local.resize(n);
+  for (int v = 0; v < n; ++v)
+    if (best_side[v] == 2) t->own.push_back(g.id[v]);
+  Part left = sub_part(g, best_side, 0, n0, local);
+  Part right = sub_part(g, best_side, 1, n1, local);
+  g = Part();
+  if (threads > 1 && n >= THREAD_NODES) {
+    std::exception_ptr err[2];
+    auto half = [&](Part& part, int k, int th) {
+      try {
+        t->child[k] = dissect(std::move(part), th);
+      } catch (...) {
+        err[k] = std::current_exception();
+      }
+    };
+    std::thread other;
+    try {
+      other = std::thread([&] { half(right, 1, threads / 2); });
+    } catch (const std::system_error&) {   // no thread to be had: both halves here
+    }
+    half(left, 0, threads - threads / 2);
+    if (other.joinable())
+      other.join();
+    else
+      half(right, 1, 1);
+    for (const std::exception_ptr& e : err)
+      if (e) std::rethrow_exception(e);
+  } else {
+    t->child[0] = dissect(std::move(left), 1);
+    t->child[1] = dissect(std::move(right), 1);
+  }
+  return t;
+}
+
+struct Front0 {            // a front while the plan is built
+  int own_off, own_cnt;    // own nodes: range of `order`
+  int child[2];
+  int level;
+};
+
+struct Dissection {
+  std::vector<int32_t> order;       // nodes in elimination order
+  std::vector<Front0> fronts;       // children before parents
+
+  int flatten(const Tree* t) {
+    if (!t) return -1;
+    Front0 f;
+    f.level = 0;
+    for (int c = 0; c < 2; ++c) {
+      f.child[c] = flatten(t->child[c].get());
+      if (f.child[c] >= 0) f.level = std::max(f.level, fronts[f.child[c]].level + 1);
+    }
+    f.own_off = (int)order.size();
+    f.own_cnt = (int)t->own.size();
+    order.insert(order.end(), t->own.begin(), t->own.end());
+    fronts.push_back(f);
+    return (int)fronts.size() - 1;
+  }
+
+  // [a, b) of the list of components under one front without own nodes
+  int join(std::vector<Part>& comps, int a, int b, int threads) {
+    if (b - a == 1) return flatten(dissect(std::move(comps[a]), threads).get());
+    Front0 f;
+    f.child[0] = join(comps, a, (a + b) / 2, threads);
+    f.child[1] = join(comps, (a + b) / 2, b, threads);
+    f.own_off = (int)order.size();
+    f.own_cnt = 0;
+    f.level = 1 + std::max(fronts[f.child[0]].level, fronts[f.child[1]].level);
+    fronts.push_back(f);
+    return (int)fronts.size() - 1;
+  }
+
+  void run(int n, const int32_t* rp, const int32_t* col, int threads) {
+    std::vector<int32_t> comp(n, -1), local(n), queue;
+    std::vector<Part> parts;
+    order.reserve(n);
+    for (int v0 = 0; v0 < n; ++v0) {
+      if (comp[v0] >= 0) continue;
+      const int c = (int)parts.size();
+      queue.assign(1, v0);
+      comp[v0] = c;
+      for (size_t h = 0; h < queue.size(); ++h)
+        for (int e = rp[queue[h]]; e < rp[queue[h] + 1]; ++e)
+          if (comp[col[e]] < 0) {
+            comp[col[e]] = c;
+            queue.push_back(col[e]);
+          }
+      parts.emplace_back();
+      Part& g = parts.back();
+      g.id = queue;
+      std::sort(g.id.begin(), g.id.end());
+      for (size_t k = 0; k < g.id.size(); ++k) local[g.id[k]] = (int32_t)k;
+      g.rp.push_back(0);
+      for (int v : g.id) {
+        for (int e = rp[v]; e < rp[v + 1]; ++e)
+          if (col[e] != v) g.col.push_back(local[col[e]]);
+        g.rp.push_back((int32_t)g.col.size());
+      }
+    }
+    join(parts, 0, (int)parts.size(), threads);
+  }
+};
+
+// Offsets for arrays that live from one level to a later one: first fit over the free gaps.
+struct Gaps {
+  std::map<int64_t, int64_t> gaps;   // offset -> length
+  int64_t top = 0;
+  int64_t take(int64_t len) {
+    if (len == 0) return 0;
+    for (auto it = gaps.begin(); it != gaps.end(); ++it)
+      if (it->second >= len) {
+        const int64_t off = it->first, rest = it->second - len;
+        gaps.erase(it);
+        if (rest) gaps[off + len] = rest;
+        return off;
+      }
+    const int64_t off = top;
+    top += len;
+    return off;
+  }
+  void give(int64_t off, int64_t len) {
+    if (len == 0) return;
+    auto next = gaps.lower_bound(off);
+    if (next != gaps.begin()) {
+      auto prev = std::prev(next);
+      if (prev->first + prev->second == off) {
+        off = prev->first;
+        len += prev->second;
+        gaps.erase(prev);
+      }
+    }
+    if (next != gaps.end() && next->first == off + len) {
+      len += next->second;
+      gaps.erase(next);
+    }
+    gaps[off] = len;
+  }
+};
+
+inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+inline int64_t even(int64_t v) { return (v + 1) & ~(int64_t)1; }
+
+}  // namespace
+
+bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_bytes,
+                       DirectPlan& plan) {
+  plan = DirectPlan();
+  plan.n_nodes = n;
+  Dissection ds;
+  ds.run(n, rp, col, MAX_THREADS);
+  const int nf = (int)ds.fronts.size();
+
+  // level by level, children's order within a level kept
+  std::vector<int> order(nf), rank(nf);
+  for (int i = 0; i < nf; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return ds.fronts[a].level < ds.fronts[b].level; });
+  for (int i = 0; i < nf; ++i) rank[order[i]] = i;
+  const int nl = ds.fronts.back().level + 1;
+
+  // elimination position of each node: fronts children-first, own nodes in their order
+  std::vector<int32_t> pos(n), owner(n);
+  {
+    int p = 0;
+    for (int f = 0; f < nf; ++f)
+      for (int k = 0; k < ds.fronts[f].own_cnt; ++k) {
+        const int v = ds.order[ds.fronts[f].own_off + k];
+        pos[v] = p++;
+        owner[v] = f;
+      }
+  }
+
+  // boundaries, children first: the children's boundary nodes and the own nodes' neighbours that
+  // are eliminated later
+  std::vector<std::vector<int32_t>> bnd(nf);
+  std::vector<int32_t> stamp(n, -1);
+  double bytes = 0.0;
+  for (int f = 0; f < nf; ++f) {
+    const Front0& F = ds.fronts[f];
+    std::vector<int32_t>& b = bnd[f];
+    auto add = [&](int v) {
+      if (stamp[v] != f && owner[v] > f) {
+        stamp[v] = f;
+        b.push_back(v);
+      }
+    };
+    for (int c : F.child)
+      if (c >= 0)
+        for (int v : bnd[c]) add(v);
+    for (int k = 0; k < F.own_cnt; ++k) {
+      const int q = ds.order[F.own_off + k];
+      for (int e = rp[q]; e < rp[q + 1]; ++e) add(col[e]);
+    }
+    std::sort(b.begin(), b.end(), [&](int x, int y) { return pos[x] < pos[y]; });
+    const double s = 6.0 * F.own_cnt, t = 6.0 * (double)b.size();
+    bytes += 8.0 * (s + t) * s;
+    if (bytes > max_bytes || s > DIRECT_MAX_OWN) return false;
+  }
+
+  plan.fronts.resize(nf);
+  plan.level_off.resize(nl);
+  plan.level_np.assign(nl, 0);
+  std::vector<std::vector<int>> by_level(nl);
+  for (int i = 0; i < nf; ++i) by_level[ds.fronts[order[i]].level].push_back(i);
+
+  size_t n_list = 0;
+  for (int f = 0; f < nf; ++f) n_list += ds.fronts[f].own_cnt + bnd[f].size();
+  plan.nodes.reserve(n_list);
+  plan.maps.reserve(2 * n_list);
+  std::vector<int32_t> local(n, -1);    // position of a node in the front at hand
+  Gaps schur;
+  int64_t b_off = 0;
+
+  for (int h = 0; h < nl; ++h) {
+    int64_t work = 0, again = 0, w = 0;
+    for (int i : by_level[h]) {
+      const int f0 = order[i];
+      const Front0& F = ds.fronts[f0];
+      DirectFront& D = plan.fronts[i];
+      const int ns = F.own_cnt, nb = (int)bnd[f0].size();
+      D.ns6 = 6 * ns;
+      D.nb6 = 6 * nb;
+      D.np = ceil_div(D.ns6, DIRECT_NB);
+      D.level = h;
+      for (int c = 0; c < 2; ++c) D.child[c] = F.child[c] < 0 ? -1 : rank[F.child[c]];
+      D.nodes_off = (int32_t)plan.nodes.size();
+      plan.nodes.insert(plan.nodes.end(), ds.order.begin() + F.own_off,
+                        ds.order.begin() + F.own_off + ns);
+      plan.nodes.insert(plan.nodes.end(), bnd[f0].begin(), bnd[f0].end());
+      const int32_t* list = plan.nodes.data() + D.nodes_off;
+      const int cnt = ns + nb;
+      // maps into the children's boundaries
+      D.map_off = (int32_t)plan.maps.size();
+      for (int c = 0; c < 2; ++c) {
+        const int ch = F.child[c];
+        if (ch >= 0)
+          for (size_t k = 0; k < bnd[ch].size(); ++k) local[bnd[ch][k]] = (int32_t)k;
+        for (int k = 0; k < cnt; ++k) plan.maps.push_back(ch >= 0 ? local[list[k]] : -1);
+        if (ch >= 0)
+          for (int v : bnd[ch]) local[v] = -1;
+      }
+      D.fact_off = plan.fact_len;
+      plan.fact_len += even((int64_t)(D.ns6 + D.nb6) * D.ns6);
+      D.work_off = work;
+      work += even((int64_t)(D.ns6 + D.nb6) * D.ns6);
+      // a single panel goes straight into the factor; two panels need one copy between
+      D.again_off = again;
+      D.w_off = w;
+      if (D.np > 1) {
+        again += even((int64_t)(D.ns6 + D.nb6) * D.ns6);
+        w += (int64_t)DIRECT_NB * DIRECT_NB * (D.np + ceil_div(D.nb6, DIRECT_NB));
+      }
+      D.u_off = schur.take(even((int64_t)D.nb6 * D.nb6));
+      D.v_off = plan.v_len;
+      plan.v_len += D.nb6;
+      D.b_off = b_off;
+      b_off += D.ns6;
+      plan.level_np[h] = std::max(plan.level_np[h], D.np);
+    }
+    plan.work_len = std::max(plan.work_len, work);
+    plan.again_len = std::max(plan.again_len, again);
+    plan.w_len = std::max(plan.w_len, w);
+    for (int i : by_level[h])
+      for (int c : plan.fronts[i].child)
+        if (c >= 0) {
+          const DirectFront& C = plan.fronts[c];
+          schur.give(C.u_off, even((int64_t)C.nb6 * C.nb6));
+        }
+  }
+  plan.u_len = schur.top;
+  if (8.0 * (double)plan.values() > max_bytes) return false;
+
+  // work lists
+  std::vector<int32_t> start;
+  std::vector<DirectEntry> bucket;
+  std::vector<int32_t> key;
+  for (int h = 0; h < nl; ++h) {
+    const int np = plan.level_np[h];
+    plan.level_off[h] = (int32_t)plan.steps.size();
+    plan.steps.resize(plan.steps.size() + STEP_PANEL + 2 * np, DirectRange{0, 0});
+    DirectRange* st = plan.steps.data() + plan.level_off[h];
+    auto open = [&](int s) { st[s].off = (int32_t)plan.items.size(); };
+    auto close = [&](int s) { st[s].cnt = (int32_t)plan.items.size() - st[s].off; };
+    open(STEP_ASM);
+    for (int i : by_level[h]) {
+      const DirectFront& D = plan.fronts[i];
+      const int ns = D.ns6 / 6, cnt = ns + D.nb6 / 6;
+      if (ns == 0) continue;
+      const int32_t* list = plan.nodes.data() + D.nodes_off;
+      for (int k = 0; k < cnt; ++k) local[list[k]] = k;
+      const int tr = ceil_div(cnt, DIRECT_ASM_ROWS), tc = ceil_div(ns, DIRECT_ASM_COLS);
+      // blocks of K with a column among the own nodes, bucketed by tile
+      bucket.clear();
+      key.clear();
+      start.assign(tr * tc + 1, 0);
+      for (int q = 0; q < ns; ++q) {
+        const int v = list[q];
+        for (int e = rp[v]; e < rp[v + 1]; ++e) {
+          const int r = local[col[e]];
+          if (r < 0) continue;             // eliminated below
+          const int k = (r / DIRECT_ASM_ROWS) * tc + q / DIRECT_ASM_COLS;
+          bucket.push_back({(r % DIRECT_ASM_ROWS) << 16 | (q % DIRECT_ASM_COLS), e});
+          key.push_back(k);
+          ++start[k + 1];
+        }
+      }
+      for (int k = 0; k < tr * tc; ++k) start[k + 1] += start[k];
+      const int32_t e0 = (int32_t)plan.entries.size();
+      plan.entries.resize(e0 + bucket.size());
+      std::vector<int32_t> fill(start.begin(), start.end() - 1);
+      for (size_t k = 0; k < bucket.size(); ++k)
+        plan.entries[e0 + fill[key[k]]++] = bucket[k];
+      for (int a = 0; a < tr; ++a)
+        for (int b = 0; b < tc; ++b)
+          plan.items.push_back({i, a, b, e0 + start[a * tc + b], e0 + start[a * tc + b + 1]});
+      for (int k = 0; k < cnt; ++k) local[list[k]] = -1;
+    }
+    close(STEP_ASM);
+    for (int k = 0; k < np; ++k) {
+      open(STEP_PANEL + 2 * k);
+      for (int i : by_level[h]) {
+        const DirectFront& D = plan.fronts[i];
+        if (D.np <= k) continue;
+        const int rows = D.np + ceil_div(D.nb6, DIRECT_NB);
+        for (int r = 0; r < rows; ++r) plan.items.push_back({i, r, 0, 0, 0});
+      }
+      close(STEP_PANEL + 2 * k);
+      open(STEP_PANEL + 2 * k + 1);
+      for (int i : by_level[h]) {
+        const DirectFront& D = plan.fronts[i];
+        if (D.np <= k || D.np == 1) continue;   // a single panel is finished by its scaling
+        const int rows = D.np + ceil_div(D.nb6, DIRECT_NB);
+        for (int r = 0; r < rows; ++r)
+          for (int c = 0; c < D.np; ++c) plan.items.push_back({i, r, c, 0, 0});
+      }
+      close(STEP_PANEL + 2 * k + 1);
+    }
+    open(STEP_SCHUR);
+    for (int i : by_level[h]) {
+      const int t = ceil_div(plan.fronts[i].nb6, DIRECT_NB);
+      for (int a = 0; a < t; ++a)
+        for (int b = 0; b <= a; ++b) plan.items.push_back({i, a, b, 0, 0});
+    }
+    close(STEP_SCHUR);
+    open(STEP_FWD);
+    for (int i : by_level[h]) {
+      const DirectFront& D = plan.fronts[i];
+      const int t = std::max(ceil_div(D.nb6, DIRECT_FWD_ROWS), D.ns6 > 0 ? 1 : 0);
+      for (int a = 0; a < t; ++a) plan.items.push_back({i, a, 0, 0, 0});
+    }
+    close(STEP_FWD);
+    open(STEP_BWD);
+    for (int i : by_level[h])
+      for (int a = 0; a < ceil_div(plan.fronts[i].ns6, DIRECT_BWD_COLS); ++a)
+        plan.items.push_back({i, a, 0, 0, 0});
+    close(STEP_BWD);
+  }
+  return true;
+}
+
+int check_direct_plan(int n, const int32_t* rp, const int32_t* col, const DirectPlan& plan,
+                      char* msg, size_t len) {
+  auto fail = [&](int code, const char* what, long long at) {
+    std::snprintf(msg, len, "direct plan: %s (at %lld)", what, at);
+    return code;
+  };
+  // every node is eliminated once, in a front whose list holds its neighbours eliminated later
+  std::vector<int32_t> front(n, -1), at(n, -1);
+  for (size_t f = 0; f < plan.fronts.size(); ++f) {
+    const DirectFront& D = plan.fronts[f];
+    for (int k = 0; k < D.ns6 / 6; ++k) {
+      const int v = plan.nodes[D.nodes_off + k];
+      if (v < 0 || v >= n || front[v] >= 0) return fail(1, "node eliminated twice", v);
+      front[v] = (int32_t)f;
+    }
+  }
+  for (int v = 0; v < n; ++v)
+    if (front[v] < 0) return fail(1, "node never eliminated", v);
+  size_t blocks = 0;
+  for (size_t f = 0; f < plan.fronts.size(); ++f) {
+    const DirectFront& D = plan.fronts[f];
+    const int ns = D.ns6 / 6, cnt = ns + D.nb6 / 6;
+    const int32_t* list = plan.nodes.data() + D.nodes_off;
+    for (int k = 0; k < cnt; ++k) {
+      if (at[list[k]] >= 0) return fail(2, "node listed twice in a front", list[k]);
+      at[list[k]] = k;
+      if (k >= ns && plan.fronts[front[list[k]]].level <= D.level)
+        return fail(3, "boundary node eliminated too early", list[k]);
+    }
+    for (int k = 0; k < ns; ++k)
+      for (int e = rp[list[k]]; e < rp[list[k] + 1]; ++e)
+        if (at[col[e]] < 0) {
+          if (plan.fronts[front[col[e]]].level >= D.level)
+            return fail(4, "neighbour missing from a front", list[k]);
+        } else {
+          ++blocks;
+        }
+    // each child's boundary lies in this front, in the same order
+    for (int c = 0; c < 2; ++c) {
+      const int32_t* map = plan.maps.data() + D.map_off + c * cnt;
+      int prev = -1, seen = 0;
+      for (int k = 0; k < cnt; ++k) {
+        if (map[k] < 0) continue;
+        if (D.child[c] < 0) return fail(5, "map without a child", (long long)f);
+        const DirectFront& C = plan.fronts[D.child[c]];
+        if (map[k] <= prev || map[k] >= C.nb6 / 6 ||
+            plan.nodes[C.nodes_off + C.ns6 / 6 + map[k]] != list[k])
+          return fail(5, "child map", (long long)f);
+        prev = map[k];
+        ++seen;
+      }
+      if (D.child[c] >= 0 && (seen != plan.fronts[D.child[c]].nb6 / 6 ||
+                              plan.fronts[D.child[c]].level >= D.level))
+        return fail(6, "child boundary lost", (long long)f);
+    }
+    for (int k = 0; k < cnt; ++k) at[list[k]] = -1;
+    const int64_t panel = (int64_t)(D.ns6 + D.nb6) * D.ns6;
+    if (D.fact_off + panel > plan.fact_len || D.work_off + panel > plan.work_len ||
+        D.u_off + (int64_t)D.nb6 * D.nb6 > plan.u_len || D.v_off + D.nb6 > plan.v_len ||
+        D.b_off + D.ns6 > 6 * (int64_t)n ||
+        (D.np > 1 && (D.again_off + panel > plan.again_len ||
+                      D.w_off + (int64_t)DIRECT_NB * DIRECT_NB *
+                                    (D.np + ceil_div(D.nb6, DIRECT_NB)) > plan.w_len)))
+      return fail(7, "array too short", (long long)f);
+  }
+  if (blocks != plan.entries.size()) return fail(8, "blocks of K", (long long)blocks);
+  // Schur complements alive at the same time do not overlap
+  std::vector<int> parent(plan.fronts.size(), -1);
+  for (size_t f = 0; f < plan.fronts.size(); ++f)
+    for (int c : plan.fronts[f].child)
+      if (c >= 0) parent[c] = (int)f;
+  for (int h = 0; h < plan.levels(); ++h) {
+    std::vector<std::pair<int64_t, int64_t>> live;
+    for (size_t f = 0; f < plan.fronts.size(); ++f) {
+      const DirectFront& D = plan.fronts[f];
+      const int last = parent[f] < 0 ? D.level : plan.fronts[parent[f]].level;
+      if (D.nb6 && D.level <= h && last >= h)
+        live.emplace_back(D.u_off, D.u_off + (int64_t)D.nb6 * D.nb6);
+    }
+    std::sort(live.begin(), live.end());
+    for (size_t k = 1; k < live.size(); ++k)
+      if (live[k].first < live[k - 1].second) return fail(9, "Schur complements overlap", h);
+  }
+  return 0;
+}
+
+}  // namespace sso

@@ -1,0 +1,100 @@
+// Plan of the sparse direct solver: nested dissection of the node graph and the fronts of a
+// multifrontal elimination, with the work lists of its kernels.  Host code; built once per
+// topology from the block pattern of K alone (never from coordinates, so that every problem of a
+// topology eliminates in the same order and gives the same bits).
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include <vector>
+
+namespace sso {
+
+// Panel width of the elimination inside a front, and the rows of a work item of its kernels.
+constexpr int DIRECT_NB = 64;
+// Node tile of the assembly's work items: 8 nodes down, 16 across (48 x 96 entries).
+constexpr int DIRECT_ASM_ROWS = 8;
+constexpr int DIRECT_ASM_COLS = 16;
+// Columns of a backward-substitution work item, rows of a forward-substitution one.
+constexpr int DIRECT_BWD_COLS = 32;
+constexpr int DIRECT_FWD_ROWS = 64;
+// Most own DOFs of a front (a substitution stages them in LDS).
+constexpr int DIRECT_MAX_OWN = 6144;
+
+// One front: ns own nodes (eliminated here), nb boundary nodes (ancestors' nodes that the front's
+// subtree touches).  Its rows are the DOFs of the own nodes, then of the boundary nodes; its
+// columns those of the own nodes.  Offsets are in values of the array named.
+struct DirectFront {
+  int32_t ns6, nb6;          // 6 ns, 6 nb
+  int32_t nodes_off;         // own nodes, then boundary nodes (global node numbers)
+  int32_t map_off;           // for each of its ns + nb nodes: position in child 0's boundary or
+                             //   -1; then the same for child 1
+  int32_t child[2];          // fronts, -1: none
+  int32_t np;                // panels: ceil(ns6 / DIRECT_NB)
+  int32_t level;             // height: every child has a lower level
+  int64_t fact_off;          // factor [(ns6 + nb6) x ns6]
+  int64_t work_off;          // assembled panel of the level, same shape
+  int64_t again_off;         // np > 1: second work panel of the level, same shape
+  int64_t w_off;             // np > 1: scaled panel of a step, DIRECT_NB x DIRECT_NB row tiles
+  int64_t u_off;             // Schur complement [nb6 x nb6], lower triangle
+  int64_t v_off;             // update vector of the forward substitution [nb6]
+  int64_t b_off;             // right-hand side of the own DOFs [ns6]
+};
+
+// A work item: the front and up to two tile indices; entries [e0, e1) of an assembly item.
+struct DirectItem {
+  int32_t front, i, j, e0, e1;
+};
+
+// One 6x6 block of K in a front: local row and column within its assembly tile, value slot (the
+// block of (column node, row node), read transposed: K is bitwise symmetric).
+struct DirectEntry {
+  int32_t rc;                // row node in tile << 16 | column node in tile
+  int32_t slot;
+};
+
+struct DirectRange {
+  int32_t off, cnt;
+};
+
+// Step lists of a level: assembly, Schur complement, forward and backward substitution, then for
+// each panel the scaling and the update.
+enum { STEP_ASM = 0, STEP_SCHUR = 1, STEP_FWD = 2, STEP_BWD = 3, STEP_PANEL = 4 };
+
+struct DirectPlan {
+  std::vector<DirectFront> fronts;    // level by level, leaves first
+  std::vector<int32_t> nodes, maps;
+  std::vector<DirectEntry> entries;
+  std::vector<DirectItem> items;
+  std::vector<DirectRange> steps;     // steps[level_off[h] + STEP_*] (panels: + 2 k, + 2 k + 1)
+  std::vector<int32_t> level_off;     // per level
+  std::vector<int32_t> level_np;      // most panels of a front of the level
+  int n_nodes = 0;
+  int64_t fact_len = 0, work_len = 0, again_len = 0, w_len = 0, u_len = 0, v_len = 0;
+  // values of a problem's numeric arrays: the five above, v, and two vectors of all DOFs
+  int64_t values() const {
+    return fact_len + work_len + again_len + w_len + u_len + v_len + 12 * (int64_t)n_nodes;
+  }
+  int levels() const { return (int)level_off.size(); }
+  // Keeps what the launches need once the other tables are on the device.
+  void drop_tables() {
+    fronts = {};
+    nodes = {};
+    maps = {};
+    entries = {};
+    items = {};
+  }
+};
+
+// Builds the plan for a block pattern (brow_ptr [n + 1], bcol, columns of a row ascending, the
+// pattern symmetric).  Returns false when its numeric arrays would take more than max_bytes or a
+// front has more than DIRECT_MAX_OWN own DOFs.
+bool build_direct_plan(int n, const int32_t* brow_ptr, const int32_t* bcol, double max_bytes,
+                       DirectPlan& plan);
+// 0 when every invariant of the plan holds, else the number of the first failed check, with a
+// message in msg.
+int check_direct_plan(int n, const int32_t* brow_ptr, const int32_t* bcol,
+                      const DirectPlan& plan, char* msg, size_t len);
+
+}  // namespace sso

@@ -8,6 +8,7 @@
 #include <utility>
 #include <vector>
 
+#include "direct_plan.h"
 #include "hipsso.h"
 
 namespace sso {
@@ -300,6 +301,27 @@ hipError_t launch_apply_prescribed(const Mesh& m, double* u, hipStream_t s);
 hipError_t launch_mask_vector(const Mesh& m, const double* in, double* out, hipStream_t s);
 hipError_t launch_scalar_values(const Mesh& m, const Pattern& pat, const double* K,
                                 double* vals, hipStream_t s);
+
+// direct.hip
+// What the kernels of the direct solver read: the plan's tables and a problem's arrays.
+struct DirectArgs {
+  const DirectFront* fronts;
+  const int32_t *nodes, *maps;
+  const DirectEntry* entries;
+  const DirectItem* items;
+  const DirectRange* steps;
+  const int32_t *level_off, *level_np;
+  const int32_t* bdiag;
+  const double* K;
+  double *fact, *f0, *x1, *w, *u, *v, *b;
+  const double* rhs;
+  double* sol;
+  unsigned* flag;          // set when a pivot is too small
+  int n_levels;
+};
+// Factor K (a.K) into a.fact; then sol = K^-1 rhs as often as wanted.
+hipError_t launch_direct_factor(const DirectPlan& pl, const DirectArgs& a, hipStream_t s);
+hipError_t launch_direct_solve(const DirectPlan& pl, const DirectArgs& a, hipStream_t s);
 
 // pcg.hip
 struct PcgWork {

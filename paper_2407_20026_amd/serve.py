@@ -22,6 +22,7 @@ from __future__ import annotations
 
 import collections
 import hashlib
+import math
 import threading
 import time
 from dataclasses import dataclass, field, replace
@@ -52,9 +53,9 @@ def _arena_bound(bufs) -> int:
 
 def footprint_bytes(mesh, mixed: bool | None = False) -> int:
     """Upper bound of the device memory one problem holds after its forward and adjoint
-    (mesh copies, pattern, element list, K, packed preconditioner, B = K M of the
-    single-reduction PCG or the FP32 copies of mixed precision, solver vectors, gradients),
-    in the chunks the library carves them from.  mixed=None: the precision is picked by the
+    (mesh copies, pattern, element list, K, packed preconditioner, the direct solver's arrays or
+    B = K M of the single-reduction PCG, or the FP32 copies of mixed precision, solver vectors,
+    gradients), in the chunks the library carves them from.  mixed=None: the precision is picked by the
     library (AUTO), either bound.  Checked against the library's own count (sso_problem_bytes)
     in the serving tests."""
     if mixed is None:
@@ -73,8 +74,13 @@ def footprint_bytes(mesh, mixed: bool | None = False) -> int:
     bufs += [8 * 11 * 1024, 4096, 64]                                              # partials
     if mixed:
         bufs += [144 * max(blocks, padded), 4 * dinv] + [4 * ndof] * 11
-    elif nn <= FUSED_MAX_NODES:
-        bufs += [288 * max(blocks, padded)]  # B = K M in FP64 (single-reduction recurrences)
+    else:
+        # the direct solver's arrays, at most what the library lets them take (a structure that
+        # would fill more runs PCG), and its tables, some 200 bytes a node
+        direct = 288 * (math.log2(nn + 1) + 1) * (1.3 * nn + 2.6 * nb + 7.0 * nq) + (1 << 20)
+        if nn <= FUSED_MAX_NODES:   # or B = K M in FP64 (single-reduction recurrences)
+            direct = max(direct, 288 * max(blocks, padded))
+        bufs += [int(direct), 256 * nn]
     return int(1.05 * (_arena_bound(pattern) + _arena_bound(bufs))) + (1 << 20)
 
 

@@ -1,0 +1,294 @@
+// Host checks of the direct solver's plan (built with AddressSanitizer and
+// UndefinedBehaviorSanitizer, run on the CPU): on node graphs of every kind that the solver meets,
+// grids of members and quads in several numberings, chains, hubs, pieces, the plan's invariants
+// hold (check_direct_plan), and eliminating with it -- the work lists walked as the kernels walk
+// them, in plain loops over bounds-checked arrays -- solves a random symmetric positive definite
+// block system.
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <set>
+#include <string>
+#include <vector>
+
+#include "direct_plan.h"
+
+using namespace sso;
+
+struct Graph {
+  int n = 0;
+  std::vector<std::set<int>> adj;
+  explicit Graph(int n_) : n(n_), adj(n_) {
+    for (int i = 0; i < n; ++i) adj[i].insert(i);
+  }
+  void edge(int a, int b) {
+    adj[a].insert(b);
+    adj[b].insert(a);
+  }
+};
+
+static Graph quads(int mx, int my) {
+  Graph g((mx + 1) * (my + 1));
+  for (int j = 0; j < my; ++j)
+    for (int i = 0; i < mx; ++i) {
+      const int a = j * (mx + 1) + i, q[4] = {a, a + 1, a + mx + 2, a + mx + 1};
+      for (int x : q)
+        for (int y : q) g.edge(x, y);
+    }
+  return g;
+}
+static Graph members(int nx, int ny) {
+  Graph g(nx * ny);
+  for (int j = 0; j < ny; ++j)
+    for (int i = 0; i < nx; ++i) {
+      if (i + 1 < nx) g.edge(j * nx + i, j * nx + i + 1);
+      if (j + 1 < ny) g.edge(j * nx + i, j * nx + i + nx);
+    }
+  return g;
+}
+static Graph hub(int spokes) {
+  Graph g(spokes + 1);
+  for (int i = 0; i < spokes; ++i) {
+    g.edge(0, 1 + i);
+    g.edge(1 + i, 1 + (i + 1) % spokes);
+  }
+  return g;
+}
+static Graph complete(int n) {
+  Graph g(n);
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < i; ++j) g.edge(i, j);
+  return g;
+}
+static Graph pieces(const std::vector<Graph>& parts) {
+  int n = 0;
+  for (const Graph& p : parts) n += p.n;
+  Graph g(n);
+  int o = 0;
+  for (const Graph& p : parts) {
+    for (int i = 0; i < p.n; ++i)
+      for (int j : p.adj[i]) g.edge(o + i, o + j);
+    o += p.n;
+  }
+  return g;
+}
+static Graph shuffled(const Graph& g, unsigned seed) {
+  std::mt19937 r(seed);
+  std::vector<int> p(g.n);
+  for (int i = 0; i < g.n; ++i) p[i] = i;
+  for (int i = g.n - 1; i > 0; --i) std::swap(p[i], p[r() % (i + 1)]);
+  Graph s(g.n);
+  for (int i = 0; i < g.n; ++i)
+    for (int j : g.adj[i]) s.edge(p[i], p[j]);
+  return s;
+}
+
+// Sum over the children of the entry (r, c), DOF rows of front f.
+static double children(const DirectPlan& pl, const std::vector<double>& u, const DirectFront& F,
+                       int r, int c) {
+  const int cnt = (F.ns6 + F.nb6) / 6;
+  double s = 0.0;
+  for (int k = 0; k < 2; ++k) {
+    if (F.child[k] < 0) continue;
+    const DirectFront& C = pl.fronts.at(F.child[k]);
+    const int mr = pl.maps.at(F.map_off + k * cnt + r / 6);
+    const int mc = pl.maps.at(F.map_off + k * cnt + c / 6);
+    if (mr < 0 || mc < 0) continue;
+    const int a = 6 * mr + r % 6, b = 6 * mc + c % 6;
+    s += u.at(C.u_off + (int64_t)std::max(a, b) * C.nb6 + std::min(a, b));
+  }
+  return s;
+}
+
+static int run(const std::string& name, const Graph& g, bool numeric) {
+  std::vector<int32_t> rp{0}, col;
+  for (const auto& a : g.adj) {
+    col.insert(col.end(), a.begin(), a.end());
+    rp.push_back((int32_t)col.size());
+  }
+  DirectPlan pl;
+  char msg[256] = "";
+  if (!build_direct_plan(g.n, rp.data(), col.data(), 1e12, pl) ||
+      check_direct_plan(g.n, rp.data(), col.data(), pl, msg, sizeof msg) != 0) {
+    std::printf("FAIL %s: %s\n", name.c_str(), msg);
+    return 1;
+  }
+  // the plan depends on the graph alone
+  DirectPlan again;
+  build_direct_plan(g.n, rp.data(), col.data(), 1e12, again);
+  if (again.nodes != pl.nodes || again.maps != pl.maps) {
+    std::printf("FAIL %s: two plans of one graph differ\n", name.c_str());
+    return 1;
+  }
+  DirectPlan none;
+  if (build_direct_plan(g.n, rp.data(), col.data(), 8.0 * (double)pl.values() - 1.0, none)) {
+    std::printf("FAIL %s: limit not kept\n", name.c_str());
+    return 1;
+  }
+  if (!numeric) return 0;
+  // K: diagonally dominant, symmetric
+  std::mt19937 rng(7);
+  std::uniform_real_distribution<double> ud(-1.0, 1.0);
+  const int n6 = 6 * g.n;
+  std::vector<double> K(36 * col.size());
+  auto slot = [&](int I, int J) {
+    for (int e = rp[I]; e < rp[I + 1]; ++e)
+      if (col[e] == J) return e;
+    return -1;
+  };
+  for (int I = 0; I < g.n; ++I)
+    for (int e = rp[I]; e < rp[I + 1]; ++e) {
+      const int J = col[e];
+      if (J > I) continue;
+      const int m = slot(J, I);
+      for (int a = 0; a < 6; ++a)
+        for (int b = 0; b < 6; ++b) {
+          if (I == J && b > a) continue;
+          const double v = I == J && a == b ? 8.0 * (rp[I + 1] - rp[I]) : ud(rng);
+          K[36 * (size_t)e + 6 * a + b] = v;
+          K[36 * (size_t)m + 6 * b + a] = v;
+        }
+    }
+  std::vector<double> f(n6), x(n6, 0.0);
+  for (double& v : f) v = ud(rng);
+  std::vector<double> fact(pl.fact_len), f0(pl.work_len), u(pl.u_len, NAN), v(pl.v_len),
+      b(n6), seen(pl.fact_len, 0.0);
+  for (int h = 0; h < pl.levels(); ++h) {
+    const DirectRange* st = pl.steps.data() + pl.level_off[h];
+    for (int q = 0; q < st[STEP_ASM].cnt; ++q) {
+      const DirectItem it = pl.items.at(st[STEP_ASM].off + q);
+      const DirectFront& F = pl.fronts.at(it.front);
+      const int r0 = 6 * DIRECT_ASM_ROWS * it.i, c0 = 6 * DIRECT_ASM_COLS * it.j;
+      for (int r = r0; r < std::min(r0 + 6 * DIRECT_ASM_ROWS, F.ns6 + F.nb6); ++r)
+        for (int c = c0; c < std::min(c0 + 6 * DIRECT_ASM_COLS, F.ns6); ++c) {
+          f0.at(F.work_off + (int64_t)r * F.ns6 + c) = children(pl, u, F, r, c);
+          seen.at(F.fact_off + (int64_t)r * F.ns6 + c) += 1.0;
+        }
+      for (int e = it.e0; e < it.e1; ++e) {
+        const DirectEntry en = pl.entries.at(e);
+        for (int cb = 0; cb < 6; ++cb)
+          for (int ca = 0; ca < 6; ++ca)
+            f0.at(F.work_off + (int64_t)(r0 + 6 * (en.rc >> 16) + ca) * F.ns6 + c0 +
+                  6 * (en.rc & 0xffff) + cb) += K.at(36 * (size_t)en.slot + 6 * cb + ca);
+      }
+    }
+    for (int i = 0; i < (int)pl.fronts.size(); ++i) {
+      const DirectFront& F = pl.fronts[i];
+      if (F.level != h) continue;
+      const int s = F.ns6, m = F.ns6 + F.nb6;
+      for (int64_t q = 0; q < (int64_t)m * s; ++q)
+        if (seen[F.fact_off + q] != 1.0) {
+          std::printf("FAIL %s: panel entry assembled %g times\n", name.c_str(),
+                      seen[F.fact_off + q]);
+          return 1;
+        }
+      // sweep column by column; the boundary rows follow
+      std::vector<double> A(f0.begin() + F.work_off, f0.begin() + F.work_off + (int64_t)m * s);
+      for (int k = 0; k < s; ++k) {
+        const double d = 1.0 / A[k * s + k];
+        std::vector<double> ck(m), rk(A.begin() + k * s, A.begin() + (k + 1) * s);
+        for (int r = 0; r < m; ++r) ck[r] = A[r * s + k];
+        for (int r = 0; r < m; ++r)
+          for (int c = 0; c < s; ++c)
+            A[r * s + c] = r == k ? (c == k ? -d : rk[c] * d)
+                                  : (c == k ? ck[r] * d : A[r * s + c] - ck[r] * d * rk[c]);
+      }
+      std::copy(A.begin(), A.end(), fact.begin() + F.fact_off);
+      for (int r = 0; r < F.nb6; ++r)
+        for (int c = 0; c <= r; ++c) {
+          double t = children(pl, u, F, s + r, s + c);
+          for (int k = 0; k < s; ++k)
+            t -= A[(s + r) * s + k] * f0[F.work_off + (int64_t)(s + c) * s + k];
+          u.at(F.u_off + (int64_t)r * F.nb6 + c) = t;
+        }
+    }
+  }
+  auto up = [&](const DirectFront& F, int r) {
+    const int cnt = (F.ns6 + F.nb6) / 6;
+    double t = 0.0;
+    for (int k = 0; k < 2; ++k) {
+      const int mm = pl.maps.at(F.map_off + k * cnt + r / 6);
+      if (mm >= 0) t += v.at(pl.fronts.at(F.child[k]).v_off + 6 * mm + r % 6);
+    }
+    return t;
+  };
+  for (int h = 0; h < pl.levels(); ++h) {
+    const DirectRange r = pl.steps[pl.level_off[h] + STEP_FWD];
+    for (int q = 0; q < r.cnt; ++q) {
+      const DirectItem it = pl.items.at(r.off + q);
+      const DirectFront& F = pl.fronts.at(it.front);
+      for (int c = 0; c < F.ns6; ++c)
+        b.at(F.b_off + c) = f.at(6 * pl.nodes.at(F.nodes_off + c / 6) + c % 6) + up(F, c);
+      for (int k = it.i * DIRECT_FWD_ROWS; k < std::min(F.nb6, (it.i + 1) * DIRECT_FWD_ROWS); ++k) {
+        double t = up(F, F.ns6 + k);
+        for (int c = 0; c < F.ns6; ++c)
+          t -= fact.at(F.fact_off + (int64_t)(F.ns6 + k) * F.ns6 + c) * b[F.b_off + c];
+        v.at(F.v_off + k) = t;
+      }
+    }
+  }
+  for (int h = pl.levels() - 1; h >= 0; --h) {
+    const DirectRange r = pl.steps[pl.level_off[h] + STEP_BWD];
+    for (int q = 0; q < r.cnt; ++q) {
+      const DirectItem it = pl.items.at(r.off + q);
+      const DirectFront& F = pl.fronts.at(it.front);
+      for (int c = it.i * DIRECT_BWD_COLS; c < std::min(F.ns6, (it.i + 1) * DIRECT_BWD_COLS); ++c) {
+        double t = 0.0;
+        for (int k = 0; k < F.ns6 + F.nb6; ++k) {
+          const int node = pl.nodes.at(F.nodes_off + k / 6);
+          t -= fact.at(F.fact_off + (int64_t)k * F.ns6 + c) *
+               (k < F.ns6 ? b[F.b_off + k] : x.at(6 * node + k % 6));
+        }
+        x.at(6 * pl.nodes.at(F.nodes_off + c / 6) + c % 6) = t;
+      }
+    }
+  }
+  double worst = 0.0;
+  for (int I = 0; I < g.n; ++I)
+    for (int a = 0; a < 6; ++a) {
+      double t = f[6 * I + a];
+      for (int e = rp[I]; e < rp[I + 1]; ++e)
+        for (int c = 0; c < 6; ++c) t -= K[36 * (size_t)e + 6 * a + c] * x[6 * col[e] + c];
+      worst = std::fmax(worst, std::fabs(t));
+    }
+  // K is diagonally dominant with entries of order 1 to 1000: a backward stable solve leaves
+  // some n_terms * eps * |K| |x|, far below 1e-11
+  if (!(worst <= 1e-11)) {
+    std::printf("FAIL %s: residual %g\n", name.c_str(), worst);
+    return 1;
+  }
+  return 0;
+}
+
+int main() {
+  int bad = 0;
+  struct {
+    const char* name;
+    Graph g;
+    bool numeric;
+  } all[] = {
+      {"one node", Graph(1), true},
+      {"two nodes", members(2, 1), true},
+      {"one quad", quads(1, 1), true},
+      {"leaf", members(5, 2), true},
+      {"leaf and one more", members(11, 1), true},
+      {"quads 9x7", quads(9, 7), true},
+      {"quads 16x16", quads(16, 16), true},
+      {"quads 3x60", quads(3, 60), true},
+      {"members 13x13", members(13, 13), true},
+      {"chain", members(400, 1), true},
+      {"chain, shuffled", shuffled(members(301, 1), 3), true},
+      {"quads 11x14, shuffled", shuffled(quads(11, 14), 5), true},
+      {"hub", hub(20), true},
+      {"large hub", hub(90), true},
+      {"complete", complete(25), true},
+      {"no edges", Graph(9), true},
+      {"pieces", pieces({quads(4, 4), Graph(1), members(30, 1), hub(12), quads(7, 2)}), true},
+      {"quads 60x60", quads(60, 60), false},
+      {"quads 80x70, shuffled", shuffled(quads(80, 70), 9), false},
+  };
+  for (auto& c : all) bad += run(c.name, c.g, c.numeric);
+  std::printf("%s (%d failures)\n", bad ? "failed" : "ok", bad);
+  return bad ? 1 : 0;
+}
