@@ -87,13 +87,14 @@ enum { SSO_PREC_FP64 = 0, SSO_PREC_MIXED = 1, SSO_PREC_AUTO = 2 };
 /* PCG recurrences.  STANDARD: Hestenes-Stiefel CG, two kernels and two reductions per
  * iteration.  FUSED: the single-reduction form of Chronopoulos & Gear (one kernel and one
  * reduction per iteration; keeps B = K M, M the block-Jacobi inverse, beside K: one more array
- * of K's size).  AUTO: sso_solve in FP64 solves
- * directly (multifrontal elimination in a nested dissection order, refined on the true residual
- * until rtol is met; no PCG iterations) where the solver's arrays stay within what a surface
- * structure fills, some 2 KB per node and doubling of the node count.  Measured against the
- * recurrences named below, one design step: 11 x 11 grid-shell 0.55 against 3.3 ms, 60 x 60 shell
- * 1.9 against 16 ms, 300 x 300 shell 20 against 510 ms.  A structure that fills more, a K that is
- * not positive definite to working precision, or a target below what refinement reaches runs PCG:
+ * of K's size).  AUTO solves directly
+ * (multifrontal elimination in FP64 in a nested dissection order, refined on the true residual
+ * until rtol is met; no PCG iterations), single and begun solves alike, where the solver's arrays
+ * stay within what a surface structure fills, some 2 KB per node and doubling of the node count.
+ * Measured against the recurrences named below, one design step: 11 x 11 grid-shell 0.51 against
+ * 3.2 ms, 60 x 60 shell 1.6 against 14 ms, 300 x 300 shell 19 against 480 ms; 16 served requests
+ * of 8 to 60 a side 16 against 100 ms.  A structure that fills more, a K that is not positive
+ * definite to working precision, or a target below what refinement reaches runs PCG:
  * sso_solve takes WG for FP64 problems resident in one workgroup's LDS
  * (at most 144 nodes; measured 3.07 against 4.39 ms on the 121-node grid-shell), FUSED up to
  * 8,192 nodes (latency-bound sizes; 13.4 against 20.2 ms on a 60 x 60 shell, equal on 90 x 90,
@@ -130,8 +131,9 @@ typedef struct {
 } sso_mesh;
 
 typedef struct {
-  int32_t precision;          /* SSO_PREC_FP64, SSO_PREC_AUTO (above), or SSO_PREC_MIXED:
-                                 FP64 flexible CG (one
+  int32_t precision;          /* SSO_PREC_FP64, SSO_PREC_AUTO (above), or SSO_PREC_MIXED.  Where
+                                 SSO_SOLVER_AUTO solves directly, mixed precision does so too
+                                 (in FP64 throughout); otherwise FP64 flexible CG (one
                                  stored direction) whose preconditioner is an FP32 PCG solve
                                  (FP32 K, vectors, SpMV and dot accumulation); element
                                  stiffness, the outer products with K, the step lengths and
@@ -166,7 +168,8 @@ typedef struct {
                                  recurrences, k_cg1_iter1 of the single-reduction ones       */
   int32_t spmv_samples;       /* number of sampled iterations                                */
   double spmv_bytes;          /* algorithmic bytes of one iteration                          */
-  int32_t refine_steps;       /* mixed precision: outer steps (FP32 inner solves) run        */
+  int32_t refine_steps;       /* mixed precision: outer steps run (FP32 inner solves, or
+                                 substitutions of a direct solve)                            */
   int32_t solver;             /* SSO_SOLVER_STANDARD, _FUSED or _WG: recurrences that ran;
                                  SSO_SOLVER_AUTO: solved directly                            */
   int32_t sym_products;       /* 1: the standard recurrences' products read only K's upper
@@ -235,8 +238,8 @@ int sso_solve(sso_problem* p, double* u_out, sso_stats* stats);
 
 /* Forward analysis split for multi-problem launches: sso_solve_begin runs everything up to the
  * first PCG iteration (elements, loads, assembly, masking, block-Jacobi, PCG initialisation),
- * FP64 or mixed precision, either recurrence (SSO_SOLVER_AUTO picks STANDARD here: the faster
- * form when many problems share the launches); sso_batch_iterate then advances many begun
+ * FP64 or mixed precision, either recurrence (where SSO_SOLVER_AUTO does not solve directly it
+ * picks STANDARD here: the faster form when many problems share the launches); sso_batch_iterate then advances many begun
  * problems together (mixed precision: including the FP64 outer steps between FP32 inner
  * solves); sso_solve_end finishes one (FP64 correction of the true residual, u_out as in
  * sso_solve, stats) once its iteration has stopped.  With the same precision and recurrence,
@@ -250,7 +253,9 @@ typedef struct sso_batch sso_batch;
 int sso_batch_create(hipStream_t stream, sso_batch** out);
 /* Launch n_iter PCG iterations for every problem of ps[0..n) whose iteration has not stopped,
  * all problems of one recurrence kind (sso_options.solver at sso_solve_begin) in one launch per
- * kernel, then read back their states: done[i] (host, may be NULL) = 1 when problem i's
+ * kernel -- for a problem that is solved directly, its factorisation and first solution, then one
+ * refinement step a call (all such problems in one launch per kernel); one whose elimination plan
+ * is still being made by the library's host thread is left for a later call -- then read back their states: done[i] (host, may be NULL) = 1 when problem i's
  * iteration has stopped (converged, limit or breakdown).  Errors: SSO_EINVAL (problem not
  * begun, on another stream, or listed twice), SSO_EHIP. */
 int sso_batch_iterate(sso_batch* b, sso_problem* const* ps, int n, int n_iter, int32_t* done);
@@ -382,7 +387,7 @@ int sso_matrix(sso_problem* p, double* vals, double* f);
  * its behalf so far -- mesh copies, pattern, element list, K, preconditioner, solver vectors, and
  * what later calls added (mixed-precision copies, the size objective's scratch, the scalar CSR
  * view) -- all kept until sso_problem_destroy; buffers freed within a call are not counted.
- * Buffers above 512 KiB are taken one by one; smaller ones are carved from 2 MiB chunks, counted
+ * Buffers above 512 KiB are taken one by one, their sizes rounded up to eighths of a power of two; smaller ones are carved from 2 MiB chunks, counted
  * whole (a chunk is left for a new one only with less than 512 KiB free).  For admission by
  * memory footprint in a request loop.  Errors: SSO_EINVAL (NULL argument). */
 int sso_problem_bytes(const sso_problem* p, int64_t* bytes);
@@ -398,7 +403,7 @@ void sso_problem_destroy(sso_problem* p);
 
 /* Device memory: every buffer the library allocates comes from a memory pool of its own on the
  * problem's device, which keeps freed memory for the next allocation instead of returning it to
- * the driver (a request loop creates and destroys problems of recurring sizes; mapping fresh
+ * the driver, and an ended problem's chunks (up to 8 GiB of them) are kept whole for the next (a request loop creates and destroys problems of recurring sizes; mapping fresh
  * memory each time cost about 1 ms per problem).  The pool therefore holds up to the peak of what
  * problems held at once.  sso_pool_trim releases what the pool holds beyond keep_bytes of unused
  * memory back to the driver; memory freed on a stream whose work has not completed is released

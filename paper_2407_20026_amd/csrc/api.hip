@@ -2,11 +2,15 @@
 // the problem's stream, error mapping and per-stage timing.
 #include <new>
 #include <atomic>
+#include <condition_variable>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <mutex>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "sso_internal.h"
@@ -22,18 +26,34 @@ static_assert(SSO_NOALLOC_MAX_QUADS * 15 + 2 * 1024 <=
                   (int64_t)(SSO_NOALLOC_SCRATCH_BYTES / sizeof(double)),
               "the no-allocation scratch holds the partials and 15 values per quad");
 
+// Signalled whenever a direct solver's plan is done, for launches that have nothing else to do.
+static std::mutex plan_mutex;
+static std::condition_variable plan_cv;
+
 // A block pattern shared by the problems of one topology (sso_problem_create_like); the last
 // problem to be destroyed frees it.
 struct SharedPattern {
   Pattern pat;
   std::atomic<int> refs{1};
-  // the direct solver's plan, built by the first solve that may use it (under the mutex; read-only
-  // afterwards); its device tables live in the pattern's arena
+  // The direct solver's plan: built by a thread of its own while the creating call and the ones
+  // after it go on (or by the first solve that may use it), uploaded by that solve.  Under the
+  // mutex until READY or REFUSED, read-only afterwards; the host tables stay until the pattern
+  // ends, so the upload is not waited for.
   std::mutex direct_mutex;
-  enum { DIRECT_UNKNOWN, DIRECT_READY, DIRECT_REFUSED };
-  int direct_state = DIRECT_UNKNOWN;
+  enum { DIRECT_UNKNOWN, DIRECT_BUILT, DIRECT_READY, DIRECT_REFUSED };
+  std::atomic<int> direct_state{DIRECT_UNKNOWN};
+  std::vector<int32_t> brow, bcol;       // the pattern on the host, until the plan is built
+  std::thread builder;
+  bool builder_started = false;          // set by the creating call
+  std::atomic<bool> builder_done{false};
+  bool built = false;                    // the builder's result, read after joining it
   DirectPlan plan;
-  DirectArgs tables{};
+  DirectArgs tables{};                   // device tables, in the pattern's arena
+  hipEvent_t uploaded = nullptr;         // orders other streams after the upload
+  ~SharedPattern() {
+    if (builder.joinable()) builder.join();
+    if (uploaded) (void)hipEventDestroy(uploaded);
+  }
 };
 
 struct sso_problem {
@@ -74,6 +94,9 @@ struct sso_problem {
   bool direct = false;          // the last solve chose the direct solver
   bool factored = false;        // its factor is that of the current K
   DirectArgs da{};              // its arrays (allocated on first use)
+  int direct_steps = 0;         // substitutions of the last solve
+  double direct_rr = -1.0, direct_bb = 0.0;   // its last true residual and load, squared norms
+  bool direct_done = false;     // begun solve: nothing left to iterate
   bool solved = false;
   bool in_batch = false;        // started with sso_solve_begin, not yet finished
   bool batch_pending = false;   // listed in a multi-problem launch not yet waited for
@@ -93,6 +116,9 @@ struct sso_batch {
   bool pending = false;                  // a launch not yet waited for
   std::vector<sso_problem*> listed;      // its problem list, in the caller's order
   std::vector<int> idx[5];               // positions in that list by launch kind
+  DirectBatch db;                        // the direct solver's part of a launch
+  std::vector<int> direct;               // its positions in the list
+  bool idle = false;                     // the launch found nothing to do yet
   // sso_batch_profile: timing samples of the FP64 standard iterations
   int prof_every = 0, prof_span = 0;
   int64_t prof_calls = 0;                // launches that could be sampled so far
@@ -104,6 +130,8 @@ struct sso_batch {
 
 namespace {
 
+constexpr int MAX_DEVICES = 64;
+
 // Most device memory that the direct solver's numeric arrays may take: what the fill of a surface
 // structure (grid-shell or shell of any outline) or of a chain needs, which grows as n log n.  A
 // structure that fills more (members joined in space; a solid lattice of 20 x 20 x 20 nodes takes
@@ -111,7 +139,7 @@ namespace {
 // keeps it.  The serving loops' admission bounds a request's memory by the same formula.
 double direct_max_bytes(const Mesh& m) {
   const double n = m.n_nodes;
-  return 288.0 * (std::log2(n + 1.0) + 1.0) * (1.3 * n + 2.6 * m.n_beams + 7.0 * m.n_quads) +
+  return 288.0 * (std::log2(n + 1.0) + 1.0) * (1.2 * n + 2.3 * m.n_beams + 6.3 * m.n_quads) +
          1048576.0;
 }
 
@@ -184,22 +212,27 @@ void free_problem(sso_problem* p) {
                   (void*)p->perm, (void*)p->seg, (void*)m.u_presc, (void*)p->fm,
                   (void*)p->gw, (void*)p->wv, (void*)p->xpart})
     dev_release(q, &p->mem, s);
-  if (p->shared) {
-    if (p->shared->refs.fetch_sub(1) == 1) {   // the last problem of this topology
-      free_pattern(p->shared->pat, s);
-      delete p->shared;
-    }
-  } else {
-    free_pattern(p->pat, s);
-  }
   pcg_free(p->w, &p->mem, s);
-  arena_free(p->mem, s);
   delete[] p->h_scal;
   delete p->h_err;
   for (auto& e : p->ev)
     if (e) (void)hipEventDestroy(e);
   if (p->ev_move) (void)hipEventDestroy(p->ev_move);
-  (void)hipStreamSynchronize(s);
+  // the chunks are idle once the stream is: for the next problem, unless the device has failed
+  const bool idle = hipStreamSynchronize(s) == hipSuccess;
+  if (p->shared) {
+    if (p->shared->refs.fetch_sub(1) == 1) {   // the last problem of this topology
+      if (p->shared->builder.joinable()) p->shared->builder.join();
+      free_pattern(p->shared->pat, s, idle);
+      delete p->shared;
+    }
+  } else {
+    free_pattern(p->pat, s, idle);
+  }
+  if (idle)
+    arena_recycle(p->mem, s);
+  else
+    arena_free(p->mem, s);
   delete p;
 }
 
@@ -271,8 +304,35 @@ __global__ void k_same_topology(int64_t n, const int32_t* a, const int32_t* b, u
   if (i < n && a[i] != b[i]) atomicOr(err, ERR_TOPO);
 }
 
+// Builds the direct solver's plan from the pattern's host copy; never throws.
+void make_plan(SharedPattern* sh, double max_bytes) {
+  try {
+    sh->built = build_direct_plan((int)sh->brow.size() - 1, sh->brow.data(), sh->bcol.data(),
+                                  max_bytes, sh->plan);
+  } catch (...) {   // out of host memory: PCG needs none of this
+    sh->built = false;
+  }
+}
+
+void start_plan(SharedPattern* sh, const Mesh& m) {
+  const double max_bytes = direct_max_bytes(m);
+  try {
+    sh->builder = std::thread([sh, max_bytes] {
+      make_plan(sh, max_bytes);
+      {
+        std::lock_guard<std::mutex> lock(plan_mutex);
+        sh->builder_done = true;
+      }
+      plan_cv.notify_all();
+    });
+    sh->builder_started = true;
+  } catch (const std::system_error&) {   // no thread to be had: the first solve builds it
+  }
+}
+
+// scratch: buffers that only the creation uses, idle once it has synchronised the stream.
 int create_impl(const sso_mesh* mesh, const sso_options* opts, hipStream_t stream,
-                sso_problem* p, const sso_problem* like) {
+                sso_problem* p, const sso_problem* like, Arena& scratch) {
   p->s = stream;
   TRY_HIP(hipGetDevice(&p->device));
   p->opt = opts ? *opts : default_options();
@@ -345,12 +405,26 @@ int create_impl(const sso_mesh* mesh, const sso_options* opts, hipStream_t strea
   } else {
     {
       AllocScope ps(&p->bytes, &p->pat.mem);   // the pattern outlives this problem if shared
-      TRY_HIP(build_pattern(m, p->pat, p->d_err, s, p->h_err));
+      TRY_HIP(build_pattern(m, p->pat, p->d_err, s, p->h_err, scratch));
     }
     if (*p->h_err) return SSO_EINVAL;
     p->shared = new (std::nothrow) SharedPattern();
     if (!p->shared) return SSO_ENOMEM;
     p->shared->pat = p->pat;
+    if (p->opt.solver == SSO_SOLVER_AUTO) {
+      // the pattern for the direct solver's plan (its build starts after the synchronisation below)
+      SharedPattern* sh = p->shared;
+      try {
+        sh->brow.resize(nn + 1);
+        sh->bcol.resize(p->pat.n_blocks);
+      } catch (...) {
+        return SSO_ENOMEM;
+      }
+      TRY_HIP(hipMemcpyAsync(sh->brow.data(), p->pat.brow_ptr, sizeof(int32_t) * sh->brow.size(),
+                             hipMemcpyDeviceToHost, s));
+      TRY_HIP(hipMemcpyAsync(sh->bcol.data(), p->pat.bcol, sizeof(int32_t) * sh->bcol.size(),
+                             hipMemcpyDeviceToHost, s));
+    }
     if (debug_mode()) {
       const int st = debug_check_pattern(p);
       if (st != SSO_OK) return st;
@@ -372,6 +446,7 @@ int create_impl(const sso_mesh* mesh, const sso_options* opts, hipStream_t strea
   if (like) TRY_HIP(hipMemcpyAsync(p->h_err, p->d_err, sizeof(unsigned), hipMemcpyDeviceToHost, s));
   TRY_HIP(hipStreamSynchronize(s));
   if (like && *p->h_err) return SSO_EINVAL;
+  if (!like && p->opt.solver == SSO_SOLVER_AUTO) start_plan(p->shared, m);
   return SSO_OK;
 }
 
@@ -399,11 +474,14 @@ int sso_problem_create(const sso_mesh* mesh, const sso_options* opts, hipStream_
   sso_problem* p = new (std::nothrow) sso_problem();
   if (!p) return SSO_ENOMEM;
   AllocScope ac(&p->bytes, &p->mem);
-  int st = create_impl(mesh, opts, stream, p, nullptr);
+  Arena scratch;
+  int st = create_impl(mesh, opts, stream, p, nullptr, scratch);
   if (st != SSO_OK) {
+    arena_free(scratch, stream);
     free_problem(p);
     return st;
   }
+  arena_recycle(scratch, stream);
   *out = p;
   return SSO_OK;
 }
@@ -424,11 +502,14 @@ int sso_problem_create_like(const sso_problem* like, const sso_mesh* mesh,
   sso_problem* p = new (std::nothrow) sso_problem();
   if (!p) return SSO_ENOMEM;
   AllocScope ac(&p->bytes, &p->mem);
-  int st = create_impl(mesh, opts, stream, p, like);
+  Arena scratch;
+  int st = create_impl(mesh, opts, stream, p, like, scratch);
   if (st != SSO_OK) {
+    arena_free(scratch, stream);
     free_problem(p);
     return st;
   }
+  arena_recycle(scratch, stream);
   *out = p;
   return SSO_OK;
 }
@@ -466,7 +547,9 @@ bool mixed(const sso_problem* p) { return mixed_for(p->opt, p->pat.n_blocks); }
 bool fused(const sso_problem* p) { return p->solver_used == SSO_SOLVER_FUSED; }
 bool one_wg(const sso_problem* p) { return p->solver_used == SSO_SOLVER_WG; }
 // iteration of a begun problem has stopped (mixed precision: the refinement loop has)
-bool stopped(const sso_problem* p) { return mixed(p) ? p->ms.done : p->w.h_st->done != 0; }
+bool stopped(const sso_problem* p) {
+  return p->direct ? p->direct_done : mixed(p) ? p->ms.done : p->w.h_st->done != 0;
+}
 
 MixedParams mixed_params(const sso_problem* p) {
   MixedParams mp;
@@ -484,72 +567,91 @@ MixedParams mixed_params(const sso_problem* p) {
   return mp;
 }
 
-// The direct solver's plan and tables for the problem's topology, built on first use; false: the
-// direct solver is not for this structure.
+// The direct solver's plan and tables for the problem's topology, on the device by the time the
+// problem's stream gets there; *ready false: the direct solver is not for this structure.
 int direct_tables(sso_problem* p, bool* ready) {
   SharedPattern* sh = p->shared;
+  hipStream_t s = p->s;
+  *ready = false;
   std::lock_guard<std::mutex> lock(sh->direct_mutex);
   if (sh->direct_state == SharedPattern::DIRECT_UNKNOWN) {
-    const int n = p->m.n_nodes;
-    hipStream_t s = p->s;
-    DirectPlan& pl = sh->plan;
-    bool ok = false;
-    try {
-      std::vector<int32_t> rp(n + 1), col(p->pat.n_blocks);
-      TRY_HIP(hipMemcpyAsync(rp.data(), p->pat.brow_ptr, sizeof(int32_t) * rp.size(),
-                             hipMemcpyDeviceToHost, s));
-      TRY_HIP(hipMemcpyAsync(col.data(), p->pat.bcol, sizeof(int32_t) * col.size(),
-                             hipMemcpyDeviceToHost, s));
-      TRY_HIP(hipStreamSynchronize(s));
-      ok = build_direct_plan(n, rp.data(), col.data(), direct_max_bytes(p->m), pl);
-      if (ok && debug_mode()) {
-        char msg[256];
-        if (check_direct_plan(n, rp.data(), col.data(), pl, msg, sizeof msg) != 0) {
-          std::fprintf(stderr, "hipsso debug: %s\n", msg);
-          return SSO_EINVAL;
-        }
-      }
-    } catch (...) {   // out of host memory
-      ok = false;
-    }
-    if (ok) {
-      AllocScope ts(&p->bytes, &sh->pat.mem);
-      DirectArgs& t = sh->tables;
-      auto put = [&](auto** dst, const auto& v) {
-        using V = typename std::decay_t<decltype(v)>::value_type;
-        V* d = nullptr;
-        hipError_t e = dev_alloc(&d, (int64_t)v.size(), s);
-        if (e == hipSuccess && !v.empty())
-          e = hipMemcpyAsync(d, v.data(), sizeof(V) * v.size(), hipMemcpyHostToDevice, s);
-        *dst = d;
-        return e;
-      };
-      TRY_HIP(put(&t.fronts, pl.fronts));
-      TRY_HIP(put(&t.nodes, pl.nodes));
-      TRY_HIP(put(&t.maps, pl.maps));
-      TRY_HIP(put(&t.entries, pl.entries));
-      TRY_HIP(put(&t.items, pl.items));
-      TRY_HIP(put(&t.steps, pl.steps));
-      TRY_HIP(put(&t.level_off, pl.level_off));
-      TRY_HIP(put(&t.level_np, pl.level_np));
-      TRY_HIP(hipStreamSynchronize(s));
-      t.n_levels = pl.levels();
-      t.bdiag = p->pat.bdiag;
-      pl.drop_tables();
+    if (sh->builder.joinable()) {
+      sh->builder.join();
     } else {
-      pl = DirectPlan();
+      try {
+        sh->brow.resize(p->m.n_nodes + 1);
+        sh->bcol.resize(p->pat.n_blocks);
+      } catch (...) {
+        return SSO_ENOMEM;
+      }
+      TRY_HIP(hipMemcpyAsync(sh->brow.data(), p->pat.brow_ptr, sizeof(int32_t) * sh->brow.size(),
+                             hipMemcpyDeviceToHost, s));
+      TRY_HIP(hipMemcpyAsync(sh->bcol.data(), p->pat.bcol, sizeof(int32_t) * sh->bcol.size(),
+                             hipMemcpyDeviceToHost, s));
+      TRY_HIP(hipStreamSynchronize(s));
+      make_plan(sh, direct_max_bytes(p->m));
     }
-    sh->direct_state = ok ? SharedPattern::DIRECT_READY : SharedPattern::DIRECT_REFUSED;
+    if (sh->built && debug_mode()) {
+      char msg[256];
+      if (check_direct_plan(p->m.n_nodes, sh->brow.data(), sh->bcol.data(), sh->plan, msg,
+                            sizeof msg) != 0) {
+        std::fprintf(stderr, "hipsso debug: %s\n", msg);
+        return SSO_EINVAL;
+      }
+    }
+    sh->brow = {};
+    sh->bcol = {};
+    sh->direct_state = sh->built ? SharedPattern::DIRECT_BUILT : SharedPattern::DIRECT_REFUSED;
+  }
+  if (sh->direct_state == SharedPattern::DIRECT_BUILT) {
+    AllocScope ts(&p->bytes, &sh->pat.mem);
+    DirectPlan& pl = sh->plan;
+    DirectArgs t{};
+    auto put = [&](auto** dst, const auto& v) {
+      using V = typename std::decay_t<decltype(v)>::value_type;
+      V* d = nullptr;
+      hipError_t e = dev_alloc(&d, (int64_t)v.size(), s);
+      if (e == hipSuccess && !v.empty())
+        e = hipMemcpyAsync(d, v.data(), sizeof(V) * v.size(), hipMemcpyHostToDevice, s);
+      *dst = d;
+      return e;
+    };
+    TRY_HIP(put(&t.fronts, pl.fronts));
+    TRY_HIP(put(&t.nodes, pl.nodes));
+    TRY_HIP(put(&t.maps, pl.maps));
+    TRY_HIP(put(&t.entries, pl.entries));
+    TRY_HIP(put(&t.items, pl.items));
+    TRY_HIP(put(&t.steps, pl.steps));
+    TRY_HIP(put(&t.level_off, pl.level_off));
+    TRY_HIP(put(&t.level_np, pl.level_np));
+    if (!sh->uploaded)
+      TRY_HIP(hipEventCreateWithFlags(&sh->uploaded, hipEventDisableTiming));
+    TRY_HIP(hipEventRecord(sh->uploaded, s));
+    t.n_levels = pl.levels();
+    t.bdiag = p->pat.bdiag;
+    sh->tables = t;
+    sh->direct_state = SharedPattern::DIRECT_READY;
   }
   *ready = sh->direct_state == SharedPattern::DIRECT_READY;
   return SSO_OK;
 }
 
-// Whether the direct solver takes the coming solve, with its arrays in place if so.
-int choose_direct(sso_problem* p) {
-  p->factored = false;
+// Whether the direct solver takes the coming solve: decided when the solve starts for a single
+// one (with the solver's arrays in place), at the first launch for a begun one (direct_attach).
+bool may_be_direct(const sso_problem* p) {
+  return p->opt.solver == SSO_SOLVER_AUTO && p->shared->direct_state != SharedPattern::DIRECT_REFUSED;
+}
+
+// Whether the plan is still in the making.
+bool plan_pending(const sso_problem* p) {
+  const SharedPattern* sh = p->shared;
+  return sh->direct_state == SharedPattern::DIRECT_UNKNOWN && sh->builder_started &&
+         !sh->builder_done;
+}
+
+// The solver's arrays; p->direct becomes false where it does not apply.
+int direct_attach(sso_problem* p) {
   p->direct = false;
-  if (p->opt.solver != SSO_SOLVER_AUTO || mixed(p)) return SSO_OK;
   bool ready = false;
   const int st = direct_tables(p, &ready);
   if (st != SSO_OK || !ready) return st;
@@ -557,6 +659,7 @@ int choose_direct(sso_problem* p) {
     const DirectPlan& pl = p->shared->plan;
     const int64_t n = 6 * (int64_t)p->m.n_nodes;
     DirectArgs a = p->shared->tables;
+    TRY_HIP(hipStreamWaitEvent(p->s, p->shared->uploaded, 0));
     double* d = nullptr;
     const hipError_t e = dev_alloc(&d, pl.values() + 2, p->s);   // one buffer, cut below
     if (e == hipErrorOutOfMemory) {
@@ -585,53 +688,85 @@ int choose_direct(sso_problem* p) {
   return SSO_OK;
 }
 
+// What follows from the squared norms rr of the true residual and bb of the load after a
+// substitution: the target is met, another substitution on the residual is worth it, refinement
+// has done what it can (the rest is for PCG's corrections), or the factor is no good.
+enum DirectNext { DIRECT_MET, DIRECT_AGAIN, DIRECT_STUCK, DIRECT_FAILED };
+DirectNext direct_next(sso_problem* p, double rr, double bb, unsigned flag) {
+  constexpr int MAX_STEPS = 7;
+  const double rn = std::sqrt(rr), bn = std::sqrt(bb);
+  const double prev = p->direct_rr < 0.0 ? -1.0 : std::sqrt(p->direct_rr);
+  p->direct_rr = rr;
+  p->direct_bb = bb;
+  const int step = ++p->direct_steps;
+  if (flag || !std::isfinite(rn)) return DIRECT_FAILED;
+  p->factored = true;
+  // a first solution that only just meets the target takes one more step: a refined one is
+  // orders of magnitude below it
+  if (rn <= (step == 1 ? 0.5 : 1.0) * p->opt.rtol * bn) return DIRECT_MET;
+  if (step == MAX_STEPS || (prev >= 0.0 && rn > 0.5 * prev)) return DIRECT_STUCK;
+  return DIRECT_AGAIN;
+}
+
 // K x = b with the direct solver: factor K if the current one is not yet factored, substitute,
 // and refine on the true residual (row sums in double-double) until it meets rtol, as long as a
 // step gains a factor of two.  *done: met; otherwise x is the best so far.  A K that is not
-// positive definite to working precision leaves *done false and x = 0.
+// positive definite to working precision leaves p->direct false and x = 0.
 int run_direct(sso_problem* p, const double* b, double* x, bool* done) {
   hipStream_t s = p->s;
   const DirectPlan& pl = p->shared->plan;
-  DirectArgs& a = p->da;
+  const DirectArgs& a = p->da;
   const int64_t n = 6 * (int64_t)p->m.n_nodes;
   *done = false;
   if (!p->factored) {
-    TRY_HIP(hipMemsetAsync(a.flag, 0, sizeof(unsigned), s));
+    TRY_HIP(launch_direct_clear(a, s));
     TRY_HIP(launch_direct_factor(pl, a, s));
   }
   DirectArgs q = a;
   q.rhs = b;
   q.sol = x;
   TRY_HIP(launch_direct_solve(pl, q, s));
-  double prev = -1.0;
-  constexpr int MAX_STEPS = 6;
-  for (int step = 0;; ++step) {
+  p->direct_rr = -1.0;
+  p->direct_steps = 0;
+  for (;;) {
     TRY_HIP(launch_true_residual(p->m, p->pat, p->K, x, b, p->w.r, p->w, p->d_scal, s));
     unsigned flag = 0;
     TRY_HIP(hipMemcpyAsync(p->h_scal, p->d_scal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     if (!p->factored)
       TRY_HIP(hipMemcpyAsync(&flag, a.flag, sizeof(unsigned), hipMemcpyDeviceToHost, s));
     TRY_HIP(hipStreamSynchronize(s));
-    const double rn = std::sqrt(p->h_scal[0]), bn = std::sqrt(p->h_scal[1]);
-    if (flag || !std::isfinite(rn)) {
+    const bool was = p->factored;
+    const DirectNext next = direct_next(p, p->h_scal[0], p->h_scal[1], flag);
+    if (next == DIRECT_FAILED && was) {   // a good factor: the right-hand side is not finite
+      *done = true;
+      return SSO_EBREAKDOWN;
+    }
+    if (next == DIRECT_FAILED) {
       TRY_HIP(hipMemsetAsync(x, 0, sizeof(double) * n, s));
       p->direct = false;
       return SSO_OK;
     }
-    p->factored = true;
-    // a first solution that only just meets the target takes one more step: a refined one is
-    // orders of magnitude below it
-    if (rn <= (step == 0 ? 0.5 : 1.0) * p->opt.rtol * bn) {
-      *done = true;
+    if (next != DIRECT_AGAIN) {
+      *done = next == DIRECT_MET;
       return SSO_OK;
     }
-    if (step == MAX_STEPS || (prev >= 0.0 && rn > 0.5 * prev)) return SSO_OK;
-    prev = rn;
     q.rhs = p->w.r;
     q.sol = a.sol;
     TRY_HIP(launch_direct_solve(pl, q, s));
     TRY_HIP(launch_axpy(1.0, a.sol, x, n, s));
   }
+}
+
+// The FP32 copies that mixed precision's standard inner solves need, where the direct solver was
+// to do without them.
+int mixed_operands(sso_problem* p) {
+  hipStream_t s = p->s;
+  const int64_t nk = 36 * p->pat.n_blocks;
+  if (!p->Dinv32) TRY_HIP(dev_alloc(&p->Dinv32, dinv_packed_len(p->m.n_nodes), s));
+  if (!p->K32) TRY_HIP(dev_alloc(&p->K32, nk, s));
+  TRY_HIP(launch_block_jacobi(p->m, p->pat, p->K, p->Dinv, p->Dinv32, p->d_err, s));
+  TRY_HIP(launch_convert_f32(p->K, p->K32, nk, s));
+  return SSO_OK;
 }
 
 // Solve K x = b (b masked) in the problem's precision mode.
@@ -641,11 +776,16 @@ int run_solver(sso_problem* p, const double* b, double* x, int* iters, int* oute
   if (p->direct) {
     bool done = false;
     const int st = run_direct(p, b, x, &done);
+    if (mixed(p)) *outer = p->direct_steps;
     if (st != SSO_OK || done) return st;
     if (p->direct) {   // the target lies below what refinement reaches: corrections by PCG
       TRY_HIP(pcg_correct(p->m, p->pat, p->K, p->Dinv, b, x, p->opt.rtol, p->opt.max_it, p->w,
                           p->s, iters, &status));
       return status;
+    }
+    if (mixed(p)) {
+      const int sm = mixed_operands(p);
+      if (sm != SSO_OK) return sm;
     }
   }
   if (one_wg(p)) {
@@ -676,13 +816,20 @@ int prepare(sso_problem* p, bool batch) {
   // median latency 14.5 -> 5.1 ms at the same capacity).
   if (batch && p->opt.solver == SSO_SOLVER_AUTO && p->solver_used != SSO_SOLVER_WG)
     p->solver_used = SSO_SOLVER_STANDARD;
-  p->direct = p->factored = false;
-  if (!batch) {
-    const int st = choose_direct(p);
-    if (st != SSO_OK) return st;
-    if (p->direct) p->solver_used = SSO_SOLVER_STANDARD;   // should it go back to PCG
+  p->direct = p->factored = p->direct_done = false;
+  p->direct_rr = -1.0;
+  p->direct_steps = 0;
+  if (may_be_direct(p)) {
+    if (batch) {
+      p->direct = true;     // attached by the first launch: its plan may still be in the making
+    } else {
+      const int st = direct_attach(p);
+      if (st != SSO_OK) return st;
+    }
+    // should it go back to PCG: the standard recurrences, which need the least beside K
+    if (p->direct && p->solver_used != SSO_SOLVER_WG) p->solver_used = SSO_SOLVER_STANDARD;
   }
-  const bool mx = mixed(p), fu = fused(p);
+  const bool mx = mixed(p) && !p->direct, fu = fused(p);
   const int64_t nk = 36 * p->pat.n_blocks;
   const int64_t nb = 36 * right_precondition_blocks(p->pat, p->m.n_nodes);
   if (mx && !p->Dinv32) TRY_HIP(dev_alloc(&p->Dinv32, dinv_packed_len(p->m.n_nodes), s));
@@ -708,6 +855,31 @@ int prepare(sso_problem* p, bool batch) {
                                       mx ? p->B32 : nullptr, s));
   TRY_HIP(hipEventRecord(p->ev[2], s));
   return read_errors(p);
+}
+
+// The start of a begun solve's PCG iteration (x = 0).
+int begin_pcg(sso_problem* p) {
+  hipStream_t s = p->s;
+  if (mixed(p))
+    TRY_HIP(mixed_begin(p->m, p->pat, p->K, p->K32, p->Dinv32, p->B32, p->f, p->u,
+                        mixed_params(p), p->w, s, p->ms));
+  else if (fused(p))
+    TRY_HIP(fused_begin(p->m, p->pat, p->B, p->Dinv, p->f, p->u, p->opt.rtol, p->opt.max_it,
+                        p->w, s, &p->fdesc));
+  else
+    TRY_HIP(pcg_begin(p->m, p->pat, p->K, p->Dinv, p->f, p->u, p->opt.rtol, p->opt.max_it,
+                      p->w, s, &p->desc));
+  return SSO_OK;
+}
+
+// A begun solve that the direct solver does not take, or could not finish.
+int back_to_pcg(sso_problem* p) {
+  p->direct = false;
+  if (mixed(p)) {
+    const int st = mixed_operands(p);
+    if (st != SSO_OK) return st;
+  }
+  return begin_pcg(p);
 }
 
 bool fused_used(const sso_problem* p) { return p->solver_used == SSO_SOLVER_FUSED; }
@@ -770,7 +942,6 @@ int size_objective_impl(sso_problem* p, double eps1, double u_max, double t_min,
   return status;
 }
 
-constexpr int MAX_DEVICES = 64;
 std::mutex scratch_mutex;
 double* scratch_ptr[MAX_DEVICES] = {};
 
@@ -839,12 +1010,66 @@ hipError_t pool_alloc(void** p, size_t bytes, hipStream_t s) {
   return hipMallocFromPoolAsync(p, bytes, pool, s);
 }
 
+// Chunks of ended problems, idle and still allocated, for the next problem on the device.  A
+// stream-ordered free costs the host 20 to 150 us and an allocation up to 30, ten of each a served
+// request: 1.6 ms to finish one and 0.95 to admit it, against 0.5 and 0.7 from here.  At most
+// CACHE_BYTES are kept, sso_pool_trim gives all of it back, and so does an allocation that fails.
+constexpr size_t CACHE_BYTES = (size_t)8 << 30;
+struct ChunkCache {
+  std::mutex mu;
+  std::map<size_t, std::vector<char*>> idle;   // by size
+  size_t bytes = 0;
+};
+static ChunkCache chunk_caches[MAX_DEVICES];
+
+static ChunkCache* cache_of(hipStream_t s) {
+  int device = 0;
+  if (hipStreamGetDevice(s, &device) != hipSuccess || device < 0 || device >= MAX_DEVICES)
+    return nullptr;
+  return &chunk_caches[device];
+}
+
+static void cache_flush(ChunkCache& c, hipStream_t s) {
+  std::map<size_t, std::vector<char*>> idle;
+  {
+    std::lock_guard<std::mutex> lock(c.mu);
+    idle.swap(c.idle);
+    c.bytes = 0;
+  }
+  for (const auto& k : idle)
+    for (char* p : k.second) (void)hipFreeAsync(p, s);
+}
+
+// A chunk of exactly `bytes` (a chunk_size, or ARENA_CHUNK).
+static hipError_t chunk_take(size_t bytes, hipStream_t s, void** out) {
+  ChunkCache* c = cache_of(s);
+  if (c) {
+    std::lock_guard<std::mutex> lock(c->mu);
+    auto it = c->idle.find(bytes);
+    if (it != c->idle.end() && !it->second.empty()) {
+      *out = it->second.back();
+      it->second.pop_back();
+      c->bytes -= bytes;
+      return hipSuccess;
+    }
+  }
+  hipError_t e = pool_alloc(out, bytes, s);
+  if (e == hipErrorOutOfMemory && c) {
+    (void)hipGetLastError();
+    cache_flush(*c, s);
+    e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = pool_alloc(out, bytes, s);
+  }
+  return e;
+}
+
 hipError_t arena_alloc(Arena& a, size_t bytes, hipStream_t s, void** out, int64_t* held) {
   bytes = (bytes + ARENA_ALIGN - 1) / ARENA_ALIGN * ARENA_ALIGN;
   *held = 0;
   if (bytes > ARENA_CHUNK / 4) {   // a chunk of its own
+    bytes = chunk_size(bytes);
     void* q = nullptr;
-    const hipError_t e = pool_alloc(&q, bytes, s);
+    const hipError_t e = chunk_take(bytes, s, &q);
     if (e != hipSuccess) return e;
     a.chunks.emplace_back(static_cast<char*>(q), bytes);
     *held = (int64_t)bytes;
@@ -853,7 +1078,7 @@ hipError_t arena_alloc(Arena& a, size_t bytes, hipStream_t s, void** out, int64_
   }
   if (bytes > a.left) {
     void* q = nullptr;
-    const hipError_t e = pool_alloc(&q, ARENA_CHUNK, s);
+    const hipError_t e = chunk_take(ARENA_CHUNK, s, &q);
     if (e != hipSuccess) return e;
     a.chunks.emplace_back(static_cast<char*>(q), ARENA_CHUNK);
     a.cur = static_cast<char*>(q);
@@ -864,6 +1089,26 @@ hipError_t arena_alloc(Arena& a, size_t bytes, hipStream_t s, void** out, int64_
   a.cur += bytes;
   a.left -= bytes;
   return hipSuccess;
+}
+
+void arena_recycle(Arena& a, hipStream_t s) {
+  ChunkCache* c = cache_of(s);
+  for (const auto& k : a.chunks) {
+    bool kept = false;
+    if (c) {
+      std::lock_guard<std::mutex> lock(c->mu);
+      if (c->bytes + k.second <= CACHE_BYTES) {
+        try {
+          c->idle[k.second].push_back(k.first);
+          c->bytes += k.second;
+          kept = true;
+        } catch (...) {   // no host memory for the entry
+        }
+      }
+    }
+    if (!kept) (void)hipFreeAsync(k.first, s);
+  }
+  a = Arena();
 }
 
 bool arena_owns(const Arena& a, const void* p) {
@@ -928,20 +1173,14 @@ int sso_solve_begin(sso_problem* p) {
   if (!p) return SSO_EINVAL;
   AllocScope ac(&p->bytes, &p->mem);
   // multi-problem launches run FP64 iterations of either kind and FP32 single-reduction ones
-  hipStream_t s = p->s;
   p->solved = false;
   p->in_batch = false;
   int st = prepare(p, true);
   if (st != SSO_OK) return st;
-  if (mixed(p))
-    TRY_HIP(mixed_begin(p->m, p->pat, p->K, p->K32, p->Dinv32, p->B32, p->f, p->u,
-                        mixed_params(p), p->w, s, p->ms));
-  else if (fused(p))
-    TRY_HIP(fused_begin(p->m, p->pat, p->B, p->Dinv, p->f, p->u, p->opt.rtol, p->opt.max_it,
-                        p->w, s, &p->fdesc));
-  else
-    TRY_HIP(pcg_begin(p->m, p->pat, p->K, p->Dinv, p->f, p->u, p->opt.rtol, p->opt.max_it,
-                      p->w, s, &p->desc));
+  if (!p->direct) {
+    st = begin_pcg(p);
+    if (st != SSO_OK) return st;
+  }
   p->in_batch = true;
   return SSO_OK;
 }
@@ -950,21 +1189,45 @@ int sso_solve_end(sso_problem* p, double* u_out, sso_stats* stats) {
   if (!p || !p->in_batch || p->batch_pending) return SSO_EINVAL;
   AllocScope ac(&p->bytes, &p->mem);
   hipStream_t s = p->s;
-  TRY_HIP(hipMemcpyAsync(p->w.h_st, p->w.st, sizeof(PcgState), hipMemcpyDeviceToHost, s));
-  TRY_HIP(launch_true_residual(p->m, p->pat, p->K, p->u, p->f, nullptr, p->w, p->d_scal, s));
-  TRY_HIP(hipMemcpyAsync(p->h_scal, p->d_scal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-  TRY_HIP(hipStreamSynchronize(s));
-  int status = p->w.h_st->done ? p->w.h_st->status : SSO_ENOTCONV;
-  int iters = p->w.h_st->it, outer = 0;
-  if (mixed(p)) {   // the refinement loop already ended on the FP64 true residual
-    status = p->ms.done ? p->ms.status : SSO_ENOTCONV;
-    iters = p->ms.iters;
-    outer = p->ms.outer;
-  } else if (status == SSO_OK) {
-    TRY_HIP(pcg_correct(p->m, p->pat, p->K, p->Dinv, p->f, p->u, p->opt.rtol, p->opt.max_it, p->w,
-                        s, &iters, &status));
-    TRY_HIP(launch_true_residual(p->m, p->pat, p->K, p->u, p->f, nullptr, p->w, p->d_scal, s));
-    TRY_HIP(hipMemcpyAsync(p->h_scal, p->d_scal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+  int status = SSO_OK, iters = 0, outer = 0;
+  auto residual = [&] {   // into h_scal, once the stream gets there
+    hipError_t e = launch_true_residual(p->m, p->pat, p->K, p->u, p->f, nullptr, p->w, p->d_scal, s);
+    return e != hipSuccess ? e
+                           : hipMemcpyAsync(p->h_scal, p->d_scal, 2 * sizeof(double),
+                                            hipMemcpyDeviceToHost, s);
+  };
+  if (p->direct) {
+    if (mixed(p)) outer = p->direct_steps;
+    if (p->direct_steps == 0) {            // ended before it was launched
+      TRY_HIP(hipMemsetAsync(p->u, 0, sizeof(double) * 6 * (size_t)p->m.n_nodes, s));
+      status = SSO_ENOTCONV;
+      TRY_HIP(residual());
+    } else if (!p->direct_done) {
+      status = SSO_ENOTCONV;
+      TRY_HIP(residual());
+    } else if (!(std::sqrt(p->direct_rr) <= p->opt.rtol * std::sqrt(p->direct_bb))) {
+      TRY_HIP(pcg_correct(p->m, p->pat, p->K, p->Dinv, p->f, p->u, p->opt.rtol, p->opt.max_it,
+                          p->w, s, &iters, &status));
+      TRY_HIP(residual());
+    } else {
+      p->h_scal[0] = p->direct_rr;
+      p->h_scal[1] = p->direct_bb;
+    }
+  } else {
+    TRY_HIP(hipMemcpyAsync(p->w.h_st, p->w.st, sizeof(PcgState), hipMemcpyDeviceToHost, s));
+    TRY_HIP(residual());
+    TRY_HIP(hipStreamSynchronize(s));
+    status = p->w.h_st->done ? p->w.h_st->status : SSO_ENOTCONV;
+    iters = p->w.h_st->it;
+    if (mixed(p)) {   // the refinement loop already ended on the FP64 true residual
+      status = p->ms.done ? p->ms.status : SSO_ENOTCONV;
+      iters = p->ms.iters;
+      outer = p->ms.outer;
+    } else if (status == SSO_OK) {
+      TRY_HIP(pcg_correct(p->m, p->pat, p->K, p->Dinv, p->f, p->u, p->opt.rtol, p->opt.max_it,
+                          p->w, s, &iters, &status));
+      TRY_HIP(residual());
+    }
   }
   if (p->m.u_presc) TRY_HIP(launch_apply_prescribed(p->m, p->u, s));
   if (u_out)
@@ -980,7 +1243,7 @@ int sso_solve_end(sso_problem* p, double* u_out, sso_stats* stats) {
     stats->spmv_bytes =
         fused(p) ? fused_bytes_per_iteration(p->m.n_nodes, p->pat.n_blocks, mixed(p))
                  : pcg_bytes_per_iteration(p->m.n_nodes, p->pat.n_blocks, mixed(p), false);
-    stats->solver = p->solver_used;
+    stats->solver = p->direct ? SSO_SOLVER_AUTO : p->solver_used;
   }
   p->in_batch = false;
   p->solved = (status == SSO_OK || status == SSO_ENOTCONV);
@@ -1006,9 +1269,44 @@ int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) {
   }
   BatchLists lists;
   for (auto& v : b->idx) v.clear();
+  b->direct.clear();
+  std::vector<DirectJob> jobs, more;
+  std::vector<int> at_more;
+  // a problem whose plan is still in the making is left for a later launch
+  b->idle = n_iter > 0;
+  for (int i = 0; i < n && n_iter > 0; ++i) {
+    sso_problem* p = ps[i];
+    if (!p->direct || p->direct_done) continue;
+    AllocScope ac(&p->bytes, &p->mem);
+    if (p->direct_steps == 0) {
+      if (plan_pending(p)) continue;
+      const int st = direct_attach(p);
+      if (st != SSO_OK) return st;
+      if (!p->direct) {                // not for this structure
+        const int sb = back_to_pcg(p);
+        if (sb != SSO_OK) return sb;
+        continue;
+      }
+    }
+    DirectJob j{&p->shared->plan, p->da, p->direct_steps == 0, &p->m, &p->pat,
+                p->f, p->u, &p->w, p->d_scal};
+    j.a.rhs = j.factor ? p->f : p->w.r;
+    j.a.sol = j.factor ? p->u : p->da.sol;
+    j.a.scal = p->d_scal;
+    if (j.factor) {
+      jobs.push_back(j);
+      b->direct.push_back(i);
+    } else {
+      more.push_back(j);
+      at_more.push_back(i);
+    }
+  }
+  jobs.insert(jobs.end(), more.begin(), more.end());
+  b->direct.insert(b->direct.end(), at_more.begin(), at_more.end());
   for (int i = 0; i < n; ++i) {
     sso_problem* p = ps[i];
-    if (stopped(p)) continue;          // finished at an earlier poll
+    if (p->direct || stopped(p)) continue;   // the direct solver's, or finished at an earlier poll
+    b->idle = false;
     if (mixed(p) && fused(p)) {
       lists.fused32.push_back(p->ms.fdesc);
       b->idx[3].push_back(i);
@@ -1040,6 +1338,10 @@ int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) {
   }
   b->bw.time_span = b->armed;
   TRY_HIP(pcg_batch_launch(lists, n_iter, b->bw, b->s));
+  if (!jobs.empty()) {
+    b->idle = false;
+    TRY_HIP(direct_batch_launch(jobs, b->db, b->s));
+  }
   b->listed.assign(ps, ps + n);
   for (int i = 0; i < n; ++i) ps[i]->batch_pending = true;
   b->pending = true;
@@ -1053,6 +1355,34 @@ int sso_batch_wait(sso_batch* b, sso_problem* const* ps, int n, int32_t* done) {
   b->pending = false;
   for (int i = 0; i < n; ++i) ps[i]->batch_pending = false;
   TRY_HIP(pcg_batch_wait(b->bw));
+  if (b->idle) {
+    // every problem that is not done waits for its plan: until the first of them is there
+    std::unique_lock<std::mutex> lock(plan_mutex);
+    plan_cv.wait(lock, [&] {
+      bool pending = false;
+      for (int i = 0; i < n; ++i) {
+        if (stopped(ps[i])) continue;
+        if (!plan_pending(ps[i])) return true;
+        pending = true;
+      }
+      return !pending;
+    });
+  }
+  if (!b->direct.empty()) {
+    TRY_HIP(direct_batch_wait(b->db, b->s));
+    for (size_t k = 0; k < b->direct.size(); ++k) {
+      sso_problem* p = ps[b->direct[k]];
+      const double* r = b->db.out.data() + 3 * k;
+      const DirectNext next = direct_next(p, r[0], r[1], r[2] != 0.0);
+      p->direct_done = next == DIRECT_MET || next == DIRECT_STUCK;
+      if (next == DIRECT_FAILED) {
+        AllocScope ac(&p->bytes, &p->mem);
+        const int st = back_to_pcg(p);
+        if (st != SSO_OK) return st;
+      }
+    }
+    b->direct.clear();
+  }
   size_t k0 = 0;
   for (const auto& v : b->idx)
     for (int i : v) *ps[i]->w.h_st = b->bw.h_states[k0++];
@@ -1138,6 +1468,7 @@ void sso_batch_destroy(sso_batch* b) {
   for (sso_problem* p : b->listed)   // a launch never waited for: its problems are free again
     if (b->pending && p) p->batch_pending = false;
   batch_free(b->bw, b->s);
+  direct_batch_free(b->db, b->s);
   (void)hipStreamSynchronize(b->s);
   delete b;
 }
@@ -1328,6 +1659,15 @@ int sso_pool_trim(int device, uint64_t keep_bytes) {
     pool = pools[device];
   }
   if (!pool) return SSO_OK;
+  {
+    int cur = 0;
+    TRY_HIP(hipGetDevice(&cur));
+    if (cur != device) TRY_HIP(hipSetDevice(device));
+    cache_flush(chunk_caches[device], nullptr);
+    const hipError_t e = hipStreamSynchronize(nullptr);
+    if (cur != device) (void)hipSetDevice(cur);
+    TRY_HIP(e);
+  }
   TRY_HIP(hipMemPoolTrimTo(pool, (size_t)keep_bytes));
   return SSO_OK;
 }

@@ -14,15 +14,19 @@
 // F_SS is inverted by the symmetric sweep operator on panels of DIRECT_NB columns.  A sweep of
 // panel J with D = F_JJ takes every row I of the front's columns through
 //   F_IK -= (F_IJ D^-1) F_KJ^T,  F_IJ = F_IJ D^-1,  F_JK = its transpose,  F_JJ = -D^-1,
-// after which the own rows hold -W and the boundary rows G.  Sweeps alternate between two copies
-// of the panel (k_front_scale forms F_IJ D^-1, k_front_update the rest), so no work item reads
-// what another one of the same launch writes.  The products run on the matrix cores
+// after which the own rows hold -W and the boundary rows G.  A level's panels are a chain of
+// launches: launch q scales panel q (F_IJ D^-1 into a buffer of its own) and updates all columns
+// with panel q - 1; what the scaling needs of that update it forms itself, one more product of
+// tiles, so that a panel costs one launch instead of two.  Sweeps alternate between two copies of
+// the columns and of the scaled panel, so no work item reads what another one of the same launch
+// writes.  The products run on the matrix cores
 // (v_mfma_f64_16x16x4_f64) from LDS tiles.  All fronts of one level share the launches; the items
 // of a launch come from the plan, so a front's arithmetic does not depend on what else is in the
 // launch.  No atomics: every entry has one writer and a fixed order of additions.
 #include <cmath>
 
 #include "sso_internal.h"
+#include "wave.h"
 
 namespace sso {
 namespace {
@@ -33,6 +37,7 @@ constexpr int KC = 32;                // depth of an LDS tile
 constexpr int LDK = KC + 1;           // its row length: odd, so that 16 rows spread over the banks
 constexpr int LDN = NB + 1;
 constexpr int ASM_R = 6 * DIRECT_ASM_ROWS, ASM_C = 6 * DIRECT_ASM_COLS;
+constexpr int FWD_ROWS_WAVE = DIRECT_FWD_ROWS / (TPB / 64);
 constexpr int BWD_TPB = 512;
 constexpr int BWD_GROUPS = BWD_TPB / DIRECT_BWD_COLS;
 constexpr int BWD_CHUNK = 2048;       // rows of the vector staged at a time
@@ -49,7 +54,7 @@ __device__ __forceinline__ bool take_item(DirectArgs& a, const DirectArgs* __res
   if (probs) {
     a = probs[blockIdx.y];
     if (level >= a.n_levels) return false;
-    if (step >= STEP_PANEL && (step - STEP_PANEL) / 2 >= a.level_np[level]) return false;
+    if (step >= STEP_PANEL && step - STEP_PANEL > a.level_np[level]) return false;
     const DirectRange r = a.steps[a.level_off[level] + step];
     if ((int)blockIdx.x >= r.cnt) return false;
     first = r.off;
@@ -58,62 +63,84 @@ __device__ __forceinline__ bool take_item(DirectArgs& a, const DirectArgs* __res
   return true;
 }
 
-// Entry (r, c) of the Schur complements of a front's children at two nodes given by their
-// positions in the children's boundaries (-1: not there), components ca and cb.  A child's U
-// holds its lower triangle; the maps ascend, so both children keep the order of the rows.
+// A child's Schur complement (its lower triangle is stored).  at(r, c): the entry at DOF rows r, c
+// of its boundary, 0 where either is negative (not in the boundary).  Loads are unconditional, from
+// entry 0 then, so that a thread's loads are all in flight together.
 struct ChildU {
-  const double* u;
-  int ld;
-};
-__device__ __forceinline__ double child_entry(const ChildU& u, int mr, int mc, int ca, int cb) {
-  if ((mr | mc) < 0) return 0.0;
-  const int r = 6 * mr + ca, c = 6 * mc + cb;
-  const int hi = r > c ? r : c, lo = r > c ? c : r;
-  return u.u[(int64_t)hi * u.ld + lo];
-}
-__device__ __forceinline__ ChildU child_of(const DirectArgs& a, int f) {
-  ChildU u{nullptr, 0};
-  if (f >= 0) {
-    u.u = a.u + a.fronts[f].u_off;
-    u.ld = a.fronts[f].nb6;
+  const double* __restrict__ u;
+  __device__ __forceinline__ double at(int r, int c) const {
+    const bool in = (r | c) >= 0;
+    const int hi = r > c ? r : c, lo = r > c ? c : r;
+    const double v = u[in ? direct_tri(hi) + lo : 0];
+    return in ? v : 0.0;
   }
-  return u;
+};
+__device__ __forceinline__ ChildU child_of(const DirectArgs& a, int f) {
+  return ChildU{f >= 0 ? a.u + a.fronts[f].u_off : a.u};
 }
 
 // A front's columns: children's Schur complements and K's blocks, a tile of 8 x 16 nodes in LDS.
 __global__ void __launch_bounds__(TPB)
 k_front_assemble(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
   __shared__ double tile[ASM_R * ASM_C];
-  __shared__ int mr[2][DIRECT_ASM_ROWS], mc[2][DIRECT_ASM_COLS];
+  __shared__ int mr[2][ASM_R], mc[2][ASM_C];   // DOF rows in the children's boundaries, -1: none
   DirectItem it;
   if (!take_item(a, probs, first, level, STEP_ASM, it)) return;
   const DirectFront F = a.fronts[it.front];
   const int ns = F.ns6 / 6, cnt = ns + F.nb6 / 6;
   const int rn0 = it.i * DIRECT_ASM_ROWS, cn0 = it.j * DIRECT_ASM_COLS;
   const int t = threadIdx.x;
-  if (t < 2 * DIRECT_ASM_ROWS) {
-    const int k = t / DIRECT_ASM_ROWS, r = t % DIRECT_ASM_ROWS;
-    mr[k][r] = rn0 + r < cnt ? a.maps[F.map_off + k * cnt + rn0 + r] : -1;
-  } else if (t >= 64 && t < 64 + 2 * DIRECT_ASM_COLS) {
-    const int k = (t - 64) / DIRECT_ASM_COLS, c = (t - 64) % DIRECT_ASM_COLS;
-    mc[k][c] = cn0 + c < ns ? a.maps[F.map_off + k * cnt + cn0 + c] : -1;
-  }
   const ChildU u0 = child_of(a, F.child[0]), u1 = child_of(a, F.child[1]);
+  // the first of K's entries, on their way meanwhile
+  const int ne = 36 * (it.e1 - it.e0);
+  const int k0 = t / 36, q0 = t - 36 * k0;
+  DirectEntry en0{0, 0};
+  double kv0 = 0.0;
+  if (t < ne) {
+    en0 = a.entries[it.e0 + k0];
+    kv0 = a.K[36 * (int64_t)en0.slot + q0];
+  }
+  for (int e = t; e < 2 * (ASM_R + ASM_C); e += TPB) {
+    const int k = e >= ASM_R + ASM_C, r = e - k * (ASM_R + ASM_C);
+    const bool row = r < ASM_R;
+    const int dof = row ? r : r - ASM_R, node = dof / 6;
+    const bool in = row ? rn0 + node < cnt : cn0 + node < ns;
+    int m = in ? a.maps[F.map_off + k * cnt + (row ? rn0 : cn0) + node] : -1;
+    if (m >= 0) m = 6 * m + dof - 6 * node;
+    if (row)
+      mr[k][dof] = m;
+    else
+      mc[k][dof] = m;
+  }
   __syncthreads();
-  for (int e = t; e < ASM_R * ASM_C; e += TPB) {
-    const int r = e / ASM_C, c = e - r * ASM_C;
-    const int rn = r / 6, cn = c / 6;
-    tile[e] = child_entry(u0, mr[0][rn], mc[0][cn], r - 6 * rn, c - 6 * cn) +
-              child_entry(u1, mr[1][rn], mc[1][cn], r - 6 * rn, c - 6 * cn);
+  if (F.child[0] < 0 && F.child[1] < 0) {
+    for (int e = t; e < ASM_R * ASM_C; e += TPB) tile[e] = 0.0;
+  } else {
+    constexpr int AT_ONCE = 6;
+    static_assert(ASM_R * ASM_C % (AT_ONCE * TPB) == 0, "whole rounds");
+    for (int e0 = t; e0 < ASM_R * ASM_C; e0 += AT_ONCE * TPB) {
+      double v[AT_ONCE], w[AT_ONCE];
+#pragma unroll
+      for (int u = 0; u < AT_ONCE; ++u) {
+        const int e = e0 + u * TPB, r = e / ASM_C, c = e - r * ASM_C;
+        v[u] = u0.at(mr[0][r], mc[0][c]);
+        w[u] = u1.at(mr[1][r], mc[1][c]);
+      }
+#pragma unroll
+      for (int u = 0; u < AT_ONCE; ++u) tile[e0 + u * TPB] = v[u] + w[u];
+    }
   }
   __syncthreads();
   // K's blocks: block (row, col) of the front is the transpose of K's (col, row)
-  for (int e = t; e < 36 * (it.e1 - it.e0); e += TPB) {
+  auto add = [&](const DirectEntry& en, int q, double v) {
+    const int cb = q / 6, ca = q - 6 * cb;       // K entry (cb, ca) of block (col node, row node)
+    tile[(6 * (en.rc >> 16) + ca) * ASM_C + 6 * (en.rc & 0xffff) + cb] += v;
+  };
+  if (t < ne) add(en0, q0, kv0);
+  for (int e = t + TPB; e < ne; e += TPB) {
     const int k = e / 36, q = e - 36 * k;
     const DirectEntry en = a.entries[it.e0 + k];
-    const int cb = q / 6, ca = q - 6 * cb;       // K entry (cb, ca) of block (col node, row node)
-    tile[(6 * (en.rc >> 16) + ca) * ASM_C + 6 * (en.rc & 0xffff) + cb] +=
-        a.K[36 * (int64_t)en.slot + q];
+    add(en, q, a.K[36 * (int64_t)en.slot + q]);
   }
   __syncthreads();
   double* out = a.f0 + F.work_off;
@@ -151,35 +178,74 @@ __device__ __forceinline__ RowTile row_tile(const DirectFront& F, int i) {
   return t;
 }
 
-// A tile of up to 64 rows x KC columns of a row-major array into LDS, zero outside.
-__device__ __forceinline__ void load_tile(const double* __restrict__ src, int64_t ld, int rows,
-                                          int k0, int kn, double* dst) {
-  // 16-byte loads: rows start at even offsets (every row length is a multiple of 6 or 64)
-  for (int e = threadIdx.x; e < NB * KC / 2; e += TPB) {
-    const int r = e / (KC / 2), c = 2 * (e - r * (KC / 2));
-    double2 v{0.0, 0.0};
-    if (r < rows && k0 + c < kn)
-      v = *reinterpret_cast<const double2*>(src + (int64_t)r * ld + k0 + c);
-    dst[r * LDK + c] = v.x;
-    dst[r * LDK + c + 1] = v.y;   // kn is even: a pair lies inside or outside as a whole
+// Up to 64 rows x KC columns of a row-major array on their way into an LDS tile, zero outside.
+// 16-byte loads: rows start at even offsets (every row length is a multiple of 6 or 64), and the
+// number of columns is even, so a pair lies inside or outside as a whole.
+struct TileLoad {
+  static constexpr int PER = NB * KC / 2 / TPB;
+  double2 v[PER];
+  __device__ __forceinline__ void load(const double* __restrict__ src, int64_t ld, int rows,
+                                       int k0, int kn) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = (int)threadIdx.x + u * TPB, r = e / (KC / 2), c = 2 * (e % (KC / 2));
+      v[u] = double2{0.0, 0.0};
+      if (r < rows && k0 + c < kn)
+        v[u] = *reinterpret_cast<const double2*>(src + (int64_t)r * ld + k0 + c);
+    }
   }
-}
+  __device__ __forceinline__ void store(double* dst) const {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = (int)threadIdx.x + u * TPB, r = e / (KC / 2), c = 2 * (e % (KC / 2));
+      dst[r * LDK + c] = v[u].x;
+      dst[r * LDK + c + 1] = v[u].y;
+    }
+  }
+};
 
-// acc += A B^T over KC columns of LDS tiles A, B (64 x KC each): the wave's 32 x 32 quadrant as
-// 2 x 2 matrix-core tiles.  kn: columns that hold values.
+// acc += A B^T over kn columns of LDS tiles A, B (64 rows each): the wave's 32 x 32 quadrant as
+// 2 x 2 matrix-core tiles.
 __device__ __forceinline__ void mma_tile(const double* A, int lda, const double* B, int ldb,
                                          int kn, d4 acc[2][2]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, kq = lane >> 4;
   const double* pa = A + (32 * (wave >> 1) + l16) * lda + kq;
   const double* pb = B + (32 * (wave & 1) + l16) * ldb + kq;
-  for (int k = 0; k < kn; k += 4) {
+  auto step = [&](int k) {
     const double a0 = pa[k], a1 = pa[16 * lda + k];
     const double b0 = pb[k], b1 = pb[16 * ldb + k];
     acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
     acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
     acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
     acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+  };
+  if (kn == KC) {
+#pragma unroll
+    for (int k = 0; k < KC; k += 4) step(k);
+  } else {
+    for (int k = 0; k < kn; k += 4) step(k);
+  }
+}
+
+// acc += A B^T, both row-major in memory, over kn columns: the next KC columns are on their way
+// while the matrix cores work on the ones in LDS (as, bs: NB x LDK each).
+__device__ __forceinline__ void product(const double* __restrict__ A, int64_t lda, int ra,
+                                        const double* __restrict__ B, int64_t ldb, int rb, int kn,
+                                        double* as, double* bs, d4 acc[2][2]) {
+  TileLoad ta, tb;
+  ta.load(A, lda, ra, 0, kn);
+  tb.load(B, ldb, rb, 0, kn);
+  for (int k0 = 0; k0 < kn; k0 += KC) {
+    if (k0) __syncthreads();
+    ta.store(as);
+    tb.store(bs);
+    __syncthreads();
+    if (k0 + KC < kn) {
+      ta.load(A, lda, ra, k0 + KC, kn);
+      tb.load(B, ldb, rb, k0 + KC, kn);
+    }
+    mma_tile(as, LDK, bs, LDK, kn - k0 < KC ? kn - k0 : KC, acc);
   }
 }
 
@@ -203,154 +269,248 @@ __device__ __forceinline__ void clear(d4 acc[2][2]) {
     for (int j = 0; j < 2; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 }
 
-// Sweep p, first half: D^-1 of the front's pivot block (by every workgroup of the front for
-// itself: it costs no more time than one of them doing it first) and F_IJ D^-1 for one row tile.
-// D is swept column by column in registers, 4 x 4 entries a thread; a step publishes the pivot
-// column through LDS (the matrix stays symmetric, so it is the pivot row as well) and needs one
-// barrier, the buffers alternating.
-__global__ void __launch_bounds__(TPB)
-k_front_scale(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level, int p) {
-  __shared__ double ds[NB * LDN];
-  __shared__ double as[NB * LDK];
-  __shared__ double col[2][NB];
-  DirectItem it;
-  if (!take_item(a, probs, first, level, STEP_PANEL + 2 * p, it)) return;
-  const DirectFront F = a.fronts[it.front];
-  const double* __restrict__ src = sweep_src(a, F, p);
-  const int64_t ld = F.ns6;
-  const int j0 = p * NB;
-  const int nb = F.ns6 - j0 < NB ? F.ns6 - j0 : NB;
-  const int t = threadIdx.x, ty = t >> 4, tx = t & 15;
-  double d[4][4];
+// 1 / x for a pivot: the hardware's estimate and two Newton steps (relative error some 1e-16).
+__device__ __forceinline__ double reciprocal(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+  r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+  return r;
+}
+
+// Sweeps the leading nb columns of a 64 x 64 symmetric block, held as matrix-core accumulators
+// (each_acc's layout): the block becomes minus its inverse.  A step publishes its column through
+// LDS, which by symmetry is its row as well, in the order in which a lane reads its eight rows
+// (contiguous), and takes one barrier, the two buffers alternating.  With t = column / pivot the
+// update is d -= t row throughout: the swept column's entries are cleared beforehand and their
+// factor of the row is -1, the swept row's likewise and their t is -1 / pivot.  Returns the pivot
+// of step threadIdx.x.  A step is a chain of LDS write, barrier, LDS reads, reciprocal and update;
+// with the selections of a plain form of it (no cleared entries) it took 750 cycles, 20 us a block.
+__device__ __forceinline__ int swept_at(int r) {   // where row r of the column lies
+  return (r & 32) + 8 * (r & 3) + 4 * ((r >> 4) & 1) + ((r >> 2) & 3);
+}
+__device__ __forceinline__ double sweep(d4 d[2][2], int nb, double (*col)[NB]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l16 = lane & 15, kq = lane >> 4, wr = wave >> 1, wc = wave & 1;
+  const int mine = 32 * wr + 8 * kq;                       // my eight rows' place
+  const int across = 32 * wc + 8 * (l16 & 3) + (l16 >> 2); // my two columns' place, 4 apart
+  double pivot = 0.0;
+  for (int half = 0; half < 2; ++half) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int s = 0; s < 2; ++s) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = 4 * ty + i, c = 4 * tx + j;
-      d[i][j] = r < nb && c < nb ? src[(int64_t)(j0 + r) * ld + j0 + c] : (r == c ? 1.0 : 0.0);
-    }
-  // the smallest pivot allowed at this thread's diagonal entries
-  double least[4] = {0.0, 0.0, 0.0, 0.0};
-  if (ty == tx && it.i == p) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 4 * ty + i;
-      if (r < nb) {
-        const int q = (j0 + r) / 6, c = (j0 + r) - 6 * q;
-        least[i] = PIVOT_MIN * a.K[36 * (int64_t)a.bdiag[a.nodes[F.nodes_off + q]] + 7 * c];
-      }
-    }
-  }
-  bool bad = false;
-  const int steps = (nb + 3) / 4;
-  for (int k4 = 0; k4 < steps; ++k4) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int k = 4 * k4 + kk;
-      double* cb = col[k & 1];
-      if (tx == k4) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) cb[4 * ty + i] = d[i][kk];
-      }
-      __syncthreads();
-      const double piv = cb[k];
-      if (ty == k4 && tx == k4 && !(piv > least[kk])) bad = true;
-      const double inv = 1.0 / piv;
-      double cr[4], cc[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) cr[i] = cb[4 * ty + i] * inv;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) cc[j] = cb[4 * tx + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const bool rk = 4 * ty + i == k, ck = 4 * tx + j == k;
-          const double up = d[i][j] - cr[i] * cc[j];
-          d[i][j] = rk ? (ck ? -inv : cc[j] * inv) : (ck ? cr[i] : up);
+      for (int kk = 0; kk < 16; ++kk) {
+        const int k = 32 * half + 16 * s + kk;
+        if (k >= nb) return pivot;
+        double* cb = col[kk & 1];
+        const bool own_c = wc == half && l16 == kk;
+        if (own_c) {
+          *reinterpret_cast<d4*>(cb + mine) = d[0][s];
+          *reinterpret_cast<d4*>(cb + mine + 4) = d[1][s];
+          d[0][s] = d4{0.0, 0.0, 0.0, 0.0};
+          d[1][s] = d4{0.0, 0.0, 0.0, 0.0};
         }
+        __syncthreads();
+        const double piv = cb[swept_at(k)];
+        d4 t0 = *reinterpret_cast<const d4*>(cb + mine);
+        d4 t1 = *reinterpret_cast<const d4*>(cb + mine + 4);
+        double r0 = cb[across], r1 = cb[across + 4];
+        const double inv = reciprocal(piv);
+        if ((int)threadIdx.x == k) pivot = piv;
+        t0 *= inv;
+        t1 *= inv;
+        if (own_c) {
+          if (s == 0)
+            r0 = -1.0;
+          else
+            r1 = -1.0;
+        }
+        if (wr == half && kq == (kk & 3)) {
+          if (s == 0)
+            t0[kk >> 2] = -inv;
+          else
+            t1[kk >> 2] = -inv;
+          d[s][0][kk >> 2] = 0.0;
+          d[s][1][kk >> 2] = 0.0;
+        }
+        d[0][0] -= t0 * r0;
+        d[0][1] -= t0 * r1;
+        d[1][0] -= t1 * r0;
+        d[1][1] -= t1 * r1;
+      }
     }
   }
-  if (it.i == p && bad) atomicOr(a.flag, 1u);
-  const RowTile R = row_tile(F, it.i);
-  const bool only = F.np == 1;    // no second half: straight into the factor
-  if (it.i == p) {
-    double* out = only ? a.fact + F.fact_off : a.w + F.w_off + (int64_t)it.i * NB * NB;
-    const int64_t ldo = only ? ld : NB;
+  return pivot;
+}
+
+constexpr int POOL = 3 * NB * LDK;    // doubles of LDS that the panel kernels cut their tiles from
+static_assert(NB * LDN + NB * LDK <= POOL, "the inverse and a tile of the row tile fit");
+
+// The scaled panel of step q: q even and odd alternate.
+__device__ __forceinline__ double* scaled(const DirectArgs& a, const DirectFront& F, int q, int i) {
+  return a.w + F.w_off + ((int64_t)(q & 1) * F.nt + i) * NB * NB;
+}
+
+// Panel q of a front scaled, row tile i: D^-1 of its pivot block (by every workgroup of the front
+// for itself, which takes no longer than one of them doing it for the others) and F_IJ D^-1.  For
+// q > 0 both are first brought up to date with panel q - 1.
+__device__ __forceinline__ void scale_tile(const DirectArgs& a, const DirectFront& F, int q, int i,
+                                           double* pool, double (*col)[NB]) {
+  const int64_t ld = F.ns6;
+  const int j0 = q * NB;
+  const int nb = F.ns6 - j0 < NB ? F.ns6 - j0 : NB;
+  const RowTile R = row_tile(F, i);
+  const bool pivot = i == q;
+  const double* __restrict__ src = q == 0 ? a.f0 + F.work_off : sweep_src(a, F, q - 1);
+  double least = 0.0;         // the pivot of step threadIdx.x must lie above it
+  if (pivot && (int)threadIdx.x < nb) {
+    const int r = j0 + (int)threadIdx.x, n = r / 6;
+    least = PIVOT_MIN * a.K[36 * (int64_t)a.bdiag[a.nodes[F.nodes_off + n]] + 7 * (r - 6 * n)];
+  }
+  // the pivot block and the row tile as accumulators (identity past the last column)
+  d4 d[2][2], f[2][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool swept = q > 0 && i == q - 1;   // rows of the panel before: its scaled tile, transposed
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = 4 * ty + i, c = 4 * tx + j;
-        if (r < nb && c < nb) out[(int64_t)r * ldo + c] = only ? d[i][j] : -d[i][j];
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = 32 * (wave >> 1) + 16 * u + (lane >> 4) + 4 * v;
+        const int c = 32 * (wave & 1) + 16 * w + (lane & 15);
+        d[u][w][v] = r < nb && c < nb ? src[(int64_t)(j0 + r) * ld + j0 + c] : (r == c ? 1.0 : 0.0);
+        f[u][w][v] = 0.0;
+        if (!pivot && r < R.n && c < nb)
+          f[u][w][v] = swept ? scaled(a, F, q - 1, q)[c * NB + r]
+                             : src[(int64_t)(R.r0 + r) * ld + j0 + c];
       }
+  if (q > 0) {
+    double* ws = pool;                    // scaled rows of the pivot block
+    double* wi = pool + NB * LDK;         // scaled rows of the row tile
+    double* cs = pool + 2 * NB * LDK;     // the pivot rows' entries in the panel before
+    TileLoad tw, ti, tc;
+    const double* __restrict__ pw = scaled(a, F, q - 1, q);
+    const double* __restrict__ pi = scaled(a, F, q - 1, i);
+    const double* __restrict__ pc = src + (int64_t)j0 * ld + j0 - NB;
+    const bool row = !pivot && !swept;
+    d4 ud[2][2], uf[2][2];
+    clear(ud);
+    clear(uf);
+    tw.load(pw, NB, nb, 0, NB);
+    tc.load(pc, ld, nb, 0, NB);
+    if (row) ti.load(pi, NB, R.n, 0, NB);
+    for (int k0 = 0; k0 < NB; k0 += KC) {
+      if (k0) __syncthreads();
+      tw.store(ws);
+      tc.store(cs);
+      if (row) ti.store(wi);
+      __syncthreads();
+      if (k0 + KC < NB) {
+        tw.load(pw, NB, nb, k0 + KC, NB);
+        tc.load(pc, ld, nb, k0 + KC, NB);
+        if (row) ti.load(pi, NB, R.n, k0 + KC, NB);
+      }
+      mma_tile(ws, LDK, cs, LDK, KC, ud);
+      if (row) mma_tile(wi, LDK, cs, LDK, KC, uf);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        d[u][w] -= ud[u][w];
+        if (row) f[u][w] -= uf[u][w];
+      }
+  }
+  const double piv = sweep(d, nb, col);
+  if (pivot && (int)threadIdx.x < nb && !(piv > least)) atomicOr(a.flag, 1u);
+  __syncthreads();      // the pool is free (nb is at least 6: the sweep held a barrier)
+  const bool only = F.np == 1;    // nothing to update: straight into the factor
+  double* out = only ? a.fact + F.fact_off + (int64_t)R.r0 * ld : scaled(a, F, q, i);
+  const int64_t ldo = only ? ld : NB;
+  if (pivot) {
+    each_acc(d, [&](int r, int c, double v) {
+      if (r < nb && c < nb) out[(int64_t)r * ldo + c] = only ? v : -v;
+    });
     return;
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ds[(4 * ty + i) * LDN + 4 * tx + j] = -d[i][j];
+  double* ds = pool;
+  double* fs = pool + NB * LDN;
+  each_acc(d, [&](int r, int c, double v) { ds[r * LDN + c] = -v; });
   d4 acc[2][2];
   clear(acc);
-  for (int k0 = 0; k0 < nb; k0 += KC) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {      // columns 32 h .. of the row tile: the waves of that half
+    if (32 * h >= nb) break;
+    if (h) __syncthreads();
+    if ((wave & 1) == h)
+      each_acc(f, [&](int r, int c, double v) { fs[r * LDK + c - 32 * h] = v; });
     __syncthreads();
-    load_tile(src + (int64_t)R.r0 * ld + j0, ld, R.n, k0, nb, as);
-    __syncthreads();
-    mma_tile(as, LDK, ds + k0, LDN, nb - k0 < KC ? nb - k0 : KC, acc);
+    const int kn = nb - 32 * h < KC ? nb - 32 * h : KC;
+    mma_tile(fs, LDK, ds + 32 * h, LDN, kn, acc);
   }
-  double* out = only ? a.fact + F.fact_off + (int64_t)R.r0 * ld
-                     : a.w + F.w_off + (int64_t)it.i * NB * NB;
-  const int64_t ldo = only ? ld : NB;
   each_acc(acc, [&](int r, int c, double v) {
     if (r < R.n && c < nb) out[(int64_t)r * ldo + c] = v;
   });
 }
 
-// Sweep p, second half: tile (i, j) of the front's columns from one copy to the other.
-__global__ void __launch_bounds__(TPB)
-k_front_update(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level, int p) {
-  __shared__ double as[NB * LDK];
-  __shared__ double bs[NB * LDK];
-  DirectItem it;
-  if (!take_item(a, probs, first, level, STEP_PANEL + 2 * p + 1, it)) return;
-  const DirectFront F = a.fronts[it.front];
+// Tile (i, j) of a front's columns from one copy to the other, with panel p.
+__device__ __forceinline__ void update_tile(const DirectArgs& a, const DirectFront& F, int p, int i,
+                                            int j, double* pool) {
   const double* __restrict__ src = sweep_src(a, F, p);
   double* __restrict__ dst = sweep_dst(a, F, p);
   const int64_t ld = F.ns6;
   const int j0 = p * NB;
   const int nb = F.ns6 - j0 < NB ? F.ns6 - j0 : NB;
-  const RowTile R = row_tile(F, it.i);
-  const int c0 = it.j * NB;
+  const RowTile R = row_tile(F, i);
+  const int c0 = j * NB;
   const int nc = F.ns6 - c0 < NB ? F.ns6 - c0 : NB;
-  const double* __restrict__ w = a.w + F.w_off;
-  if (it.j == p || it.i == p) {
+  const double* __restrict__ wi = scaled(a, F, p, i);
+  if (j == p || i == p) {
     // the panel's own column (F_IJ D^-1, -D^-1 on the diagonal) and row (its transpose)
-    const double* __restrict__ wi = w + (int64_t)it.i * NB * NB;
-    const double* __restrict__ wj = w + (int64_t)it.j * NB * NB;
+    const double* __restrict__ wj = scaled(a, F, p, j);
     for (int e = threadIdx.x; e < NB * NB; e += TPB) {
       const int r = e / NB, c = e - r * NB;
       if (r >= R.n || c >= nc) continue;
-      const double v = it.j == p ? (it.i == p ? -wi[r * NB + c] : wi[r * NB + c])
-                                 : wj[c * NB + r];
+      const double v = j == p ? (i == p ? -wi[r * NB + c] : wi[r * NB + c]) : wj[c * NB + r];
       dst[(int64_t)(R.r0 + r) * ld + c0 + c] = v;
     }
     return;
   }
-  d4 acc[2][2];
+  d4 f[2][2], acc[2][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = 32 * (wave >> 1) + 16 * u + (lane >> 4) + 4 * v;
+        const int c = 32 * (wave & 1) + 16 * w + (lane & 15);
+        f[u][w][v] = r < R.n && c < nc ? src[(int64_t)(R.r0 + r) * ld + c0 + c] : 0.0;
+      }
   clear(acc);
-  for (int k0 = 0; k0 < nb; k0 += KC) {
-    load_tile(w + (int64_t)it.i * NB * NB, NB, R.n, k0, nb, as);
-    load_tile(src + (int64_t)c0 * ld + j0, ld, nc, k0, nb, bs);
-    __syncthreads();
-    mma_tile(as, LDK, bs, LDK, nb - k0 < KC ? nb - k0 : KC, acc);
-    __syncthreads();
-  }
-  each_acc(acc, [&](int r, int c, double v) {
-    if (r < R.n && c < nc) {
-      const int64_t q = (int64_t)(R.r0 + r) * ld + c0 + c;
-      dst[q] = src[q] - v;
-    }
+  product(wi, NB, R.n, src + (int64_t)c0 * ld + j0, ld, nc, nb, pool, pool + NB * LDK, acc);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int w = 0; w < 2; ++w) f[u][w] -= acc[u][w];
+  each_acc(f, [&](int r, int c, double v) {
+    if (r < R.n && c < nc) dst[(int64_t)(R.r0 + r) * ld + c0 + c] = v;
   });
+}
+
+// Step q of a level's panels: panel q scaled, all columns updated with panel q - 1.
+__global__ void __launch_bounds__(TPB, 2)
+k_front_panel(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level, int q) {
+  __shared__ __align__(16) double pool[POOL];
+  __shared__ __align__(32) double col[2][NB];
+  DirectItem it;
+  if (!take_item(a, probs, first, level, STEP_PANEL + q, it)) return;
+  const DirectFront F = a.fronts[it.front];
+  if (it.j < 0)
+    scale_tile(a, F, q, it.i, pool, col);
+  else
+    update_tile(a, F, q - 1, it.i, it.j, pool);
 }
 
 // Tile (i, j), j <= i, of a front's Schur complement: the children's minus G F_BS^T.
@@ -380,32 +540,37 @@ k_front_schur(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int
   }
   const double* __restrict__ G = a.fact + F.fact_off + (int64_t)(F.ns6 + r0) * F.ns6;
   const double* __restrict__ B = a.f0 + F.work_off + (int64_t)(F.ns6 + c0) * F.ns6;
-  d4 acc[2][2];
-  clear(acc);
-  for (int k0 = 0; k0 < F.ns6; k0 += KC) {
-    load_tile(G, F.ns6, nr, k0, F.ns6, as);
-    load_tile(B, F.ns6, nc, k0, F.ns6, bs);
-    __syncthreads();
-    mma_tile(as, LDK, bs, LDK, F.ns6 - k0 < KC ? (F.ns6 - k0 + 3) & ~3 : KC, acc);
-    __syncthreads();
-  }
-  if (F.ns6 == 0) __syncthreads();
   const ChildU u0 = child_of(a, F.child[0]), u1 = child_of(a, F.child[1]);
+  d4 acc[2][2], sum[2][2];
+  clear(acc);
+  clear(sum);
+  __syncthreads();
+  if (F.child[0] >= 0 || F.child[1] >= 0) {   // on their way while the product runs
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int w = 0; w < 2; ++w)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = 32 * (wave >> 1) + 16 * u + (lane >> 4) + 4 * v;
+          const int c = 32 * (wave & 1) + 16 * w + (lane & 15);
+          sum[u][w][v] = u0.at(mr[0][r], mc[0][c]) + u1.at(mr[1][r], mc[1][c]);
+        }
+  }
+  product(G, F.ns6, nr, B, F.ns6, nc, F.ns6, as, bs, acc);
   double* __restrict__ U = a.u + F.u_off;
-  each_acc(acc, [&](int r, int c, double v) {
-    if (r >= nr || c >= nc) return;
-    auto child = [&](const ChildU& u, int ir, int ic) {
-      if ((ir | ic) < 0) return 0.0;
-      const int hi = ir > ic ? ir : ic, lo = ir > ic ? ic : ir;
-      return u.u[(int64_t)hi * u.ld + lo];
-    };
-    const double s = child(u0, mr[0][r], mc[0][c]) + child(u1, mr[1][r], mc[1][c]);
-    U[(int64_t)(r0 + r) * F.nb6 + c0 + c] = s - v;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int w = 0; w < 2; ++w) sum[u][w] -= acc[u][w];
+  each_acc(sum, [&](int r, int c, double v) {
+    if (r < nr && c0 + c <= r0 + r) U[direct_tri(r0 + r) + c0 + c] = v;
   });
 }
 
-// Up: b_S (every workgroup of the front for itself) and 64 rows of v_B.  A wave takes a row at a
-// time, its lanes along the row.
+// Up: b_S (every workgroup of the front for itself) and 16 rows of v_B, 4 a wave, whose lanes lie
+// along the rows.
 __global__ void __launch_bounds__(TPB)
 k_front_forward(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
   __shared__ __align__(16) double b[DIRECT_MAX_OWN];
@@ -429,30 +594,29 @@ k_front_forward(DirectArgs a, const DirectArgs* __restrict__ probs, int first, i
   }
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r_end = F.nb6 < (it.i + 1) * DIRECT_FWD_ROWS ? F.nb6 : (it.i + 1) * DIRECT_FWD_ROWS;
   const double* __restrict__ G = a.fact + F.fact_off + (int64_t)F.ns6 * F.ns6;
-  // 4 rows at a time: their loads are in flight together
-  for (int r = it.i * DIRECT_FWD_ROWS + 4 * wave; r < r_end; r += 4 * (TPB / 64)) {
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    const double* g[4];
+  const int r0 = it.i * DIRECT_FWD_ROWS + FWD_ROWS_WAVE * wave;
+  if (r0 >= F.nb6) return;
+  double s[FWD_ROWS_WAVE];
+  const double* g[FWD_ROWS_WAVE];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) g[k] = G + (int64_t)(r + k < r_end ? r + k : r_end - 1) * F.ns6;
-    for (int c = 2 * lane; c < F.ns6; c += 128) {
-      const double2 bv = *reinterpret_cast<const double2*>(b + c);
+  for (int k = 0; k < FWD_ROWS_WAVE; ++k) {
+    s[k] = 0.0;
+    g[k] = G + (int64_t)(r0 + k < F.nb6 ? r0 + k : F.nb6 - 1) * F.ns6;
+  }
+  for (int c = 2 * lane; c < F.ns6; c += 128) {
+    const double2 bv = *reinterpret_cast<const double2*>(b + c);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const double2 gv = *reinterpret_cast<const double2*>(g[k] + c);
-        s[k] += gv.x * bv.x + gv.y * bv.y;
-      }
+    for (int k = 0; k < FWD_ROWS_WAVE; ++k) {
+      const double2 gv = *reinterpret_cast<const double2*>(g[k] + c);
+      s[k] += gv.x * bv.x + gv.y * bv.y;
     }
+  }
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      for (int o = 32; o > 0; o >>= 1) s[k] += __shfl_xor(s[k], o, 64);
-    if (lane < 4 && r + lane < r_end) {
-      const int row = r + lane, q = row / 6;
-      const double dot = lane == 0 ? s[0] : lane == 1 ? s[1] : lane == 2 ? s[2] : s[3];
-      a.v[F.v_off + row] = children(ns + q, row - 6 * q) - dot;
-    }
+  for (int k = 0; k < FWD_ROWS_WAVE; ++k) {
+    const double dot = wave_sum(s[k]);
+    const int row = r0 + k;
+    if (lane == k && row < F.nb6) a.v[F.v_off + row] = children(ns + row / 6, row % 6) - dot;
   }
 }
 
@@ -499,13 +663,55 @@ k_front_backward(DirectArgs a, const DirectArgs* __restrict__ probs, int first, 
   }
 }
 
-template <class Fn>
-hipError_t launch_step(const DirectPlan& pl, int level, int step, Fn launch) {
-  const DirectRange r = pl.steps[pl.level_off[level] + step];
-  if (r.cnt == 0) return hipSuccess;
-  launch(dim3((unsigned)r.cnt), r.off);
-  return hipGetLastError();
+__global__ void k_direct_clear(DirectArgs a, const DirectArgs* __restrict__ probs, int n) {
+  const int i = (int)threadIdx.x + (int)(blockIdx.x * blockDim.x);
+  if (i < n) *(probs ? probs[i].flag : a.flag) = 0u;
 }
+
+__global__ void k_direct_collect(const DirectArgs* __restrict__ probs, int n, double* out) {
+  const int i = (int)threadIdx.x + (int)(blockIdx.x * blockDim.x);
+  if (i >= n) return;
+  out[3 * i] = probs[i].scal[0];
+  out[3 * i + 1] = probs[i].scal[1];
+  out[3 * i + 2] = *probs[i].flag ? 1.0 : 0.0;
+}
+
+// The problems of one launch: a single one by value, or n with their arguments on the device.
+struct Launch {
+  const DirectPlan* const* plans;
+  int n;
+  const DirectArgs* one;       // n == 1 and probs == nullptr
+  const DirectArgs* probs;
+  hipStream_t s;
+
+  int levels() const {
+    int h = 0;
+    for (int i = 0; i < n; ++i) h = plans[i]->levels() > h ? plans[i]->levels() : h;
+    return h;
+  }
+  int panels(int level) const {
+    int q = 0;
+    for (int i = 0; i < n; ++i)
+      if (level < plans[i]->levels() && plans[i]->level_np[level] > q)
+        q = plans[i]->level_np[level];
+    return q;
+  }
+  // launch(grid, first item) for a step of a level, if any problem has items there
+  template <class Fn>
+  hipError_t step(int level, int step, Fn launch) const {
+    int cnt = 0, first = 0;
+    for (int i = 0; i < n; ++i) {
+      const DirectPlan& pl = *plans[i];
+      if (level >= pl.levels() || step - STEP_PANEL > pl.level_np[level]) continue;
+      const DirectRange r = pl.steps[pl.level_off[level] + step];
+      cnt = r.cnt > cnt ? r.cnt : cnt;
+      first = r.off;
+    }
+    if (cnt == 0) return hipSuccess;
+    launch(dim3((unsigned)cnt, (unsigned)n), first);
+    return hipGetLastError();
+  }
+};
 
 }  // namespace
 
@@ -515,38 +721,108 @@ hipError_t launch_step(const DirectPlan& pl, int level, int step, Fn launch) {
     if (e_ != hipSuccess) return e_; \
   } while (0)
 
-hipError_t launch_direct_factor(const DirectPlan& pl, const DirectArgs& a, hipStream_t s) {
-  const DirectArgs* none = nullptr;
-  for (int h = 0; h < pl.levels(); ++h) {
-    SSO_TRY(launch_step(pl, h, STEP_ASM, [&](dim3 g, int off) {
-      hipLaunchKernelGGL(k_front_assemble, g, dim3(TPB), 0, s, a, none, off, h);
+static hipError_t factor(const Launch& L) {
+  const DirectArgs a = L.one ? *L.one : DirectArgs{};
+  for (int h = 0; h < L.levels(); ++h) {
+    SSO_TRY(L.step(h, STEP_ASM, [&](dim3 g, int off) {
+      hipLaunchKernelGGL(k_front_assemble, g, dim3(TPB), 0, L.s, a, L.probs, off, h);
     }));
-    for (int p = 0; p < pl.level_np[h]; ++p) {
-      SSO_TRY(launch_step(pl, h, STEP_PANEL + 2 * p, [&](dim3 g, int off) {
-        hipLaunchKernelGGL(k_front_scale, g, dim3(TPB), 0, s, a, none, off, h, p);
+    for (int q = 0; q <= L.panels(h); ++q)
+      SSO_TRY(L.step(h, STEP_PANEL + q, [&](dim3 g, int off) {
+        hipLaunchKernelGGL(k_front_panel, g, dim3(TPB), 0, L.s, a, L.probs, off, h, q);
       }));
-      SSO_TRY(launch_step(pl, h, STEP_PANEL + 2 * p + 1, [&](dim3 g, int off) {
-        hipLaunchKernelGGL(k_front_update, g, dim3(TPB), 0, s, a, none, off, h, p);
-      }));
-    }
-    SSO_TRY(launch_step(pl, h, STEP_SCHUR, [&](dim3 g, int off) {
-      hipLaunchKernelGGL(k_front_schur, g, dim3(TPB), 0, s, a, none, off, h);
+    SSO_TRY(L.step(h, STEP_SCHUR, [&](dim3 g, int off) {
+      hipLaunchKernelGGL(k_front_schur, g, dim3(TPB), 0, L.s, a, L.probs, off, h);
     }));
   }
   return hipSuccess;
 }
 
-hipError_t launch_direct_solve(const DirectPlan& pl, const DirectArgs& a, hipStream_t s) {
-  const DirectArgs* none = nullptr;
-  for (int h = 0; h < pl.levels(); ++h)
-    SSO_TRY(launch_step(pl, h, STEP_FWD, [&](dim3 g, int off) {
-      hipLaunchKernelGGL(k_front_forward, g, dim3(TPB), 0, s, a, none, off, h);
+static hipError_t substitute(const Launch& L) {
+  const DirectArgs a = L.one ? *L.one : DirectArgs{};
+  for (int h = 0; h < L.levels(); ++h)
+    SSO_TRY(L.step(h, STEP_FWD, [&](dim3 g, int off) {
+      hipLaunchKernelGGL(k_front_forward, g, dim3(TPB), 0, L.s, a, L.probs, off, h);
     }));
-  for (int h = pl.levels() - 1; h >= 0; --h)
-    SSO_TRY(launch_step(pl, h, STEP_BWD, [&](dim3 g, int off) {
-      hipLaunchKernelGGL(k_front_backward, g, dim3(BWD_TPB), 0, s, a, none, off, h);
+  for (int h = L.levels() - 1; h >= 0; --h)
+    SSO_TRY(L.step(h, STEP_BWD, [&](dim3 g, int off) {
+      hipLaunchKernelGGL(k_front_backward, g, dim3(BWD_TPB), 0, L.s, a, L.probs, off, h);
     }));
   return hipSuccess;
+}
+
+hipError_t launch_direct_clear(const DirectArgs& a, hipStream_t s) {
+  const DirectArgs* none = nullptr;
+  hipLaunchKernelGGL(k_direct_clear, dim3(1), dim3(64), 0, s, a, none, 1);
+  return hipGetLastError();
+}
+
+hipError_t launch_direct_factor(const DirectPlan& pl, const DirectArgs& a, hipStream_t s) {
+  const DirectPlan* p = &pl;
+  return factor(Launch{&p, 1, &a, nullptr, s});
+}
+
+hipError_t launch_direct_solve(const DirectPlan& pl, const DirectArgs& a, hipStream_t s) {
+  const DirectPlan* p = &pl;
+  return substitute(Launch{&p, 1, &a, nullptr, s});
+}
+
+hipError_t direct_batch_launch(const std::vector<DirectJob>& jobs, DirectBatch& db,
+                               hipStream_t s) {
+  const int n = (int)jobs.size();
+  if (n > db.cap) {   // nothing is pending: the last launch was waited for
+    dev_free(db.d, s);
+    dev_free(db.d_out, s);
+    db.d = nullptr;
+    db.d_out = nullptr;
+    db.cap = 0;
+    SSO_TRY(dev_alloc_scratch(&db.d, 2 * n, s));
+    SSO_TRY(dev_alloc_scratch(&db.d_out, 6 * n, s));
+    db.cap = 2 * n;
+  }
+  if (!db.ev) SSO_TRY(hipEventCreateWithFlags(&db.ev, hipEventDisableTiming));
+  db.h.resize(n);
+  std::vector<const DirectPlan*> plans(n);
+  int nf = 0;
+  for (int i = 0; i < n; ++i) {
+    db.h[i] = jobs[i].a;
+    plans[i] = jobs[i].plan;
+    if (jobs[i].factor) nf = i + 1;
+  }
+  SSO_TRY(hipMemcpyAsync(db.d, db.h.data(), sizeof(DirectArgs) * n, hipMemcpyHostToDevice, s));
+  if (nf > 0) {
+    hipLaunchKernelGGL(k_direct_clear, dim3((unsigned)((nf + 63) / 64)), dim3(64), 0, s,
+                       DirectArgs{}, db.d, nf);
+    SSO_TRY(hipGetLastError());
+    SSO_TRY(factor(Launch{plans.data(), nf, nullptr, db.d, s}));
+  }
+  SSO_TRY(substitute(Launch{plans.data(), n, nullptr, db.d, s}));
+  for (const DirectJob& j : jobs) {
+    if (!j.factor) SSO_TRY(launch_axpy(1.0, j.a.sol, j.x, 6 * (int64_t)j.m->n_nodes, s));
+    SSO_TRY(launch_true_residual(*j.m, *j.pat, j.a.K, j.x, j.b, j.w->r, *j.w, j.d_scal, s));
+  }
+  hipLaunchKernelGGL(k_direct_collect, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, db.d, n,
+                     db.d_out);
+  SSO_TRY(hipGetLastError());
+  return hipEventRecord(db.ev, s);
+}
+
+hipError_t direct_batch_wait(DirectBatch& db, hipStream_t s) {
+  SSO_TRY(hipEventSynchronize(db.ev));
+  db.out.resize(3 * db.h.size());
+  SSO_TRY(hipMemcpyAsync(db.out.data(), db.d_out, sizeof(double) * db.out.size(),
+                         hipMemcpyDeviceToHost, s));
+  return hipStreamSynchronize(s);
+}
+
+void direct_batch_free(DirectBatch& db, hipStream_t s) {
+  if (db.ev) {
+    (void)hipEventSynchronize(db.ev);
+    (void)hipEventDestroy(db.ev);
+  }
+  dev_free(db.d, s);
+  dev_free(db.d_out, s);
+  db = DirectBatch();
 }
 
 }  // namespace sso

@@ -111,50 +111,79 @@ void coordinates(Part& g) {
   }
 }
 
-// Cuts the part at the median of a coordinate.  side: 0, 1, or 2 in the separator (the nodes of
-// one side that touch the other).  Returns the separator's size; n0, n1: the sides without it.
-int try_split(const Part& g, const std::vector<int32_t>& c, std::vector<int8_t>& side,
-              std::vector<int32_t>& hist, int& n0, int& n1) {
+// A cut of a part at a value of one coordinate (side 0: below at; by_list: the first half of the
+// list instead) and its separator: the nodes of one side that touch the other.
+struct Cut {
+  int k = 0, at = 0;
+  bool by_list = false;
+  int from = 1;                 // the side that the separator is taken from
+  int size = 0, n0 = 0, n1 = 0;
+};
+
+// The most balanced cut along coordinate k.  A distance changes by at most 1 along an edge, so a
+// coordinate (sums and differences of at most four of them) by at most 4: only nodes that close
+// to the cut can touch the other side, and only their edges are looked at.
+Cut try_split(const Part& g, int k, std::vector<int32_t>& hist) {
   const int n = g.n();
-  const auto range = std::minmax_element(c.begin(), c.end());
-  const int lo = *range.first, hi = *range.second;
-  int left = 0, cut_at = 0;        // side 0: c < cut_at
+  const std::vector<int32_t>& c = g.coord[k];
+  int lo = c[0], hi = c[0];
+  for (int v : c) {
+    lo = v < lo ? v : lo;
+    hi = v > hi ? v : hi;
+  }
+  Cut t;
+  t.k = k;
+  int left = n / 2;
   if (lo < hi) {
     hist.assign(hi - lo + 2, 0);
     for (int v : c) ++hist[v - lo + 1];
     int below = 0, best = n + 1;
-    for (int k = 1; k <= hi - lo; ++k) {       // side 0 = values below lo + k
-      below += hist[k];
+    for (int q = 1; q <= hi - lo; ++q) {       // side 0: values below lo + q
+      below += hist[q];
       const int off = std::abs(n - 2 * below);
       if (off < best) {
         best = off;
         left = below;
-        cut_at = lo + k;
+        t.at = lo + q;
       }
     }
-    for (int v = 0; v < n; ++v) side[v] = c[v] >= cut_at;
-  } else {                          // one value: cut the list where it lies
-    left = n / 2;
-    for (int v = 0; v < n; ++v) side[v] = v >= left;
+  } else {
+    t.by_list = true;
   }
   int touch[2] = {0, 0};
   for (int v = 0; v < n; ++v) {
-    const int s = side[v] & 1;
-    for (int e = g.rp[v]; e < g.rp[v + 1]; ++e)
-      if ((side[g.col[e]] & 1) != s) {
+    if (!t.by_list && (c[v] < t.at - 4 || c[v] > t.at + 3)) continue;
+    const bool s = t.by_list ? v >= left : c[v] >= t.at;
+    for (int e = g.rp[v]; e < g.rp[v + 1]; ++e) {
+      const int w = g.col[e];
+      if ((t.by_list ? w >= left : c[w] >= t.at) != s) {
         ++touch[s];
-        side[v] = (int8_t)(s | 4);
+        break;
+      }
+    }
+  }
+  t.from = touch[1] < touch[0] || (touch[1] == touch[0] && left <= n - left) ? 1 : 0;
+  t.size = touch[t.from];
+  t.n0 = left - (t.from == 0 ? touch[0] : 0);
+  t.n1 = n - left - (t.from == 1 ? touch[1] : 0);
+  return t;
+}
+
+// Each node's side (0, 1) under the cut, 2 in the separator.
+void take_split(const Part& g, const Cut& t, std::vector<int8_t>& side) {
+  const int n = g.n();
+  const std::vector<int32_t>& c = g.coord[t.k];
+  auto of = [&](int v) { return (int8_t)(t.by_list ? v >= n / 2 : c[v] >= t.at); };
+  for (int v = 0; v < n; ++v) side[v] = of(v);
+  for (int v = 0; v < n; ++v) {
+    if (side[v] != t.from) continue;
+    if (!t.by_list && (c[v] < t.at - 4 || c[v] > t.at + 3)) continue;
+    for (int e = g.rp[v]; e < g.rp[v + 1]; ++e)
+      if (of(g.col[e]) != t.from) {
+        side[v] = 2;
         break;
       }
   }
-  const int from = touch[1] < touch[0] || (touch[1] == touch[0] && left <= n - left) ? 1 : 0;
-  for (int v = 0; v < n; ++v) {
-    const int s = side[v] & 1;
-    side[v] = (int8_t)((side[v] & 4) && s == from ? 2 : s);
-  }
-  n0 = left - (from == 0 ? touch[0] : 0);
-  n1 = n - left - (from == 1 ? touch[1] : 0);
-  return touch[from];
 }
 
 Part sub_part(const Part& g, const std::vector<int8_t>& side, int which, int n,
@@ -198,28 +227,26 @@ std::unique_ptr<Tree> dissect(Part g, int threads) {
     return t;
   }
   if (g.coord[0].empty()) coordinates(g);
-  std::vector<int8_t> side(n), best_side;
+  std::vector<int8_t> side(n);
   std::vector<int32_t> hist;
   double cost = 0.0;
-  int n0 = 0, n1 = 0;
+  Cut best;
   for (int k = 0; k < 4; ++k) {
-    int a, b;
-    const int s = try_split(g, g.coord[k], side, hist, a, b);
-    const double balance = (double)std::max(a, b) / n;
-    const double ck = s * (1.0 + 2.0 * std::max(0.0, balance - 0.55)) + 1e-6 * balance;
+    const Cut t = try_split(g, k, hist);
+    const double balance = (double)std::max(t.n0, t.n1) / n;
+    const double ck = t.size * (1.0 + 2.0 * std::max(0.0, balance - 0.55)) + 1e-6 * balance;
     if (k == 0 || ck < cost) {
       cost = ck;
-      n0 = a;
-      n1 = b;
-      best_side = side;
+      best = t;
     }
   }
+  take_split(g, best, side);
   std::vector<int32_t>& local = hist;
   local.resize(n);
   for (int v = 0; v < n; ++v)
-    if (best_side[v] == 2) t->own.push_back(g.id[v]);
-  Part left = sub_part(g, best_side, 0, n0, local);
-  Part right = sub_part(g, best_side, 1, n1, local);
+    if (side[v] == 2) t->own.push_back(g.id[v]);
+  Part left = sub_part(g, side, 0, best.n0, local);
+  Part right = sub_part(g, side, 1, best.n1, local);
   g = Part();
   if (threads > 1 && n >= THREAD_NODES) {
     std::exception_ptr err[2];
@@ -438,6 +465,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       D.ns6 = 6 * ns;
       D.nb6 = 6 * nb;
       D.np = ceil_div(D.ns6, DIRECT_NB);
+      D.nt = D.np + ceil_div(D.nb6, DIRECT_NB);
       D.level = h;
       for (int c = 0; c < 2; ++c) D.child[c] = F.child[c] < 0 ? -1 : rank[F.child[c]];
       D.nodes_off = (int32_t)plan.nodes.size();
@@ -465,9 +493,9 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       D.w_off = w;
       if (D.np > 1) {
         again += even((int64_t)(D.ns6 + D.nb6) * D.ns6);
-        w += (int64_t)DIRECT_NB * DIRECT_NB * (D.np + ceil_div(D.nb6, DIRECT_NB));
+        w += 2 * (int64_t)DIRECT_NB * DIRECT_NB * D.nt;
       }
-      D.u_off = schur.take(even((int64_t)D.nb6 * D.nb6));
+      D.u_off = schur.take(direct_tri(D.nb6));
       D.v_off = plan.v_len;
       plan.v_len += D.nb6;
       D.b_off = b_off;
@@ -481,10 +509,10 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       for (int c : plan.fronts[i].child)
         if (c >= 0) {
           const DirectFront& C = plan.fronts[c];
-          schur.give(C.u_off, even((int64_t)C.nb6 * C.nb6));
+          schur.give(C.u_off, direct_tri(C.nb6));
         }
   }
-  plan.u_len = schur.top;
+  plan.u_len = even(schur.top);
   if (8.0 * (double)plan.values() > max_bytes) return false;
 
   // work lists
@@ -494,7 +522,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
   for (int h = 0; h < nl; ++h) {
     const int np = plan.level_np[h];
     plan.level_off[h] = (int32_t)plan.steps.size();
-    plan.steps.resize(plan.steps.size() + STEP_PANEL + 2 * np, DirectRange{0, 0});
+    plan.steps.resize(plan.steps.size() + STEP_PANEL + np + 1, DirectRange{0, 0});
     DirectRange* st = plan.steps.data() + plan.level_off[h];
     auto open = [&](int s) { st[s].off = (int32_t)plan.items.size(); };
     auto close = [&](int s) { st[s].cnt = (int32_t)plan.items.size() - st[s].off; };
@@ -533,24 +561,19 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       for (int k = 0; k < cnt; ++k) local[list[k]] = -1;
     }
     close(STEP_ASM);
-    for (int k = 0; k < np; ++k) {
-      open(STEP_PANEL + 2 * k);
-      for (int i : by_level[h]) {
+    for (int q = 0; q <= np; ++q) {
+      open(STEP_PANEL + q);
+      for (int i : by_level[h]) {          // the longer work first
         const DirectFront& D = plan.fronts[i];
-        if (D.np <= k) continue;
-        const int rows = D.np + ceil_div(D.nb6, DIRECT_NB);
-        for (int r = 0; r < rows; ++r) plan.items.push_back({i, r, 0, 0, 0});
+        for (int r = 0; q < D.np && r < D.nt; ++r) plan.items.push_back({i, r, -1, 0, 0});
       }
-      close(STEP_PANEL + 2 * k);
-      open(STEP_PANEL + 2 * k + 1);
       for (int i : by_level[h]) {
         const DirectFront& D = plan.fronts[i];
-        if (D.np <= k || D.np == 1) continue;   // a single panel is finished by its scaling
-        const int rows = D.np + ceil_div(D.nb6, DIRECT_NB);
-        for (int r = 0; r < rows; ++r)
+        if (q == 0 || q > D.np || D.np == 1) continue;   // a single panel is done once scaled
+        for (int r = 0; r < D.nt; ++r)
           for (int c = 0; c < D.np; ++c) plan.items.push_back({i, r, c, 0, 0});
       }
-      close(STEP_PANEL + 2 * k + 1);
+      close(STEP_PANEL + q);
     }
     open(STEP_SCHUR);
     for (int i : by_level[h]) {
@@ -633,11 +656,10 @@ int check_direct_plan(int n, const int32_t* rp, const int32_t* col, const Direct
     for (int k = 0; k < cnt; ++k) at[list[k]] = -1;
     const int64_t panel = (int64_t)(D.ns6 + D.nb6) * D.ns6;
     if (D.fact_off + panel > plan.fact_len || D.work_off + panel > plan.work_len ||
-        D.u_off + (int64_t)D.nb6 * D.nb6 > plan.u_len || D.v_off + D.nb6 > plan.v_len ||
+        D.u_off + direct_tri(D.nb6) > plan.u_len || D.v_off + D.nb6 > plan.v_len ||
         D.b_off + D.ns6 > 6 * (int64_t)n ||
         (D.np > 1 && (D.again_off + panel > plan.again_len ||
-                      D.w_off + (int64_t)DIRECT_NB * DIRECT_NB *
-                                    (D.np + ceil_div(D.nb6, DIRECT_NB)) > plan.w_len)))
+                      D.w_off + 2 * (int64_t)DIRECT_NB * DIRECT_NB * D.nt > plan.w_len)))
       return fail(7, "array too short", (long long)f);
   }
   if (blocks != plan.entries.size()) return fail(8, "blocks of K", (long long)blocks);
@@ -652,7 +674,7 @@ int check_direct_plan(int n, const int32_t* rp, const int32_t* col, const Direct
       const DirectFront& D = plan.fronts[f];
       const int last = parent[f] < 0 ? D.level : plan.fronts[parent[f]].level;
       if (D.nb6 && D.level <= h && last >= h)
-        live.emplace_back(D.u_off, D.u_off + (int64_t)D.nb6 * D.nb6);
+        live.emplace_back(D.u_off, D.u_off + direct_tri(D.nb6));
     }
     std::sort(live.begin(), live.end());
     for (size_t k = 1; k < live.size(); ++k)

@@ -18,7 +18,7 @@ constexpr int DIRECT_ASM_ROWS = 8;
 constexpr int DIRECT_ASM_COLS = 16;
 // Columns of a backward-substitution work item, rows of a forward-substitution one.
 constexpr int DIRECT_BWD_COLS = 32;
-constexpr int DIRECT_FWD_ROWS = 64;
+constexpr int DIRECT_FWD_ROWS = 16;
 // Most own DOFs of a front (a substitution stages them in LDS).
 constexpr int DIRECT_MAX_OWN = 6144;
 
@@ -32,15 +32,23 @@ struct DirectFront {
                              //   -1; then the same for child 1
   int32_t child[2];          // fronts, -1: none
   int32_t np;                // panels: ceil(ns6 / DIRECT_NB)
+  int32_t nt;                // row tiles: np, then ceil(nb6 / DIRECT_NB)
   int32_t level;             // height: every child has a lower level
+  int32_t pad;
   int64_t fact_off;          // factor [(ns6 + nb6) x ns6]
   int64_t work_off;          // assembled panel of the level, same shape
   int64_t again_off;         // np > 1: second work panel of the level, same shape
-  int64_t w_off;             // np > 1: scaled panel of a step, DIRECT_NB x DIRECT_NB row tiles
-  int64_t u_off;             // Schur complement [nb6 x nb6], lower triangle
+  int64_t w_off;             // np > 1: scaled panels of two steps, DIRECT_NB x DIRECT_NB row tiles
+  int64_t u_off;             // Schur complement, lower triangle row by row (direct_tri)
   int64_t v_off;             // update vector of the forward substitution [nb6]
   int64_t b_off;             // right-hand side of the own DOFs [ns6]
 };
+
+// Entries of a lower triangle in front of row r, and of the triangle of r rows.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int64_t direct_tri(int r) { return (int64_t)r * (r + 1) / 2; }
 
 // A work item: the front and up to two tile indices; entries [e0, e1) of an assembly item.
 struct DirectItem {
@@ -58,8 +66,9 @@ struct DirectRange {
   int32_t off, cnt;
 };
 
-// Step lists of a level: assembly, Schur complement, forward and backward substitution, then for
-// each panel the scaling and the update.
+// Step lists of a level: assembly, Schur complement, forward and backward substitution, then the
+// panel steps 0 .. np: step q scales panel q (items with j < 0: row tile i) and updates with panel
+// q - 1 (tile i, j).
 enum { STEP_ASM = 0, STEP_SCHUR = 1, STEP_FWD = 2, STEP_BWD = 3, STEP_PANEL = 4 };
 
 struct DirectPlan {
@@ -67,7 +76,7 @@ struct DirectPlan {
   std::vector<int32_t> nodes, maps;
   std::vector<DirectEntry> entries;
   std::vector<DirectItem> items;
-  std::vector<DirectRange> steps;     // steps[level_off[h] + STEP_*] (panels: + 2 k, + 2 k + 1)
+  std::vector<DirectRange> steps;     // steps[level_off[h] + STEP_*] (panels: STEP_PANEL + q)
   std::vector<int32_t> level_off;     // per level
   std::vector<int32_t> level_np;      // most panels of a front of the level
   int n_nodes = 0;

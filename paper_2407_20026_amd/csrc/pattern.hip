@@ -303,20 +303,13 @@ __global__ void k_ell_cols(int n_nodes, int w, const int32_t* brow_ptr, const in
 }
 
 hipError_t build_pattern(const Mesh& m, Pattern& pat, unsigned* d_err, hipStream_t s,
-                         unsigned* h_err) {
+                         unsigned* h_err, Arena& scratch) {
   const int n = m.n_nodes;
   pat.n_bcoo = 4 * (int64_t)m.n_beams + 16 * (int64_t)m.n_quads;
   int32_t *cnt = nullptr, *fill = nullptr, *tmp = nullptr, *ucnt = nullptr;
   uint64_t* keys = nullptr;
   int64_t nt = (n + SCAN_TILE - 1) / SCAN_TILE + 2;
   int64_t nk = pat.n_bcoo > 0 ? pat.n_bcoo : 1;
-  // the build's own scratch: one arena, freed on every way out of this function
-  Arena scratch;
-  struct Release {
-    Arena& a;
-    hipStream_t s;
-    ~Release() { arena_free(a, s); }
-  } release{scratch, s};
   {
     AllocScope sc(nullptr, &scratch);
     SSO_TRY(dev_alloc(&cnt, (n + 1), s));
@@ -391,12 +384,15 @@ hipError_t build_scalar_view(const Mesh& m, const Pattern& pat, int32_t* row_ptr
   return hipGetLastError();
 }
 
-void free_pattern(Pattern& pat, hipStream_t s) {
+void free_pattern(Pattern& pat, hipStream_t s, bool idle) {
   for (void* q : {(void*)pat.brow_ptr, (void*)pat.bcol, (void*)pat.bseg, (void*)pat.bperm,
                   (void*)pat.bslot, (void*)pat.bdiag, (void*)pat.estart, (void*)pat.bsrow,
                   (void*)pat.bcol_ell, (void*)pat.bsym})
     dev_release(q, &pat.mem, s);
-  arena_free(pat.mem, s);
+  if (idle)
+    arena_recycle(pat.mem, s);
+  else
+    arena_free(pat.mem, s);
   pat = Pattern();
 }
 

@@ -96,6 +96,13 @@ struct Arena {
 };
 constexpr size_t ARENA_CHUNK = (size_t)2 << 20;
 constexpr size_t ARENA_ALIGN = 256;
+// Sizes of chunks that hold one buffer: rounded up to a multiple of an eighth of the power of two
+// below, so that a chunk given back fits the next request of about its size.
+inline size_t chunk_size(size_t bytes) {
+  size_t step = ARENA_ALIGN;
+  while (16 * step <= bytes) step *= 2;
+  return (bytes + step - 1) / step * step;
+}
 
 // Block-level pattern (6x6 blocks, one block row per node).
 struct Pattern {
@@ -193,6 +200,8 @@ hipError_t pool_alloc(void** p, size_t bytes, hipStream_t s);
 hipError_t arena_alloc(Arena& a, size_t bytes, hipStream_t s, void** out, int64_t* held);
 bool arena_owns(const Arena& a, const void* p);
 void arena_free(Arena& a, hipStream_t s);   // every chunk, stream-ordered on s
+// Every chunk to the device's cache of idle chunks: no work that uses them may be pending.
+void arena_recycle(Arena& a, hipStream_t s);
 
 // While an entry point works on a problem, an AllocScope points this thread's allocations at
 // the problem's arena and its byte count (sso_problem_bytes: the chunks held); the pattern build
@@ -260,11 +269,13 @@ int check_pattern(const HostPattern& h, char* msg, size_t len);
 // ---- launch helpers (each defined in its own translation unit) ----------------------------
 
 // pattern.hip
+// scratch: buffers that only the build uses; the caller frees them, in stream order or once the
+// stream is idle.
 hipError_t build_pattern(const Mesh& m, Pattern& pat, unsigned* d_err, hipStream_t s,
-                         unsigned* h_err);
+                         unsigned* h_err, Arena& scratch);
 hipError_t build_scalar_view(const Mesh& m, const Pattern& pat, int32_t* row_ptr, int32_t* col,
                              int32_t* perm, int32_t* seg, hipStream_t s);
-void free_pattern(Pattern& pat, hipStream_t s);
+void free_pattern(Pattern& pat, hipStream_t s, bool idle);   // idle: nothing uses it any more
 
 // elements.hip
 hipError_t launch_element_stiffness(const Mesh& m, double* coo, double* qarea, unsigned* d_err,
@@ -317,11 +328,13 @@ struct DirectArgs {
   const double* rhs;
   double* sol;
   unsigned* flag;          // set when a pivot is too small
+  const double* scal;      // multi-problem launches: where the residual's squared norms are left
   int n_levels;
 };
 // Factor K (a.K) into a.fact; then sol = K^-1 rhs as often as wanted.
 hipError_t launch_direct_factor(const DirectPlan& pl, const DirectArgs& a, hipStream_t s);
 hipError_t launch_direct_solve(const DirectPlan& pl, const DirectArgs& a, hipStream_t s);
+hipError_t launch_direct_clear(const DirectArgs& a, hipStream_t s);   // *a.flag = 0
 
 // pcg.hip
 struct PcgWork {
@@ -483,6 +496,32 @@ hipError_t pcg_batch_wait(BatchWork& bw);
 // synchronises the stream).
 hipError_t pcg_batch_iterate(const BatchLists& lists, int n_iter, BatchWork& bw, hipStream_t s);
 void batch_free(BatchWork& bw, hipStream_t s);
+// Multi-problem launches of the direct solver: one launch per kernel and step for all jobs, each
+// problem's fronts as in a launch of its own.  A job factors and substitutes (factor) or
+// substitutes for the residual and adds to x, and leaves its true residual's norms.
+struct DirectJob {
+  const DirectPlan* plan;
+  DirectArgs a;            // rhs, sol, scal of this launch
+  bool factor;
+  const Mesh* m;
+  const Pattern* pat;
+  const double* b;         // right-hand side of the system
+  double* x;
+  PcgWork* w;
+  double* d_scal;
+};
+struct DirectBatch {
+  std::vector<DirectArgs> h;
+  DirectArgs* d = nullptr;
+  double* d_out = nullptr;   // [n][3]: rr, bb, flag
+  std::vector<double> out;
+  int cap = 0;
+  hipEvent_t ev = nullptr;
+};
+// jobs: those that factor first.  direct_batch_wait waits for the results and fills db.out.
+hipError_t direct_batch_wait(DirectBatch& db, hipStream_t s);
+hipError_t direct_batch_launch(const std::vector<DirectJob>& jobs, DirectBatch& db, hipStream_t s);
+void direct_batch_free(DirectBatch& db, hipStream_t s);
 // Deterministic dot product a^T b; result written to *d_out (device).
 hipError_t launch_dot(const double* a, const double* b, int64_t n, PcgWork& w, double* d_out,
                       hipStream_t s);

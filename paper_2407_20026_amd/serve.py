@@ -41,11 +41,20 @@ FUSED_MAX_NODES = 8192
 ARENA_CHUNK = 2 << 20      # the library's chunk size for the buffers of one owner
 
 
+def _chunk(b: int) -> int:
+    """Size of the chunk that a large buffer gets: the library rounds to eighths of a power of
+    two."""
+    step = 256
+    while 16 * step <= b:
+        step *= 2
+    return -(-b // step) * step
+
+
 def _arena_bound(bufs) -> int:
     """Device memory an owner holds for buffers of the given byte sizes: a buffer above a
     quarter chunk has a chunk of its own, smaller ones share chunks that are left only when
     less than a quarter chunk is free (so each but the last is at least 3/4 used)."""
-    big = sum(-(-b // 256) * 256 for b in bufs if b > ARENA_CHUNK // 4)
+    big = sum(_chunk(b) for b in bufs if b > ARENA_CHUNK // 4)
     small = sum(-(-b // 256) * 256 for b in bufs if b <= ARENA_CHUNK // 4)
     chunks = 0 if small == 0 else int(small * 4 / 3 // ARENA_CHUNK) + 1
     return big + chunks * ARENA_CHUNK
@@ -72,15 +81,15 @@ def footprint_bytes(mesh, mixed: bool | None = False) -> int:
     bufs += [288 * blocks, 8 * dinv]                                               # K, Dinv
     bufs += [8 * ndof] * 14 + [8 * 6 * nb, 8 * 14 * nq]                            # vectors, grads
     bufs += [8 * 11 * 1024, 4096, 64]                                              # partials
-    if mixed:
-        bufs += [144 * max(blocks, padded), 4 * dinv] + [4 * ndof] * 11
-    else:
-        # the direct solver's arrays, at most what the library lets them take (a structure that
-        # would fill more runs PCG), and its tables, some 200 bytes a node
-        direct = 288 * (math.log2(nn + 1) + 1) * (1.3 * nn + 2.6 * nb + 7.0 * nq) + (1 << 20)
-        if nn <= FUSED_MAX_NODES:   # or B = K M in FP64 (single-reduction recurrences)
-            direct = max(direct, 288 * max(blocks, padded))
-        bufs += [int(direct), 256 * nn]
+    # the direct solver's arrays, at most what the library lets them take (a structure that would
+    # fill more runs PCG), and its tables, some 200 bytes a node
+    direct = 288 * (math.log2(nn + 1) + 1) * (1.2 * nn + 2.3 * nb + 6.3 * nq) + (1 << 20)
+    if mixed:                       # or the FP32 copies of mixed precision's inner solves
+        bufs += [4 * ndof] * 11
+        direct = max(direct, 144 * max(blocks, padded) + 4 * dinv)
+    elif nn <= FUSED_MAX_NODES:     # or B = K M in FP64 (single-reduction recurrences)
+        direct = max(direct, 288 * max(blocks, padded))
+    bufs += [int(direct), 256 * nn]
     return int(1.05 * (_arena_bound(pattern) + _arena_bound(bufs))) + (1 << 20)
 
 
@@ -320,6 +329,14 @@ def streams_overlap(a, b, spin_cycles: int = 4_000_000):
     return overlap
 
 
+# Direct solves (SOLVER_AUTO) are one launch each, bound by the latency of its some 60 kernels: a
+# few requests in it take little longer than one.  A launch of fewer than COMPANY requests that has
+# not begun therefore waits for the next arrival if that is at most COMPANY_S away, about the time
+# of a launch.
+COMPANY = 4
+COMPANY_S = 2.5e-3
+
+
 class BatchedServer:
     """Admission by slot count and device-memory budget; the iterations of all requests in
     flight advance together in multi-problem launches on one stream.
@@ -393,7 +410,7 @@ class BatchedServer:
         results: list[Result] = []
         free = self.budget
         peak_inflight = peak_bytes = 0
-        nxt = 0
+        nxt = fresh = 0      # fresh: requests of `active` that no launch has taken yet
         t_start = time.perf_counter()
         phase = dict(admit=0.0, iterate=0.0, finish=0.0, idle=0.0)
 
@@ -435,20 +452,38 @@ class BatchedServer:
                 while nxt < len(reqs) and reqs[nxt].arrival <= now:
                     waiting.append(reqs[nxt])
                     nxt += 1
+                fresh += len(joining)
                 for item in joining:
                     item[0].set_stream(it_stream)
                     active.append(item)
                 joining.clear()
-                peak_inflight = max(peak_inflight, len(active))
-                peak_bytes = max(peak_bytes, self.budget - free)
+                if fresh == len(active) and 0 < fresh < min(COMPANY, self.slots) and \
+                        self.options.solver == SOLVER_AUTO and nxt < len(reqs) and \
+                        reqs[nxt].arrival - clock() <= COMPANY_S:
+                    finish()
+                    time.sleep(max(0.0, reqs[nxt].arrival - clock()))
+                    while nxt < len(reqs) and reqs[nxt].arrival <= clock():
+                        waiting.append(reqs[nxt])
+                        nxt += 1
+                    admit()
+                    peak_inflight = max(peak_inflight, len(active) + len(joining))
+                    peak_bytes = max(peak_bytes, self.budget - free)
+                    if joining:
+                        continue
+                # in flight: admitted and not finished (iterating, stopped at the last poll and
+                # not yet finished, or, below, joining at the next launch)
+                peak_inflight = max(peak_inflight, len(active) + len(finishing))
                 t0 = time.perf_counter()
                 if active:
                     batch.launch([a[0] for a in active], self.chunk)
+                    fresh = 0
                 # while the chunk runs: finish what stopped at the last poll, admit arrivals
                 t1 = time.perf_counter()
                 finish()
                 t2 = time.perf_counter()
                 admit()
+                peak_inflight = max(peak_inflight, len(active) + len(joining))
+                peak_bytes = max(peak_bytes, self.budget - free)
                 t3 = time.perf_counter()
                 phase["finish"] += t2 - t1
                 phase["admit"] += t3 - t2

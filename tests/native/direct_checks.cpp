@@ -96,7 +96,7 @@ static double children(const DirectPlan& pl, const std::vector<double>& u, const
     const int mc = pl.maps.at(F.map_off + k * cnt + c / 6);
     if (mr < 0 || mc < 0) continue;
     const int a = 6 * mr + r % 6, b = 6 * mc + c % 6;
-    s += u.at(C.u_off + (int64_t)std::max(a, b) * C.nb6 + std::min(a, b));
+    s += u.at(C.u_off + direct_tri(std::max(a, b)) + std::min(a, b));
   }
   return s;
 }
@@ -200,7 +200,7 @@ static int run(const std::string& name, const Graph& g, bool numeric) {
           double t = children(pl, u, F, s + r, s + c);
           for (int k = 0; k < s; ++k)
             t -= A[(s + r) * s + k] * f0[F.work_off + (int64_t)(s + c) * s + k];
-          u.at(F.u_off + (int64_t)r * F.nb6 + c) = t;
+          u.at(F.u_off + direct_tri(r) + c) = t;
         }
     }
   }
