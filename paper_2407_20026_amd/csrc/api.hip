@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <system_error>
@@ -83,9 +84,11 @@ struct sso_problem {
   double* wv = nullptr;         //   partials (allocated on first use)
   double* xpart = nullptr;
   double* d_scal = nullptr;     // small device scalars (dot products, residual norms)
-  double* h_scal = nullptr;     // host mirror of d_scal (pageable)
+  double* h_scal = nullptr;     // pinned slot, what the stream leaves for the host: ||r||^2,
+                                // ||b||^2 (or a dot product), the direct solver's flag and the
+                                // elements' errors; [4, 6) the size objective's sums
   unsigned* d_err = nullptr;
-  unsigned* h_err = nullptr;    // host mirror of d_err (pageable)
+  unsigned* h_err = nullptr;    // host mirror of d_err, in the same slot
   PcgWork w;
   int32_t* row_ptr = nullptr;   // scalar CSR view (built on demand)
   int32_t* col = nullptr;
@@ -93,6 +96,7 @@ struct sso_problem {
   int32_t* seg = nullptr;
   bool direct = false;          // the last solve chose the direct solver
   bool factored = false;        // its factor is that of the current K
+  bool unchecked = false;       // the elements' errors are still to be looked at
   DirectArgs da{};              // its arrays (allocated on first use)
   int direct_steps = 0;         // substitutions of the last solve
   double direct_rr = -1.0, direct_bb = 0.0;   // its last true residual and load, squared norms
@@ -199,6 +203,57 @@ float elapsed_us(hipEvent_t a, hipEvent_t b) {
   return 1000.f * ms;
 }
 
+// Pinned host memory that kernels write a problem's scalars into, so that the host reads them after
+// a synchronisation without a copy: slots of 128 bytes from one block for the life of the process
+// (pinning and unpinning cost up to a millisecond each), more from blocks of their own.
+constexpr int PIN_SLOTS = 4096;
+constexpr size_t PIN_DOUBLES = 16;
+struct PinnedSlots {
+  std::mutex mu;
+  double* block = nullptr;
+  std::vector<int> idle;
+};
+PinnedSlots pinned_slots;
+
+hipError_t pinned_take(double** out) {
+  *out = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(pinned_slots.mu);
+    if (!pinned_slots.block) {
+      try {
+        pinned_slots.idle.reserve(PIN_SLOTS);
+      } catch (...) {
+        return hipErrorOutOfMemory;
+      }
+      const hipError_t e =
+          hipHostMalloc(reinterpret_cast<void**>(&pinned_slots.block),
+                        sizeof(double) * PIN_DOUBLES * PIN_SLOTS, hipHostMallocPortable);
+      if (e != hipSuccess) return e;
+      for (int i = PIN_SLOTS - 1; i >= 0; --i) pinned_slots.idle.push_back(i);
+    }
+    if (!pinned_slots.idle.empty()) {
+      *out = pinned_slots.block + PIN_DOUBLES * (size_t)pinned_slots.idle.back();
+      pinned_slots.idle.pop_back();
+    }
+  }
+  if (!*out) {
+    const hipError_t e = hipHostMalloc(reinterpret_cast<void**>(out),
+                                       sizeof(double) * PIN_DOUBLES, hipHostMallocPortable);
+    if (e != hipSuccess) return e;
+  }
+  std::memset(*out, 0, sizeof(double) * PIN_DOUBLES);
+  return hipSuccess;
+}
+
+void pinned_give(double* p) {
+  if (!p) return;
+  std::lock_guard<std::mutex> lock(pinned_slots.mu);
+  if (p >= pinned_slots.block && p < pinned_slots.block + PIN_DOUBLES * PIN_SLOTS)
+    pinned_slots.idle.push_back((int)((p - pinned_slots.block) / (ptrdiff_t)PIN_DOUBLES));
+  else
+    (void)hipHostFree(p);
+}
+
 void free_problem(sso_problem* p) {
   if (!p) return;
   hipStream_t s = p->s;
@@ -213,8 +268,6 @@ void free_problem(sso_problem* p) {
                   (void*)p->gw, (void*)p->wv, (void*)p->xpart})
     dev_release(q, &p->mem, s);
   pcg_free(p->w, &p->mem, s);
-  delete[] p->h_scal;
-  delete p->h_err;
   for (auto& e : p->ev)
     if (e) (void)hipEventDestroy(e);
   if (p->ev_move) (void)hipEventDestroy(p->ev_move);
@@ -233,6 +286,7 @@ void free_problem(sso_problem* p) {
     arena_recycle(p->mem, s);
   else
     arena_free(p->mem, s);
+  if (idle) pinned_give(p->h_scal);   // else a kernel could still write it
   delete p;
 }
 
@@ -383,9 +437,9 @@ int create_impl(const sso_mesh* mesh, const sso_options* opts, hipStream_t strea
     }
   }
   TRY_HIP(dev_alloc(&p->d_err, 1, s));
-  p->h_err = new unsigned(0);
   TRY_HIP(dev_alloc(&p->d_scal, 8, s));
-  p->h_scal = new double[8]();
+  TRY_HIP(pinned_take(&p->h_scal));
+  p->h_err = reinterpret_cast<unsigned*>(p->h_scal + 8);
   TRY_HIP(hipMemsetAsync(p->d_err, 0, sizeof(unsigned), s));
   *p->h_err = 0;
   if (like) {
@@ -708,11 +762,15 @@ DirectNext direct_next(sso_problem* p, double rr, double bb, unsigned flag) {
   return DIRECT_AGAIN;
 }
 
+// Work that follows a solution on the stream, whatever the residual turns out to be: enqueued
+// behind each substitution, so that the host's look at the residual does not hold it up.
+using Tail = std::function<hipError_t()>;
+
 // K x = b with the direct solver: factor K if the current one is not yet factored, substitute,
 // and refine on the true residual (row sums in double-double) until it meets rtol, as long as a
-// step gains a factor of two.  *done: met; otherwise x is the best so far.  A K that is not
-// positive definite to working precision leaves p->direct false and x = 0.
-int run_direct(sso_problem* p, const double* b, double* x, bool* done) {
+// step gains a factor of two.  *done: met, and the stream idle; otherwise x is the best so far.  A
+// K that is not positive definite to working precision leaves p->direct false and x = 0.
+int run_direct(sso_problem* p, const double* b, double* x, bool* done, const Tail& tail) {
   hipStream_t s = p->s;
   const DirectPlan& pl = p->shared->plan;
   const DirectArgs& a = p->da;
@@ -729,14 +787,17 @@ int run_direct(sso_problem* p, const double* b, double* x, bool* done) {
   p->direct_rr = -1.0;
   p->direct_steps = 0;
   for (;;) {
-    TRY_HIP(launch_true_residual(p->m, p->pat, p->K, x, b, p->w.r, p->w, p->d_scal, s));
-    unsigned flag = 0;
-    TRY_HIP(hipMemcpyAsync(p->h_scal, p->d_scal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-    if (!p->factored)
-      TRY_HIP(hipMemcpyAsync(&flag, a.flag, sizeof(unsigned), hipMemcpyDeviceToHost, s));
+    TRY_HIP(launch_true_residual(p->m, p->pat, p->K, x, b, p->w.r, p->w, p->h_scal, s, a.flag,
+                                 p->d_err));
+    if (tail) TRY_HIP(tail());
     TRY_HIP(hipStreamSynchronize(s));
+    if (p->unchecked) {
+      p->unchecked = false;
+      if (p->h_scal[3] != 0.0) return SSO_EINVAL;
+    }
     const bool was = p->factored;
-    const DirectNext next = direct_next(p, p->h_scal[0], p->h_scal[1], flag);
+    const DirectNext next = direct_next(p, p->h_scal[0], p->h_scal[1],
+                                        !was && p->h_scal[2] != 0.0);
     if (next == DIRECT_FAILED && was) {   // a good factor: the right-hand side is not finite
       *done = true;
       return SSO_EBREAKDOWN;
@@ -769,14 +830,18 @@ int mixed_operands(sso_problem* p) {
   return SSO_OK;
 }
 
-// Solve K x = b (b masked) in the problem's precision mode.
-int run_solver(sso_problem* p, const double* b, double* x, int* iters, int* outer) {
+// Solve K x = b (b masked) in the problem's precision mode.  *tailed (may be null): the tail has
+// run behind the solution and the stream is idle.
+int run_solver(sso_problem* p, const double* b, double* x, int* iters, int* outer,
+               const Tail& tail = nullptr, bool* tailed = nullptr) {
   int status = SSO_OK;
   *outer = 0;
+  if (tailed) *tailed = false;
   if (p->direct) {
     bool done = false;
-    const int st = run_direct(p, b, x, &done);
+    const int st = run_direct(p, b, x, &done, tail);
     if (mixed(p)) *outer = p->direct_steps;
+    if (st == SSO_OK && done && tailed) *tailed = true;
     if (st != SSO_OK || done) return st;
     if (p->direct) {   // the target lies below what refinement reaches: corrections by PCG
       TRY_HIP(pcg_correct(p->m, p->pat, p->K, p->Dinv, b, x, p->opt.rtol, p->opt.max_it, p->w,
@@ -854,7 +919,10 @@ int prepare(sso_problem* p, bool batch) {
     TRY_HIP(launch_right_precondition(p->m, p->pat, p->K, p->Dinv, mx ? nullptr : p->B,
                                       mx ? p->B32 : nullptr, s));
   TRY_HIP(hipEventRecord(p->ev[2], s));
-  return read_errors(p);
+  p->unchecked = p->direct && !batch;
+  // a direct solve looks at the elements' errors together with its residual: what runs between is
+  // bounded by the plan whatever the values
+  return p->unchecked ? SSO_OK : read_errors(p);
 }
 
 // The start of a begun solve's PCG iteration (x = 0).
@@ -920,17 +988,27 @@ int size_objective_impl(sso_problem* p, double eps1, double u_max, double t_min,
   // volume terms, then dc/du (masked) with the sums c and W in d_scal[2..3]
   TRY_HIP(launch_volume_terms(m, t_min, gw, wv, s));
   TRY_HIP(launch_size_terms(m, p->u, u_max, wv, p->rhs, xpart, SIZE_XWG, p->d_scal + 2, s));
+  auto terms = [&] {
+    hipError_t e =
+        launch_adjoint_terms(m, p->pat, p->u, p->lam, 1.0, 0.0, p->gbeam, p->gquad, s);
+    if (e == hipSuccess) e = launch_size_combine(m, eps1, p->d_scal + 2, gw, p->gbeam, p->gquad, s);
+    if (e == hipSuccess)
+      e = launch_gather(m, p->pat, p->gbeam, p->gquad, dg_dxyz, dg_dt, nullptr, s);
+    if (e == hipSuccess) e = hipEventRecord(p->ev[5], s);
+    return e != hipSuccess ? e
+                           : hipMemcpyAsync(p->h_scal + 4, p->d_scal + 2, 2 * sizeof(double),
+                                            hipMemcpyDeviceToHost, s);
+  };
   int iters = 0, outer = 0;
-  const int status = run_solver(p, p->rhs, p->lam, &iters, &outer);
+  bool tailed = false;
+  const int status =
+      run_solver(p, p->rhs, p->lam, &iters, &outer, std::ref(terms), &tailed);
   if (status != SSO_OK && status != SSO_ENOTCONV) return status;
-  TRY_HIP(launch_adjoint_terms(m, p->pat, p->u, p->lam, 1.0, 0.0, p->gbeam, p->gquad, s));
-  TRY_HIP(launch_size_combine(m, eps1, p->d_scal + 2, gw, p->gbeam, p->gquad, s));
-  TRY_HIP(launch_gather(m, p->pat, p->gbeam, p->gquad, dg_dxyz, dg_dt, nullptr, s));
-  TRY_HIP(hipEventRecord(p->ev[5], s));
-  TRY_HIP(hipMemcpyAsync(p->h_scal + 2, p->d_scal + 2, 2 * sizeof(double),
-                         hipMemcpyDeviceToHost, s));
-  TRY_HIP(hipStreamSynchronize(s));
-  const double c = p->h_scal[2], W = p->h_scal[3];
+  if (!tailed) {
+    TRY_HIP(terms());
+    TRY_HIP(hipStreamSynchronize(s));
+  }
+  const double c = p->h_scal[4], W = p->h_scal[5];
   out_host[0] = (1.0 + eps1 * c) * W;
   out_host[1] = c;
   out_host[2] = W;
@@ -1136,16 +1214,26 @@ int sso_solve(sso_problem* p, double* u_out, sso_stats* stats) {
   int st = prepare(p, false);
   if (st != SSO_OK) return st;
   int iters = 0, outer = 0;
-  int status = run_solver(p, p->f, p->u, &iters, &outer);
-  if (status == SSO_EHIP || status == SSO_ENOMEM) return status;
-  TRY_HIP(hipEventRecord(p->ev[3], s));
-  TRY_HIP(launch_true_residual(p->m, p->pat, p->K, p->u, p->f, nullptr, p->w, p->d_scal, s));
-  TRY_HIP(hipMemcpyAsync(p->h_scal, p->d_scal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-  if (p->m.u_presc) TRY_HIP(launch_apply_prescribed(p->m, p->u, s));
-  if (u_out)
-    TRY_HIP(hipMemcpyAsync(u_out, p->u, sizeof(double) * 6 * (size_t)p->m.n_nodes,
-                           hipMemcpyDeviceToDevice, s));
-  TRY_HIP(hipStreamSynchronize(s));
+  const size_t u_bytes = sizeof(double) * 6 * (size_t)p->m.n_nodes;
+  bool tailed = false;
+  // prescribed displacements are written into u last, and refinement must not see them
+  auto copy_out = [&] {
+    hipError_t e = hipEventRecord(p->ev[3], s);
+    if (e == hipSuccess && u_out && !p->m.u_presc)
+      e = hipMemcpyAsync(u_out, p->u, u_bytes, hipMemcpyDeviceToDevice, s);
+    return e;
+  };
+  int status = run_solver(p, p->f, p->u, &iters, &outer, std::ref(copy_out), &tailed);
+  if (status == SSO_EHIP || status == SSO_ENOMEM || status == SSO_EINVAL) return status;
+  if (!tailed) {
+    TRY_HIP(hipEventRecord(p->ev[3], s));
+    TRY_HIP(launch_true_residual(p->m, p->pat, p->K, p->u, p->f, nullptr, p->w, p->h_scal, s));
+  }
+  if (!tailed || p->m.u_presc) {
+    if (p->m.u_presc) TRY_HIP(launch_apply_prescribed(p->m, p->u, s));
+    if (u_out) TRY_HIP(hipMemcpyAsync(u_out, p->u, u_bytes, hipMemcpyDeviceToDevice, s));
+    TRY_HIP(hipStreamSynchronize(s));
+  }
   if (stats) {
     std::memset(stats, 0, sizeof(*stats));
     stats->iters = iters;
@@ -1191,10 +1279,7 @@ int sso_solve_end(sso_problem* p, double* u_out, sso_stats* stats) {
   hipStream_t s = p->s;
   int status = SSO_OK, iters = 0, outer = 0;
   auto residual = [&] {   // into h_scal, once the stream gets there
-    hipError_t e = launch_true_residual(p->m, p->pat, p->K, p->u, p->f, nullptr, p->w, p->d_scal, s);
-    return e != hipSuccess ? e
-                           : hipMemcpyAsync(p->h_scal, p->d_scal, 2 * sizeof(double),
-                                            hipMemcpyDeviceToHost, s);
+    return launch_true_residual(p->m, p->pat, p->K, p->u, p->f, nullptr, p->w, p->h_scal, s);
   };
   if (p->direct) {
     if (mixed(p)) outer = p->direct_steps;
@@ -1489,8 +1574,7 @@ int sso_objective(sso_problem* p, int kind, const double* a, double* g_host) {
     return SSO_EINVAL;
   }
   const int64_t n = 6 * (int64_t)p->m.n_nodes;
-  TRY_HIP(launch_dot(lhs, p->u, n, p->w, p->d_scal, p->s));
-  TRY_HIP(hipMemcpyAsync(p->h_scal, p->d_scal, sizeof(double), hipMemcpyDeviceToHost, p->s));
+  TRY_HIP(launch_dot(lhs, p->u, n, p->w, p->h_scal, p->s));
   TRY_HIP(hipStreamSynchronize(p->s));
   *g_host = scale * p->h_scal[0];
   return SSO_OK;
@@ -1504,31 +1588,38 @@ int sso_adjoint(sso_problem* p, int kind, const double* dg_du, double* dg_dxyz, 
   double c_lam = 1.0, c_u = 1.0;
   const double* lam = p->u;
   int iters = 0, status = SSO_OK;
+  bool tailed = false;
+  auto terms = [&] {
+    hipError_t e = launch_adjoint_terms(p->m, p->pat, p->u, lam, c_lam, c_u, p->gbeam, p->gquad, s);
+    if (e == hipSuccess)
+      e = launch_gather(p->m, p->pat, p->gbeam, p->gquad, dg_dxyz, dg_dt, dg_dscale, s);
+    return e == hipSuccess ? hipEventRecord(p->ev[5], s) : e;
+  };
   TRY_HIP(hipEventRecord(p->ev[4], s));
   if (kind == SSO_OBJ_COMPLIANCE || kind == SSO_OBJ_STRAIN_ENERGY) {
     if (kind == SSO_OBJ_STRAIN_ENERGY) c_lam = c_u = 0.5;
     if (p->fm) {
       // prescribed displacements: u solves the lifted system, so K lambda = f needs a solve
       int outer = 0;
-      status = run_solver(p, p->fm, p->lam, &iters, &outer);
-      if (status != SSO_OK && status != SSO_ENOTCONV) return status;
       lam = p->lam;
+      status = run_solver(p, p->fm, p->lam, &iters, &outer, std::ref(terms), &tailed);
+      if (status != SSO_OK && status != SSO_ENOTCONV) return status;
     }
   } else if (kind == SSO_OBJ_LINEAR || kind == SSO_OBJ_USER) {
     if (!dg_du) return SSO_EINVAL;
     c_u = 0.0;
     TRY_HIP(launch_mask_vector(p->m, dg_du, p->rhs, s));
     int outer = 0;
-    status = run_solver(p, p->rhs, p->lam, &iters, &outer);
-    if (status != SSO_OK && status != SSO_ENOTCONV) return status;
     lam = p->lam;
+    status = run_solver(p, p->rhs, p->lam, &iters, &outer, std::ref(terms), &tailed);
+    if (status != SSO_OK && status != SSO_ENOTCONV) return status;
   } else {
     return SSO_EINVAL;
   }
-  TRY_HIP(launch_adjoint_terms(p->m, p->pat, p->u, lam, c_lam, c_u, p->gbeam, p->gquad, s));
-  TRY_HIP(launch_gather(p->m, p->pat, p->gbeam, p->gquad, dg_dxyz, dg_dt, dg_dscale, s));
-  TRY_HIP(hipEventRecord(p->ev[5], s));
-  TRY_HIP(hipStreamSynchronize(s));
+  if (!tailed) {
+    TRY_HIP(terms());
+    TRY_HIP(hipStreamSynchronize(s));
+  }
   if (stats) {
     std::memset(stats, 0, sizeof(*stats));
     stats->iters = iters;

@@ -2185,9 +2185,11 @@ k_dot(int64_t n, const double* __restrict__ a, const double* __restrict__ b, dou
   write_partials<1, double>(v, partials);
 }
 
-// One workgroup: out[k] = sum of partials array k (nv arrays of n), fixed order.
+// One workgroup: out[k] = sum of partials array k (nv arrays of n), fixed order; w0, w1, if
+// given, into out[nv] and out[nv + 1].  out may be pinned host memory.
 __global__ void __launch_bounds__(256) k_finish(const double* partials, int n, int nv,
-                                                double* out) {
+                                                double* out, const unsigned* w0 = nullptr,
+                                                const unsigned* w1 = nullptr) {
   double tot[2] = {0.0, 0.0};
   if (nv == 1) {
     finish_partials<1>(partials, n, tot);
@@ -2196,6 +2198,8 @@ __global__ void __launch_bounds__(256) k_finish(const double* partials, int n, i
   }
   if (threadIdx.x == 0)
     for (int k = 0; k < nv; ++k) out[k] = tot[k];
+  if (threadIdx.x == 64 && w0) out[nv] = (double)*w0;
+  if (threadIdx.x == 128 && w1) out[nv + 1] = (double)*w1;
 }
 
 // Copy the state records of a multi-problem launch into one array (one read-back per poll).
@@ -3269,13 +3273,13 @@ static hipError_t mixed_inner_done(const Mesh& m, const Pattern& pat, const doub
   double* p_new = w.p[(ms.k + 1) & 1];
   hipLaunchKernelGGL(k_fcg_z, dim3(g), dim3(256), 0, s, n, ms.rn, w.x32, w.Ap, w.z,
                      ms.k > 0 ? 1 : 0, part);
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, g, 1, sc + 2);
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, g, 1, sc + 2, nullptr, nullptr);
   hipLaunchKernelGGL(k_fcg_direction, dim3(w.n_wg), dim3(MAX_TPB), 0, s, m.n_nodes,
                      pat.brow_ptr, pat.bcol, K, w.z, p_prev, w.r, sc, ms.k == 0 ? 1 : 0, p_new,
                      w.Ap, part);
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, w.n_wg, 2, sc + 3);
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, w.n_wg, 2, sc + 3, nullptr, nullptr);
   hipLaunchKernelGGL(k_fcg_update, dim3(g), dim3(256), 0, s, n, sc, p_new, w.Ap, x, w.r, part);
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, g, 1, sc);
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, g, 1, sc, nullptr, nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   double h[5];
@@ -3380,17 +3384,18 @@ hipError_t launch_dot(const double* a, const double* b, int64_t n, PcgWork& w, d
   if (nwg < 1) nwg = 1;
   double* part = part_once(w);
   hipLaunchKernelGGL(k_dot, dim3(nwg), dim3(256), 0, s, n, a, b, part);
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, nwg, 1, d_out);
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, nwg, 1, d_out, nullptr, nullptr);
   return hipGetLastError();
 }
 
 hipError_t launch_true_residual(const Mesh& m, const Pattern& pat, const double* K,
                                 const double* x, const double* b, double* r, PcgWork& w,
-                                double* d_out, hipStream_t s) {
+                                double* d_out, hipStream_t s, const unsigned* w0,
+                                const unsigned* w1) {
   double* part = part_once(w);
   hipLaunchKernelGGL(k_residual, dim3(w.n_wg), dim3(MAX_TPB), 0, s, m.n_nodes, pat.brow_ptr,
                      pat.bcol, K, x, b, r, part);
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, w.n_wg, 2, d_out);
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, part, w.n_wg, 2, d_out, w0, w1);
   return hipGetLastError();
 }
 

@@ -526,10 +526,12 @@ void direct_batch_free(DirectBatch& db, hipStream_t s);
 hipError_t launch_dot(const double* a, const double* b, int64_t n, PcgWork& w, double* d_out,
                       hipStream_t s);
 // r = b - K x (row sums in double-double, rounded to FP64 once), and rr = ||r||^2,
-// bb = ||b||^2 into d_out[0], d_out[1].
+// bb = ||b||^2 into d_out[0], d_out[1] (device or pinned host memory); the words w0, w1 at d_out[2],
+// d_out[3] if given.
 hipError_t launch_true_residual(const Mesh& m, const Pattern& pat, const double* K,
                                 const double* x, const double* b, double* r, PcgWork& w,
-                                double* d_out, hipStream_t s);
+                                double* d_out, hipStream_t s, const unsigned* w0 = nullptr,
+                                const unsigned* w1 = nullptr);
 // Single standard FP64 solves of a K of at least 128 MiB read only its upper triangle.
 bool pcg_sym_products(int64_t n_blocks, bool mixed);
 double pcg_bytes_per_iteration(int64_t n_nodes, int64_t n_blocks, bool mixed, bool sym);
