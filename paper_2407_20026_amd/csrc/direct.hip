@@ -277,73 +277,158 @@ __device__ __forceinline__ double reciprocal(double x) {
   return r;
 }
 
-// Sweeps the leading nb columns of a 64 x 64 symmetric block, held as matrix-core accumulators
-// (each_acc's layout): the block becomes minus its inverse.  A step publishes its column through
-// LDS, which by symmetry is its row as well, in the order in which a lane reads its eight rows
-// (contiguous), and takes one barrier, the two buffers alternating.  With t = column / pivot the
-// update is d -= t row throughout: the swept column's entries are cleared beforehand and their
-// factor of the row is -1, the swept row's likewise and their t is -1 / pivot.  Returns the pivot
-// of step threadIdx.x.  A step is a chain of LDS write, barrier, LDS reads, reciprocal and update;
-// with the selections of a plain form of it (no cleared entries) it took 750 cycles, 20 us a block.
-__device__ __forceinline__ int swept_at(int r) {   // where row r of the column lies
-  return (r & 32) + 8 * (r & 3) + 4 * ((r >> 4) & 1) + ((r >> 2) & 3);
+// d[j] += t * (lane K's d[j], of each row of 16 lanes) for all j but K, d[K + 1] first: the next
+// step waits for it.  One instruction an entry, the broadcast being a DPP control of the multiply-
+// add; the compiler makes a move and a multiply-add of it, through one pair of registers (253
+// cycles a step instead of 154).  The waits are those that DPP asks for after a write of its source.
+template <int K>
+__device__ __forceinline__ void sweep_update(double (&d)[16], double t) {
+#define SSO_FMA(n) "v_fmac_f64_dpp %" #n ", %" #n ", %15 row_newbcast:%c16 row_mask:0xf bank_mask:0xf\n"
+#define SSO_ARG(n) "+&v"(d[(K + 1 + n) & 15])
+  asm("s_nop 1\n" SSO_FMA(0) SSO_FMA(1) SSO_FMA(2) SSO_FMA(3) SSO_FMA(4) SSO_FMA(5) SSO_FMA(6)
+          SSO_FMA(7) SSO_FMA(8) SSO_FMA(9) SSO_FMA(10) SSO_FMA(11) SSO_FMA(12) SSO_FMA(13)
+              SSO_FMA(14) "s_nop 1"
+      : SSO_ARG(0), SSO_ARG(1), SSO_ARG(2), SSO_ARG(3), SSO_ARG(4), SSO_ARG(5), SSO_ARG(6),
+        SSO_ARG(7), SSO_ARG(8), SSO_ARG(9), SSO_ARG(10), SSO_ARG(11), SSO_ARG(12), SSO_ARG(13),
+        SSO_ARG(14)
+      : "v"(t), "n"(K));
+#undef SSO_FMA
+#undef SSO_ARG
 }
-__device__ __forceinline__ double sweep(d4 d[2][2], int nb, double (*col)[NB]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+
+// Steps K .. 15 of the sweep of a symmetric 16 x 16 block, row l of it in lane l of each row of 16
+// lanes.  A row is left times its pivot from its step on (in a sweep only the rows still to come
+// are read by others), so that a step is one multiply-add an entry and no selection.
+template <int K>
+__device__ __forceinline__ void sweep_steps(double (&d)[16], int l16, double& pivot) {
+  if constexpr (K < 16) {
+    const double p = dpp_move<0x150 + K>(d[K]);          // row_newbcast
+    const double x = __builtin_amdgcn_rcp(p);
+    const bool me = l16 == K;
+    const double c = me ? 0.0 : -d[K];
+    if (me) pivot = p;
+    const double e = __builtin_fma(-p, x, 1.0);          // 1 / p = x (1 + e + e^2)
+    const double c0 = c * x;
+    const double t = __builtin_fma(c0, __builtin_fma(e, e, e), c0);
+    sweep_update<K>(d, t);
+    d[K] = me ? -1.0 : -t;
+    sweep_steps<K + 1>(d, l16, pivot);
+  }
+}
+
+constexpr int LDS16 = 18;     // row length of 16 columns in LDS: 16-byte reads, spread over the banks
+constexpr int SWEEP_LDS = (NB + 16) * LDS16;
+
+// Sweeps the leading nb columns of a 64 x 64 symmetric block, held as matrix-core accumulators
+// (each_acc's layout): the block becomes minus its inverse; pivot[k], k < nb rounded up to 16, are
+// the pivots.  The workgroup enters with lds free and pivot unused, and leaves with lds free.
+//
+// Panels of 16 columns: the wave that holds the pivot block inverts it by itself, register to
+// register; the others publish the panel's columns meanwhile; and all update their tiles on the
+// matrix cores.  The product -F D^-1 comes out transposed, which is the order of the next product's
+// left operand, and an accumulator of a symmetric block that of its right one, so nothing goes
+// through LDS in between.  A panel takes 5600 cycles, a block 9 us at 2.4 GHz: 16 steps of 154 in
+// the inversion (issue-bound), 1800 in up to 24 matrix products of one wave, the rest in LDS.  Swept
+// one column at a time, each published through LDS with a barrier, a block took 20 us.
+__device__ __forceinline__ void sweep(d4 d[2][2], int nb, double* lds, double* pivot) {
+  double* P = lds;                    // the panel's columns; column c at 4 (c % 4) + c / 4
+  double* D = lds + NB * LDS16;       // minus the pivot block's inverse, the same
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, kq = lane >> 4, wr = wave >> 1, wc = wave & 1;
-  const int mine = 32 * wr + 8 * kq;                       // my eight rows' place
-  const int across = 32 * wc + 8 * (l16 & 3) + (l16 >> 2); // my two columns' place, 4 apart
-  double pivot = 0.0;
+  auto four = [](const double* q, double (&o)[4]) {
+    const double2 y = *reinterpret_cast<const double2*>(q);
+    const double2 z = *reinterpret_cast<const double2*>(q + 2);
+    o[0] = y.x;
+    o[1] = y.y;
+    o[2] = z.x;
+    o[3] = z.y;
+  };
   for (int half = 0; half < 2; ++half) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
+      const int first = 32 * half + 16 * s;
+      if (first >= nb) return;
+      if (wr == half && wc == half) {
+        double* T = P + first * LDS16;           // nothing else of P lies here
 #pragma unroll
-      for (int kk = 0; kk < 16; ++kk) {
-        const int k = 32 * half + 16 * s + kk;
-        if (k >= nb) return pivot;
-        double* cb = col[kk & 1];
-        const bool own_c = wc == half && l16 == kk;
-        if (own_c) {
-          *reinterpret_cast<d4*>(cb + mine) = d[0][s];
-          *reinterpret_cast<d4*>(cb + mine + 4) = d[1][s];
-          d[0][s] = d4{0.0, 0.0, 0.0, 0.0};
-          d[1][s] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int v = 0; v < 4; ++v) T[l16 * LDS16 + kq + 4 * v] = d[s][s][v];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        double x[16];
+#pragma unroll
+        for (int j = 0; j < 16; j += 2) {
+          const double2 y = *reinterpret_cast<const double2*>(T + l16 * LDS16 + j);
+          x[j] = y.x;
+          x[j + 1] = y.y;
         }
-        __syncthreads();
-        const double piv = cb[swept_at(k)];
-        d4 t0 = *reinterpret_cast<const d4*>(cb + mine);
-        d4 t1 = *reinterpret_cast<const d4*>(cb + mine + 4);
-        double r0 = cb[across], r1 = cb[across + 4];
-        const double inv = reciprocal(piv);
-        if ((int)threadIdx.x == k) pivot = piv;
-        t0 *= inv;
-        t1 *= inv;
-        if (own_c) {
-          if (s == 0)
-            r0 = -1.0;
-          else
-            r1 = -1.0;
+        double p = 1.0;
+        sweep_steps<0>(x, l16, p);
+        const double inv = reciprocal(p);
+        if (kq == 0) {
+          pivot[first + l16] = p;
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int v = 0; v < 4; v += 2)
+              *reinterpret_cast<double2*>(D + l16 * LDS16 + 4 * g + v) =
+                  double2{x[g + 4 * v] * inv, x[g + 4 * v + 4] * inv};
         }
-        if (wr == half && kq == (kk & 3)) {
-          if (s == 0)
-            t0[kk >> 2] = -inv;
-          else
-            t1[kk >> 2] = -inv;
-          d[s][0][kk >> 2] = 0.0;
-          d[s][1][kk >> 2] = 0.0;
-        }
-        d[0][0] -= t0 * r0;
-        d[0][1] -= t0 * r1;
-        d[1][0] -= t1 * r0;
-        d[1][1] -= t1 * r1;
       }
+      if (wc == half) {
+        const int at = 4 * (l16 & 3) + (l16 >> 2);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          if (wr == half && i == s) continue;
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            P[(32 * wr + 16 * i + kq + 4 * v) * LDS16 + at] = d[i][s][v];
+        }
+      }
+      __syncthreads();
+      double inv[4], row[2][4], col[2][4];
+      four(D + l16 * LDS16 + 4 * kq, inv);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        four(P + (32 * wr + 16 * i + l16) * LDS16 + 4 * kq, row[i]);
+        four(P + (32 * wc + 16 * i + l16) * LDS16 + 4 * kq, col[i]);
+      }
+      d4 w[2];                                   // minus the scaled rows, transposed
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (wr == half && i == s) continue;
+        w[i] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          w[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(inv[v], row[i][v], w[i], 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const bool in_row = wr == half && i == s, in_col = wc == half && j == s;
+          if (in_row && in_col) {
+            d[i][j] = d4{inv[0], inv[1], inv[2], inv[3]};
+          } else if (in_row || in_col) {
+            d4 x = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              x = __builtin_amdgcn_mfma_f64_16x16x4f64(in_row ? inv[v] : row[i][v],
+                                                       in_row ? col[j][v] : inv[v], x, 0, 0, 0);
+            d[i][j] = -x;
+          } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              d[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i][v], col[j][v], d[i][j], 0, 0, 0);
+          }
+        }
+      __syncthreads();
     }
   }
-  return pivot;
 }
 
 constexpr int POOL = 3 * NB * LDK;    // doubles of LDS that the panel kernels cut their tiles from
 static_assert(NB * LDN + NB * LDK <= POOL, "the inverse and a tile of the row tile fit");
+static_assert(SWEEP_LDS <= POOL, "the sweep's panel fits");
 
 // The scaled panel of step q: q even and odd alternate.
 __device__ __forceinline__ double* scaled(const DirectArgs& a, const DirectFront& F, int q, int i) {
@@ -354,18 +439,13 @@ __device__ __forceinline__ double* scaled(const DirectArgs& a, const DirectFront
 // for itself, which takes no longer than one of them doing it for the others) and F_IJ D^-1.  For
 // q > 0 both are first brought up to date with panel q - 1.
 __device__ __forceinline__ void scale_tile(const DirectArgs& a, const DirectFront& F, int q, int i,
-                                           double* pool, double (*col)[NB]) {
+                                           double* pool, double* pivots) {
   const int64_t ld = F.ns6;
   const int j0 = q * NB;
   const int nb = F.ns6 - j0 < NB ? F.ns6 - j0 : NB;
   const RowTile R = row_tile(F, i);
   const bool pivot = i == q;
   const double* __restrict__ src = q == 0 ? a.f0 + F.work_off : sweep_src(a, F, q - 1);
-  double least = 0.0;         // the pivot of step threadIdx.x must lie above it
-  if (pivot && (int)threadIdx.x < nb) {
-    const int r = j0 + (int)threadIdx.x, n = r / 6;
-    least = PIVOT_MIN * a.K[36 * (int64_t)a.bdiag[a.nodes[F.nodes_off + n]] + 7 * (r - 6 * n)];
-  }
   // the pivot block and the row tile as accumulators (identity past the last column)
   d4 d[2][2], f[2][2];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -421,13 +501,17 @@ __device__ __forceinline__ void scale_tile(const DirectArgs& a, const DirectFron
         if (row) f[u][w] -= uf[u][w];
       }
   }
-  const double piv = sweep(d, nb, col);
-  if (pivot && (int)threadIdx.x < nb && !(piv > least)) atomicOr(a.flag, 1u);
-  __syncthreads();      // the pool is free (nb is at least 6: the sweep held a barrier)
+  if (q > 0) __syncthreads();     // the pool is free
+  sweep(d, nb, pool, pivots);
   const bool only = F.np == 1;    // nothing to update: straight into the factor
   double* out = only ? a.fact + F.fact_off + (int64_t)R.r0 * ld : scaled(a, F, q, i);
   const int64_t ldo = only ? ld : NB;
   if (pivot) {
+    if ((int)threadIdx.x < nb) {
+      const int r = j0 + (int)threadIdx.x, n = r / 6;
+      const double k = a.K[36 * (int64_t)a.bdiag[a.nodes[F.nodes_off + n]] + 7 * (r - 6 * n)];
+      if (!(pivots[threadIdx.x] > PIVOT_MIN * k)) atomicOr(a.flag, 1u);
+    }
     each_acc(d, [&](int r, int c, double v) {
       if (r < nb && c < nb) out[(int64_t)r * ldo + c] = only ? v : -v;
     });
@@ -503,12 +587,12 @@ __device__ __forceinline__ void update_tile(const DirectArgs& a, const DirectFro
 __global__ void __launch_bounds__(TPB, 2)
 k_front_panel(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level, int q) {
   __shared__ __align__(16) double pool[POOL];
-  __shared__ __align__(32) double col[2][NB];
+  __shared__ double pivots[NB];
   DirectItem it;
   if (!take_item(a, probs, first, level, STEP_PANEL + q, it)) return;
   const DirectFront F = a.fronts[it.front];
   if (it.j < 0)
-    scale_tile(a, F, q, it.i, pool, col);
+    scale_tile(a, F, q, it.i, pool, pivots);
   else
     update_tile(a, F, q - 1, it.i, it.j, pool);
 }
