@@ -674,6 +674,7 @@ int direct_tables(sso_problem* p, bool* ready) {
     TRY_HIP(put(&t.nodes, pl.nodes));
     TRY_HIP(put(&t.maps, pl.maps));
     TRY_HIP(put(&t.entries, pl.entries));
+    TRY_HIP(put(&t.tile_end, pl.tile_end));
     TRY_HIP(put(&t.items, pl.items));
     TRY_HIP(put(&t.steps, pl.steps));
     TRY_HIP(put(&t.level_off, pl.level_off));

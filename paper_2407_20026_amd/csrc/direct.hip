@@ -36,7 +36,6 @@ constexpr int TPB = 256;
 constexpr int KC = 32;                // depth of an LDS tile
 constexpr int LDK = KC + 1;           // its row length: odd, so that 16 rows spread over the banks
 constexpr int LDN = NB + 1;
-constexpr int ASM_R = 6 * DIRECT_ASM_ROWS, ASM_C = 6 * DIRECT_ASM_COLS;
 constexpr int FWD_ROWS_WAVE = DIRECT_FWD_ROWS / (TPB / 64);
 constexpr int BWD_TPB = 512;
 constexpr int BWD_GROUPS = BWD_TPB / DIRECT_BWD_COLS;
@@ -44,6 +43,19 @@ constexpr int BWD_CHUNK = 2048;       // rows of the vector staged at a time
 // A pivot below this share of K's diagonal entry means that K is singular to working precision
 // (rounding leaves some 1e-15 of it in place of a zero pivot); the solve then goes back to PCG.
 constexpr double PIVOT_MIN = 1e-13;
+
+// The wave's number in its workgroup, in a scalar register.
+__device__ __forceinline__ int wave_id() {
+  return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+}
+
+// The lane's number, computed anew here: what follows from it is then not carried in registers
+// through a caller's loop.
+__device__ __forceinline__ int lane_here() {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
@@ -65,91 +77,19 @@ __device__ __forceinline__ bool take_item(DirectArgs& a, const DirectArgs* __res
 
 // A child's Schur complement (its lower triangle is stored).  at(r, c): the entry at DOF rows r, c
 // of its boundary, 0 where either is negative (not in the boundary).  Loads are unconditional, from
-// entry 0 then, so that a thread's loads are all in flight together.
+// entry 0 then, so that a thread's loads are all in flight together; the byte offset fits 32 bits
+// (DIRECT_MAX_BOUNDARY), which leaves the base in scalar registers.
 struct ChildU {
   const double* __restrict__ u;
   __device__ __forceinline__ double at(int r, int c) const {
     const bool in = (r | c) >= 0;
-    const int hi = r > c ? r : c, lo = r > c ? c : r;
-    const double v = u[in ? direct_tri(hi) + lo : 0];
+    const unsigned hi = r > c ? r : c, lo = r > c ? c : r;
+    const unsigned e = in ? hi * (hi + 1) / 2 + lo : 0u;
+    const double v =
+        *reinterpret_cast<const double*>(reinterpret_cast<const char*>(u) + (e * 8u));
     return in ? v : 0.0;
   }
 };
-__device__ __forceinline__ ChildU child_of(const DirectArgs& a, int f) {
-  return ChildU{f >= 0 ? a.u + a.fronts[f].u_off : a.u};
-}
-
-// A front's columns: children's Schur complements and K's blocks, a tile of 8 x 16 nodes in LDS.
-__global__ void __launch_bounds__(TPB)
-k_front_assemble(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
-  __shared__ double tile[ASM_R * ASM_C];
-  __shared__ int mr[2][ASM_R], mc[2][ASM_C];   // DOF rows in the children's boundaries, -1: none
-  DirectItem it;
-  if (!take_item(a, probs, first, level, STEP_ASM, it)) return;
-  const DirectFront F = a.fronts[it.front];
-  const int ns = F.ns6 / 6, cnt = ns + F.nb6 / 6;
-  const int rn0 = it.i * DIRECT_ASM_ROWS, cn0 = it.j * DIRECT_ASM_COLS;
-  const int t = threadIdx.x;
-  const ChildU u0 = child_of(a, F.child[0]), u1 = child_of(a, F.child[1]);
-  // the first of K's entries, on their way meanwhile
-  const int ne = 36 * (it.e1 - it.e0);
-  const int k0 = t / 36, q0 = t - 36 * k0;
-  DirectEntry en0{0, 0};
-  double kv0 = 0.0;
-  if (t < ne) {
-    en0 = a.entries[it.e0 + k0];
-    kv0 = a.K[36 * (int64_t)en0.slot + q0];
-  }
-  for (int e = t; e < 2 * (ASM_R + ASM_C); e += TPB) {
-    const int k = e >= ASM_R + ASM_C, r = e - k * (ASM_R + ASM_C);
-    const bool row = r < ASM_R;
-    const int dof = row ? r : r - ASM_R, node = dof / 6;
-    const bool in = row ? rn0 + node < cnt : cn0 + node < ns;
-    int m = in ? a.maps[F.map_off + k * cnt + (row ? rn0 : cn0) + node] : -1;
-    if (m >= 0) m = 6 * m + dof - 6 * node;
-    if (row)
-      mr[k][dof] = m;
-    else
-      mc[k][dof] = m;
-  }
-  __syncthreads();
-  if (F.child[0] < 0 && F.child[1] < 0) {
-    for (int e = t; e < ASM_R * ASM_C; e += TPB) tile[e] = 0.0;
-  } else {
-    constexpr int AT_ONCE = 6;
-    static_assert(ASM_R * ASM_C % (AT_ONCE * TPB) == 0, "whole rounds");
-    for (int e0 = t; e0 < ASM_R * ASM_C; e0 += AT_ONCE * TPB) {
-      double v[AT_ONCE], w[AT_ONCE];
-#pragma unroll
-      for (int u = 0; u < AT_ONCE; ++u) {
-        const int e = e0 + u * TPB, r = e / ASM_C, c = e - r * ASM_C;
-        v[u] = u0.at(mr[0][r], mc[0][c]);
-        w[u] = u1.at(mr[1][r], mc[1][c]);
-      }
-#pragma unroll
-      for (int u = 0; u < AT_ONCE; ++u) tile[e0 + u * TPB] = v[u] + w[u];
-    }
-  }
-  __syncthreads();
-  // K's blocks: block (row, col) of the front is the transpose of K's (col, row)
-  auto add = [&](const DirectEntry& en, int q, double v) {
-    const int cb = q / 6, ca = q - 6 * cb;       // K entry (cb, ca) of block (col node, row node)
-    tile[(6 * (en.rc >> 16) + ca) * ASM_C + 6 * (en.rc & 0xffff) + cb] += v;
-  };
-  if (t < ne) add(en0, q0, kv0);
-  for (int e = t + TPB; e < ne; e += TPB) {
-    const int k = e / 36, q = e - 36 * k;
-    const DirectEntry en = a.entries[it.e0 + k];
-    add(en, q, a.K[36 * (int64_t)en.slot + q]);
-  }
-  __syncthreads();
-  double* out = a.f0 + F.work_off;
-  const int rows = F.ns6 + F.nb6 - 6 * rn0, cols = F.ns6 - 6 * cn0;
-  for (int e = t; e < ASM_R * ASM_C; e += TPB) {
-    const int r = e / ASM_C, c = e - r * ASM_C;
-    if (r < rows && c < cols) out[(int64_t)(6 * rn0 + r) * F.ns6 + 6 * cn0 + c] = tile[e];
-  }
-}
 
 // Where a front's sweep p reads and writes its columns: the last one writes the factor, the ones
 // before alternate, the first reads the assembled front.
@@ -159,23 +99,6 @@ __device__ __forceinline__ double* sweep_dst(const DirectArgs& a, const DirectFr
 __device__ __forceinline__ const double* sweep_src(const DirectArgs& a, const DirectFront& F,
                                                    int p) {
   return p == 0 ? a.f0 + F.work_off : sweep_dst(a, F, p - 1);
-}
-
-// Rows of row tile i of a front (own rows first, boundary rows in tiles of their own).
-struct RowTile {
-  int r0, n;
-};
-__device__ __forceinline__ RowTile row_tile(const DirectFront& F, int i) {
-  RowTile t;
-  if (i < F.np) {
-    t.r0 = i * NB;
-    t.n = F.ns6 - t.r0;
-  } else {
-    t.r0 = F.ns6 + (i - F.np) * NB;
-    t.n = F.ns6 + F.nb6 - t.r0;
-  }
-  if (t.n > NB) t.n = NB;
-  return t;
 }
 
 // Up to 64 rows x KC columns of a row-major array on their way into an LDS tile, zero outside.
@@ -208,7 +131,7 @@ struct TileLoad {
 // 2 x 2 matrix-core tiles.
 __device__ __forceinline__ void mma_tile(const double* A, int lda, const double* B, int ldb,
                                          int kn, d4 acc[2][2]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = lane_here(), wave = wave_id();
   const int l16 = lane & 15, kq = lane >> 4;
   const double* pa = A + (32 * (wave >> 1) + l16) * lda + kq;
   const double* pb = B + (32 * (wave & 1) + l16) * ldb + kq;
@@ -253,7 +176,7 @@ __device__ __forceinline__ void product(const double* __restrict__ A, int64_t ld
 // l / 16 + 4 v of each 16 x 16 tile.
 template <class Fn>
 __device__ __forceinline__ void each_acc(const d4 acc[2][2], Fn f) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = lane_here(), wave = wave_id();
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -333,8 +256,8 @@ constexpr int SWEEP_LDS = (NB + 16) * LDS16;
 __device__ __forceinline__ void sweep(d4 d[2][2], int nb, double* lds, double* pivot) {
   double* P = lds;                    // the panel's columns; column c at 4 (c % 4) + c / 4
   double* D = lds + NB * LDS16;       // minus the pivot block's inverse, the same
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = lane_here();
+  const int wave = wave_id();
   const int l16 = lane & 15, kq = lane >> 4, wr = wave >> 1, wc = wave & 1;
   auto four = [](const double* q, double (&o)[4]) {
     const double2 y = *reinterpret_cast<const double2*>(q);
@@ -435,21 +358,30 @@ __device__ __forceinline__ double* scaled(const DirectArgs& a, const DirectFront
   return a.w + F.w_off + ((int64_t)(q & 1) * F.nt + i) * NB * NB;
 }
 
-// Panel q of a front scaled, row tile i: D^-1 of its pivot block (by every workgroup of the front
-// for itself, which takes no longer than one of them doing it for the others) and F_IJ D^-1.  For
-// q > 0 both are first brought up to date with panel q - 1.
+// Sets the flag where a pivot of the nb from own DOF j0 on is too small.
+__device__ __forceinline__ void check_pivots(const DirectArgs& a, const DirectFront& F, int j0,
+                                             int nb, const double* pivots) {
+  if ((int)threadIdx.x >= nb) return;
+  const int r = j0 + (int)threadIdx.x, n = r / 6;
+  const double k = a.K[36 * (int64_t)a.bdiag[a.nodes[F.nodes_off + n]] + 7 * (r - 6 * n)];
+  if (!(pivots[threadIdx.x] > PIVOT_MIN * k)) atomicOr(a.flag, 1u);
+}
+
+// Panel q > 0 of a front scaled, row tile i: D^-1 of its pivot block (by every workgroup of the
+// front for itself, which takes no longer than one of them doing it for the others) and F_IJ D^-1,
+// both first brought up to date with panel q - 1.
 __device__ __forceinline__ void scale_tile(const DirectArgs& a, const DirectFront& F, int q, int i,
                                            double* pool, double* pivots) {
   const int64_t ld = F.ns6;
   const int j0 = q * NB;
   const int nb = F.ns6 - j0 < NB ? F.ns6 - j0 : NB;
-  const RowTile R = row_tile(F, i);
+  const DirectRows R = direct_rows(F, i);
   const bool pivot = i == q;
-  const double* __restrict__ src = q == 0 ? a.f0 + F.work_off : sweep_src(a, F, q - 1);
+  const double* __restrict__ src = sweep_src(a, F, q - 1);
   // the pivot block and the row tile as accumulators (identity past the last column)
   d4 d[2][2], f[2][2];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bool swept = q > 0 && i == q - 1;   // rows of the panel before: its scaled tile, transposed
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const bool swept = i == q - 1;   // rows of the panel before: its scaled tile, transposed
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -464,56 +396,48 @@ __device__ __forceinline__ void scale_tile(const DirectArgs& a, const DirectFron
           f[u][w][v] = swept ? scaled(a, F, q - 1, q)[c * NB + r]
                              : src[(int64_t)(R.r0 + r) * ld + j0 + c];
       }
-  if (q > 0) {
-    double* ws = pool;                    // scaled rows of the pivot block
-    double* wi = pool + NB * LDK;         // scaled rows of the row tile
-    double* cs = pool + 2 * NB * LDK;     // the pivot rows' entries in the panel before
-    TileLoad tw, ti, tc;
-    const double* __restrict__ pw = scaled(a, F, q - 1, q);
-    const double* __restrict__ pi = scaled(a, F, q - 1, i);
-    const double* __restrict__ pc = src + (int64_t)j0 * ld + j0 - NB;
-    const bool row = !pivot && !swept;
-    d4 ud[2][2], uf[2][2];
-    clear(ud);
-    clear(uf);
-    tw.load(pw, NB, nb, 0, NB);
-    tc.load(pc, ld, nb, 0, NB);
-    if (row) ti.load(pi, NB, R.n, 0, NB);
-    for (int k0 = 0; k0 < NB; k0 += KC) {
-      if (k0) __syncthreads();
-      tw.store(ws);
-      tc.store(cs);
-      if (row) ti.store(wi);
-      __syncthreads();
-      if (k0 + KC < NB) {
-        tw.load(pw, NB, nb, k0 + KC, NB);
-        tc.load(pc, ld, nb, k0 + KC, NB);
-        if (row) ti.load(pi, NB, R.n, k0 + KC, NB);
-      }
-      mma_tile(ws, LDK, cs, LDK, KC, ud);
-      if (row) mma_tile(wi, LDK, cs, LDK, KC, uf);
+  double* ws = pool;                    // scaled rows of the pivot block
+  double* wi = pool + NB * LDK;         // scaled rows of the row tile
+  double* cs = pool + 2 * NB * LDK;     // the pivot rows' entries in the panel before
+  TileLoad tw, ti, tc;
+  const double* __restrict__ pw = scaled(a, F, q - 1, q);
+  const double* __restrict__ pi = scaled(a, F, q - 1, i);
+  const double* __restrict__ pc = src + (int64_t)j0 * ld + j0 - NB;
+  const bool row = !pivot && !swept;
+  d4 ud[2][2], uf[2][2];
+  clear(ud);
+  clear(uf);
+  tw.load(pw, NB, nb, 0, NB);
+  tc.load(pc, ld, nb, 0, NB);
+  if (row) ti.load(pi, NB, R.n, 0, NB);
+  for (int k0 = 0; k0 < NB; k0 += KC) {
+    if (k0) __syncthreads();
+    tw.store(ws);
+    tc.store(cs);
+    if (row) ti.store(wi);
+    __syncthreads();
+    if (k0 + KC < NB) {
+      tw.load(pw, NB, nb, k0 + KC, NB);
+      tc.load(pc, ld, nb, k0 + KC, NB);
+      if (row) ti.load(pi, NB, R.n, k0 + KC, NB);
     }
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int w = 0; w < 2; ++w) {
-        d[u][w] -= ud[u][w];
-        if (row) f[u][w] -= uf[u][w];
-      }
+    mma_tile(ws, LDK, cs, LDK, KC, ud);
+    if (row) mma_tile(wi, LDK, cs, LDK, KC, uf);
   }
-  if (q > 0) __syncthreads();     // the pool is free
-  sweep(d, nb, pool, pivots);
-  const bool only = F.np == 1;    // nothing to update: straight into the factor
-  double* out = only ? a.fact + F.fact_off + (int64_t)R.r0 * ld : scaled(a, F, q, i);
-  const int64_t ldo = only ? ld : NB;
-  if (pivot) {
-    if ((int)threadIdx.x < nb) {
-      const int r = j0 + (int)threadIdx.x, n = r / 6;
-      const double k = a.K[36 * (int64_t)a.bdiag[a.nodes[F.nodes_off + n]] + 7 * (r - 6 * n)];
-      if (!(pivots[threadIdx.x] > PIVOT_MIN * k)) atomicOr(a.flag, 1u);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      d[u][w] -= ud[u][w];
+      if (row) f[u][w] -= uf[u][w];
     }
+  __syncthreads();     // the pool is free
+  sweep(d, nb, pool, pivots);
+  double* out = scaled(a, F, q, i);
+  if (pivot) {
+    check_pivots(a, F, j0, nb, pivots);
     each_acc(d, [&](int r, int c, double v) {
-      if (r < nb && c < nb) out[(int64_t)r * ldo + c] = only ? v : -v;
+      if (r < nb && c < nb) out[r * NB + c] = -v;
     });
     return;
   }
@@ -533,7 +457,7 @@ __device__ __forceinline__ void scale_tile(const DirectArgs& a, const DirectFron
     mma_tile(fs, LDK, ds + 32 * h, LDN, kn, acc);
   }
   each_acc(acc, [&](int r, int c, double v) {
-    if (r < R.n && c < nb) out[(int64_t)r * ldo + c] = v;
+    if (r < R.n && c < nb) out[r * NB + c] = v;
   });
 }
 
@@ -545,7 +469,7 @@ __device__ __forceinline__ void update_tile(const DirectArgs& a, const DirectFro
   const int64_t ld = F.ns6;
   const int j0 = p * NB;
   const int nb = F.ns6 - j0 < NB ? F.ns6 - j0 : NB;
-  const RowTile R = row_tile(F, i);
+  const DirectRows R = direct_rows(F, i);
   const int c0 = j * NB;
   const int nc = F.ns6 - c0 < NB ? F.ns6 - c0 : NB;
   const double* __restrict__ wi = scaled(a, F, p, i);
@@ -561,7 +485,7 @@ __device__ __forceinline__ void update_tile(const DirectArgs& a, const DirectFro
     return;
   }
   d4 f[2][2], acc[2][2];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = wave_id();
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -583,7 +507,7 @@ __device__ __forceinline__ void update_tile(const DirectArgs& a, const DirectFro
   });
 }
 
-// Step q of a level's panels: panel q scaled, all columns updated with panel q - 1.
+// Step q > 0 of a level's panels: panel q scaled, all columns updated with panel q - 1.
 __global__ void __launch_bounds__(TPB, 2)
 k_front_panel(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level, int q) {
   __shared__ __align__(16) double pool[POOL];
@@ -595,6 +519,275 @@ k_front_panel(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int
     scale_tile(a, F, q, it.i, pool, pivots);
   else
     update_tile(a, F, q - 1, it.i, it.j, pool);
+}
+
+// A tile of a front's assembled columns in the making: K's blocks and the children's Schur
+// complements, in LDS with rows of LDN, zero outside.  Tiles lie on the front's diagonal or below.
+struct Assembly {
+  DirectRows R;
+  int c0, nc;
+  int e0, e1;             // K's entries
+  double* T;              // NB x LDN
+};
+
+// Up to ALL of K's blocks of a tile, two values of each of AT_ONCE a thread: all of a thread's loads
+// are in flight together (one block after the other took 1.5 us each).
+struct KBlocks {
+  static constexpr int AT_ONCE = 4, BLOCKS = TPB / 18, ALL = AT_ONCE * BLOCKS;
+  DirectEntry en[AT_ONCE];
+  double2 x[AT_ONCE];
+  __device__ __forceinline__ void entries(const DirectArgs& a, int e0, int e1) {
+    const int b = (64 * wave_id() + lane_here()) / 18;
+#pragma unroll
+    for (int u = 0; u < AT_ONCE; ++u) {
+      const int e = e0 + b + u * BLOCKS;
+      en[u].rc = -1;
+      if (b < BLOCKS && e < e1) en[u] = a.entries[e];
+    }
+  }
+  __device__ __forceinline__ void values(const DirectArgs& a) {
+    const int q = 2 * ((64 * wave_id() + lane_here()) % 18);
+#pragma unroll
+    for (int u = 0; u < AT_ONCE; ++u)
+      if (en[u].rc >= 0)
+        x[u] = *reinterpret_cast<const double2*>(a.K + 36 * (int64_t)en[u].slot + q);
+  }
+  // block (row, col) of the front is the transpose of K's (col, row); every value has one place
+  __device__ __forceinline__ void put(const Assembly& A) const {
+    const int q = 2 * ((64 * wave_id() + lane_here()) % 18), cb = q / 6, ca = q - 6 * cb;
+#pragma unroll
+    for (int u = 0; u < AT_ONCE; ++u) {
+      if (en[u].rc < 0) continue;
+      const int r = (en[u].rc >> 16) - DIRECT_EDGE + ca, c = (en[u].rc & 0xffff) - DIRECT_EDGE + cb;
+      if (c < 0 || c >= A.nc) continue;
+      if (r >= 0 && r < A.R.n) A.T[r * LDN + c] = x[u].x;
+      if (r + 1 >= 0 && r + 1 < A.R.n) A.T[(r + 1) * LDN + c] = x[u].y;
+    }
+  }
+};
+
+// A tile's entries a thread holds: column lane, rows wave + TILE_STEP u.
+constexpr int TILE_STEP = TPB / 64, TILE_PER = NB / TILE_STEP;
+static_assert(NB == 64, "a wave takes a row, and a lane of it knows the map of a row");
+
+// The children's part of a tile.  A lane's column is the lower index in the children as well
+// (boundaries keep the order of the parent), so that a wave reads along a row of their triangles:
+// a scalar base, and one offset a lane for all rows.  A tile on the diagonal is read in its lower
+// half and mirrored.  All of a thread's loads are in flight together from load to add; where a
+// column is not wanted, they read the row's first entry.
+struct ChildValues {
+  int row[2], col[2];            // DOF row lane, column lane of the tile in the children, or -1
+  double v[2][TILE_PER];
+  __device__ __forceinline__ void maps(const DirectArgs& a, const DirectFront& F,
+                                       const Assembly& A) {
+    const int lane = lane_here(), cnt = (F.ns6 + F.nb6) / 6;
+    const int r = A.R.r0 + lane, c = A.c0 + lane;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int32_t* __restrict__ map = a.maps + F.map_off + k * cnt;
+      row[k] = lane < A.R.n ? map[r / 6] : -1;
+      col[k] = lane < A.nc ? map[c / 6] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      row[k] = row[k] < 0 ? -1 : 6 * row[k] + r % 6;
+      col[k] = col[k] < 0 ? -1 : 6 * col[k] + c % 6;
+    }
+  }
+  __device__ __forceinline__ void load(const DirectArgs& a, const DirectFront& F,
+                                       const Assembly& A) {
+    const int lane = lane_here(), wave = wave_id();
+    const int last = A.c0 == A.R.r0 ? 0 : NB;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const double* __restrict__ U = a.u + F.child_u[k];
+      const unsigned at = col[k] < 0 ? 0u : 8u * (unsigned)col[k];
+#pragma unroll
+      for (int u = 0; u < TILE_PER; ++u) {
+        const int r = __builtin_amdgcn_readlane(row[k], wave + TILE_STEP * u);
+        v[k][u] = 0.0;
+        if (r >= 0) {
+          const char* line = reinterpret_cast<const char*>(U + direct_tri(r));
+          const bool low = lane <= wave + TILE_STEP * u + last;
+          v[k][u] = *reinterpret_cast<const double*>(line + (low ? at : 0u));
+        }
+      }
+    }
+  }
+  // into the tile, and into the front's assembled columns where out
+  __device__ __forceinline__ void add(const DirectArgs& a, const DirectFront& F, const Assembly& A,
+                                      bool leaf, bool out) const {
+    const int lane = lane_here(), wave = wave_id();
+    const bool diagonal = A.c0 == A.R.r0;
+    double* __restrict__ p = a.f0 + F.work_off + (int64_t)(A.R.r0 + wave) * F.ns6 + A.c0 + lane;
+    double* __restrict__ q = a.f0 + F.work_off + (int64_t)(A.c0 + lane) * F.ns6 + A.R.r0 + wave;
+    double x[TILE_PER];
+#pragma unroll
+    for (int u = 0; u < TILE_PER; ++u) x[u] = A.T[(wave + TILE_STEP * u) * LDN + lane];
+#pragma unroll
+    for (int u = 0; u < TILE_PER; ++u) {
+      const int r = wave + TILE_STEP * u;
+      if (!diagonal || lane <= r) {
+        if (!leaf) {
+          x[u] += (col[0] >= 0 ? v[0][u] : 0.0) + (col[1] >= 0 ? v[1][u] : 0.0);
+          A.T[r * LDN + lane] = x[u];
+          if (diagonal) A.T[lane * LDN + r] = x[u];
+        }
+        if (out && lane < A.nc && r < A.R.n) {
+          *p = x[u];
+          if (diagonal) *q = x[u];
+        }
+      }
+      p += TILE_STEP * F.ns6;
+      q += TILE_STEP;
+    }
+  }
+};
+
+// A tile's transpose into the other half of the front's own columns.
+__device__ __forceinline__ void store_mirror(const DirectArgs& a, const DirectFront& F,
+                                             const Assembly& A) {
+  if (A.c0 == A.R.r0 || A.R.r0 >= F.ns6) return;
+  const int lane = lane_here(), wave = wave_id();
+  double* __restrict__ p = a.f0 + F.work_off + (int64_t)(A.c0 + wave) * F.ns6 + A.R.r0 + lane;
+#pragma unroll
+  for (int u = 0; u < TILE_PER; ++u) {
+    const int c = wave + TILE_STEP * u;
+    if (lane < A.R.n && c < A.nc) *p = A.T[lane * LDN + c];
+    p += TILE_STEP * F.ns6;
+  }
+}
+
+// Assembles N tiles in LDS and, where out, into the front's columns.  What waits for memory is on
+// its way for all tiles at once: K's entries and the maps, then K's blocks and the children's
+// values.  The workgroup enters with T free.
+template <int N>
+__device__ __forceinline__ void assemble(const DirectArgs& a, const DirectFront& F, bool leaf,
+                                         const Assembly (&A)[N], const bool (&out)[N]) {
+  KBlocks kb[N];
+  ChildValues cv[N];
+  const int lane = lane_here(), wave = wave_id();
+#pragma unroll
+  for (int k = 0; k < N; ++k) kb[k].entries(a, A[k].e0, A[k].e1);
+  if (!leaf) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) cv[k].maps(a, F, A[k]);
+#pragma unroll
+    for (int k = 0; k < N; ++k)     // here, not in front of each child's loads
+      asm volatile("" : "+v"(cv[k].row[0]), "+v"(cv[k].row[1]), "+v"(cv[k].col[0]),
+                        "+v"(cv[k].col[1]));
+  }
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    double* T = A[k].T + wave * LDN + lane;
+#pragma unroll
+    for (int u = 0; u < TILE_PER; ++u) T[u * TILE_STEP * LDN] = 0.0;
+  }
+#pragma unroll
+  for (int k = 0; k < N; ++k) kb[k].values(a);
+  if (!leaf) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) cv[k].load(a, F, A[k]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    kb[k].put(A[k]);
+    for (int e = A[k].e0 + KBlocks::ALL; e < A[k].e1; e += KBlocks::ALL) {
+      kb[k].entries(a, e, A[k].e1);
+      kb[k].values(a);
+      kb[k].put(A[k]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) cv[k].add(a, F, A[k], leaf, out[k]);
+  __syncthreads();
+}
+
+// Step 0 of a level's panels.  Items with j >= 0 assemble tile (i, j) of the front's columns.  The
+// others assemble the first column of tiles, -j row tiles from i on, and scale panel 0: the pivot
+// block, which each item assembles and inverts for itself, and F_I0 D^-1; the only panel of a front
+// goes straight into the factor.  The kernel must not use scratch memory: with 400 bytes of it a
+// launch took 10 us longer.
+__global__ void __launch_bounds__(TPB, 2)
+k_front_first(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
+  __shared__ __align__(16) double T0[NB * LDN];
+  __shared__ __align__(16) double T1[NB * LDN];
+  __shared__ double pivots[NB];
+  static_assert(SWEEP_LDS <= NB * LDN, "the sweep's panel fits a tile");
+  DirectItem it;
+  if (!take_item(a, probs, first, level, STEP_PANEL, it)) return;
+  const DirectFront F = a.fronts[it.front];
+  const bool leaf = F.child[0] < 0 && F.child[1] < 0;
+  int i = it.i;
+  if (it.j >= 0) {
+    const int c0 = it.j * NB;
+    const Assembly tile{direct_rows(F, i), c0, F.ns6 - c0 < NB ? F.ns6 - c0 : NB, it.e0, it.e1, T1};
+    assemble<1>(a, F, leaf, {tile}, {true});
+    store_mirror(a, F, tile);
+    return;
+  }
+  const int nb = F.ns6 < NB ? F.ns6 : NB;
+  const bool only = F.np == 1;      // then only the boundary rows are read again, by the Schur step
+  const int64_t ldo = only ? F.ns6 : NB;
+  const int end = i - it.j;
+  const Assembly pivot{direct_rows(F, 0), 0, nb, F.e0, F.e1, T0};
+  if (i == 0) {
+    assemble<1>(a, F, leaf, {pivot}, {!only});
+  } else {
+    const Assembly tile{direct_rows(F, i), 0, nb, it.e0, it.e1, T1};
+    assemble<2>(a, F, leaf, {pivot, tile}, {false, true});
+    store_mirror(a, F, tile);
+  }
+  {
+    d4 d[2][2];
+    const int lane = lane_here(), wave = wave_id();
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int w = 0; w < 2; ++w)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = 32 * (wave >> 1) + 16 * u + (lane >> 4) + 4 * v;
+          const int c = 32 * (wave & 1) + 16 * w + (lane & 15);
+          d[u][w][v] = r < nb && c < nb ? T0[r * LDN + c] : (r == c ? 1.0 : 0.0);
+        }
+    __syncthreads();
+    sweep(d, nb, T0, pivots);
+    each_acc(d, [&](int r, int c, double v) { T0[r * LDN + c] = -v; });
+    if (i == 0) {
+      check_pivots(a, F, 0, nb, pivots);
+      double* __restrict__ out = only ? a.fact + F.fact_off : scaled(a, F, 0, 0);
+      each_acc(d, [&](int r, int c, double v) {
+        if (r < nb && c < nb) out[(int64_t)r * ldo + c] = only ? v : -v;
+      });
+    }
+  }
+  __syncthreads();
+  for (bool first_row = true; i < end; ++i, first_row = false) {
+    if (i == 0) continue;
+    const DirectRows R = direct_rows(F, i);
+    if (!first_row) {
+      const Assembly tile{R, 0, nb, a.tile_end[F.tile_off + i - 1], a.tile_end[F.tile_off + i], T1};
+      __syncthreads();
+      assemble<1>(a, F, leaf, {tile}, {true});
+      store_mirror(a, F, tile);
+    }
+    double* __restrict__ out =
+        only ? a.fact + F.fact_off + (int64_t)R.r0 * F.ns6 : scaled(a, F, 0, i);
+    d4 acc[2][2];
+    clear(acc);
+    if (nb == NB) {
+      mma_tile(T1, LDN, T0, LDN, KC, acc);
+      mma_tile(T1 + KC, LDN, T0 + KC, LDN, KC, acc);
+    } else {
+      mma_tile(T1, LDN, T0, LDN, (nb + 3) & ~3, acc);
+    }
+    each_acc(acc, [&](int r, int c, double v) {
+      if (r < R.n && c < nb) out[(int64_t)r * ldo + c] = v;
+    });
+  }
 }
 
 // Tile (i, j), j <= i, of a front's Schur complement: the children's minus G F_BS^T.
@@ -624,13 +817,13 @@ k_front_schur(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int
   }
   const double* __restrict__ G = a.fact + F.fact_off + (int64_t)(F.ns6 + r0) * F.ns6;
   const double* __restrict__ B = a.f0 + F.work_off + (int64_t)(F.ns6 + c0) * F.ns6;
-  const ChildU u0 = child_of(a, F.child[0]), u1 = child_of(a, F.child[1]);
+  const ChildU u0{a.u + F.child_u[0]}, u1{a.u + F.child_u[1]};
   d4 acc[2][2], sum[2][2];
   clear(acc);
   clear(sum);
   __syncthreads();
   if (F.child[0] >= 0 || F.child[1] >= 0) {   // on their way while the product runs
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = wave_id();
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -677,7 +870,7 @@ k_front_forward(DirectArgs a, const DirectArgs* __restrict__ probs, int first, i
     if (it.i == 0) a.b[F.b_off + c] = v;
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = wave_id();
   const double* __restrict__ G = a.fact + F.fact_off + (int64_t)F.ns6 * F.ns6;
   const int r0 = it.i * DIRECT_FWD_ROWS + FWD_ROWS_WAVE * wave;
   if (r0 >= F.nb6) return;
@@ -808,10 +1001,10 @@ struct Launch {
 static hipError_t factor(const Launch& L) {
   const DirectArgs a = L.one ? *L.one : DirectArgs{};
   for (int h = 0; h < L.levels(); ++h) {
-    SSO_TRY(L.step(h, STEP_ASM, [&](dim3 g, int off) {
-      hipLaunchKernelGGL(k_front_assemble, g, dim3(TPB), 0, L.s, a, L.probs, off, h);
+    SSO_TRY(L.step(h, STEP_PANEL, [&](dim3 g, int off) {
+      hipLaunchKernelGGL(k_front_first, g, dim3(TPB), 0, L.s, a, L.probs, off, h);
     }));
-    for (int q = 0; q <= L.panels(h); ++q)
+    for (int q = 1; q <= L.panels(h); ++q)
       SSO_TRY(L.step(h, STEP_PANEL + q, [&](dim3 g, int off) {
         hipLaunchKernelGGL(k_front_panel, g, dim3(TPB), 0, L.s, a, L.probs, off, h, q);
       }));

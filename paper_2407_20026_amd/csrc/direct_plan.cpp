@@ -438,7 +438,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
     std::sort(b.begin(), b.end(), [&](int x, int y) { return pos[x] < pos[y]; });
     const double s = 6.0 * F.own_cnt, t = 6.0 * (double)b.size();
     bytes += 8.0 * (s + t) * s;
-    if (bytes > max_bytes || s > DIRECT_MAX_OWN) return false;
+    if (bytes > max_bytes || s > DIRECT_MAX_OWN || t > DIRECT_MAX_BOUNDARY) return false;
   }
 
   plan.fronts.resize(nf);
@@ -495,6 +495,8 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
         again += even((int64_t)(D.ns6 + D.nb6) * D.ns6);
         w += 2 * (int64_t)DIRECT_NB * DIRECT_NB * D.nt;
       }
+      for (int c = 0; c < 2; ++c)
+        D.child_u[c] = D.child[c] < 0 ? 0 : plan.fronts[D.child[c]].u_off;
       D.u_off = schur.take(direct_tri(D.nb6));
       D.v_off = plan.v_len;
       plan.v_len += D.nb6;
@@ -517,8 +519,8 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
 
   // work lists
   std::vector<int32_t> start;
-  std::vector<DirectEntry> bucket;
-  std::vector<int32_t> key;
+  std::vector<int32_t> lo, hi, fill;
+  std::vector<DirectItem> assemble;
   for (int h = 0; h < nl; ++h) {
     const int np = plan.level_np[h];
     plan.level_off[h] = (int32_t)plan.steps.size();
@@ -526,50 +528,72 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
     DirectRange* st = plan.steps.data() + plan.level_off[h];
     auto open = [&](int s) { st[s].off = (int32_t)plan.items.size(); };
     auto close = [&](int s) { st[s].cnt = (int32_t)plan.items.size() - st[s].off; };
-    open(STEP_ASM);
+    // step 0: blocks of K with a column among the own nodes, bucketed by tile, first columns first
+    assemble.clear();
+    int first_tiles = 0;
+    for (int i : by_level[h]) first_tiles += plan.fronts[i].np > 0 ? plan.fronts[i].nt : 0;
+    const int at_once =
+        std::min(DIRECT_FIRST_MOST, std::max(1, first_tiles / DIRECT_FIRST_ITEMS));
+    open(STEP_PANEL);
     for (int i : by_level[h]) {
-      const DirectFront& D = plan.fronts[i];
+      DirectFront& D = plan.fronts[i];
       const int ns = D.ns6 / 6, cnt = ns + D.nb6 / 6;
       if (ns == 0) continue;
       const int32_t* list = plan.nodes.data() + D.nodes_off;
       for (int k = 0; k < cnt; ++k) local[list[k]] = k;
-      const int tr = ceil_div(cnt, DIRECT_ASM_ROWS), tc = ceil_div(ns, DIRECT_ASM_COLS);
-      // blocks of K with a column among the own nodes, bucketed by tile
-      bucket.clear();
-      key.clear();
-      start.assign(tr * tc + 1, 0);
-      for (int q = 0; q < ns; ++q) {
-        const int v = list[q];
-        for (int e = rp[v]; e < rp[v + 1]; ++e) {
-          const int r = local[col[e]];
-          if (r < 0) continue;             // eliminated below
-          const int k = (r / DIRECT_ASM_ROWS) * tc + q / DIRECT_ASM_COLS;
-          bucket.push_back({(r % DIRECT_ASM_ROWS) << 16 | (q % DIRECT_ASM_COLS), e});
-          key.push_back(k);
-          ++start[k + 1];
-        }
+      start.assign(D.nt * D.np + 1, 0);
+      lo.resize(cnt);                        // first and last row tile of a node
+      hi.resize(cnt);
+      for (int k = 0; k < cnt; ++k) {
+        const int first = k < ns ? 0 : D.np, row = k < ns ? 6 * k : 6 * k - D.ns6;
+        lo[k] = first + row / DIRECT_NB;
+        hi[k] = first + (row + 5) / DIRECT_NB;
       }
-      for (int k = 0; k < tr * tc; ++k) start[k + 1] += start[k];
-      const int32_t e0 = (int32_t)plan.entries.size();
-      plan.entries.resize(e0 + bucket.size());
-      std::vector<int32_t> fill(start.begin(), start.end() - 1);
-      for (size_t k = 0; k < bucket.size(); ++k)
-        plan.entries[e0 + fill[key[k]]++] = bucket[k];
-      for (int a = 0; a < tr; ++a)
-        for (int b = 0; b < tc; ++b)
-          plan.items.push_back({i, a, b, e0 + start[a * tc + b], e0 + start[a * tc + b + 1]});
+      auto each = [&](auto&& f) {            // over K's blocks and the tiles they lie in
+        for (int q = 0; q < ns; ++q) {
+          const int v = list[q];
+          const int b0 = 6 * q / DIRECT_NB, b1 = (6 * q + 5) / DIRECT_NB;
+          for (int e = rp[v]; e < rp[v + 1]; ++e) {
+            const int r = local[col[e]];
+            if (r < 0) continue;             // eliminated below
+            for (int a = lo[r]; a <= hi[r]; ++a)
+              for (int b = b0; b <= b1 && b <= a; ++b) f(b * D.nt + a, a, b, q, r, e);
+          }
+        }
+      };
+      each([&](int k, int, int, int, int, int) { ++start[k + 1]; });
+      start[0] = (int32_t)plan.entries.size();
+      for (int k = 0; k < D.nt * D.np; ++k) start[k + 1] += start[k];
+      plan.entries.resize(start.back());
+      fill.assign(start.begin(), start.end() - 1);
+      each([&](int k, int a, int b, int q, int r, int e) {
+        const int off = a < D.np ? a * DIRECT_NB : D.ns6 + (a - D.np) * DIRECT_NB;
+        plan.entries[fill[k]++] = {(6 * r - off + DIRECT_EDGE) << 16 |
+                                       (6 * q - b * DIRECT_NB + DIRECT_EDGE),
+                                   e};
+      });
+      D.e0 = start[0];
+      D.e1 = start[1];
+      D.tile_off = (int32_t)plan.tile_end.size();
+      plan.tile_end.insert(plan.tile_end.end(), start.begin() + 1, start.begin() + 1 + D.nt);
+      for (int a = 0; a < D.nt; a += at_once)
+        plan.items.push_back({i, a, -std::min(at_once, D.nt - a), start[a], start[a + 1]});
+      for (int b = 1; b < D.np; ++b)
+        for (int a = b; a < D.nt; ++a)
+          assemble.push_back({i, a, b, start[b * D.nt + a], start[b * D.nt + a + 1]});
       for (int k = 0; k < cnt; ++k) local[list[k]] = -1;
     }
-    close(STEP_ASM);
-    for (int q = 0; q <= np; ++q) {
+    plan.items.insert(plan.items.end(), assemble.begin(), assemble.end());   // the longer work first
+    close(STEP_PANEL);
+    for (int q = 1; q <= np; ++q) {
       open(STEP_PANEL + q);
-      for (int i : by_level[h]) {          // the longer work first
+      for (int i : by_level[h]) {
         const DirectFront& D = plan.fronts[i];
         for (int r = 0; q < D.np && r < D.nt; ++r) plan.items.push_back({i, r, -1, 0, 0});
       }
       for (int i : by_level[h]) {
         const DirectFront& D = plan.fronts[i];
-        if (q == 0 || q > D.np || D.np == 1) continue;   // a single panel is done once scaled
+        if (q > D.np || D.np == 1) continue;   // a single panel is done once scaled
         for (int r = 0; r < D.nt; ++r)
           for (int c = 0; c < D.np; ++c) plan.items.push_back({i, r, c, 0, 0});
       }
@@ -649,6 +673,8 @@ int check_direct_plan(int n, const int32_t* rp, const int32_t* col, const Direct
         prev = map[k];
         ++seen;
       }
+      if (D.child_u[c] != (D.child[c] < 0 ? 0 : plan.fronts[D.child[c]].u_off))
+        return fail(5, "child's Schur complement", (long long)f);
       if (D.child[c] >= 0 && (seen != plan.fronts[D.child[c]].nb6 / 6 ||
                               plan.fronts[D.child[c]].level >= D.level))
         return fail(6, "child boundary lost", (long long)f);
@@ -662,7 +688,36 @@ int check_direct_plan(int n, const int32_t* rp, const int32_t* col, const Direct
                       D.w_off + 2 * (int64_t)DIRECT_NB * DIRECT_NB * D.nt > plan.w_len)))
       return fail(7, "array too short", (long long)f);
   }
-  if (blocks != plan.entries.size()) return fail(8, "blocks of K", (long long)blocks);
+  // the first panel step's tiles hold every value of those blocks once
+  size_t values = 0;
+  auto count = [&](const DirectFront& D, int i, int j, int e0, int e1) {
+    const DirectRows R = direct_rows(D, i);
+    const int nc = std::min(DIRECT_NB, D.ns6 - j * DIRECT_NB);
+    for (int e = e0; e < e1; ++e) {
+      const int r = (plan.entries[e].rc >> 16) - DIRECT_EDGE;
+      const int c = (plan.entries[e].rc & 0xffff) - DIRECT_EDGE;
+      values += (i < D.np && i != j ? 2 : 1) *
+                (size_t)std::max(0, std::min(r + 6, R.n) - std::max(r, 0)) *
+                (size_t)std::max(0, std::min(c + 6, nc) - std::max(c, 0));
+    }
+  };
+  for (int h = 0; h < plan.levels(); ++h) {
+    const DirectRange st = plan.steps[plan.level_off[h] + STEP_PANEL];
+    for (int k = 0; k < st.cnt; ++k) {
+      const DirectItem& it = plan.items[st.off + k];
+      const DirectFront& D = plan.fronts[it.front];
+      if (D.e1 != plan.tile_end[D.tile_off]) return fail(8, "first tile's entries", it.front);
+      for (int t = 0; t < (it.j < 0 ? -it.j : 1); ++t) {
+        if (it.i + t >= D.nt || it.j > it.i) return fail(8, "row tile out of range", it.front);
+        const int e0 = t == 0 ? it.e0 : plan.tile_end[D.tile_off + it.i + t - 1];
+        const int e1 = t == 0 ? it.e1 : plan.tile_end[D.tile_off + it.i + t];
+        if (e0 < 0 || e0 > e1 || e1 > (int)plan.entries.size())
+          return fail(8, "entries out of range", it.front);
+        count(D, it.i + t, it.j < 0 ? 0 : it.j, e0, e1);
+      }
+    }
+  }
+  if (36 * blocks != values) return fail(8, "blocks of K", (long long)blocks);
   // Schur complements alive at the same time do not overlap
   std::vector<int> parent(plan.fronts.size(), -1);
   for (size_t f = 0; f < plan.fronts.size(); ++f)

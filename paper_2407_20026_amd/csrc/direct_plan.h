@@ -13,14 +13,13 @@ namespace sso {
 
 // Panel width of the elimination inside a front, and the rows of a work item of its kernels.
 constexpr int DIRECT_NB = 64;
-// Node tile of the assembly's work items: 8 nodes down, 16 across (48 x 96 entries).
-constexpr int DIRECT_ASM_ROWS = 8;
-constexpr int DIRECT_ASM_COLS = 16;
 // Columns of a backward-substitution work item, rows of a forward-substitution one.
 constexpr int DIRECT_BWD_COLS = 32;
 constexpr int DIRECT_FWD_ROWS = 16;
 // Most own DOFs of a front (a substitution stages them in LDS).
 constexpr int DIRECT_MAX_OWN = 6144;
+// Most boundary DOFs of a front (byte offsets within its Schur complement have 32 bits).
+constexpr int DIRECT_MAX_BOUNDARY = 32766;
 
 // One front: ns own nodes (eliminated here), nb boundary nodes (ancestors' nodes that the front's
 // subtree touches).  Its rows are the DOFs of the own nodes, then of the boundary nodes; its
@@ -34,11 +33,13 @@ struct DirectFront {
   int32_t np;                // panels: ceil(ns6 / DIRECT_NB)
   int32_t nt;                // row tiles: np, then ceil(nb6 / DIRECT_NB)
   int32_t level;             // height: every child has a lower level
-  int32_t pad;
+  int32_t tile_off;          // its row tiles' ends in tile_end
+  int32_t e0, e1;            // entries of its first tile
   int64_t fact_off;          // factor [(ns6 + nb6) x ns6]
-  int64_t work_off;          // assembled panel of the level, same shape
+  int64_t work_off;          // assembled columns of the level, same shape
   int64_t again_off;         // np > 1: second work panel of the level, same shape
   int64_t w_off;             // np > 1: scaled panels of two steps, DIRECT_NB x DIRECT_NB row tiles
+  int64_t child_u[2];        // the children's u_off, 0 without a child
   int64_t u_off;             // Schur complement, lower triangle row by row (direct_tri)
   int64_t v_off;             // update vector of the forward substitution [nb6]
   int64_t b_off;             // right-hand side of the own DOFs [ns6]
@@ -50,15 +51,38 @@ __host__ __device__
 #endif
 inline int64_t direct_tri(int r) { return (int64_t)r * (r + 1) / 2; }
 
-// A work item: the front and up to two tile indices; entries [e0, e1) of an assembly item.
+// Rows of row tile i of a front: own rows first, boundary rows in tiles of their own.
+struct DirectRows {
+  int32_t r0, n;
+};
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline DirectRows direct_rows(const DirectFront& F, int i) {
+  DirectRows t;
+  if (i < F.np) {
+    t.r0 = i * DIRECT_NB;
+    t.n = F.ns6 - t.r0;
+  } else {
+    t.r0 = F.ns6 + (i - F.np) * DIRECT_NB;
+    t.n = F.ns6 + F.nb6 - t.r0;
+  }
+  if (t.n > DIRECT_NB) t.n = DIRECT_NB;
+  return t;
+}
+
+// A work item: the front and up to two tile indices; K's entries [e0, e1) of tile (i, max(j, 0))
+// in the first panel step.
 struct DirectItem {
   int32_t front, i, j, e0, e1;
 };
 
-// One 6x6 block of K in a front: local row and column within its assembly tile, value slot (the
-// block of (column node, row node), read transposed: K is bitwise symmetric).
+// One 6x6 block of K in a tile of a front (a block across tiles is listed in each): where its first
+// row and column lie in the tile, plus DIRECT_EDGE each, and its value slot (the block of (column
+// node, row node), read transposed: K is bitwise symmetric).
+constexpr int DIRECT_EDGE = 8;
 struct DirectEntry {
-  int32_t rc;                // row node in tile << 16 | column node in tile
+  int32_t rc;                // row << 16 | column
   int32_t slot;
 };
 
@@ -66,15 +90,23 @@ struct DirectRange {
   int32_t off, cnt;
 };
 
-// Step lists of a level: assembly, Schur complement, forward and backward substitution, then the
-// panel steps 0 .. np: step q scales panel q (items with j < 0: row tile i) and updates with panel
-// q - 1 (tile i, j).
-enum { STEP_ASM = 0, STEP_SCHUR = 1, STEP_FWD = 2, STEP_BWD = 3, STEP_PANEL = 4 };
+// Step lists of a level: Schur complement, forward and backward substitution, then the panel steps
+// 0 .. np: step q scales panel q (items with j < 0: row tile i) and updates with panel q - 1 (tile
+// i, j).  Step 0 assembles as well, tiles on the diagonal and below it (those above it are their
+// transposes): its items with j < 0 the first column of tiles, -j row tiles from i on; the others
+// tile (i, j).
+enum { STEP_SCHUR = 0, STEP_FWD = 1, STEP_BWD = 2, STEP_PANEL = 3 };
+// Row tiles of a scaling item of step 0: one, so that a front's tiles spread over the chip, or more
+// where the level has more than these for each workgroup the chip holds (each item sweeps the
+// pivot block for itself).
+constexpr int DIRECT_FIRST_ITEMS = 1024;
+constexpr int DIRECT_FIRST_MOST = 8;
 
 struct DirectPlan {
   std::vector<DirectFront> fronts;    // level by level, leaves first
   std::vector<int32_t> nodes, maps;
   std::vector<DirectEntry> entries;
+  std::vector<int32_t> tile_end;      // per row tile: end of the entries of its first tile
   std::vector<DirectItem> items;
   std::vector<DirectRange> steps;     // steps[level_off[h] + STEP_*] (panels: STEP_PANEL + q)
   std::vector<int32_t> level_off;     // per level
@@ -92,13 +124,14 @@ struct DirectPlan {
     nodes = {};
     maps = {};
     entries = {};
+    tile_end = {};
     items = {};
   }
 };
 
 // Builds the plan for a block pattern (brow_ptr [n + 1], bcol, columns of a row ascending, the
 // pattern symmetric).  Returns false when its numeric arrays would take more than max_bytes or a
-// front has more than DIRECT_MAX_OWN own DOFs.
+// front has more than DIRECT_MAX_OWN own or DIRECT_MAX_BOUNDARY boundary DOFs.
 bool build_direct_plan(int n, const int32_t* brow_ptr, const int32_t* bcol, double max_bytes,
                        DirectPlan& plan);
 // 0 when every invariant of the plan holds, else the number of the first failed check, with a

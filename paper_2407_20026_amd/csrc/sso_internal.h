@@ -319,6 +319,7 @@ struct DirectArgs {
   const DirectFront* fronts;
   const int32_t *nodes, *maps;
   const DirectEntry* entries;
+  const int32_t* tile_end;
   const DirectItem* items;
   const DirectRange* steps;
   const int32_t *level_off, *level_np;

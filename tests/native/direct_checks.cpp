@@ -156,21 +156,35 @@ static int run(const std::string& name, const Graph& g, bool numeric) {
       b(n6), seen(pl.fact_len, 0.0);
   for (int h = 0; h < pl.levels(); ++h) {
     const DirectRange* st = pl.steps.data() + pl.level_off[h];
-    for (int q = 0; q < st[STEP_ASM].cnt; ++q) {
-      const DirectItem it = pl.items.at(st[STEP_ASM].off + q);
+    for (int q = 0; q < st[STEP_PANEL].cnt; ++q) {
+      const DirectItem it = pl.items.at(st[STEP_PANEL].off + q);
       const DirectFront& F = pl.fronts.at(it.front);
-      const int r0 = 6 * DIRECT_ASM_ROWS * it.i, c0 = 6 * DIRECT_ASM_COLS * it.j;
-      for (int r = r0; r < std::min(r0 + 6 * DIRECT_ASM_ROWS, F.ns6 + F.nb6); ++r)
-        for (int c = c0; c < std::min(c0 + 6 * DIRECT_ASM_COLS, F.ns6); ++c) {
-          f0.at(F.work_off + (int64_t)r * F.ns6 + c) = children(pl, u, F, r, c);
-          seen.at(F.fact_off + (int64_t)r * F.ns6 + c) += 1.0;
+      for (int t = 0; t < (it.j < 0 ? -it.j : 1); ++t) {
+        const DirectRows R = direct_rows(F, it.i + t);
+        const int r0 = R.r0, c0 = DIRECT_NB * std::max(it.j, 0);
+        const int nr = R.n, nc = std::min(DIRECT_NB, F.ns6 - c0);
+        for (int r = r0; r < r0 + nr; ++r)
+          for (int c = c0; c < c0 + nc; ++c) {
+            f0.at(F.work_off + (int64_t)r * F.ns6 + c) = children(pl, u, F, r, c);
+            seen.at(F.fact_off + (int64_t)r * F.ns6 + c) += 1.0;
+            if (r < F.ns6 && r0 != c0) seen.at(F.fact_off + (int64_t)c * F.ns6 + r) += 1.0;
+          }
+        const int e0 = t == 0 ? it.e0 : pl.tile_end.at(F.tile_off + it.i + t - 1);
+        const int e1 = t == 0 ? it.e1 : pl.tile_end.at(F.tile_off + it.i + t);
+        for (int e = e0; e < e1; ++e) {
+          const DirectEntry en = pl.entries.at(e);
+          const int er = (en.rc >> 16) - DIRECT_EDGE, ec = (en.rc & 0xffff) - DIRECT_EDGE;
+          for (int cb = 0; cb < 6; ++cb)
+            for (int ca = 0; ca < 6; ++ca) {
+              const int r = er + ca, c = ec + cb;
+              if (r >= 0 && r < nr && c >= 0 && c < nc)
+                f0.at(F.work_off + (int64_t)(r0 + r) * F.ns6 + c0 + c) +=
+                    K.at(36 * (size_t)en.slot + 6 * cb + ca);
+            }
         }
-      for (int e = it.e0; e < it.e1; ++e) {
-        const DirectEntry en = pl.entries.at(e);
-        for (int cb = 0; cb < 6; ++cb)
-          for (int ca = 0; ca < 6; ++ca)
-            f0.at(F.work_off + (int64_t)(r0 + 6 * (en.rc >> 16) + ca) * F.ns6 + c0 +
-                  6 * (en.rc & 0xffff) + cb) += K.at(36 * (size_t)en.slot + 6 * cb + ca);
+        for (int r = r0; r < r0 + nr && r < F.ns6; ++r)     // the other half
+          for (int c = c0; c < c0 + nc; ++c)
+            f0.at(F.work_off + (int64_t)c * F.ns6 + r) = f0.at(F.work_off + (int64_t)r * F.ns6 + c);
       }
     }
     for (int i = 0; i < (int)pl.fronts.size(); ++i) {
