@@ -520,7 +520,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
   // work lists
   std::vector<int32_t> start;
   std::vector<int32_t> lo, hi, fill;
-  std::vector<DirectItem> assemble;
+  std::vector<DirectItem> assemble, spare;
   for (int h = 0; h < nl; ++h) {
     const int np = plan.level_np[h];
     plan.level_off[h] = (int32_t)plan.steps.size();
@@ -528,6 +528,20 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
     DirectRange* st = plan.steps.data() + plan.level_off[h];
     auto open = [&](int s) { st[s].off = (int32_t)plan.items.size(); };
     auto close = [&](int s) { st[s].cnt = (int32_t)plan.items.size() - st[s].off; };
+    // The items from `from` on so that an XCD gets a run of them: neighbours in the list read the
+    // same rows of a front, from its L2 then.
+    auto spread = [&](int s, int from) {
+      const int cnt = (int)plan.items.size() - from, phase = (from - st[s].off) % DIRECT_XCDS;
+      int at[DIRECT_XCDS], run = 0;
+      for (int x = 0; x < DIRECT_XCDS; ++x) {
+        const int p = (x + DIRECT_XCDS - phase) % DIRECT_XCDS;     // its first position
+        at[x] = run;
+        run += p < cnt ? (cnt - p - 1) / DIRECT_XCDS + 1 : 0;
+      }
+      spare.assign(plan.items.begin() + from, plan.items.end());
+      for (int p = 0; p < cnt; ++p)
+        plan.items[from + p] = spare[at[(phase + p) % DIRECT_XCDS]++];
+    };
     // step 0: blocks of K with a column among the own nodes, bucketed by tile, first columns first
     assemble.clear();
     int first_tiles = 0;
@@ -583,7 +597,10 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
           assemble.push_back({i, a, b, start[b * D.nt + a], start[b * D.nt + a + 1]});
       for (int k = 0; k < cnt; ++k) local[list[k]] = -1;
     }
-    plan.items.insert(plan.items.end(), assemble.begin(), assemble.end());   // the longer work first
+    spread(STEP_PANEL, st[STEP_PANEL].off);
+    const int from = (int)plan.items.size();                 // the longer work first
+    plan.items.insert(plan.items.end(), assemble.begin(), assemble.end());
+    spread(STEP_PANEL, from);
     close(STEP_PANEL);
     for (int q = 1; q <= np; ++q) {
       open(STEP_PANEL + q);
@@ -591,12 +608,15 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
         const DirectFront& D = plan.fronts[i];
         for (int r = 0; q < D.np && r < D.nt; ++r) plan.items.push_back({i, r, -1, 0, 0});
       }
+      spread(STEP_PANEL + q, st[STEP_PANEL + q].off);
+      const int updates = (int)plan.items.size();
       for (int i : by_level[h]) {
         const DirectFront& D = plan.fronts[i];
         if (q > D.np || D.np == 1) continue;   // a single panel is done once scaled
         for (int r = 0; r < D.nt; ++r)
           for (int c = 0; c < D.np; ++c) plan.items.push_back({i, r, c, 0, 0});
       }
+      spread(STEP_PANEL + q, updates);
       close(STEP_PANEL + q);
     }
     open(STEP_SCHUR);
@@ -605,6 +625,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       for (int a = 0; a < t; ++a)
         for (int b = 0; b <= a; ++b) plan.items.push_back({i, a, b, 0, 0});
     }
+    spread(STEP_SCHUR, st[STEP_SCHUR].off);
     close(STEP_SCHUR);
     open(STEP_FWD);
     for (int i : by_level[h]) {
@@ -612,11 +633,13 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       const int t = std::max(ceil_div(D.nb6, DIRECT_FWD_ROWS), D.ns6 > 0 ? 1 : 0);
       for (int a = 0; a < t; ++a) plan.items.push_back({i, a, 0, 0, 0});
     }
+    spread(STEP_FWD, st[STEP_FWD].off);
     close(STEP_FWD);
     open(STEP_BWD);
     for (int i : by_level[h])
       for (int a = 0; a < ceil_div(plan.fronts[i].ns6, DIRECT_BWD_COLS); ++a)
         plan.items.push_back({i, a, 0, 0, 0});
+    spread(STEP_BWD, st[STEP_BWD].off);
     close(STEP_BWD);
   }
   return true;

@@ -90,6 +90,9 @@ struct DirectRange {
   int32_t off, cnt;
 };
 
+// Workgroups go to the chip's XCDs, each with an L2 of its own, in turn.
+constexpr int DIRECT_XCDS = 8;
+
 // Step lists of a level: Schur complement, forward and backward substitution, then the panel steps
 // 0 .. np: step q scales panel q (items with j < 0: row tile i) and updates with panel q - 1 (tile
 // i, j).  Step 0 assembles as well, tiles on the diagonal and below it (those above it are their
