@@ -36,7 +36,7 @@ constexpr int TPB = 256;
 constexpr int KC = 32;                // depth of an LDS tile
 constexpr int LDK = KC + 1;           // its row length: odd, so that 16 rows spread over the banks
 constexpr int LDN = NB + 1;
-constexpr int FWD_ROWS_WAVE = DIRECT_FWD_ROWS / (TPB / 64);
+constexpr int FWD_LANES = TPB / DIRECT_FWD_ROWS;    // lanes of a row
 constexpr int BWD_TPB = 512;
 constexpr int BWD_GROUPS = BWD_TPB / DIRECT_BWD_COLS;
 constexpr int BWD_CHUNK = 2048;       // rows of the vector staged at a time
@@ -846,11 +846,19 @@ k_front_schur(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int
   });
 }
 
-// Up: b_S (every workgroup of the front for itself) and 16 rows of v_B, 4 a wave, whose lanes lie
-// along the rows.
+// Up: b_S (every item of the front for itself, in LDS) and rows [i, e0) of v_B, 16 a pass, 16 lanes
+// a row.  A row's first 128 columns are on their way before b_S is there, those of the next pass
+// before this one's sum is taken.
+//
+// Bound by the factor's bytes on levels with many fronts, by latency on the others.  Rows of 64
+// lanes left most of them idle on the lowest levels (35 own DOFs on average), and LDS for the
+// largest front let three workgroups on a CU: for a 300 x 300 shell (1.05 GB of it) 1.05 ms then,
+// 0.36 now; 6.4 us a level of a 60 x 60 one then, 4.7 now.
 __global__ void __launch_bounds__(TPB)
 k_front_forward(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
-  __shared__ __align__(16) double b[DIRECT_MAX_OWN];
+  extern __shared__ __align__(16) double b[];
+  static_assert(FWD_LANES == 16, "a row's sum is taken over a DPP row");
+  constexpr int AT_ONCE = 4, COLS = 2 * FWD_LANES;
   DirectItem it;
   if (!take_item(a, probs, first, level, STEP_FWD, it)) return;
   const DirectFront F = a.fronts[it.front];
@@ -859,45 +867,62 @@ k_front_forward(DirectArgs a, const DirectArgs* __restrict__ probs, int first, i
   const int32_t* __restrict__ m1 = m0 + cnt;
   const double* v0 = F.child[0] >= 0 ? a.v + a.fronts[F.child[0]].v_off : nullptr;
   const double* v1 = F.child[1] >= 0 ? a.v + a.fronts[F.child[1]].v_off : nullptr;
-  auto children = [&](int node, int c) {
-    const int p0 = m0[node], p1 = m1[node];
-    return (p0 >= 0 ? v0[6 * p0 + c] : 0.0) + (p1 >= 0 ? v1[6 * p1 + c] : 0.0);
+  const int l = threadIdx.x % FWD_LANES, r0 = it.i + (int)threadIdx.x / FWD_LANES;
+  const double* __restrict__ G = a.fact + F.fact_off + (int64_t)F.ns6 * F.ns6;
+  double2 g[AT_ONCE];
+  double child = 0.0;                   // lanes 0 and 1: the children's part of the row
+  auto fetch = [&](int row, int c0) {
+    const double* __restrict__ p = G + (int64_t)row * F.ns6;
+#pragma unroll
+    for (int k = 0; k < AT_ONCE; ++k) {
+      const int c = c0 + 2 * l + COLS * k;
+      g[k] = double2{0.0, 0.0};
+      if (row < it.e0 && c < F.ns6) g[k] = *reinterpret_cast<const double2*>(p + c);
+    }
   };
+  auto fetch_child = [&](int row) {
+    child = 0.0;
+    if (l < 2 && row < it.e0) {
+      const int m = (l ? m1 : m0)[ns + row / 6];
+      if (m >= 0) child = (l ? v1 : v0)[6 * m + row % 6];
+    }
+  };
+  fetch(r0, 0);
   for (int c = threadIdx.x; c < F.ns6; c += TPB) {
     const int q = c / 6, d = c - 6 * q;
-    const double v = a.rhs[6 * (int64_t)a.nodes[F.nodes_off + q] + d] + children(q, d);
+    const int p0 = m0[q], p1 = m1[q];
+    const double v = a.rhs[6 * (int64_t)a.nodes[F.nodes_off + q] + d] +
+                     ((p0 >= 0 ? v0[6 * p0 + d] : 0.0) + (p1 >= 0 ? v1[6 * p1 + d] : 0.0));
     b[c] = v;
     if (it.i == 0) a.b[F.b_off + c] = v;
   }
+  fetch_child(r0);
   __syncthreads();
-  const int lane = threadIdx.x & 63, wave = wave_id();
-  const double* __restrict__ G = a.fact + F.fact_off + (int64_t)F.ns6 * F.ns6;
-  const int r0 = it.i * DIRECT_FWD_ROWS + FWD_ROWS_WAVE * wave;
-  if (r0 >= F.nb6) return;
-  double s[FWD_ROWS_WAVE];
-  const double* g[FWD_ROWS_WAVE];
+  for (int base = it.i; base < it.e0; base += DIRECT_FWD_ROWS) {
+    const int row = r0 + base - it.i;
+    double s = -child;
+    for (int c0 = 0; c0 < F.ns6; c0 += COLS * AT_ONCE) {
+      if (c0) fetch(row, c0);
 #pragma unroll
-  for (int k = 0; k < FWD_ROWS_WAVE; ++k) {
-    s[k] = 0.0;
-    g[k] = G + (int64_t)(r0 + k < F.nb6 ? r0 + k : F.nb6 - 1) * F.ns6;
-  }
-  for (int c = 2 * lane; c < F.ns6; c += 128) {
-    const double2 bv = *reinterpret_cast<const double2*>(b + c);
-#pragma unroll
-    for (int k = 0; k < FWD_ROWS_WAVE; ++k) {
-      const double2 gv = *reinterpret_cast<const double2*>(g[k] + c);
-      s[k] += gv.x * bv.x + gv.y * bv.y;
+      for (int k = 0; k < AT_ONCE; ++k) {
+        const int c = c0 + 2 * l + COLS * k;
+        if (c < F.ns6) {
+          const double2 bv = *reinterpret_cast<const double2*>(b + c);
+          s += g[k].x * bv.x + g[k].y * bv.y;
+        }
+      }
     }
-  }
-#pragma unroll
-  for (int k = 0; k < FWD_ROWS_WAVE; ++k) {
-    const double dot = wave_sum(s[k]);
-    const int row = r0 + k;
-    if (lane == k && row < F.nb6) a.v[F.v_off + row] = children(ns + row / 6, row % 6) - dot;
+    if (base + DIRECT_FWD_ROWS < it.e0) {
+      fetch(row + DIRECT_FWD_ROWS, 0);
+      fetch_child(row + DIRECT_FWD_ROWS);
+    }
+    s = row_sum(s);
+    if (l == 0 && row < it.e0) a.v[F.v_off + row] = -s;
   }
 }
 
-// Down: 32 columns of x_S = -(panel^T [b_S; x_B]), the panel's rows dealt to 16 groups of lanes.
+// Down: 32 columns of x_S = -(panel^T [b_S; x_B]), the panel's rows dealt to 16 groups of lanes, the
+// first 8 of each on their way while the vector is gathered: 5.9 -> 5.4 us a level of a 60 x 60 shell.
 __global__ void __launch_bounds__(BWD_TPB)
 k_front_backward(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
   __shared__ double y[BWD_CHUNK];
@@ -911,8 +936,18 @@ k_front_backward(DirectArgs a, const DirectArgs* __restrict__ probs, int first, 
   const int cl = c < F.ns6 ? c : F.ns6 - 1;
   const double* __restrict__ P = a.fact + F.fact_off + cl;
   double s = 0.0;
+  constexpr int AT_ONCE = 8;
+  double v[AT_ONCE];
+  auto fetch = [&](int r, int end) {      // past the end, the last row
+#pragma unroll
+    for (int u = 0; u < AT_ONCE; ++u) {
+      const int k = r + u * BWD_GROUPS;
+      v[u] = P[(int64_t)(k < end ? k : end - 1) * F.ns6];
+    }
+  };
   for (int base = 0; base < rows; base += BWD_CHUNK) {
     const int n = rows - base < BWD_CHUNK ? rows - base : BWD_CHUNK;
+    fetch(base + g, base + n);          // on its way while y is gathered
     __syncthreads();
     for (int k = threadIdx.x; k < n; k += BWD_TPB) {
       const int r = base + k, q = r / 6;
@@ -920,15 +955,14 @@ k_front_backward(DirectArgs a, const DirectArgs* __restrict__ probs, int first, 
                        : a.sol[6 * (int64_t)a.nodes[F.nodes_off + q] + r - 6 * q];
     }
     __syncthreads();
-    int k = g;
-    for (; k + 7 * BWD_GROUPS < n; k += 8 * BWD_GROUPS) {
-      double v[8];
+    for (int k = g; k < n; k += AT_ONCE * BWD_GROUPS) {
+      if (k != g) fetch(base + k, base + n);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = P[(int64_t)(base + k + u * BWD_GROUPS) * F.ns6];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u] * y[k + u * BWD_GROUPS];
+      for (int u = 0; u < AT_ONCE; ++u) {
+        const int r = k + u * BWD_GROUPS;
+        s += v[u] * (r < n ? y[r] : 0.0);
+      }
     }
-    for (; k < n; k += BWD_GROUPS) s += P[(int64_t)(base + k) * F.ns6] * y[k];
   }
   part[g][lc] = s;
   __syncthreads();
@@ -972,6 +1006,13 @@ struct Launch {
       if (level < plans[i]->levels() && plans[i]->level_np[level] > q)
         q = plans[i]->level_np[level];
     return q;
+  }
+  size_t own(int level) const {
+    int c = 0;
+    for (int i = 0; i < n; ++i)
+      if (level < plans[i]->levels() && plans[i]->level_own[level] > c)
+        c = plans[i]->level_own[level];
+    return sizeof(double) * (size_t)c;
   }
   // launch(grid, first item) for a step of a level, if any problem has items there
   template <class Fn>
@@ -1019,7 +1060,7 @@ static hipError_t substitute(const Launch& L) {
   const DirectArgs a = L.one ? *L.one : DirectArgs{};
   for (int h = 0; h < L.levels(); ++h)
     SSO_TRY(L.step(h, STEP_FWD, [&](dim3 g, int off) {
-      hipLaunchKernelGGL(k_front_forward, g, dim3(TPB), 0, L.s, a, L.probs, off, h);
+      hipLaunchKernelGGL(k_front_forward, g, dim3(TPB), L.own(h), L.s, a, L.probs, off, h);
     }));
   for (int h = L.levels() - 1; h >= 0; --h)
     SSO_TRY(L.step(h, STEP_BWD, [&](dim3 g, int off) {

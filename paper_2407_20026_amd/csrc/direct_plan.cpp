@@ -444,6 +444,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
   plan.fronts.resize(nf);
   plan.level_off.resize(nl);
   plan.level_np.assign(nl, 0);
+  plan.level_own.assign(nl, 0);
   std::vector<std::vector<int>> by_level(nl);
   for (int i = 0; i < nf; ++i) by_level[ds.fronts[order[i]].level].push_back(i);
 
@@ -503,6 +504,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       D.b_off = b_off;
       b_off += D.ns6;
       plan.level_np[h] = std::max(plan.level_np[h], D.np);
+      plan.level_own[h] = std::max(plan.level_own[h], D.ns6);
     }
     plan.work_len = std::max(plan.work_len, work);
     plan.again_len = std::max(plan.again_len, again);
@@ -628,10 +630,15 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
     spread(STEP_SCHUR, st[STEP_SCHUR].off);
     close(STEP_SCHUR);
     open(STEP_FWD);
+    int passes = 0;
+    for (int i : by_level[h]) passes += ceil_div(plan.fronts[i].nb6, DIRECT_FWD_ROWS);
+    const int rows = DIRECT_FWD_ROWS *
+                     std::min(DIRECT_FWD_MOST, std::max(1, passes / DIRECT_FWD_ITEMS));
     for (int i : by_level[h]) {
       const DirectFront& D = plan.fronts[i];
-      const int t = std::max(ceil_div(D.nb6, DIRECT_FWD_ROWS), D.ns6 > 0 ? 1 : 0);
-      for (int a = 0; a < t; ++a) plan.items.push_back({i, a, 0, 0, 0});
+      if (D.nb6 == 0 && D.ns6 > 0) plan.items.push_back({i, 0, 0, 0, 0});
+      for (int a = 0; a < D.nb6; a += rows)
+        plan.items.push_back({i, a, 0, std::min(a + rows, D.nb6), 0});
     }
     spread(STEP_FWD, st[STEP_FWD].off);
     close(STEP_FWD);

@@ -13,9 +13,13 @@ namespace sso {
 
 // Panel width of the elimination inside a front, and the rows of a work item of its kernels.
 constexpr int DIRECT_NB = 64;
-// Columns of a backward-substitution work item, rows of a forward-substitution one.
+// Columns of a backward-substitution work item; rows of a forward-substitution one: one pass of a
+// workgroup, or more, up to DIRECT_FWD_MOST, where the level has more than DIRECT_FWD_ITEMS passes
+// for each (an item gathers the front's right-hand side for itself).
 constexpr int DIRECT_BWD_COLS = 32;
 constexpr int DIRECT_FWD_ROWS = 16;
+constexpr int DIRECT_FWD_ITEMS = 2048;
+constexpr int DIRECT_FWD_MOST = 4;
 // Most own DOFs of a front (a substitution stages them in LDS).
 constexpr int DIRECT_MAX_OWN = 6144;
 // Most boundary DOFs of a front (byte offsets within its Schur complement have 32 bits).
@@ -72,7 +76,7 @@ inline DirectRows direct_rows(const DirectFront& F, int i) {
 }
 
 // A work item: the front and up to two tile indices; K's entries [e0, e1) of tile (i, max(j, 0))
-// in the first panel step.
+// in the first panel step; boundary rows [i, e0) in the forward substitution.
 struct DirectItem {
   int32_t front, i, j, e0, e1;
 };
@@ -114,6 +118,7 @@ struct DirectPlan {
   std::vector<DirectRange> steps;     // steps[level_off[h] + STEP_*] (panels: STEP_PANEL + q)
   std::vector<int32_t> level_off;     // per level
   std::vector<int32_t> level_np;      // most panels of a front of the level
+  std::vector<int32_t> level_own;     // most own DOFs
   int n_nodes = 0;
   int64_t fact_len = 0, work_len = 0, again_len = 0, w_len = 0, u_len = 0, v_len = 0;
   // values of a problem's numeric arrays: the five above, v, and two vectors of all DOFs

@@ -32,15 +32,22 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// Sum over the 64 lanes of a wave, the same value in every lane: each quad by two quad_perm
-// exchanges, each 16-lane row by rotations of 4 and 8 (lane 16r then holds its row's sum), and
-// the four row sums in a fixed order.
+// Sums over each row of 16 lanes, in every lane of it: each quad by two quad_perm exchanges, the
+// row by rotations of 4 and 8.
 template <class A>
-__device__ __forceinline__ A wave_sum(A v) {
+__device__ __forceinline__ A row_sum(A v) {
   v += dpp_move<0xb1>(v);    // quad_perm [1, 0, 3, 2]
   v += dpp_move<0x4e>(v);    // quad_perm [2, 3, 0, 1]
   v += dpp_move<0x124>(v);   // row_ror:4
   v += dpp_move<0x128>(v);   // row_ror:8
+  return v;
+}
+
+// Sum over the 64 lanes of a wave, the same value in every lane: the rows of 16, then the four row
+// sums in a fixed order.
+template <class A>
+__device__ __forceinline__ A wave_sum(A v) {
+  v = row_sum(v);
   return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 

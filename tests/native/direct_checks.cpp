@@ -234,7 +234,7 @@ static int run(const std::string& name, const Graph& g, bool numeric) {
       const DirectFront& F = pl.fronts.at(it.front);
       for (int c = 0; c < F.ns6; ++c)
         b.at(F.b_off + c) = f.at(6 * pl.nodes.at(F.nodes_off + c / 6) + c % 6) + up(F, c);
-      for (int k = it.i * DIRECT_FWD_ROWS; k < std::min(F.nb6, (it.i + 1) * DIRECT_FWD_ROWS); ++k) {
+      for (int k = it.i; k < it.e0; ++k) {
         double t = up(F, F.ns6 + k);
         for (int c = 0; c < F.ns6; ++c)
           t -= fact.at(F.fact_off + (int64_t)(F.ns6 + k) * F.ns6 + c) * b[F.b_off + c];
