@@ -265,76 +265,183 @@ __device__ inline bool quad_prop_ok(const double* pr, double scale) {
          scale >= 0.0 && isfinite(t) && isfinite(E) && isfinite(scale);
 }
 
-// ---- shell stiffness: one wavefront per element --------------------------------------------
+// ---- shell stiffness: 16 lanes per element, one 6 x 6 corner block each ----------------------
 
-constexpr int QW = 4;   // elements (wavefronts) per workgroup
-
-__global__ void __launch_bounds__(64 * QW) k_quad_stiffness(Mesh m, double* coo, double* qarea,
-                                                            unsigned* err) {
-  __shared__ double Gs[QW][36][24];
-  __shared__ double Hs[QW][36][24];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t e = (int64_t)blockIdx.x * QW + w;
-  const bool active = e < m.n_quads;
-  bool ok = true;
-  if (active) {
-    double X[4][3];
-    for (int i = 0; i < 4; ++i) {
-      int nd = m.quad_nodes[4 * e + i];
-      for (int k = 0; k < 3; ++k) X[i][k] = m.xyz[3 * (int64_t)nd + k];
-    }
-    const double* pr = m.quad_prop + 5 * e;
-    const double sc = m.quad_scale[e];
-    QGeom<double> g;
-    ok = quad_prop_ok(pr, sc) && quad_geom(X, g);
-    if (ok) {
-      QMat<double> mt = quad_mat<double>(pr[0], pr[1], pr[2]);
-      for (int pass = 0; pass < 2; ++pass) {
-        int pair = lane + 64 * pass;       // (gauss point, global column) pairs: 4 x 24
-        if (pair < 96) {
-          int gp = pair / 24, col = pair % 24;
-          int i = col / 6, c = col % 6;
-          QGP<double> q;
-          quad_gp(g, gp, q);
-          if (!(q.det > 0.0)) ok = false;
-          double ug[3] = {0.0, 0.0, 0.0}, rg[3] = {0.0, 0.0, 0.0};
-          if (c < 3) ug[c] = 1.0; else rg[c - 3] = 1.0;
-          double d[6];
-          to_local_warped(g, i, ug, rg, d);
-          double eps[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, gxi = 0.0, geta = 0.0;
-          add_strains(q, i, d, eps, gxi, geta);
-          finish_shear(q, gxi, geta, eps);
-          double sig[9];
-          apply_D(mt, eps, sig);
-          double wgt = q.det * sc;
-          for (int s = 0; s < 9; ++s) {
-            Gs[w][gp * 9 + s][col] = eps[s];
-            Hs[w][gp * 9 + s][col] = sig[s] * wgt;
-          }
-        }
-      }
-      if (lane == 0) qarea[e] = g.area;
-    }
-  }
-  // a failed Jacobian on any lane marks the element
-  ok = __all(ok) != 0;
-  if (active && !ok && lane == 0) atomicOr(err, ERR_QUAD);
-  __syncthreads();
-  if (!active) return;
-  const int a0 = 3 * (lane >> 3), b0 = 3 * (lane & 7);
-  double acc[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-  for (int r = 0; r < 36; ++r) {
-    double ga[3], hb[3];
-    for (int k = 0; k < 3; ++k) {
-      ga[k] = Gs[w][r][a0 + k];
-      hb[k] = Hs[w][r][b0 + k];
-    }
-    for (int i = 0; i < 3; ++i)
-      for (int j = 0; j < 3; ++j) acc[i][j] += ga[i] * hb[j];
-  }
-  double* out = coo + 144 * (int64_t)m.n_beams + 576 * e;
+// B = R^T A R.
+__device__ inline void rotate_block(const double R[3][3], const double A[3][3], double B[3][3]) {
+  double t[3][3];
   for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) out[24 * (a0 + i) + b0 + j] = acc[i][j];
+    for (int j = 0; j < 3; ++j)
+      t[i][j] = A[i][0] * R[0][j] + A[i][1] * R[1][j] + A[i][2] * R[2][j];
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j)
+      B[i][j] = R[0][i] * t[0][j] + R[1][i] * t[1][j] + R[2][i] * t[2][j];
+}
+
+// What a corner contributes at a Gauss point: N, N,x, N,y and the two shear strains' coefficients
+// on (w, theta_x, theta_y) (quad_gp's, one corner of it: XI, ET are its reference coordinates; ex,
+// ey half its edge along xi and fx, fy along eta).
+struct QCorner {
+  double XI, ET, ex, ey, fx, fy;
+  double N, Nx, Ny, P[3], Q[3];
+  __device__ void at(double xi, double eta, const double Ji[2][2]) {
+    const double a = 1.0 + xi * XI, b = 1.0 + eta * ET;
+    const double dxi = 0.25 * XI * b, deta = 0.25 * ET * a;
+    N = 0.25 * a * b;
+    Nx = Ji[0][0] * dxi + Ji[0][1] * deta;
+    Ny = Ji[1][0] * dxi + Ji[1][1] * deta;
+    const double gx[3] = {dxi, -0.25 * b * ey, 0.25 * b * ex};      // gamma_xi
+    const double ge[3] = {deta, -0.25 * a * fy, 0.25 * a * fx};     // gamma_eta
+    for (int k = 0; k < 3; ++k) {
+      P[k] = Ji[0][0] * gx[k] + Ji[0][1] * ge[k];
+      Q[k] = Ji[1][0] * gx[k] + Ji[1][1] * ge[k];
+    }
+  }
+};
+
+// Lane (e, i, j) forms block (i, j) of element e's matrix.  In the element's frame the block falls
+// into (u, v, theta_z) and (w, theta_x, theta_y), each a sum over the Gauss points of products of
+// the two corners' derivatives; warping offsets and the rotation to global axes follow.
+//
+// Bound by the stores of the matrices (4.6 KB an element) for large meshes.  As a product of
+// 36 x 24 strain matrices through LDS, one wave an element, with a corner's values picked from
+// scratch memory by a lane's index, 90000 elements took 857 us and 3600 took 48; this form, with a
+// third of the operations, takes 124 (3.3 TB/s) and 12.
+__global__ void __launch_bounds__(256) k_quad_stiffness(Mesh m, double* coo, double* qarea,
+                                                        unsigned* err) {
+  const int64_t e = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 4;
+  if (e >= m.n_quads) return;
+  const int ij = threadIdx.x & 15, i = ij >> 2, j = ij & 3;
+  double X[4][3];
+  for (int k = 0; k < 4; ++k) {
+    const int nd = m.quad_nodes[4 * e + k];
+    for (int c = 0; c < 3; ++c) X[k][c] = m.xyz[3 * (int64_t)nd + c];
+  }
+  const double* pr = m.quad_prop + 5 * e;
+  const double sc = m.quad_scale[e];
+  QGeom<double> g;
+  bool ok = quad_prop_ok(pr, sc) && quad_geom(X, g);
+  if (!ok) {
+    if (ij == 0) atomicOr(err, ERR_QUAD);
+    return;
+  }
+  const QMat<double> mt = quad_mat<double>(pr[0], pr[1], pr[2]);
+  // a corner's values picked by comparisons: an index that differs between lanes would put the
+  // element's into scratch memory
+  auto pick = [](bool first, double a, double b) { return first ? a : b; };
+  const double x0 = g.x[0], x1 = g.x[1], x2 = g.x[2], x3 = g.x[3];
+  const double y0 = g.y[0], y1 = g.y[1], y2 = g.y[2], y3 = g.y[3];
+  auto corner = [=](int k) {
+    QCorner q;
+    const bool right = k == 1 || k == 2, top = k >= 2;
+    q.XI = right ? 1.0 : -1.0;
+    q.ET = top ? 1.0 : -1.0;
+    q.ex = 0.5 * pick(top, x2 - x3, x1 - x0);
+    q.ey = 0.5 * pick(top, y2 - y3, y1 - y0);
+    q.fx = 0.5 * pick(right, x2 - x1, x3 - x0);
+    q.fy = 0.5 * pick(right, y2 - y1, y3 - y0);
+    return q;
+  };
+  const double h0 = g.h[0], h1 = g.h[1], h2 = g.h[2], h3 = g.h[3];
+  auto offset = [=](int k) {
+    return pick(k < 2, pick(k == 0, h0, h1), pick(k == 2, h2, h3));
+  };
+  QCorner ci = corner(i), cj = corner(j);
+  double xx = 0.0, yy = 0.0, xy = 0.0, yx = 0.0, xn = 0.0, yn = 0.0, nx = 0.0, ny = 0.0, nn = 0.0;
+  double shear[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+#pragma unroll
+  for (int gp = 0; gp < 4; ++gp) {
+    const double xi = gauss_xi(gp), eta = gauss_eta(gp);
+    double J11 = 0.0, J12 = 0.0, J21 = 0.0, J22 = 0.0;
+    const double XI[4] = {-1.0, 1.0, 1.0, -1.0};
+    const double ET[4] = {-1.0, -1.0, 1.0, 1.0};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const double dxi = 0.25 * XI[k] * (1.0 + eta * ET[k]);
+      const double deta = 0.25 * ET[k] * (1.0 + xi * XI[k]);
+      J11 += dxi * g.x[k];
+      J12 += dxi * g.y[k];
+      J21 += deta * g.x[k];
+      J22 += deta * g.y[k];
+    }
+    const double det = J11 * J22 - J12 * J21;
+    if (!(det > 0.0)) ok = false;
+    const double Ji[2][2] = {{J22 / det, -J12 / det}, {-J21 / det, J11 / det}};
+    ci.at(xi, eta, Ji);
+    cj.at(xi, eta, Ji);
+    const double w = det * sc;
+    const double wx = w * ci.Nx, wy = w * ci.Ny, wn = w * ci.N;
+    xx += wx * cj.Nx;
+    xy += wx * cj.Ny;
+    xn += wx * cj.N;
+    yx += wy * cj.Nx;
+    yy += wy * cj.Ny;
+    yn += wy * cj.N;
+    nx += wn * cj.Nx;
+    ny += wn * cj.Ny;
+    nn += wn * cj.N;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+        shear[a][b] += (w * ci.P[a]) * cj.P[b] + (w * ci.Q[a]) * cj.Q[b];
+  }
+  if (!ok && ij == 0) atomicOr(err, ERR_QUAD);
+  if (ij == 0 && ok) qarea[e] = g.area;
+  // local block: translations and rotations (u, v, w | theta_x, theta_y, theta_z)
+  const double nu = mt.nu, hn = 0.5 * (1.0 - nu), dd = mt.dd, hd = 0.5 * mt.dd, qd = 0.25 * mt.dd;
+  double tt[3][3], tr[3][3], rt[3][3], rr[3][3];
+  tt[0][0] = mt.dm * (xx + hn * yy) + qd * yy;
+  tt[0][1] = mt.dm * (nu * xy + hn * yx) - qd * yx;
+  tt[1][0] = mt.dm * (nu * yx + hn * xy) - qd * xy;
+  tt[1][1] = mt.dm * (yy + hn * xx) + qd * xx;
+  tt[0][2] = tt[1][2] = tt[2][0] = tt[2][1] = 0.0;
+  tt[2][2] = mt.ds * shear[0][0];
+  tr[0][0] = tr[0][1] = tr[1][0] = tr[1][1] = tr[2][2] = 0.0;
+  tr[0][2] = hd * yn;
+  tr[1][2] = -hd * xn;
+  tr[2][0] = mt.ds * shear[0][1];
+  tr[2][1] = mt.ds * shear[0][2];
+  rt[0][0] = rt[0][1] = rt[1][0] = rt[1][1] = rt[2][2] = 0.0;
+  rt[0][2] = mt.ds * shear[1][0];
+  rt[1][2] = mt.ds * shear[2][0];
+  rt[2][0] = hd * ny;
+  rt[2][1] = -hd * nx;
+  rr[0][0] = mt.db * (yy + hn * xx) + mt.ds * shear[1][1];
+  rr[0][1] = -(mt.db * (nu * yx + hn * xy)) + mt.ds * shear[1][2];
+  rr[1][0] = -(mt.db * (nu * xy + hn * yx)) + mt.ds * shear[2][1];
+  rr[1][1] = mt.db * (xx + hn * yy) + mt.ds * shear[2][2];
+  rr[0][2] = rr[1][2] = rr[2][0] = rr[2][1] = 0.0;
+  rr[2][2] = dd * nn;
+  // offsets from the mean plane: u -= h theta_y, v += h theta_x
+  const double hi = offset(i), hj = offset(j);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    rt[0][k] += hi * tt[1][k];
+    rt[1][k] -= hi * tt[0][k];
+    rr[0][k] += hi * tr[1][k];
+    rr[1][k] -= hi * tr[0][k];
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    tr[k][0] += hj * tt[k][1];
+    tr[k][1] -= hj * tt[k][0];
+    rr[k][0] += hj * rt[k][1];
+    rr[k][1] -= hj * rt[k][0];
+  }
+  double* out = coo + 144 * (int64_t)m.n_beams + 576 * e + 24 * (6 * i) + 6 * j;
+  auto put = [&](const double A[3][3], int r, int c) {
+    double B[3][3];
+    rotate_block(g.R, A, B);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) out[24 * (r + a) + c + b] = B[a][b];
+  };
+  put(tt, 0, 0);
+  put(tr, 0, 3);
+  put(rt, 3, 0);
+  put(rr, 3, 3);
 }
 
 // ---- members -------------------------------------------------------------------------------
@@ -593,7 +700,7 @@ hipError_t launch_element_stiffness(const Mesh& m, double* coo, double* qarea, u
     hipLaunchKernelGGL(k_beam_stiffness, dim3(nblk(12 * (int64_t)m.n_beams, 192)), dim3(192), 0,
                        s, m, coo, d_err);
   if (m.n_quads)
-    hipLaunchKernelGGL(k_quad_stiffness, dim3(nblk(m.n_quads, QW)), dim3(64 * QW), 0, s, m, coo,
+    hipLaunchKernelGGL(k_quad_stiffness, dim3(nblk(16 * (int64_t)m.n_quads, 256)), dim3(256), 0, s, m, coo,
                        qarea, d_err);
   return hipGetLastError();
 }
