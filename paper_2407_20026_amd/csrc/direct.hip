@@ -240,7 +240,8 @@ __device__ __forceinline__ void sweep_steps(double (&d)[16], int l16, double& pi
 }
 
 constexpr int LDS16 = 18;     // row length of 16 columns in LDS: 16-byte reads, spread over the banks
-constexpr int SWEEP_LDS = (NB + 16) * LDS16;
+constexpr int SWEEP_PANEL = (NB + 16) * LDS16;
+constexpr int SWEEP_LDS = 2 * SWEEP_PANEL;      // two panels alternate
 
 // Sweeps the leading nb columns of a 64 x 64 symmetric block, held as matrix-core accumulators
 // (each_acc's layout): the block becomes minus its inverse; pivot[k], k < nb rounded up to 16, are
@@ -250,12 +251,11 @@ constexpr int SWEEP_LDS = (NB + 16) * LDS16;
 // register; the others publish the panel's columns meanwhile; and all update their tiles on the
 // matrix cores.  The product -F D^-1 comes out transposed, which is the order of the next product's
 // left operand, and an accumulator of a symmetric block that of its right one, so nothing goes
-// through LDS in between.  A panel takes 5600 cycles, a block 9 us at 2.4 GHz: 16 steps of 154 in
-// the inversion (issue-bound), 1800 in up to 24 matrix products of one wave, the rest in LDS.  Swept
-// one column at a time, each published through LDS with a barrier, a block took 20 us.
+// through LDS in between.  The next pivot block is updated first and inverted while the other waves
+// go on.  A block takes 8.3 us at 2.4 GHz, most of it in the chain of the four inversions, 16 steps
+// of 154 cycles each (issue-bound); 9.3 us with the update in front of the next inversion; 20 us
+// swept one column at a time, each published through LDS with a barrier.
 __device__ __forceinline__ void sweep(d4 d[2][2], int nb, double* lds, double* pivot) {
-  double* P = lds;                    // the panel's columns; column c at 4 (c % 4) + c / 4
-  double* D = lds + NB * LDS16;       // minus the pivot block's inverse, the same
   const int lane = lane_here();
   const int wave = wave_id();
   const int l16 = lane & 15, kq = lane >> 4, wr = wave >> 1, wc = wave & 1;
@@ -267,86 +267,99 @@ __device__ __forceinline__ void sweep(d4 d[2][2], int nb, double* lds, double* p
     o[2] = z.x;
     o[3] = z.y;
   };
+  // the panel's columns, column c at 4 (c % 4) + c / 4; then minus the pivot block's inverse
+  auto panel = [&](int s) { return lds + s * SWEEP_PANEL; };
+  auto invert = [&](const d4& block, int first, int s) {
+    double* T = panel(s) + first * LDS16;        // nothing else of the panel lies here
+    double* D = panel(s) + NB * LDS16;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) T[l16 * LDS16 + kq + 4 * v] = block[v];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    double x[16];
+#pragma unroll
+    for (int j = 0; j < 16; j += 2) {
+      const double2 y = *reinterpret_cast<const double2*>(T + l16 * LDS16 + j);
+      x[j] = y.x;
+      x[j + 1] = y.y;
+    }
+    double p = 1.0;
+    sweep_steps<0>(x, l16, p);
+    const double inv = reciprocal(p);
+    if (kq == 0) {
+      pivot[first + l16] = p;
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int v = 0; v < 4; v += 2)
+          *reinterpret_cast<double2*>(D + l16 * LDS16 + 4 * g + v) =
+              double2{x[g + 4 * v] * inv, x[g + 4 * v + 4] * inv};
+    }
+  };
+  auto publish = [&](int half, const int s) {
+    if (wc != half) return;
+    const int at = 4 * (l16 & 3) + (l16 >> 2);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (wr == half && i == s) continue;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        panel(s)[(32 * wr + 16 * i + kq + 4 * v) * LDS16 + at] = d[i][s][v];
+    }
+  };
+  if (wave == 0) invert(d[0][0], 0, 0);
+  publish(0, 0);
   for (int half = 0; half < 2; ++half) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const int first = 32 * half + 16 * s;
-      if (first >= nb) return;
-      if (wr == half && wc == half) {
-        double* T = P + first * LDS16;           // nothing else of P lies here
-#pragma unroll
-        for (int v = 0; v < 4; ++v) T[l16 * LDS16 + kq + 4 * v] = d[s][s][v];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        double x[16];
-#pragma unroll
-        for (int j = 0; j < 16; j += 2) {
-          const double2 y = *reinterpret_cast<const double2*>(T + l16 * LDS16 + j);
-          x[j] = y.x;
-          x[j + 1] = y.y;
-        }
-        double p = 1.0;
-        sweep_steps<0>(x, l16, p);
-        const double inv = reciprocal(p);
-        if (kq == 0) {
-          pivot[first + l16] = p;
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int v = 0; v < 4; v += 2)
-              *reinterpret_cast<double2*>(D + l16 * LDS16 + 4 * g + v) =
-                  double2{x[g + 4 * v] * inv, x[g + 4 * v + 4] * inv};
-        }
-      }
-      if (wc == half) {
-        const int at = 4 * (l16 & 3) + (l16 >> 2);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          if (wr == half && i == s) continue;
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            P[(32 * wr + 16 * i + kq + 4 * v) * LDS16 + at] = d[i][s][v];
-        }
-      }
+      if (32 * half + 16 * s >= nb) break;
+      const int next_half = half + s, n = s ^ 1, next = 32 * next_half + 16 * n;
       __syncthreads();
+      const double* P = panel(s);
       double inv[4], row[2][4], col[2][4];
-      four(D + l16 * LDS16 + 4 * kq, inv);
+      four(P + (NB + l16) * LDS16 + 4 * kq, inv);
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         four(P + (32 * wr + 16 * i + l16) * LDS16 + 4 * kq, row[i]);
         four(P + (32 * wc + 16 * i + l16) * LDS16 + 4 * kq, col[i]);
       }
       d4 w[2];                                   // minus the scaled rows, transposed
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        if (wr == half && i == s) continue;
+      auto scale = [&](const int i) {
+        if (wr == half && i == s) return;
         w[i] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           w[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(inv[v], row[i][v], w[i], 0, 0, 0);
-      }
+      };
+      auto update = [&](const int i, const int j) {
+        const bool in_row = wr == half && i == s, in_col = wc == half && j == s;
+        if (in_row && in_col) {
+          d[i][j] = d4{inv[0], inv[1], inv[2], inv[3]};
+        } else if (in_row && wr == wc) {
+          d[i][j] = -w[j];
+        } else if (in_row || in_col) {
+          d4 x = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+          for (int v = 0; v < 4; ++v)
+            x = __builtin_amdgcn_mfma_f64_16x16x4f64(in_row ? inv[v] : row[i][v],
+                                                     in_row ? col[j][v] : inv[v], x, 0, 0, 0);
+          d[i][j] = -x;
+        } else {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const bool in_row = wr == half && i == s, in_col = wc == half && j == s;
-          if (in_row && in_col) {
-            d[i][j] = d4{inv[0], inv[1], inv[2], inv[3]};
-          } else if (in_row || in_col) {
-            d4 x = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              x = __builtin_amdgcn_mfma_f64_16x16x4f64(in_row ? inv[v] : row[i][v],
-                                                       in_row ? col[j][v] : inv[v], x, 0, 0, 0);
-            d[i][j] = -x;
-          } else {
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              d[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i][v], col[j][v], d[i][j], 0, 0, 0);
-          }
+          for (int v = 0; v < 4; ++v)
+            d[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i][v], col[j][v], d[i][j], 0, 0, 0);
         }
-      __syncthreads();
+      };
+      scale(n);
+      update(n, n);
+      if (next < nb && wr == next_half && wc == next_half) invert(d[n][n], next, n);
+      scale(s);
+      update(n, s);
+      update(s, n);
+      update(s, s);
+      if (next < nb) publish(next_half, n);
     }
   }
+  __syncthreads();
 }
 
 constexpr int POOL = 3 * NB * LDK;    // doubles of LDS that the panel kernels cut their tiles from
