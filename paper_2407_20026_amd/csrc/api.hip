@@ -1374,11 +1374,13 @@ int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) {
         continue;
       }
     }
-    DirectJob j{&p->shared->plan, p->da, p->direct_steps == 0, &p->m, &p->pat,
-                p->f, p->u, &p->w, p->d_scal};
-    j.a.rhs = j.factor ? p->f : p->w.r;
-    j.a.sol = j.factor ? p->u : p->da.sol;
-    j.a.scal = p->d_scal;
+    const bool factor = p->direct_steps == 0;
+    DirectJob j{&p->shared->plan, p->da,
+                residual_job(p->m, p->pat, p->K, p->u, p->f, factor ? nullptr : p->da.sol, p->w,
+                             p->da.flag),
+                factor};
+    j.a.rhs = factor ? p->f : p->w.r;
+    j.a.sol = factor ? p->u : p->da.sol;
     if (j.factor) {
       jobs.push_back(j);
       b->direct.push_back(i);

@@ -992,14 +992,6 @@ __global__ void k_direct_clear(DirectArgs a, const DirectArgs* __restrict__ prob
   if (i < n) *(probs ? probs[i].flag : a.flag) = 0u;
 }
 
-__global__ void k_direct_collect(const DirectArgs* __restrict__ probs, int n, double* out) {
-  const int i = (int)threadIdx.x + (int)(blockIdx.x * blockDim.x);
-  if (i >= n) return;
-  out[3 * i] = probs[i].scal[0];
-  out[3 * i + 1] = probs[i].scal[1];
-  out[3 * i + 2] = *probs[i].flag ? 1.0 : 0.0;
-}
-
 // The problems of one launch: a single one by value, or n with their arguments on the device.
 struct Launch {
   const DirectPlan* const* plans;
@@ -1103,24 +1095,31 @@ hipError_t direct_batch_launch(const std::vector<DirectJob>& jobs, DirectBatch& 
   const int n = (int)jobs.size();
   if (n > db.cap) {   // nothing is pending: the last launch was waited for
     dev_free(db.d, s);
+    dev_free(db.d_res, s);
     dev_free(db.d_out, s);
     db.d = nullptr;
+    db.d_res = nullptr;
     db.d_out = nullptr;
     db.cap = 0;
     SSO_TRY(dev_alloc_scratch(&db.d, 2 * n, s));
+    SSO_TRY(dev_alloc_scratch(&db.d_res, 2 * n, s));
     SSO_TRY(dev_alloc_scratch(&db.d_out, 6 * n, s));
     db.cap = 2 * n;
   }
   if (!db.ev) SSO_TRY(hipEventCreateWithFlags(&db.ev, hipEventDisableTiming));
   db.h.resize(n);
+  db.h_res.resize(n);
   std::vector<const DirectPlan*> plans(n);
   int nf = 0;
   for (int i = 0; i < n; ++i) {
     db.h[i] = jobs[i].a;
+    db.h_res[i] = jobs[i].residual;
     plans[i] = jobs[i].plan;
     if (jobs[i].factor) nf = i + 1;
   }
   SSO_TRY(hipMemcpyAsync(db.d, db.h.data(), sizeof(DirectArgs) * n, hipMemcpyHostToDevice, s));
+  SSO_TRY(hipMemcpyAsync(db.d_res, db.h_res.data(), sizeof(ResidualJob) * n,
+                         hipMemcpyHostToDevice, s));
   if (nf > 0) {
     hipLaunchKernelGGL(k_direct_clear, dim3((unsigned)((nf + 63) / 64)), dim3(64), 0, s,
                        DirectArgs{}, db.d, nf);
@@ -1128,13 +1127,7 @@ hipError_t direct_batch_launch(const std::vector<DirectJob>& jobs, DirectBatch& 
     SSO_TRY(factor(Launch{plans.data(), nf, nullptr, db.d, s}));
   }
   SSO_TRY(substitute(Launch{plans.data(), n, nullptr, db.d, s}));
-  for (const DirectJob& j : jobs) {
-    if (!j.factor) SSO_TRY(launch_axpy(1.0, j.a.sol, j.x, 6 * (int64_t)j.m->n_nodes, s));
-    SSO_TRY(launch_true_residual(*j.m, *j.pat, j.a.K, j.x, j.b, j.w->r, *j.w, j.d_scal, s));
-  }
-  hipLaunchKernelGGL(k_direct_collect, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, db.d, n,
-                     db.d_out);
-  SSO_TRY(hipGetLastError());
+  SSO_TRY(launch_residuals(db.h_res, db.d_res, db.d_out, s));
   return hipEventRecord(db.ev, s);
 }
 
@@ -1152,6 +1145,7 @@ void direct_batch_free(DirectBatch& db, hipStream_t s) {
     (void)hipEventDestroy(db.ev);
   }
   dev_free(db.d, s);
+  dev_free(db.d_res, s);
   dev_free(db.d_out, s);
   db = DirectBatch();
 }

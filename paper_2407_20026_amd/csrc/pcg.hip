@@ -2140,17 +2140,18 @@ __device__ inline void row_product_dd(const int32_t* __restrict__ brow_ptr,
   }
 }
 
-// r = b - K x with the row sums in double-double (rounded once); partials of ||r||^2 and
-// ||b||^2.
-__global__ void __launch_bounds__(MAX_TPB)
-k_residual(int n_nodes, const int32_t* __restrict__ brow_ptr, const int32_t* __restrict__ bcol,
-           const double* __restrict__ K, const double* __restrict__ x,
-           const double* __restrict__ b, double* __restrict__ r, double* partials) {
+// r = b - K x with the row sums in double-double (rounded once), workgroup wg of ng; partials of
+// ||r||^2 and ||b||^2.
+__device__ inline void residual_rows(int n_nodes, const int32_t* __restrict__ brow_ptr,
+                                     const int32_t* __restrict__ bcol,
+                                     const double* __restrict__ K, const double* __restrict__ x,
+                                     const double* __restrict__ b, double* __restrict__ r,
+                                     double* partials, int wg, int ng) {
 #pragma clang fp contract(off)
   const SpLane L = sp_lane();
   const int wave = threadIdx.x >> 6;
   double v[2] = {0.0, 0.0};
-  for (int gi = blockIdx.x; gi * ROWS_PER_WG < n_nodes; gi += gridDim.x) {
+  for (int gi = wg; gi * ROWS_PER_WG < n_nodes; gi += ng) {
     const int I = gi * ROWS_PER_WG + wave * ROWS_PER_WAVE + L.g;
     const bool ok = L.ok && I < n_nodes;
     double hi = 0.0, lo = 0.0;
@@ -2171,7 +2172,31 @@ k_residual(int n_nodes, const int32_t* __restrict__ brow_ptr, const int32_t* __r
     }
   }
   block_sum<2, double>(v);
-  write_partials<2, double>(v, partials);
+  write_partials<2, double>(v, partials, wg, ng);
+}
+
+__global__ void __launch_bounds__(MAX_TPB)
+k_residual(int n_nodes, const int32_t* __restrict__ brow_ptr, const int32_t* __restrict__ bcol,
+           const double* __restrict__ K, const double* __restrict__ x,
+           const double* __restrict__ b, double* __restrict__ r, double* partials) {
+  residual_rows(n_nodes, brow_ptr, bcol, K, x, b, r, partials, (int)blockIdx.x, (int)gridDim.x);
+}
+
+// The same for problem blockIdx.y of several, with as many workgroups as it would have alone (so
+// that its sums are the same).  A launch each for the 8 problems of a batch took 20 us a problem,
+// nearly all of it latency.
+__global__ void __launch_bounds__(MAX_TPB) k_residual_many(const ResidualJob* __restrict__ jobs) {
+  const ResidualJob j = jobs[blockIdx.y];
+  if ((int)blockIdx.x >= j.n_wg) return;
+  residual_rows(j.n_nodes, j.brow_ptr, j.bcol, j.K, j.x, j.b, j.r, j.partials, (int)blockIdx.x,
+                j.n_wg);
+}
+
+// x += correction, for the problems that have one.
+__global__ void __launch_bounds__(256) k_correct_many(const ResidualJob* __restrict__ jobs) {
+  const ResidualJob j = jobs[blockIdx.y];
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (j.correction && i < 6 * (int64_t)j.n_nodes) j.x[i] += j.correction[i];
 }
 
 __global__ void __launch_bounds__(256)
@@ -2200,6 +2225,18 @@ __global__ void __launch_bounds__(256) k_finish(const double* partials, int n, i
     for (int k = 0; k < nv; ++k) out[k] = tot[k];
   if (threadIdx.x == 64 && w0) out[nv] = (double)*w0;
   if (threadIdx.x == 128 && w1) out[nv + 1] = (double)*w1;
+}
+
+// Problem blockIdx.x: ||r||^2, ||b||^2 and its flag into out[3 * blockIdx.x ..].
+__global__ void __launch_bounds__(256)
+k_finish_many(const ResidualJob* __restrict__ jobs, double* out) {
+  const ResidualJob j = jobs[blockIdx.x];
+  double tot[2] = {0.0, 0.0};
+  finish_partials<2>(j.partials, j.n_wg, tot);
+  if (threadIdx.x != 0) return;
+  out[3 * blockIdx.x] = tot[0];
+  out[3 * blockIdx.x + 1] = tot[1];
+  out[3 * blockIdx.x + 2] = *j.flag ? 1.0 : 0.0;
 }
 
 // Copy the state records of a multi-problem launch into one array (one read-back per poll).
@@ -3365,6 +3402,29 @@ hipError_t pcg_solve_mixed(const Mesh& m, const Pattern& pat, const double* K, c
   *status = ms.status;
   *outer = ms.outer;
   return e;
+}
+
+ResidualJob residual_job(const Mesh& m, const Pattern& pat, const double* K, double* x,
+                         const double* b, const double* correction, PcgWork& w,
+                         const unsigned* flag) {
+  return ResidualJob{m.n_nodes, w.n_wg, pat.brow_ptr, pat.bcol,     K,   x,
+                     b,         w.r,    part_once(w), correction, flag};
+}
+
+hipError_t launch_residuals(const std::vector<ResidualJob>& jobs, const ResidualJob* d_jobs,
+                            double* d_out, hipStream_t s) {
+  int n_wg = 0, n_nodes = 0;     // of the problems; those with a correction
+  for (const ResidualJob& j : jobs) {
+    n_wg = j.n_wg > n_wg ? j.n_wg : n_wg;
+    if (j.correction) n_nodes = j.n_nodes > n_nodes ? j.n_nodes : n_nodes;
+  }
+  const unsigned n = (unsigned)jobs.size();
+  if (n_nodes > 0)
+    hipLaunchKernelGGL(k_correct_many, dim3(nblk(6 * (int64_t)n_nodes, 256), n), dim3(256), 0, s,
+                       d_jobs);
+  hipLaunchKernelGGL(k_residual_many, dim3((unsigned)n_wg, n), dim3(MAX_TPB), 0, s, d_jobs);
+  hipLaunchKernelGGL(k_finish_many, dim3(n), dim3(256), 0, s, d_jobs, d_out);
+  return hipGetLastError();
 }
 
 hipError_t launch_axpy(double alpha, const double* x, double* y, int64_t n, hipStream_t s) {

@@ -329,7 +329,6 @@ struct DirectArgs {
   const double* rhs;
   double* sol;
   unsigned* flag;          // set when a pivot is too small
-  const double* scal;      // multi-problem launches: where the residual's squared norms are left
   int n_levels;
 };
 // Factor K (a.K) into a.fact; then sol = K^-1 rhs as often as wanted.
@@ -500,20 +499,35 @@ void batch_free(BatchWork& bw, hipStream_t s);
 // Multi-problem launches of the direct solver: one launch per kernel and step for all jobs, each
 // problem's fronts as in a launch of its own.  A job factors and substitutes (factor) or
 // substitutes for the residual and adds to x, and leaves its true residual's norms.
+// One problem of launch_residuals: x += correction (may be null), r = b - K x.
+struct ResidualJob {
+  int n_nodes, n_wg;
+  const int32_t *brow_ptr, *bcol;
+  const double* K;
+  double* x;
+  const double* b;
+  double *r, *partials;
+  const double* correction;
+  const unsigned* flag;
+};
+ResidualJob residual_job(const Mesh& m, const Pattern& pat, const double* K, double* x,
+                         const double* b, const double* correction, PcgWork& w,
+                         const unsigned* flag);
+// ||r||^2, ||b||^2 and the flag of each job (d_jobs: their copy on the device) into d_out [n][3].
+hipError_t launch_residuals(const std::vector<ResidualJob>& jobs, const ResidualJob* d_jobs,
+                            double* d_out, hipStream_t s);
+
 struct DirectJob {
   const DirectPlan* plan;
-  DirectArgs a;            // rhs, sol, scal of this launch
+  DirectArgs a;            // rhs and sol of this launch
+  ResidualJob residual;
   bool factor;
-  const Mesh* m;
-  const Pattern* pat;
-  const double* b;         // right-hand side of the system
-  double* x;
-  PcgWork* w;
-  double* d_scal;
 };
 struct DirectBatch {
   std::vector<DirectArgs> h;
+  std::vector<ResidualJob> h_res;
   DirectArgs* d = nullptr;
+  ResidualJob* d_res = nullptr;
   double* d_out = nullptr;   // [n][3]: rr, bb, flag
   std::vector<double> out;
   int cap = 0;
