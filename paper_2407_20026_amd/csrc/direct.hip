@@ -803,6 +803,29 @@ k_front_first(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int
   }
 }
 
+// Tile (i, j) of a front's boundary rows: G = F_BS W, from the own rows, which hold -W by then.
+// One product over all own columns, where the panel steps would read and write each boundary tile
+// once a panel: with 1806 boundary and 900 own DOFs, four fronts, 15 panel steps took 60 us each,
+// 28 without the boundary rows, which take 286 here (48 TFLOP/s); 300 x 300 shell: 12.7 -> 11.3 ms.
+__global__ void __launch_bounds__(TPB)
+k_front_gain(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
+  __shared__ double as[NB * LDK];
+  __shared__ double bs[NB * LDK];
+  DirectItem it;
+  if (!take_item(a, probs, first, level, STEP_GAIN, it)) return;
+  const DirectFront F = a.fronts[it.front];
+  const DirectRows R = direct_rows(F, it.i);
+  const int c0 = it.j * NB, nc = F.ns6 - c0 < NB ? F.ns6 - c0 : NB;
+  d4 acc[2][2];
+  clear(acc);
+  product(a.f0 + F.work_off + (int64_t)R.r0 * F.ns6, F.ns6, R.n,
+          a.fact + F.fact_off + (int64_t)c0 * F.ns6, F.ns6, nc, F.ns6, as, bs, acc);
+  double* __restrict__ out = a.fact + F.fact_off + (int64_t)R.r0 * F.ns6 + c0;
+  each_acc(acc, [&](int r, int c, double v) {
+    if (r < R.n && c < nc) out[(int64_t)r * F.ns6 + c] = -v;
+  });
+}
+
 // Tile (i, j), j <= i, of a front's Schur complement: the children's minus G F_BS^T.
 __global__ void __launch_bounds__(TPB)
 k_front_schur(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
@@ -1054,6 +1077,9 @@ static hipError_t factor(const Launch& L) {
       SSO_TRY(L.step(h, STEP_PANEL + q, [&](dim3 g, int off) {
         hipLaunchKernelGGL(k_front_panel, g, dim3(TPB), 0, L.s, a, L.probs, off, h, q);
       }));
+    SSO_TRY(L.step(h, STEP_GAIN, [&](dim3 g, int off) {
+      hipLaunchKernelGGL(k_front_gain, g, dim3(TPB), 0, L.s, a, L.probs, off, h);
+    }));
     SSO_TRY(L.step(h, STEP_SCHUR, [&](dim3 g, int off) {
       hipLaunchKernelGGL(k_front_schur, g, dim3(TPB), 0, L.s, a, L.probs, off, h);
     }));

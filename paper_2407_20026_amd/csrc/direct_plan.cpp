@@ -544,10 +544,18 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       for (int p = 0; p < cnt; ++p)
         plan.items[from + p] = spare[at[(phase + p) % DIRECT_XCDS]++];
     };
+    int bnd_tiles = 0;
+    for (int i : by_level[h])
+      if (plan.fronts[i].np > 1)
+        bnd_tiles += (plan.fronts[i].nt - plan.fronts[i].np) * plan.fronts[i].np;
+    const bool gain = bnd_tiles >= DIRECT_GAIN_TILES;
+    // row tiles of a front that its panel steps take
+    auto rows_of = [&](const DirectFront& D) { return gain && D.np > 1 ? D.np : D.nt; };
     // step 0: blocks of K with a column among the own nodes, bucketed by tile, first columns first
     assemble.clear();
     int first_tiles = 0;
-    for (int i : by_level[h]) first_tiles += plan.fronts[i].np > 0 ? plan.fronts[i].nt : 0;
+    for (int i : by_level[h])
+      first_tiles += plan.fronts[i].np > 0 ? rows_of(plan.fronts[i]) : 0;
     const int at_once =
         std::min(DIRECT_FIRST_MOST, std::max(1, first_tiles / DIRECT_FIRST_ITEMS));
     open(STEP_PANEL);
@@ -592,10 +600,11 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       D.e1 = start[1];
       D.tile_off = (int32_t)plan.tile_end.size();
       plan.tile_end.insert(plan.tile_end.end(), start.begin() + 1, start.begin() + 1 + D.nt);
-      for (int a = 0; a < D.nt; a += at_once)
-        plan.items.push_back({i, a, -std::min(at_once, D.nt - a), start[a], start[a + 1]});
-      for (int b = 1; b < D.np; ++b)
-        for (int a = b; a < D.nt; ++a)
+      const int nr = rows_of(D);
+      for (int a = 0; a < nr; a += at_once)
+        plan.items.push_back({i, a, -std::min(at_once, nr - a), start[a], start[a + 1]});
+      for (int b = 0; b < D.np; ++b)
+        for (int a = b == 0 ? nr : b; a < D.nt; ++a)
           assemble.push_back({i, a, b, start[b * D.nt + a], start[b * D.nt + a + 1]});
       for (int k = 0; k < cnt; ++k) local[list[k]] = -1;
     }
@@ -608,19 +617,27 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       open(STEP_PANEL + q);
       for (int i : by_level[h]) {
         const DirectFront& D = plan.fronts[i];
-        for (int r = 0; q < D.np && r < D.nt; ++r) plan.items.push_back({i, r, -1, 0, 0});
+        for (int r = 0; q < D.np && r < rows_of(D); ++r) plan.items.push_back({i, r, -1, 0, 0});
       }
       spread(STEP_PANEL + q, st[STEP_PANEL + q].off);
       const int updates = (int)plan.items.size();
       for (int i : by_level[h]) {
         const DirectFront& D = plan.fronts[i];
         if (q > D.np || D.np == 1) continue;   // a single panel is done once scaled
-        for (int r = 0; r < D.nt; ++r)
+        for (int r = 0; r < rows_of(D); ++r)
           for (int c = 0; c < D.np; ++c) plan.items.push_back({i, r, c, 0, 0});
       }
       spread(STEP_PANEL + q, updates);
       close(STEP_PANEL + q);
     }
+    open(STEP_GAIN);
+    for (int i : by_level[h]) {
+      const DirectFront& D = plan.fronts[i];
+      for (int r = rows_of(D); r < D.nt; ++r)
+        for (int c = 0; c < D.np; ++c) plan.items.push_back({i, r, c, 0, 0});
+    }
+    spread(STEP_GAIN, st[STEP_GAIN].off);
+    close(STEP_GAIN);
     open(STEP_SCHUR);
     for (int i : by_level[h]) {
       const int t = ceil_div(plan.fronts[i].nb6, DIRECT_NB);
@@ -717,6 +734,23 @@ int check_direct_plan(int n, const int32_t* rp, const int32_t* col, const Direct
         (D.np > 1 && (D.again_off + panel > plan.again_len ||
                       D.w_off + 2 * (int64_t)DIRECT_NB * DIRECT_NB * D.nt > plan.w_len)))
       return fail(7, "array too short", (long long)f);
+  }
+  // a front's boundary tiles are formed by the last panel step or by the gain step
+  std::vector<int> formed(plan.fronts.size(), 0);
+  for (int h = 0; h < plan.levels(); ++h)
+    for (int q = STEP_GAIN; q <= STEP_PANEL + plan.level_np[h]; ++q) {
+      const DirectRange st = plan.steps[plan.level_off[h] + q];
+      for (int k = 0; k < st.cnt; ++k) {
+        const DirectItem& it = plan.items[st.off + k];
+        const DirectFront& D = plan.fronts[it.front];
+        if (q == STEP_GAIN || (q - STEP_PANEL == D.np && it.j >= 0 && it.i >= D.np))
+          ++formed[it.front];
+      }
+    }
+  for (size_t f = 0; f < plan.fronts.size(); ++f) {
+    const DirectFront& D = plan.fronts[f];
+    if (D.np > 1 && formed[f] != (D.nt - D.np) * D.np)
+      return fail(10, "boundary tiles", (long long)f);
   }
   // the first panel step's tiles hold every value of those blocks once
   size_t values = 0;

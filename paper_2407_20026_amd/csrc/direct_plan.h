@@ -101,8 +101,13 @@ constexpr int DIRECT_XCDS = 8;
 // 0 .. np: step q scales panel q (items with j < 0: row tile i) and updates with panel q - 1 (tile
 // i, j).  Step 0 assembles as well, tiles on the diagonal and below it (those above it are their
 // transposes): its items with j < 0 the first column of tiles, -j row tiles from i on; the others
-// tile (i, j).
-enum { STEP_SCHUR = 0, STEP_FWD = 1, STEP_BWD = 2, STEP_PANEL = 3 };
+// tile (i, j).  On a level with a gain step the panel steps take the own rows only, the first one's
+// boundary tiles being assembled like the others, and the gain step forms the boundary rows G.
+enum { STEP_SCHUR = 0, STEP_FWD = 1, STEP_BWD = 2, STEP_GAIN = 3, STEP_PANEL = 4 };
+// Boundary tiles that a panel step would update, from which on a level with several panels takes the
+// gain step: four for each of the 256 CUs.  A level with 1740 (four fronts, 900 own DOFs) took 15 x
+// 60 us without it and 15 x 28 + 286 with it; one with 870 (two fronts) 15 x 32 and 15 x 25 + 178.
+constexpr int DIRECT_GAIN_TILES = 1024;
 // Row tiles of a scaling item of step 0: one, so that a front's tiles spread over the chip, or more
 // where the level has more than these for each workgroup the chip holds (each item sweeps the
 // pivot block for itself).
