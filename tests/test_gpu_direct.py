@@ -178,3 +178,63 @@ def test_a_target_below_the_floor_keeps_its_status():
         u, st = p.solve(check=False)
         assert p.last_status == sso.SSO_ENOTCONV and st["rel_residual"] < 1e-9
         assert _residual(p, u) < 1e-9
+
+
+def clique(n, seed=2):
+    """Members between every two of n nodes: one front, which no separator cuts."""
+    rng = np.random.default_rng(seed)
+    i, j = np.triu_indices(n, 1)
+    fixed = np.zeros((n, 6), np.uint8)
+    fixed[0] = 1
+    f = np.zeros((n, 6))
+    f[1:, 2] = -1e3
+    prop = np.tile([2.1e11, 8.1e10, 1e-3, 1e-6, 1e-6, 2e-6], (len(i), 1))
+    return meshgen.Mesh(xyz=rng.uniform(0.0, 3.0, (n, 3)), fixed=fixed, f_nodal=f,
+                        beam_nodes=np.stack([i, j], 1).astype(np.int32), beam_prop=prop,
+                        name="clique")
+
+
+# own DOFs 18 .. 132: up to, at and past the 16-column panels of a pivot block and its 64 columns
+@pytest.mark.parametrize("n", [3, 5, 8, 9, 10, 11, 13, 16, 19, 21, 22])
+def test_pivot_blocks_of_every_width(n):
+    """K of a clique is factored without a fallback and the residual target met in long double
+    (1 % for the sum of squares in 64 bits), at a right-hand side other than the load as well."""
+    import paper_2407_20026_amd as sso
+    print(f"[gpu] clique {n}", flush=True)
+    mesh = clique(n)
+    a = np.zeros((n, 6))
+    a[n // 2] = 1.0
+    with sso.Problem(mesh, sso.Options(rtol=1e-12)) as p:
+        u, st = p.solve()
+        assert st["solver"] == sso.SOLVER_AUTO and st["iters"] == 0
+        assert _residual(p, u) <= 1.01e-12
+        assert p.adjoint("linear", dg_du=a)["stats"]["iters"] == 0
+
+
+# 1, 15, 16, 17 and 33 elements: 16 lanes an element, 4 a wave and 16 a workgroup
+@pytest.mark.parametrize("mx,my", [(1, 1), (3, 5), (4, 4), (1, 17), (3, 11)])
+def test_shell_elements(mx, my):
+    """K and the adjoint's element terms against the oracle, for the same displacements.  An entry
+    of K is a sum over at most four elements of some 400 rounded terms, none above the largest
+    entry: 400 x 1.1e-16 x 4 < 2e-13.  A derivative has some 1000, of products of displacements
+    that exceed what the strains leave of them by up to 10^3: 1e-10 of the largest."""
+    import paper_2407_20026_amd as sso
+    from oracle import assembly, sensitivity
+    print(f"[gpu] elements {mx} x {my}", flush=True)
+    mesh = rect_shell(mx, my, 11)
+    rng = np.random.default_rng(1)
+    mesh.xyz = mesh.xyz + rng.normal(0.0, 0.03, mesh.xyz.shape)
+    mesh.quad_scale = rng.uniform(0.3, 1.0, mesh.n_quads)
+    K, f = assembly.assemble(mesh), assembly.load_vector(mesh)
+    ref = assembly.masked_system(mesh, K, f)[0].tocsr()
+    ref.sort_indices()
+    with sso.Problem(mesh, sso.Options(rtol=1e-10)) as p:
+        u, _ = p.solve()
+        g = p.adjoint("compliance")
+        vals, _ = p.matrix()
+    assert np.abs(vals.cpu().numpy() - ref.data).max() <= 2e-13 * np.abs(ref.data).max()
+    u = u.cpu().numpy().ravel()
+    gb, gq = sensitivity.element_terms(mesh, u, u, 1.0, 1.0)
+    for got, want in zip((g["dg_dxyz"], g["dg_dt"], g["dg_dscale"]),
+                         sensitivity.gather(mesh, gb, gq)):
+        assert np.abs(got.cpu().numpy() - want).max() <= 1e-10 * np.abs(want).max()
