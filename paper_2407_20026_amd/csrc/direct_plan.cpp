@@ -553,11 +553,13 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
     auto rows_of = [&](const DirectFront& D) { return gain && D.np > 1 ? D.np : D.nt; };
     // step 0: blocks of K with a column among the own nodes, bucketed by tile, first columns first
     assemble.clear();
-    int first_tiles = 0;
-    for (int i : by_level[h])
-      first_tiles += plan.fronts[i].np > 0 ? rows_of(plan.fronts[i]) : 0;
-    const int at_once =
-        std::min(DIRECT_FIRST_MOST, std::max(1, first_tiles / DIRECT_FIRST_ITEMS));
+    int at_once = 1;
+    for (; at_once < DIRECT_FIRST_MOST; ++at_once) {
+      int items = 0;
+      for (int i : by_level[h])
+        if (plan.fronts[i].np > 0) items += ceil_div(rows_of(plan.fronts[i]), at_once);
+      if (items <= DIRECT_FIRST_ITEMS) break;
+    }
     open(STEP_PANEL);
     for (int i : by_level[h]) {
       DirectFront& D = plan.fronts[i];

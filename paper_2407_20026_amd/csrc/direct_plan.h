@@ -108,10 +108,10 @@ enum { STEP_SCHUR = 0, STEP_FWD = 1, STEP_BWD = 2, STEP_GAIN = 3, STEP_PANEL = 4
 // gain step: four for each of the 256 CUs.  A level with 1740 (four fronts, 900 own DOFs) took 15 x
 // 60 us without it and 15 x 28 + 286 with it; one with 870 (two fronts) 15 x 32 and 15 x 25 + 178.
 constexpr int DIRECT_GAIN_TILES = 1024;
-// Row tiles of a scaling item of step 0: one, so that a front's tiles spread over the chip, or more
-// where the level has more than these for each workgroup the chip holds (each item sweeps the
-// pivot block for itself).
-constexpr int DIRECT_FIRST_ITEMS = 1024;
+// Row tiles of a scaling item of step 0: one, so that a front's tiles spread over the chip, or as
+// many, up to DIRECT_FIRST_MOST, as leave the level no more items than the chip holds at a time (each
+// inverts the pivot block for itself, 17 us before its first tile and 5 for each one more).
+constexpr int DIRECT_FIRST_ITEMS = 512;
 constexpr int DIRECT_FIRST_MOST = 8;
 
 struct DirectPlan {
