@@ -285,7 +285,8 @@ def stream_headline(args):
         "ms_per_step": 1000.0 * c.wall_s / n,
         "p50_ms": q.p50_ms,
         "p99_ms": q.p99_ms,
-        "dtype": {"auto": "f64, f32 inner PCG above the size crossover", "fp64": "f64",
+        "dtype": {"auto": "f64 (direct), f32 inner PCG where PCG solves above the size crossover",
+                  "fp64": "f64",
                   "mixed": "f32 inner PCG / f64 flexible CG"}[head],
         "config": {
             "workload": (f"served stream: {n} forward+adjoint requests (grid-shells n~U{{8..60}}, "
@@ -704,7 +705,7 @@ def main():
         out.update(value=run["solves_per_s"], dof_per_s=run["dof_per_s"],
                    ms_per_step=run["ms_per_step"], p50_ms=run["p50_ms"], p99_ms=run["p99_ms"],
                    dtype={"fp64": "f64", "mixed": "f32 inner PCG / f64 flexible CG",
-                          "auto": "f64, f32 inner PCG above the size crossover"}[args.precision],
+                          "auto": "f64 (direct), f32 inner PCG where PCG solves above the size crossover"}[args.precision],
                    config={"workload": desc, "n_dof": mesh.n_dof, "objective": args.objective,
                            "rtol": args.rtol, "precision": args.precision,
                            **{k: v for k, v in _public(run).items()
