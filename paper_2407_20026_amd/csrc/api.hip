@@ -380,7 +380,7 @@ void start_plan(SharedPattern* sh, const Mesh& m) {
       plan_cv.notify_all();
     });
     sh->builder_started = true;
-  } catch (const std::system_error&) {   // no thread to be had: the first solve builds it
+  } catch (...) {   // no thread to be had: the first solve builds it
   }
 }
 
@@ -670,15 +670,21 @@ int direct_tables(sso_problem* p, bool* ready) {
       *dst = d;
       return e;
     };
-    TRY_HIP(put(&t.fronts, pl.fronts));
-    TRY_HIP(put(&t.nodes, pl.nodes));
-    TRY_HIP(put(&t.maps, pl.maps));
-    TRY_HIP(put(&t.entries, pl.entries));
-    TRY_HIP(put(&t.tile_end, pl.tile_end));
-    TRY_HIP(put(&t.items, pl.items));
-    TRY_HIP(put(&t.steps, pl.steps));
-    TRY_HIP(put(&t.level_off, pl.level_off));
-    TRY_HIP(put(&t.level_np, pl.level_np));
+    hipError_t e = put(&t.fronts, pl.fronts);
+    if (e == hipSuccess) e = put(&t.nodes, pl.nodes);
+    if (e == hipSuccess) e = put(&t.maps, pl.maps);
+    if (e == hipSuccess) e = put(&t.entries, pl.entries);
+    if (e == hipSuccess) e = put(&t.tile_end, pl.tile_end);
+    if (e == hipSuccess) e = put(&t.items, pl.items);
+    if (e == hipSuccess) e = put(&t.steps, pl.steps);
+    if (e == hipSuccess) e = put(&t.level_off, pl.level_off);
+    if (e == hipSuccess) e = put(&t.level_np, pl.level_np);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      sh->direct_state = SharedPattern::DIRECT_REFUSED;   // PCG needs less
+      return SSO_OK;
+    }
+    TRY_HIP(e);
     if (!sh->uploaded)
       TRY_HIP(hipEventCreateWithFlags(&sh->uploaded, hipEventDisableTiming));
     TRY_HIP(hipEventRecord(sh->uploaded, s));
@@ -1345,7 +1351,7 @@ int sso_batch_create(hipStream_t stream, sso_batch** out) {
   return SSO_OK;
 }
 
-int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) {
+int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) try {
   if (!b || (n > 0 && !ps) || n < 0 || n_iter < 0 || b->pending) return SSO_EINVAL;
   for (int i = 0; i < n; ++i) {
     sso_problem* p = ps[i];
@@ -1434,9 +1440,11 @@ int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) {
   for (int i = 0; i < n; ++i) ps[i]->batch_pending = true;
   b->pending = true;
   return SSO_OK;
+} catch (...) {   // out of host memory for the lists
+  return SSO_ENOMEM;
 }
 
-int sso_batch_wait(sso_batch* b, sso_problem* const* ps, int n, int32_t* done) {
+int sso_batch_wait(sso_batch* b, sso_problem* const* ps, int n, int32_t* done) try {
   if (!b || !b->pending || n != (int)b->listed.size() || (n > 0 && !ps)) return SSO_EINVAL;
   for (int i = 0; i < n; ++i)
     if (ps[i] != b->listed[i]) return SSO_EINVAL;
@@ -1503,6 +1511,8 @@ int sso_batch_wait(sso_batch* b, sso_problem* const* ps, int n, int32_t* done) {
   if (done)
     for (int i = 0; i < n; ++i) done[i] = stopped(ps[i]) ? 1 : 0;
   return SSO_OK;
+} catch (...) {
+  return SSO_ENOMEM;
 }
 
 int sso_batch_iterate(sso_batch* b, sso_problem* const* ps, int n, int n_iter, int32_t* done) {
