@@ -6,8 +6,8 @@
 // values b a free row's load loses K(row, d) b[d] (lifting; u = b is written on d after the
 // solve), which keeps K symmetric positive definite and its pattern unchanged.
 //
-// Assembly is gather-based and deterministic: one thread per entry (slot, a, b) of a 6x6 block
-// sums the slot's element contributions in ascending contribution id (= ascending element, then
+// Assembly is gather-based and deterministic: a thread per two entries (slot, a, b) of a 6x6
+// block sums the slot's element contributions in ascending contribution id (= ascending element, then
 // ascending scalar index), with no atomics, so K is bitwise reproducible.  An entry below the
 // diagonal (block (I, J) with J < I, or a > b in a diagonal block) sums the contributions of its
 // transposed entry, (b, a) of block (J, I), in the same order: the element matrices are
@@ -21,31 +21,51 @@ namespace {
 inline unsigned nblk(int64_t n, int tpb) { return (unsigned)((n + tpb - 1) / tpb); }
 
 
-// K block values, row-major inside each 6x6 block, blocks in slot order.
-__global__ void k_assemble(Mesh m, int64_t n_blocks, const int32_t* bsrow, const int32_t* bcol,
-                           const int32_t* bseg, const int32_t* bperm, const int32_t* bsym,
-                           const double* coo, double* K) {
+// K block values, row-major inside each 6x6 block, blocks in slot order: entries (a, b) and (a,
+// b + 1), b even, a thread.  Contributions are taken four at a time, their loads in flight together
+// (an inner block's corner has one, two or four): a thread an entry and one contribution after the
+// other took 347 us for a 300 x 300 shell, 0.65 GB, and 16 for a 60 x 60 one, waiting for memory in
+// a chain of up to eleven loads; this takes 225 and 12 (two at a time 209 and 14).
+__global__ void __launch_bounds__(256)
+k_assemble(Mesh m, int64_t n_blocks, const int32_t* __restrict__ bsrow,
+           const int32_t* __restrict__ bcol, const int32_t* __restrict__ bseg,
+           const int32_t* __restrict__ bperm, const int32_t* __restrict__ bsym,
+           const double* __restrict__ coo, double* __restrict__ K) {
+  constexpr int AT_ONCE = 4;
   int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= 36 * n_blocks) return;
-  int64_t s = t / 36;
-  int a = (int)(t % 36) / 6, b = (int)(t % 6);
-  int I = bsrow[s], J = bcol[s];
-  double v;
-  if (m.fixed[6 * (int64_t)I + a] || m.fixed[6 * (int64_t)J + b]) {
-    v = (I == J && a == b) ? 1.0 : 0.0;
-  } else {
-    // the upper triangle's entry whose value this one takes: itself, or its transpose (in the
-    // value slot: block (J, I) for J < I, the slot itself otherwise)
-    const bool low = J < I || (J == I && a > b);
-    const int64_t su = bsym[2 * s + 1];
-    const int ra = low ? b : a, rb = low ? a : b;
-    v = 0.0;
-    for (int p = bseg[su]; p < bseg[su + 1]; ++p) {
-      BlockRef r = decode_block(bperm[p], m.n_beams);
-      v += coo[coo_index(r, ra, rb, m.n_beams)];
+  if (t >= 18 * n_blocks) return;
+  const int64_t s = t / 18;
+  const int q = (int)(t - 18 * s), a = q / 3, b = 2 * (q - 3 * a);
+  const int I = bsrow[s], J = bcol[s];
+  // the upper triangle's entries whose values these take: themselves, or their transposes (in the
+  // value slot: block (J, I) for J < I, the slot itself otherwise)
+  const int64_t su = bsym[2 * s + 1];
+  const int p0 = bseg[su], p1 = bseg[su + 1];
+  const bool fa = m.fixed[6 * (int64_t)I + a] != 0;
+  const bool f0 = fa || m.fixed[6 * (int64_t)J + b], f1 = fa || m.fixed[6 * (int64_t)J + b + 1];
+  const bool low0 = J < I || (J == I && a > b), low1 = J < I || (J == I && a > b + 1);
+  double v0 = 0.0, v1 = 0.0;
+  for (int p = p0; p < p1; p += AT_ONCE) {
+    int32_t c[AT_ONCE];
+    double x0[AT_ONCE], x1[AT_ONCE];
+#pragma unroll
+    for (int k = 0; k < AT_ONCE; ++k) c[k] = bperm[p + k < p1 ? p + k : p1 - 1];
+#pragma unroll
+    for (int k = 0; k < AT_ONCE; ++k) {
+      const BlockRef r = decode_block(c[k], m.n_beams);
+      x0[k] = coo[low0 ? coo_index(r, b, a, m.n_beams) : coo_index(r, a, b, m.n_beams)];
+      x1[k] = coo[low1 ? coo_index(r, b + 1, a, m.n_beams) : coo_index(r, a, b + 1, m.n_beams)];
     }
+#pragma unroll
+    for (int k = 0; k < AT_ONCE; ++k)
+      if (p + k < p1) {
+        v0 += x0[k];
+        v1 += x1[k];
+      }
   }
-  K[t] = v;
+  if (f0) v0 = (I == J && a == b) ? 1.0 : 0.0;
+  if (f1) v1 = (I == J && a == b + 1) ? 1.0 : 0.0;
+  *reinterpret_cast<double2*>(K + 36 * s + 6 * a + b) = double2{v0, v1};
 }
 
 // f = f_nodal + sum over incident quads (ascending element) of -(gamma t + q) A / 4 on uz,
@@ -176,7 +196,7 @@ __global__ void k_scalar_values(int n_nodes, const int32_t* brow_ptr, const doub
 
 hipError_t launch_assemble(const Mesh& m, const Pattern& pat, const double* coo, double* K,
                            hipStream_t s) {
-  hipLaunchKernelGGL(k_assemble, dim3(nblk(36 * pat.n_blocks, 256)), dim3(256), 0, s, m,
+  hipLaunchKernelGGL(k_assemble, dim3(nblk(18 * pat.n_blocks, 256)), dim3(256), 0, s, m,
                      pat.n_blocks, pat.bsrow, pat.bcol, pat.bseg, pat.bperm, pat.bsym, coo,
                      K);
   return hipGetLastError();
