@@ -152,7 +152,33 @@ __device__ __forceinline__ void mma_tile(const double* A, int lda, const double*
 }
 
 // acc += A B^T, both row-major in memory, over kn columns: the next KC columns are on their way
-// while the matrix cores work on the ones in LDS (as, bs: NB x LDK each).
+// while the matrix cores work on the ones in LDS (as, bs: NB x LDK each).  From column split on, a
+// multiple of KC, A and B are rows of NB in A2 and B2.
+__device__ __forceinline__ void product(const double* __restrict__ A, int64_t lda, int ra,
+                                        const double* __restrict__ B, int64_t ldb, int rb, int kn,
+                                        double* as, double* bs, d4 acc[2][2], int split,
+                                        const double* __restrict__ A2,
+                                        const double* __restrict__ B2) {
+  TileLoad ta, tb;
+  for (int k0 = 0; k0 < kn; k0 += KC) {
+    auto fetch = [&](int k) {
+      const bool second = k >= split;
+      const int64_t la = second ? NB : lda, lb = second ? NB : ldb;
+      ta.load(second ? A2 - split : A, la, ra, k, kn);
+      tb.load(second ? B2 - split : B, lb, rb, k, kn);
+    };
+    if (k0)
+      __syncthreads();
+    else
+      fetch(0);
+    ta.store(as);
+    tb.store(bs);
+    __syncthreads();
+    if (k0 + KC < kn) fetch(k0 + KC);
+    mma_tile(as, LDK, bs, LDK, kn - k0 < KC ? kn - k0 : KC, acc);
+  }
+}
+
 __device__ __forceinline__ void product(const double* __restrict__ A, int64_t lda, int ra,
                                         const double* __restrict__ B, int64_t ldb, int rb, int kn,
                                         double* as, double* bs, d4 acc[2][2]) {
@@ -366,9 +392,13 @@ constexpr int POOL = 3 * NB * LDK;    // doubles of LDS that the panel kernels c
 static_assert(NB * LDN + NB * LDK <= POOL, "the inverse and a tile of the row tile fit");
 static_assert(SWEEP_LDS <= POOL, "the sweep's panel fits");
 
-// The scaled panel of step q: q even and odd alternate.
+// The scaled panel of step q: q even and odd alternate.  After both, the last panel's columns
+// before they are scaled, boundary tiles only.
 __device__ __forceinline__ double* scaled(const DirectArgs& a, const DirectFront& F, int q, int i) {
   return a.w + F.w_off + ((int64_t)(q & 1) * F.nt + i) * NB * NB;
+}
+__device__ __forceinline__ double* unscaled(const DirectArgs& a, const DirectFront& F, int i) {
+  return a.w + F.w_off + (2 * (int64_t)F.nt + i - F.np) * NB * NB;
 }
 
 // Sets the flag where a pivot of the nb from own DOF j0 on is too small.
@@ -444,6 +474,12 @@ __device__ __forceinline__ void scale_tile(const DirectArgs& a, const DirectFron
       d[u][w] -= ud[u][w];
       if (row) f[u][w] -= uf[u][w];
     }
+  if (q == F.np - 1 && i >= F.np) {     // for the Schur step
+    double* X = unscaled(a, F, i);
+    each_acc(f, [&](int r, int c, double v) {
+      if (r < R.n && c < nb) X[r * NB + c] = v;
+    });
+  }
   __syncthreads();     // the pool is free
   sweep(d, nb, pool, pivots);
   double* out = scaled(a, F, q, i);
@@ -826,15 +862,24 @@ k_front_gain(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int 
   });
 }
 
-// Tile (i, j), j <= i, of a front's Schur complement: the children's minus G F_BS^T.
+// Tile (i, j), j <= i, of a front's Schur complement: the children's minus G F_BS^T.  With several
+// panels and no gain step that product is the sum over the panels but the last of G before it times
+// F_BS, plus the last panel's scaled columns times what they were before (both are G F_BS^T), so
+// that the columns' update with the last panel is other items of the same launch: one of 9 us less
+// a level.
 __global__ void __launch_bounds__(TPB)
 k_front_schur(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
-  __shared__ double as[NB * LDK];
-  __shared__ double bs[NB * LDK];
+  __shared__ double pool[2 * NB * LDK];
+  double* as = pool;
+  double* bs = pool + NB * LDK;
   __shared__ int mr[2][NB], mc[2][NB];     // 6 * position in the child's boundary, or -1
   DirectItem it;
   if (!take_item(a, probs, first, level, STEP_SCHUR, it)) return;
   const DirectFront F = a.fronts[it.front];
+  if (it.e0) {
+    update_tile(a, F, F.np - 1, it.i, it.j, pool);
+    return;
+  }
   const int ns = F.ns6 / 6, cnt = ns + F.nb6 / 6;
   const int r0 = it.i * NB, c0 = it.j * NB;
   const int nr = F.nb6 - r0 < NB ? F.nb6 - r0 : NB, nc = F.nb6 - c0 < NB ? F.nb6 - c0 : NB;
@@ -851,7 +896,11 @@ k_front_schur(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int
     else
       mr[k][q] = m;
   }
-  const double* __restrict__ G = a.fact + F.fact_off + (int64_t)(F.ns6 + r0) * F.ns6;
+  // without a gain step the boundary rows as they are before the last panel, that panel apart
+  const bool before = F.np > 1 && !F.gain;
+  const int split = before ? (F.np - 1) * NB : F.ns6;
+  const double* __restrict__ G =
+      (before ? sweep_src(a, F, F.np - 1) : a.fact + F.fact_off) + (int64_t)(F.ns6 + r0) * F.ns6;
   const double* __restrict__ B = a.f0 + F.work_off + (int64_t)(F.ns6 + c0) * F.ns6;
   const ChildU u0{a.u + F.child_u[0]}, u1{a.u + F.child_u[1]};
   d4 acc[2][2], sum[2][2];
@@ -871,7 +920,11 @@ k_front_schur(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int
           sum[u][w][v] = u0.at(mr[0][r], mc[0][c]) + u1.at(mr[1][r], mc[1][c]);
         }
   }
-  product(G, F.ns6, nr, B, F.ns6, nc, F.ns6, as, bs, acc);
+  if (before)
+    product(G, F.ns6, nr, B, F.ns6, nc, F.ns6, as, bs, acc, split,
+            scaled(a, F, F.np - 1, F.np + it.i), unscaled(a, F, F.np + it.j));
+  else
+    product(G, F.ns6, nr, B, F.ns6, nc, F.ns6, as, bs, acc);
   double* __restrict__ U = a.u + F.u_off;
 #pragma unroll
   for (int u = 0; u < 2; ++u)

@@ -494,7 +494,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       D.w_off = w;
       if (D.np > 1) {
         again += even((int64_t)(D.ns6 + D.nb6) * D.ns6);
-        w += 2 * (int64_t)DIRECT_NB * DIRECT_NB * D.nt;
+        w += (int64_t)DIRECT_NB * DIRECT_NB * (3 * D.nt - D.np);
       }
       for (int c = 0; c < 2; ++c)
         D.child_u[c] = D.child[c] < 0 ? 0 : plan.fronts[D.child[c]].u_off;
@@ -550,7 +550,8 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
         bnd_tiles += (plan.fronts[i].nt - plan.fronts[i].np) * plan.fronts[i].np;
     const bool gain = bnd_tiles >= DIRECT_GAIN_TILES;
     // row tiles of a front that its panel steps take
-    auto rows_of = [&](const DirectFront& D) { return gain && D.np > 1 ? D.np : D.nt; };
+    for (int i : by_level[h]) plan.fronts[i].gain = gain && plan.fronts[i].np > 1;
+    auto rows_of = [&](const DirectFront& D) { return D.gain ? D.np : D.nt; };
     // step 0: blocks of K with a column among the own nodes, bucketed by tile, first columns first
     assemble.clear();
     int at_once = 1;
@@ -625,7 +626,8 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
       const int updates = (int)plan.items.size();
       for (int i : by_level[h]) {
         const DirectFront& D = plan.fronts[i];
-        if (q > D.np || D.np == 1) continue;   // a single panel is done once scaled
+        // a single panel is done once scaled, the last one's update goes with the Schur step
+        if (q > D.np || D.np == 1 || (q == D.np && !gain)) continue;
         for (int r = 0; r < rows_of(D); ++r)
           for (int c = 0; c < D.np; ++c) plan.items.push_back({i, r, c, 0, 0});
       }
@@ -647,6 +649,13 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
         for (int b = 0; b <= a; ++b) plan.items.push_back({i, a, b, 0, 0});
     }
     spread(STEP_SCHUR, st[STEP_SCHUR].off);
+    const int last = (int)plan.items.size();
+    for (int i : by_level[h]) {
+      const DirectFront& D = plan.fronts[i];
+      for (int r = 0; !gain && D.np > 1 && r < D.nt; ++r)
+        for (int c = 0; c < D.np; ++c) plan.items.push_back({i, r, c, 1, 0});
+    }
+    spread(STEP_SCHUR, last);
     close(STEP_SCHUR);
     open(STEP_FWD);
     int passes = 0;
@@ -734,18 +743,20 @@ int check_direct_plan(int n, const int32_t* rp, const int32_t* col, const Direct
         D.u_off + direct_tri(D.nb6) > plan.u_len || D.v_off + D.nb6 > plan.v_len ||
         D.b_off + D.ns6 > 6 * (int64_t)n ||
         (D.np > 1 && (D.again_off + panel > plan.again_len ||
-                      D.w_off + 2 * (int64_t)DIRECT_NB * DIRECT_NB * D.nt > plan.w_len)))
+                      D.w_off + (int64_t)DIRECT_NB * DIRECT_NB * (3 * D.nt - D.np) > plan.w_len)))
       return fail(7, "array too short", (long long)f);
   }
-  // a front's boundary tiles are formed by the last panel step or by the gain step
+  // a front's boundary tiles are formed by the gain step or by the update with the last panel
   std::vector<int> formed(plan.fronts.size(), 0);
   for (int h = 0; h < plan.levels(); ++h)
-    for (int q = STEP_GAIN; q <= STEP_PANEL + plan.level_np[h]; ++q) {
+    for (int q = STEP_SCHUR; q <= STEP_PANEL + plan.level_np[h]; ++q) {
       const DirectRange st = plan.steps[plan.level_off[h] + q];
       for (int k = 0; k < st.cnt; ++k) {
         const DirectItem& it = plan.items[st.off + k];
         const DirectFront& D = plan.fronts[it.front];
-        if (q == STEP_GAIN || (q - STEP_PANEL == D.np && it.j >= 0 && it.i >= D.np))
+        if (q == STEP_GAIN ? it.i >= D.np
+                           : it.i >= D.np && it.j >= 0 &&
+                                 (q == STEP_SCHUR ? it.e0 == 1 : q - STEP_PANEL == D.np))
           ++formed[it.front];
       }
     }

@@ -39,10 +39,13 @@ struct DirectFront {
   int32_t level;             // height: every child has a lower level
   int32_t tile_off;          // its row tiles' ends in tile_end
   int32_t e0, e1;            // entries of its first tile
+  int32_t gain;              // its boundary rows are formed by the level's gain step
+  int32_t pad;
   int64_t fact_off;          // factor [(ns6 + nb6) x ns6]
   int64_t work_off;          // assembled columns of the level, same shape
   int64_t again_off;         // np > 1: second work panel of the level, same shape
-  int64_t w_off;             // np > 1: scaled panels of two steps, DIRECT_NB x DIRECT_NB row tiles
+  int64_t w_off;             // np > 1: scaled panels of two steps, DIRECT_NB x DIRECT_NB row tiles,
+                             //   and the last one's boundary tiles before they are scaled
   int64_t child_u[2];        // the children's u_off, 0 without a child
   int64_t u_off;             // Schur complement, lower triangle row by row (direct_tri)
   int64_t v_off;             // update vector of the forward substitution [nb6]
@@ -76,7 +79,8 @@ inline DirectRows direct_rows(const DirectFront& F, int i) {
 }
 
 // A work item: the front and up to two tile indices; K's entries [e0, e1) of tile (i, max(j, 0))
-// in the first panel step; boundary rows [i, e0) in the forward substitution.
+// in the first panel step; boundary rows [i, e0) in the forward substitution; e0 = 1 in the Schur
+// step: tile (i, j) is updated with the last panel instead.
 struct DirectItem {
   int32_t front, i, j, e0, e1;
 };
@@ -101,8 +105,10 @@ constexpr int DIRECT_XCDS = 8;
 // 0 .. np: step q scales panel q (items with j < 0: row tile i) and updates with panel q - 1 (tile
 // i, j).  Step 0 assembles as well, tiles on the diagonal and below it (those above it are their
 // transposes): its items with j < 0 the first column of tiles, -j row tiles from i on; the others
-// tile (i, j).  On a level with a gain step the panel steps take the own rows only, the first one's
-// boundary tiles being assembled like the others, and the gain step forms the boundary rows G.
+// tile (i, j).  The update with the last panel goes with the Schur step, which does not wait for
+// it.  On a level with a gain step, which does, it is panel step np, and
+// the panel steps take the own rows only, the first one's boundary tiles being assembled like the
+// others, and the gain step forms the boundary rows G.
 enum { STEP_SCHUR = 0, STEP_FWD = 1, STEP_BWD = 2, STEP_GAIN = 3, STEP_PANEL = 4 };
 // Boundary tiles that a panel step would update, from which on a level with several panels takes the
 // gain step: four for each of the 256 CUs.  A level with 1740 (four fronts, 900 own DOFs) took 15 x
