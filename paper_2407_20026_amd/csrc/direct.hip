@@ -17,10 +17,10 @@
 // after which the own rows hold -W and the boundary rows G.  A level's panels are a chain of
 // launches: launch q scales panel q (F_IJ D^-1 into a buffer of its own) and updates all columns
 // with panel q - 1; what the scaling needs of that update it forms itself, one more product of
-// tiles, so that a panel costs one launch instead of two.  Sweeps alternate between two copies of
-// the columns and of the scaled panel, so no work item reads what another one of the same launch
-// writes.  The products run on the matrix cores
-// (v_mfma_f64_16x16x4_f64) from LDS tiles.  All fronts of one level share the launches; the items
+// tiles, so that a panel costs one launch instead of two.  The first launch assembles the columns,
+// the last update goes with the Schur complements.  Sweeps alternate between two copies of the
+// columns and of the scaled panel, so no work item reads what another one of the same launch
+// writes.  The products run on the matrix cores (v_mfma_f64_16x16x4_f64) from LDS tiles.  All fronts of one level share the launches; the items
 // of a launch come from the plan, so a front's arithmetic does not depend on what else is in the
 // launch.  No atomics: every entry has one writer and a fixed order of additions.
 #include <cmath>
@@ -557,6 +557,11 @@ __device__ __forceinline__ void update_tile(const DirectArgs& a, const DirectFro
 }
 
 // Step q > 0 of a level's panels: panel q scaled, all columns updated with panel q - 1.
+//
+// Bound by the scaling's chain, 22 us: 2 for its loads, 4 in the two products that bring the pivot
+// block and the row tile up to date (one CU, 74 cycles a matrix instruction), 8.3 in the pivot block's
+// inversion, 2.7 in the scaling product, the launch.  With the inversion a column at a time it took
+// 33; as two launches, one for the scaling, 10 more.
 __global__ void __launch_bounds__(TPB, 2)
 k_front_panel(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level, int q) {
   __shared__ __align__(16) double pool[POOL];
@@ -757,8 +762,13 @@ __device__ __forceinline__ void assemble(const DirectArgs& a, const DirectFront&
 // Step 0 of a level's panels.  Items with j >= 0 assemble tile (i, j) of the front's columns.  The
 // others assemble the first column of tiles, -j row tiles from i on, and scale panel 0: the pivot
 // block, which each item assembles and inverts for itself, and F_I0 D^-1; the only panel of a front
-// goes straight into the factor.  The kernel must not use scratch memory: with 400 bytes of it a
-// launch took 10 us longer.
+// goes straight into the factor.
+//
+// 21 to 25 us on a level with few fronts: 9 in the assembly (four dependent loads, then up to 128 KB
+// of the children's values through one CU), 8.3 in the inversion, 2.7 in the product.  A launch that
+// assembled into memory and one that read it back took 26 to 28, and on a 300 x 300 shell's levels
+// 3.0 ms against 1.6.  The kernel must not use scratch memory: with 400 bytes of it a launch took 10
+// us longer.
 __global__ void __launch_bounds__(TPB, 2)
 k_front_first(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
   __shared__ __align__(16) double T0[NB * LDN];
@@ -867,6 +877,9 @@ k_front_gain(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int 
 // F_BS, plus the last panel's scaled columns times what they were before (both are G F_BS^T), so
 // that the columns' update with the last panel is other items of the same launch: one of 9 us less
 // a level.
+//
+// 12 to 15 us on a level with few fronts; 50 TFLOP/s on wide fronts (1806 boundary and 900 own DOFs),
+// half of that on a 300 x 300 shell's lower levels, bound by the latency of their short products.
 __global__ void __launch_bounds__(TPB)
 k_front_schur(DirectArgs a, const DirectArgs* __restrict__ probs, int first, int level) {
   __shared__ double pool[2 * NB * LDK];

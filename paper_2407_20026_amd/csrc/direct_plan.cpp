@@ -25,7 +25,9 @@
 namespace sso {
 namespace {
 
-// Parts of at most this many nodes are eliminated whole.
+// Parts of at most this many nodes are eliminated whole: 60 own DOFs, one panel.  8 took 2.0 ms
+// instead of 2.2 on a 120 x 120 shell, but 0.43 instead of 0.40 on a 16 x 16 one and 11.0 instead of
+// 10.8 on a 300 x 300 one; 14 fill more than direct_max_bytes allows small structures.
 constexpr int LEAF_NODES = 10;
 // Parts of fewer nodes keep the coordinates of the part they were cut from.
 constexpr int LANDMARK_NODES = 120;
