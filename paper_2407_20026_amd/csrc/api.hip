@@ -783,6 +783,7 @@ int run_direct(sso_problem* p, const double* b, double* x, bool* done, const Tai
   const DirectArgs& a = p->da;
   const int64_t n = 6 * (int64_t)p->m.n_nodes;
   *done = false;
+  if (!a.fact) return SSO_EHIP;   // not attached: no launch may see these arguments
   if (!p->factored) {
     TRY_HIP(launch_direct_clear(a, s));
     TRY_HIP(launch_direct_factor(pl, a, s));
@@ -832,6 +833,7 @@ int mixed_operands(sso_problem* p) {
   const int64_t nk = 36 * p->pat.n_blocks;
   if (!p->Dinv32) TRY_HIP(dev_alloc(&p->Dinv32, dinv_packed_len(p->m.n_nodes), s));
   if (!p->K32) TRY_HIP(dev_alloc(&p->K32, nk, s));
+  TRY_HIP(pcg_alloc_mixed(p->w, s));
   TRY_HIP(launch_block_jacobi(p->m, p->pat, p->K, p->Dinv, p->Dinv32, p->d_err, s));
   TRY_HIP(launch_convert_f32(p->K, p->K32, nk, s));
   return SSO_OK;
@@ -1288,13 +1290,20 @@ int sso_solve_end(sso_problem* p, double* u_out, sso_stats* stats) {
   auto residual = [&] {   // into h_scal, once the stream gets there
     return launch_true_residual(p->m, p->pat, p->K, p->u, p->f, nullptr, p->w, p->h_scal, s);
   };
-  if (p->direct) {
+  if (p->direct && p->direct_steps == 0) {
+    // ended before a launch took it: u = 0, no factor, and perhaps no arrays to hold one; an
+    // adjoint is solved by PCG, with its operands made here (some of those calls allocate nothing)
+    p->direct = false;
+    if (mixed(p)) {
+      const int st = mixed_operands(p);
+      if (st != SSO_OK) return st;
+    }
+    TRY_HIP(hipMemsetAsync(p->u, 0, sizeof(double) * 6 * (size_t)p->m.n_nodes, s));
+    status = SSO_ENOTCONV;
+    TRY_HIP(residual());
+  } else if (p->direct) {
     if (mixed(p)) outer = p->direct_steps;
-    if (p->direct_steps == 0) {            // ended before it was launched
-      TRY_HIP(hipMemsetAsync(p->u, 0, sizeof(double) * 6 * (size_t)p->m.n_nodes, s));
-      status = SSO_ENOTCONV;
-      TRY_HIP(residual());
-    } else if (!p->direct_done) {
+    if (!p->direct_done) {
       status = SSO_ENOTCONV;
       TRY_HIP(residual());
     } else if (!(std::sqrt(p->direct_rr) <= p->opt.rtol * std::sqrt(p->direct_bb))) {

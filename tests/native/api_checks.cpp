@@ -1,0 +1,198 @@
+// Checks of the C ABI's host code on the CPU (tests/test_native_api.py builds and runs them): which
+// launches and copies the library issues, with which addresses, over a HIP runtime of the check's
+// own (fake_hip.h).  Kernels do nothing; what the host reads back -- residuals, states of the
+// iterations -- is what the check says.  The structures have nodes and no elements: K has no blocks.
+#include "fake_hip.h"
+
+#include "hipsso.h"
+#include "sso_internal.h"
+
+using namespace sso;
+
+static int failures = 0;
+#define CHECK(c)                                                       \
+  do {                                                                 \
+    if (!(c)) {                                                        \
+      std::printf("FAIL %s:%d: %s\n", __FILE__, __LINE__, #c);         \
+      ++failures;                                                      \
+    }                                                                  \
+  } while (0)
+
+static bool is(const std::string& name, const char* kernel) {
+  return name.find(kernel) != std::string::npos;
+}
+static int launches(const char* kernel) {
+  int n = 0;
+  for (const auto& k : fake::state().launches)
+    if (is(k.first, kernel)) n += k.second;
+  return n;
+}
+
+// What the GPU would do, as far as the host sees it.
+struct Script {
+  std::vector<double> rr;      // ||r||^2 of the true residuals in turn, ||b||^2 being 1; then 0
+  size_t next = 0;
+  bool singular = false;       // factorisations find a pivot that is too small
+  double residual() { return next < rr.size() ? rr[next++] : 0.0; }
+} script;
+
+static void finish_state(PcgState* st) {
+  st->it = 5;
+  st->done = 1;
+  st->status = SSO_OK;
+}
+
+static void kernel(const fake::Launch& l) {
+  if (is(l.name, "k_direct_clear") || is(l.name, "k_front_")) {
+    const DirectArgs* probs = l.arg<const DirectArgs*>(1);
+    const int n = !probs ? 1 : is(l.name, "k_direct_clear") ? l.arg<int>(2) : (int)l.grid.y;
+    for (int i = 0; i < n; ++i) {
+      const DirectArgs a = probs ? probs[i] : l.arg<DirectArgs>(0);
+      bool ok = fake::valid(a.flag, sizeof *a.flag, l.stream, "the direct solver's flag");
+      if (is(l.name, "k_front_")) {
+        for (const void* p : {(const void*)a.fronts, (const void*)a.nodes, (const void*)a.items,
+                              (const void*)a.fact, (const void*)a.K})
+          ok = fake::valid(p, 8, l.stream, l.name.c_str()) && ok;
+        if (is(l.name, "forward") || is(l.name, "backward"))
+          for (const void* p : {(const void*)a.rhs, (const void*)a.sol, (const void*)a.b})
+            ok = fake::valid(p, 8, l.stream, l.name.c_str()) && ok;
+      }
+      if (ok) *a.flag = is(l.name, "k_front_first") && script.singular ? 1u : is(l.name, "clear") ? 0u : *a.flag;
+    }
+  } else if (is(l.name, "k_finish_many")) {
+    const ResidualJob* jobs = l.arg<const ResidualJob*>(0);
+    double* out = l.arg<double*>(1);
+    for (unsigned i = 0; i < l.grid.x; ++i) {
+      out[3 * i] = script.residual();
+      out[3 * i + 1] = 1.0;
+      out[3 * i + 2] = *jobs[i].flag ? 1.0 : 0.0;
+    }
+  } else if (is(l.name, "k_finish") && l.arg<int>(2) == 2) {
+    double* out = l.arg<double*>(3);
+    out[0] = script.residual();
+    out[1] = 1.0;
+    if (const unsigned* w = l.arg<const unsigned*>(4)) out[2] = *w;
+    if (const unsigned* w = l.arg<const unsigned*>(5)) out[3] = *w;
+  } else if (is(l.name, "k_pcg_init")) {
+    const PcgDesc<double>* d = l.arg<const PcgDesc<double>*>(0);
+    if (fake::valid(d, sizeof *d, l.stream, "descriptor")) *d->st = PcgState();
+  } else if (is(l.name, "k_update_single")) {
+    finish_state(l.arg<PcgState*>(7));
+  } else if (is(l.name, "k_pcg_wg")) {
+    const PcgDesc<double>* d = l.arg<const PcgDesc<double>*>(0);
+    for (unsigned i = 0; i < l.grid.x; ++i)
+      if (fake::valid(d[i].st, sizeof(PcgState), l.stream, "state")) finish_state(d[i].st);
+  } else if (is(l.name, "k_gather_states")) {
+    PcgState* const* st = l.arg<PcgState* const*>(0);
+    PcgState* out = l.arg<PcgState*>(2);
+    for (int i = 0; i < l.arg<int>(1); ++i)
+      if (fake::valid(st[i], sizeof(PcgState), l.stream, "state")) {
+        finish_state(st[i]);
+        out[i] = *st[i];
+      }
+  }
+}
+
+// Device arrays of the check.
+template <class T>
+static T* device(int64_t n) {
+  T* p = nullptr;
+  hipMallocFromPoolAsync(reinterpret_cast<void**>(&p), sizeof(T) * (size_t)n,
+                         reinterpret_cast<hipMemPool_t>((size_t)fake::state().device + 1), nullptr);
+  return p;
+}
+
+struct Structure {
+  int n;
+  sso_mesh m{};
+  double *load, *grad, *u;
+  explicit Structure(int nodes, bool prescribed = false) : n(nodes) {
+    m.n_nodes = n;
+    m.xyz = device<double>(3 * n);
+    m.fixed = device<uint8_t>(6 * n);
+    m.f_nodal = device<double>(6 * n);
+    if (prescribed) m.u_prescribed = device<double>(6 * n);
+    load = device<double>(6 * n);
+    grad = device<double>(3 * n);
+    u = device<double>(6 * n);
+  }
+};
+
+static sso_options options(int solver = SSO_SOLVER_AUTO, int precision = SSO_PREC_FP64) {
+  sso_options o{};
+  o.precision = precision;
+  o.rtol = 1e-8;
+  o.max_it = 1000;
+  o.refine_steps = 20;
+  o.solver = solver;
+  return o;
+}
+
+static sso_problem* create(const Structure& s, const sso_options& o, hipStream_t stream = nullptr) {
+  sso_problem* p = nullptr;
+  CHECK(sso_problem_create(&s.m, &o, stream, &p) == SSO_OK && p);
+  return p;
+}
+
+static void begin_check() {
+  script = Script();
+  fake::state().launches.clear();
+  fake::state().fail = nullptr;
+  fake::state().limit.clear();
+  fake::state().device = 0;
+}
+
+// ---- the checks ----------------------------------------------------------------------------
+
+// A begun solve that ends before any launch took it has displacements of 0 and no factor: what
+// follows it solves by PCG, and never with arrays that were not allocated.
+static void ended_before_a_launch() {
+  for (int precision : {SSO_PREC_FP64, SSO_PREC_MIXED})
+    for (int nodes : {20, 400})
+      for (bool prescribed : {false, true})
+        for (bool listed : {false, true}) {
+          begin_check();
+          Structure s(nodes, prescribed);
+          sso_problem* p = create(s, options(SSO_SOLVER_AUTO, precision));
+          CHECK(sso_solve_begin(p) == SSO_OK);
+          if (listed) {        // in a call that asks for no iterations
+            sso_batch* b = nullptr;
+            int32_t done = 1;
+            CHECK(sso_batch_create(nullptr, &b) == SSO_OK);
+            CHECK(sso_batch_iterate(b, &p, 1, 0, &done) == SSO_OK && done == 0);
+            sso_batch_destroy(b);
+          }
+          sso_stats st;
+          CHECK(sso_solve_end(p, s.u, &st) == SSO_ENOTCONV);
+          CHECK(sso_adjoint(p, SSO_OBJ_LINEAR, s.load, s.grad, nullptr, nullptr, &st) == SSO_OK);
+          CHECK(sso_adjoint(p, SSO_OBJ_USER, s.load, s.grad, nullptr, nullptr, &st) == SSO_OK);
+          CHECK(sso_adjoint(p, SSO_OBJ_COMPLIANCE, nullptr, s.grad, nullptr, nullptr, &st) == SSO_OK);
+          double out[3];
+          CHECK(sso_size_objective(p, 1.0, 1.0, 0.1, out, s.grad, nullptr, &st) == SSO_OK);
+          int64_t before = 0, after = 0;
+          CHECK(sso_problem_bytes(p, &before) == SSO_OK);
+          const int taken = fake::state().allocations[0];
+          CHECK(sso_size_objective_noalloc(p, 1.0, 1.0, 0.1, out, s.grad, nullptr, &st) == SSO_OK);
+          CHECK(sso_problem_bytes(p, &after) == SSO_OK && after == before &&
+                taken == fake::state().allocations[0]);
+          CHECK(launches("k_front_") == 0);
+          // and a solve of its own is direct as ever
+          CHECK(sso_solve(p, s.u, &st) == SSO_OK && st.solver == SSO_SOLVER_AUTO);
+          CHECK(launches("k_front_first") > 0);
+          sso_problem_destroy(p);
+        }
+}
+
+int main(int argc, char** argv) {
+  fake::state().kernel = kernel;
+  const std::map<std::string, void (*)()> checks = {
+      {"ended_before_a_launch", ended_before_a_launch},
+  };
+  for (const auto& c : checks)
+    if (argc < 2 || c.first == argv[1]) c.second();
+  CHECK(argc < 2 || checks.count(argv[1]));
+  CHECK(fake::state().faults == 0);
+  std::printf("%s (%d failures)\n", failures ? "failed" : "ok", failures);
+  std::fflush(stdout);
+  std::_Exit(failures ? 1 : 0);
+}
