@@ -938,8 +938,8 @@ int prepare(sso_problem* p, bool batch) {
 int begin_pcg(sso_problem* p) {
   hipStream_t s = p->s;
   if (mixed(p))
-    TRY_HIP(mixed_begin(p->m, p->pat, p->K, p->K32, p->Dinv32, p->B32, p->f, p->u,
-                        mixed_params(p), p->w, s, p->ms));
+    TRY_HIP(mixed_begin(p->m, p->pat, p->K, p->K32, p->Dinv32, fused(p) ? p->B32 : nullptr, p->f,
+                        p->u, mixed_params(p), p->w, s, p->ms));
   else if (fused(p))
     TRY_HIP(fused_begin(p->m, p->pat, p->B, p->Dinv, p->f, p->u, p->opt.rtol, p->opt.max_it,
                         p->w, s, &p->fdesc));
@@ -1514,8 +1514,8 @@ int sso_batch_wait(sso_batch* b, sso_problem* const* ps, int n, int32_t* done) t
   for (const std::vector<int>* v : {&b->idx[2], &b->idx[3]})
     for (int i : *v) {
       sso_problem* p = ps[i];
-      TRY_HIP(mixed_step(p->m, p->pat, p->K, p->K32, p->Dinv32, p->B32, p->f, p->u,
-                         mixed_params(p), p->w, p->s, p->ms));
+      TRY_HIP(mixed_step(p->m, p->pat, p->K, p->K32, p->Dinv32, fused(p) ? p->B32 : nullptr, p->f,
+                         p->u, mixed_params(p), p->w, p->s, p->ms));
     }
   if (done)
     for (int i = 0; i < n; ++i) done[i] = stopped(ps[i]) ? 1 : 0;

@@ -183,10 +183,39 @@ static void ended_before_a_launch() {
         }
 }
 
+// A begun mixed-precision solve runs the recurrences that its options name, whatever the problem ran
+// before.
+static void mixed_recurrences_named_anew() {
+  for (int second : {SSO_SOLVER_STANDARD, SSO_SOLVER_FUSED}) {
+    begin_check();
+    Structure s(400);
+    sso_options o = options(SSO_SOLVER_FUSED, SSO_PREC_MIXED);
+    o.max_it = 8;
+    o.refine_steps = 1;
+    sso_problem* p = create(s, o);
+    script.rr = {1.0, 1.0};            // of x = 0, and of the outer step's direction
+    CHECK(sso_solve(p, s.u, nullptr) == SSO_ENOTCONV);
+    o.solver = second;
+    CHECK(sso_set_options(p, &o) == SSO_OK);
+    script = Script();
+    script.rr = {1.0, 1.0};
+    CHECK(sso_solve_begin(p) == SSO_OK);
+    sso_batch* b = nullptr;
+    int32_t done = 0;
+    CHECK(sso_batch_create(nullptr, &b) == SSO_OK);
+    CHECK(sso_batch_iterate(b, &p, 1, 4, &done) == SSO_OK && done == 1);
+    sso_stats st;
+    CHECK(sso_solve_end(p, s.u, &st) == SSO_ENOTCONV && st.solver == second);
+    sso_batch_destroy(b);
+    sso_problem_destroy(p);
+  }
+}
+
 int main(int argc, char** argv) {
   fake::state().kernel = kernel;
   const std::map<std::string, void (*)()> checks = {
       {"ended_before_a_launch", ended_before_a_launch},
+      {"mixed_recurrences_named_anew", mixed_recurrences_named_anew},
   };
   for (const auto& c : checks)
     if (argc < 2 || c.first == argv[1]) c.second();

@@ -30,7 +30,7 @@ def program():
     return OUT
 
 
-@pytest.mark.parametrize("check", ["ended_before_a_launch"])
+@pytest.mark.parametrize("check", ["ended_before_a_launch", "mixed_recurrences_named_anew"])
 def test_host_code(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=120)
     print(r.stdout[-4000:], r.stderr[-2000:])
