@@ -31,6 +31,15 @@ namespace {
 constexpr int LEAF_NODES = 10;
 // Parts of fewer nodes keep the coordinates of the part they were cut from.
 constexpr int LANDMARK_NODES = 120;
+// A part that has fallen into more pieces than this (where a node with many spokes was taken out) is
+// no longer cut but taken apart piece by piece: 300 ribs of 20 nodes under one crown have 12 levels
+// instead of 152, 20,000 single members 13 instead of some 10,000.  A few pieces a cut
+// still tells apart, one or two levels deeper at most.
+constexpr int MAX_PIECES = 8;
+// After this many cuts in a row that each leave more than 7/8 of a part on one side, the rest is
+// eliminated whole: nothing separates it (the members between every two of 300 nodes took 189
+// levels).  A few nodes joined to all others are still taken out of a part one by one.
+constexpr int MAX_POOR = 12;
 // Parts of at least this many nodes hand one half to another thread, up to MAX_THREADS at once.
 constexpr int MAX_THREADS = 8;
 constexpr int THREAD_NODES = 4000;
@@ -46,6 +55,11 @@ struct Part {
 struct Tree {                   // a front of the elimination: own nodes, then up to two subtrees
   std::vector<int32_t> own;
   std::unique_ptr<Tree> child[2];
+  int level = 0;                // of the front: above its children's
+  void raise() {
+    for (const auto& c : child)
+      if (c) level = std::max(level, c->level + 1);
+  }
 };
 
 // Breadth-first distances from src (d: -1 everywhere on entry); queue: the nodes reached, in order.
@@ -69,7 +83,7 @@ void bfs(const Part& g, int src, std::vector<int32_t>& d, std::vector<int32_t>& 
 // node farthest from those before (largest smallest distance, then largest sum of distances, so
 // that on a grid the corners come before the middles of its edges); ties go to the lower degree,
 // then to the lower number.  A node that a landmark does not reach counts as farther than any
-// other (a part may fall into pieces).
+// other (a part may fall into a few pieces).
 void coordinates(Part& g) {
   const int n = g.n();
   std::vector<int32_t> dist[4], queue;
@@ -219,8 +233,93 @@ Part sub_part(const Part& g, const std::vector<int8_t>& side, int which, int n,
   return s;
 }
 
-// threads: how many this call may use, itself included
-std::unique_ptr<Tree> dissect(Part g, int threads) {
+// The connected pieces of a part, each with its nodes in the part's order; none if there are at
+// most `few`.
+std::vector<Part> pieces(const Part& g, int few) {
+  const int n = g.n();
+  std::vector<int32_t> piece(n, -1), list, local(n);   // list: the nodes, piece by piece
+  std::vector<size_t> start;
+  list.reserve(n);
+  for (int v0 = 0; v0 < n; ++v0) {
+    if (piece[v0] >= 0) continue;
+    start.push_back(list.size());
+    piece[v0] = 0;
+    list.push_back(v0);
+    for (size_t h = start.back(); h < list.size(); ++h)
+      for (int e = g.rp[list[h]]; e < g.rp[list[h] + 1]; ++e)
+        if (piece[g.col[e]] < 0) {
+          piece[g.col[e]] = 0;
+          list.push_back(g.col[e]);
+        }
+  }
+  std::vector<Part> out;
+  if (start.size() <= (size_t)few) return out;
+  start.push_back(list.size());
+  out.resize(start.size() - 1);
+  for (size_t c = 0; c < out.size(); ++c) {
+    const auto first = list.begin() + start[c], last = list.begin() + start[c + 1];
+    std::sort(first, last);
+    Part& p = out[c];
+    p.id.reserve(last - first);
+    p.rp.reserve(last - first + 1);
+    p.rp.push_back(0);
+    for (auto v = first; v != last; ++v) {
+      local[*v] = (int32_t)p.id.size();
+      p.id.push_back(g.id[*v]);
+    }
+    for (auto v = first; v != last; ++v) {
+      for (int e = g.rp[*v]; e < g.rp[*v + 1]; ++e) p.col.push_back(local[g.col[e]]);
+      p.rp.push_back((int32_t)p.col.size());
+    }
+    if (!g.coord[0].empty() && p.n() < LANDMARK_NODES && p.n() > LEAF_NODES)
+      for (int k = 0; k < 4; ++k) {
+        p.coord[k].reserve(last - first);
+        for (auto v = first; v != last; ++v) p.coord[k].push_back(g.coord[k][*v]);
+      }
+  }
+  return out;
+}
+
+std::unique_ptr<Tree> dissect(Part g, int threads, int poor = 0);
+
+// Pieces that do not touch each other under fronts without own nodes: small ones together, up to
+// LEAF_NODES in a front, and always the two lowest trees under one, so that no more levels come on
+// top of the highest than their number makes necessary.
+std::unique_ptr<Tree> dissect_pieces(std::vector<Part> parts, int threads) {
+  std::vector<std::unique_ptr<Tree>> trees;
+  Tree* leaf = nullptr;
+  for (Part& p : parts) {
+    if (p.n() > LEAF_NODES) {
+      trees.push_back(dissect(std::move(p), threads));
+      continue;
+    }
+    if (!leaf || (int)leaf->own.size() + p.n() > LEAF_NODES) {
+      trees.push_back(std::make_unique<Tree>());
+      leaf = trees.back().get();
+    }
+    leaf->own.insert(leaf->own.end(), p.id.begin(), p.id.end());
+  }
+  std::multimap<int, std::unique_ptr<Tree>> by_level;    // equal ones in the order they came
+  for (auto& t : trees) {
+    const int h = t->level;
+    by_level.emplace(h, std::move(t));
+  }
+  while (by_level.size() > 1) {
+    auto t = std::make_unique<Tree>();
+    for (auto& c : t->child) {
+      c = std::move(by_level.begin()->second);
+      by_level.erase(by_level.begin());
+    }
+    t->raise();
+    const int h = t->level;
+    by_level.emplace(h, std::move(t));
+  }
+  return std::move(by_level.begin()->second);
+}
+
+// threads: how many this call may use, itself included; poor: the cuts in a row before this one that
+// left nearly all of a part on one side
+std::unique_ptr<Tree> dissect(Part g, int threads, int poor) {
   const int n = g.n();
   if (n == 0) return nullptr;
   auto t = std::make_unique<Tree>();
@@ -242,6 +341,18 @@ std::unique_ptr<Tree> dissect(Part g, int threads) {
       best = t;
     }
   }
+  poor = 8 * std::max(best.n0, best.n1) > 7 * n ? poor + 1 : 0;
+  if (best.size == 0 || poor > 0) {      // the cuts of a part that has fallen into pieces
+    std::vector<Part> parts = pieces(g, MAX_PIECES);
+    if (!parts.empty()) {
+      g = Part();
+      return dissect_pieces(std::move(parts), threads);
+    }
+  }
+  if (poor > MAX_POOR) {
+    t->own = std::move(g.id);
+    return t;
+  }
   take_split(g, best, side);
   std::vector<int32_t>& local = hist;
   local.resize(n);
@@ -254,7 +365,7 @@ std::unique_ptr<Tree> dissect(Part g, int threads) {
     std::exception_ptr err[2];
     auto half = [&](Part& part, int k, int th) {
       try {
-        t->child[k] = dissect(std::move(part), th);
+        t->child[k] = dissect(std::move(part), th, poor);
       } catch (...) {
         err[k] = std::current_exception();
       }
@@ -272,9 +383,10 @@ std::unique_ptr<Tree> dissect(Part g, int threads) {
     for (const std::exception_ptr& e : err)
       if (e) std::rethrow_exception(e);
   } else {
-    t->child[0] = dissect(std::move(left), 1);
-    t->child[1] = dissect(std::move(right), 1);
+    t->child[0] = dissect(std::move(left), 1, poor);
+    t->child[1] = dissect(std::move(right), 1, poor);
   }
+  t->raise();
   return t;
 }
 
@@ -291,11 +403,8 @@ struct Dissection {
   int flatten(const Tree* t) {
     if (!t) return -1;
     Front0 f;
-    f.level = 0;
-    for (int c = 0; c < 2; ++c) {
-      f.child[c] = flatten(t->child[c].get());
-      if (f.child[c] >= 0) f.level = std::max(f.level, fronts[f.child[c]].level + 1);
-    }
+    f.level = t->level;
+    for (int c = 0; c < 2; ++c) f.child[c] = flatten(t->child[c].get());
     f.own_off = (int)order.size();
     f.own_cnt = (int)t->own.size();
     order.insert(order.end(), t->own.begin(), t->own.end());
@@ -303,47 +412,22 @@ struct Dissection {
     return (int)fronts.size() - 1;
   }
 
-  // [a, b) of the list of components under one front without own nodes
-  int join(std::vector<Part>& comps, int a, int b, int threads) {
-    if (b - a == 1) return flatten(dissect(std::move(comps[a]), threads).get());
-    Front0 f;
-    f.child[0] = join(comps, a, (a + b) / 2, threads);
-    f.child[1] = join(comps, (a + b) / 2, b, threads);
-    f.own_off = (int)order.size();
-    f.own_cnt = 0;
-    f.level = 1 + std::max(fronts[f.child[0]].level, fronts[f.child[1]].level);
-    fronts.push_back(f);
-    return (int)fronts.size() - 1;
-  }
-
   void run(int n, const int32_t* rp, const int32_t* col, int threads) {
-    std::vector<int32_t> comp(n, -1), local(n), queue;
-    std::vector<Part> parts;
-    order.reserve(n);
-    for (int v0 = 0; v0 < n; ++v0) {
-      if (comp[v0] >= 0) continue;
-      const int c = (int)parts.size();
-      queue.assign(1, v0);
-      comp[v0] = c;
-      for (size_t h = 0; h < queue.size(); ++h)
-        for (int e = rp[queue[h]]; e < rp[queue[h] + 1]; ++e)
-          if (comp[col[e]] < 0) {
-            comp[col[e]] = c;
-            queue.push_back(col[e]);
-          }
-      parts.emplace_back();
-      Part& g = parts.back();
-      g.id = queue;
-      std::sort(g.id.begin(), g.id.end());
-      for (size_t k = 0; k < g.id.size(); ++k) local[g.id[k]] = (int32_t)k;
-      g.rp.push_back(0);
-      for (int v : g.id) {
-        for (int e = rp[v]; e < rp[v + 1]; ++e)
-          if (col[e] != v) g.col.push_back(local[col[e]]);
-        g.rp.push_back((int32_t)g.col.size());
-      }
+    Part g;
+    g.id.resize(n);
+    g.rp.reserve(n + 1);
+    g.rp.push_back(0);
+    for (int v = 0; v < n; ++v) {
+      g.id[v] = v;
+      for (int e = rp[v]; e < rp[v + 1]; ++e)
+        if (col[e] != v) g.col.push_back(col[e]);
+      g.rp.push_back((int32_t)g.col.size());
     }
-    join(parts, 0, (int)parts.size(), threads);
+    order.reserve(n);
+    std::vector<Part> parts = pieces(g, 1);
+    flatten((parts.empty() ? dissect(std::move(g), threads)
+                           : dissect_pieces(std::move(parts), threads))
+                .get());
   }
 };
 

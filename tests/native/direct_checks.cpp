@@ -55,6 +55,26 @@ static Graph hub(int spokes) {
   }
   return g;
 }
+// Chains of `length` nodes from one node, each with two more where it branches.
+static Graph ribs(int count, int length, int branches = 0) {
+  Graph g(1 + count * length * (1 + branches));
+  int next = 1;
+  for (int i = 0; i < count; ++i)
+    for (int k = 0, at = 0; k < length; ++k) {
+      const int v = next++;
+      g.edge(at, v);
+      for (int b = 0; b < branches; ++b) g.edge(v, next++);
+      at = v;
+    }
+  return g;
+}
+// Every one of m nodes joined to every one of n others.
+static Graph joined(int m, int n) {
+  Graph g(m + n);
+  for (int i = 0; i < m; ++i)
+    for (int j = 0; j < n; ++j) g.edge(i, m + j);
+  return g;
+}
 static Graph complete(int n) {
   Graph g(n);
   for (int i = 0; i < n; ++i)
@@ -112,6 +132,11 @@ static int run(const std::string& name, const Graph& g, bool numeric) {
   if (!build_direct_plan(g.n, rp.data(), col.data(), 1e12, pl) ||
       check_direct_plan(g.n, rp.data(), col.data(), pl, msg, sizeof msg) != 0) {
     std::printf("FAIL %s: %s\n", name.c_str(), msg);
+    return 1;
+  }
+  // levels are launches in a chain: cuts halve a part, or nearly, and what no cut parts is not cut
+  if (pl.levels() > 16 + std::log2((double)g.n)) {
+    std::printf("FAIL %s: %d levels for %d nodes\n", name.c_str(), pl.levels(), g.n);
     return 1;
   }
   // the plan depends on the graph alone
@@ -299,6 +324,20 @@ int main() {
       {"complete", complete(25), true},
       {"no edges", Graph(9), true},
       {"pieces", pieces({quads(4, 4), Graph(1), members(30, 1), hub(12), quads(7, 2)}), true},
+      {"spokes", ribs(50, 1), true},
+      {"ribs", ribs(14, 15), true},
+      {"branched ribs", shuffled(ribs(30, 4, 2), 6), true},
+      {"nodes joined to all others", joined(3, 90), true},
+      {"large clique", complete(60), true},
+      {"spokes and a clique", pieces({ribs(40, 1), complete(30), Graph(3)}), true},
+      {"96 ribs", ribs(96, 20), false},
+      {"300 ribs", ribs(300, 20), false},
+      {"5000 spokes", ribs(5000, 1), false},
+      {"20000 spokes", shuffled(ribs(20000, 1), 2), false},
+      {"3000 branched spokes", ribs(3000, 1, 3), false},
+      {"2 nodes joined to 4000", joined(2, 4000), false},
+      {"30 nodes joined to 100", joined(30, 100), false},
+      {"clique of 300", complete(300), false},
       {"quads 60x60", quads(60, 60), false},
       {"quads 80x70, shuffled", shuffled(quads(80, 70), 9), false},
   };
