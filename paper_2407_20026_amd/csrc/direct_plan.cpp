@@ -33,9 +33,11 @@ constexpr int LEAF_NODES = 10;
 constexpr int LANDMARK_NODES = 120;
 // A part that has fallen into more pieces than this (where a node with many spokes was taken out) is
 // no longer cut but taken apart piece by piece: 300 ribs of 20 nodes under one crown have 12 levels
-// instead of 152, 20,000 single members 13 instead of some 10,000.  A few pieces a cut
+// instead of 152, 20,000 single members 15 instead of some 10,000.  A few pieces a cut
 // still tells apart, one or two levels deeper at most.
 constexpr int MAX_PIECES = 8;
+// Small pieces share a front of at most this many nodes: fewer fronts, but a square of values each.
+constexpr int PIECE_NODES = 4;
 // After this many cuts in a row that each leave more than 7/8 of a part on one side, the rest is
 // eliminated whole: nothing separates it (the members between every two of 300 nodes took 189
 // levels).  A few nodes joined to all others are still taken out of a part one by one.
@@ -283,17 +285,17 @@ std::vector<Part> pieces(const Part& g, int few) {
 std::unique_ptr<Tree> dissect(Part g, int threads, int poor = 0);
 
 // Pieces that do not touch each other under fronts without own nodes: small ones together, up to
-// LEAF_NODES in a front, and always the two lowest trees under one, so that no more levels come on
+// PIECE_NODES in a front, and always the two lowest trees under one, so that no more levels come on
 // top of the highest than their number makes necessary.
 std::unique_ptr<Tree> dissect_pieces(std::vector<Part> parts, int threads) {
   std::vector<std::unique_ptr<Tree>> trees;
   Tree* leaf = nullptr;
   for (Part& p : parts) {
-    if (p.n() > LEAF_NODES) {
+    if (p.n() > PIECE_NODES) {
       trees.push_back(dissect(std::move(p), threads));
       continue;
     }
-    if (!leaf || (int)leaf->own.size() + p.n() > LEAF_NODES) {
+    if (!leaf || (int)leaf->own.size() + p.n() > PIECE_NODES) {
       trees.push_back(std::make_unique<Tree>());
       leaf = trees.back().get();
     }
