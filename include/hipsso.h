@@ -246,6 +246,10 @@ int sso_solve(sso_problem* p, double* u_out, sso_stats* stats);
  * results are bitwise the same as sso_solve's. */
 int sso_solve_begin(sso_problem* p);
 int sso_solve_end(sso_problem* p, double* u_out, sso_stats* stats);
+/* *ready (host) = 0 while the next multi-problem launch of the begun problem would have to wait for
+ * its elimination plan, which the library's host thread is still making, else 1; a request loop may
+ * leave such a problem out of its next launch.  Errors: SSO_EINVAL (NULL, or not begun). */
+int sso_solve_ready(const sso_problem* p, int32_t* ready);
 
 /* A multi-problem launcher bound to one stream.  Problems iterated together must have been
  * created on that stream.  Callers: a request loop that keeps many problems in flight. */
@@ -253,16 +257,18 @@ typedef struct sso_batch sso_batch;
 int sso_batch_create(hipStream_t stream, sso_batch** out);
 /* Launch n_iter PCG iterations for every problem of ps[0..n) whose iteration has not stopped,
  * all problems of one recurrence kind (sso_options.solver at sso_solve_begin) in one launch per
- * kernel -- for a problem that is solved directly, its factorisation and first solution, then one
- * refinement step a call (all such problems in one launch per kernel); one whose elimination plan
- * is still being made by the library's host thread is left for a later call -- then read back their states: done[i] (host, may be NULL) = 1 when problem i's
- * iteration has stopped (converged, limit or breakdown).  Errors: SSO_EINVAL (problem not
+ * kernel, then read back their states: done[i] (host, may be NULL) = 1 when problem i's
+ * iteration has stopped (converged, limit or breakdown).  For a problem that is solved directly an
+ * iteration is its factorisation and first solution, or one refinement step (seven in all at most;
+ * all such problems in one launch per kernel); its elimination plan is waited for where the
+ * library's host thread is still making it (sso_solve_ready).  Errors: SSO_EINVAL (problem not
  * begun, on another stream, or listed twice), SSO_EHIP. */
 int sso_batch_iterate(sso_batch* b, sso_problem* const* ps, int n, int n_iter, int32_t* done);
 /* sso_batch_iterate in two halves, so that the host can work while the GPU iterates:
  * sso_batch_launch enqueues the n_iter iterations and the copy of the problems' states to pinned
  * host memory and returns at once; sso_batch_wait(b, ps, n, done) waits for them, then does what
- * sso_batch_iterate does after its launches (mixed precision's outer steps, done flags).  The
+ * sso_batch_iterate does after its launches (mixed precision's outer steps, a direct solve's
+ * refinement, done flags).  The
  * wait must list the same problems in the same order as the launch; between the two, the listed
  * problems may not be iterated, ended, moved to another stream or destroyed, and a batch holds at
  * most one pending launch.  Errors: SSO_EINVAL (as sso_batch_iterate; a launch while one is

@@ -67,7 +67,7 @@ EXPORTS = ("sso_problem_create", "sso_problem_create_like", "sso_problem_update"
            "sso_sizes", "sso_strerror", "sso_problem_destroy", "sso_size_objective",
            "sso_size_objective_noalloc", "sso_size_penalty_update", "sso_hat_filter",
            "sso_problem_bytes", "sso_batch_launch", "sso_batch_wait", "sso_problem_set_stream",
-           "sso_pool_trim", "sso_batch_profile", "sso_batch_timing")
+           "sso_pool_trim", "sso_batch_profile", "sso_batch_timing", "sso_solve_ready")
 
 _lib = None
 _hip = None
@@ -97,6 +97,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.sso_problem_bytes.argtypes = [_vp, P(ctypes.c_int64)]
     lib.sso_solve_begin.argtypes = [_vp]
     lib.sso_solve_end.argtypes = [_vp, _vp, P(sso_stats)]
+    lib.sso_solve_ready.argtypes = [_vp, P(ctypes.c_int32)]
     lib.sso_batch_create.argtypes = [_vp, P(_vp)]
     lib.sso_batch_iterate.argtypes = [_vp, P(_vp), ctypes.c_int, ctypes.c_int,
                                       P(ctypes.c_int32)]
@@ -314,6 +315,14 @@ class Problem:
         if check:
             _check(status, "sso_solve_end")
         return u_out, self.last_stats
+
+    def solve_ready(self) -> bool:
+        """Whether the next launch of the begun solve needs to wait for no host work
+        (sso_solve_ready)."""
+        ready = ctypes.c_int32()
+        _check(load_library().sso_solve_ready(self.handle, ctypes.byref(ready)),
+               "sso_solve_ready")
+        return bool(ready.value)
 
     def objective(self, kind="compliance", a=None) -> float:
         g = ctypes.c_double()

@@ -2,7 +2,6 @@
 // the problem's stream, error mapping and per-stage timing.
 #include <new>
 #include <atomic>
-#include <condition_variable>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -26,10 +25,6 @@ static __device__ __align__(256) double scratch[SSO_NOALLOC_SCRATCH_BYTES / size
 static_assert(SSO_NOALLOC_MAX_QUADS * 15 + 2 * 1024 <=
                   (int64_t)(SSO_NOALLOC_SCRATCH_BYTES / sizeof(double)),
               "the no-allocation scratch holds the partials and 15 values per quad");
-
-// Signalled whenever a direct solver's plan is done, for launches that have nothing else to do.
-static std::mutex plan_mutex;
-static std::condition_variable plan_cv;
 
 // A block pattern shared by the problems of one topology (sso_problem_create_like); the last
 // problem to be destroyed frees it.
@@ -122,7 +117,8 @@ struct sso_batch {
   std::vector<int> idx[5];               // positions in that list by launch kind
   DirectBatch db;                        // the direct solver's part of a launch
   std::vector<int> direct;               // its positions in the list
-  bool idle = false;                     // the launch found nothing to do yet
+  int n_iter = 0;                        // iterations asked for
+  std::vector<int> steps;                // of them the direct solver's, by position
   // sso_batch_profile: timing samples of the FP64 standard iterations
   int prof_every = 0, prof_span = 0;
   int64_t prof_calls = 0;                // launches that could be sampled so far
@@ -373,11 +369,7 @@ void start_plan(SharedPattern* sh, const Mesh& m) {
   try {
     sh->builder = std::thread([sh, max_bytes] {
       make_plan(sh, max_bytes);
-      {
-        std::lock_guard<std::mutex> lock(plan_mutex);
-        sh->builder_done = true;
-      }
-      plan_cv.notify_all();
+      sh->builder_done = true;
     });
     sh->builder_started = true;
   } catch (...) {   // no thread to be had: the first solve builds it
@@ -959,6 +951,135 @@ int back_to_pcg(sso_problem* p) {
   return begin_pcg(p);
 }
 
+// ---- the two solvers' parts of a multi-problem launch ----------------------------------------
+
+// The next step of the listed problems that the direct solver has and that have iterations left:
+// jobs, factorisations first, their positions in b->direct.  A problem whose plan is still in the
+// making is left out, or waited for; one that turns out not to be for the direct solver starts its
+// PCG iteration and joins `turned`.
+int direct_jobs(sso_batch* b, bool wait, std::vector<DirectJob>& jobs, std::vector<int>& turned) {
+  std::vector<DirectJob> more;
+  std::vector<int> at_more;
+  jobs.clear();
+  b->direct.clear();
+  for (int i = 0; i < (int)b->listed.size(); ++i) {
+    sso_problem* p = b->listed[i];
+    if (!p->direct || p->direct_done || b->steps[i] >= b->n_iter) continue;
+    AllocScope ac(&p->bytes, &p->mem);
+    const bool factor = p->direct_steps == 0;
+    if (factor) {
+      if (!wait && plan_pending(p)) continue;
+      const int st = direct_attach(p);
+      if (st != SSO_OK) return st;
+      if (!p->direct) {                // not for this structure
+        const int sb = back_to_pcg(p);
+        if (sb != SSO_OK) return sb;
+        turned.push_back(i);
+        continue;
+      }
+    }
+    DirectJob j{&p->shared->plan, p->da,
+                residual_job(p->m, p->pat, p->K, p->u, p->f, factor ? nullptr : p->da.sol, p->w,
+                             p->da.flag),
+                factor};
+    j.a.rhs = factor ? p->f : p->w.r;
+    j.a.sol = factor ? p->u : p->da.sol;
+    (factor ? jobs : more).push_back(j);
+    (factor ? b->direct : at_more).push_back(i);
+  }
+  jobs.insert(jobs.end(), more.begin(), more.end());
+  b->direct.insert(b->direct.end(), at_more.begin(), at_more.end());
+  return SSO_OK;
+}
+
+// What the launched jobs came to.
+int direct_collect(sso_batch* b, std::vector<int>& turned) {
+  if (b->direct.empty()) return SSO_OK;
+  TRY_HIP(direct_batch_wait(b->db, b->s));
+  const std::vector<int> at = std::move(b->direct);
+  b->direct.clear();
+  for (size_t k = 0; k < at.size(); ++k) {
+    sso_problem* p = b->listed[at[k]];
+    const double* r = b->db.out.data() + 3 * k;
+    const DirectNext next = direct_next(p, r[0], r[1], r[2] != 0.0);
+    ++b->steps[at[k]];
+    p->direct_done = next == DIRECT_MET || next == DIRECT_STUCK;
+    if (next == DIRECT_FAILED) {
+      AllocScope ac(&p->bytes, &p->mem);
+      const int st = back_to_pcg(p);
+      if (st != SSO_OK) return st;
+      turned.push_back(at[k]);
+    }
+  }
+  return SSO_OK;
+}
+
+// Of the problems at these positions those that iterate, by launch kind (positions in b->idx).
+BatchLists pcg_lists(sso_batch* b, const std::vector<int>& positions) {
+  BatchLists lists;
+  for (auto& v : b->idx) v.clear();
+  for (int i : positions) {
+    sso_problem* p = b->listed[i];
+    if (p->direct || stopped(p)) continue;   // the direct solver's, or finished at an earlier poll
+    if (mixed(p) && fused(p)) {
+      lists.fused32.push_back(p->ms.fdesc);
+      b->idx[3].push_back(i);
+    } else if (mixed(p)) {
+      lists.standard32.push_back(p->ms.sdesc);
+      b->idx[2].push_back(i);
+    } else if (fused(p)) {
+      lists.fused.push_back(p->fdesc);
+      b->idx[1].push_back(i);
+    } else if (one_wg(p)) {
+      PcgDesc<double> d = p->desc;
+      d.n_wg = 1;
+      lists.wg.push_back(d);
+      b->idx[4].push_back(i);
+    } else {
+      lists.standard.push_back(p->desc);
+      b->idx[0].push_back(i);
+    }
+  }
+  return lists;
+}
+
+// Waits for the launched iterations and takes their states; a timing sample, and in mixed precision
+// the outer step that follows a stopped inner solve.
+int pcg_collect(sso_batch* b) {
+  sso_problem* const* ps = b->listed.data();
+  TRY_HIP(pcg_batch_wait(b->bw));
+  size_t k0 = 0;
+  for (const auto& v : b->idx)
+    for (int i : v) *ps[i]->w.h_st = b->bw.h_states[k0++];
+  if (b->armed > 0) {
+    // each problem's iterations inside the timed span: how far its next iteration index moved
+    // (an iteration that finds the problem stopped does no work and does not move it), at most
+    // the span; bytes per iteration with all of K counted, and as the launch's product read K
+    const int span = b->armed;
+    b->armed = 0;
+    float ms = 0.0f;
+    TRY_HIP(hipEventElapsedTime(&ms, b->bw.ev_t0, b->bw.ev_t1));
+    b->prof_us += 1000.0 * (double)ms;
+    b->prof_iters += span;
+    const bool sym = b->bw.standard.sym;
+    for (size_t k = 0; k < b->idx[0].size(); ++k) {
+      const sso_problem* p = ps[b->idx[0][k]];
+      int d = p->w.h_st->jn - b->jn0[k];
+      d = d < 0 ? 0 : (d > span ? span : d);
+      b->prof_bytes += d * pcg_bytes_per_iteration(p->m.n_nodes, p->pat.n_blocks, false, false);
+      b->prof_bytes_read += d * pcg_bytes_per_iteration(p->m.n_nodes, p->pat.n_blocks, false, sym);
+    }
+  }
+  // mixed precision: a stopped inner solve is refined in FP64 and the next one started
+  for (const std::vector<int>* v : {&b->idx[2], &b->idx[3]})
+    for (int i : *v) {
+      sso_problem* p = ps[i];
+      TRY_HIP(mixed_step(p->m, p->pat, p->K, p->K32, p->Dinv32, fused(p) ? p->B32 : nullptr, p->f,
+                         p->u, mixed_params(p), p->w, p->s, p->ms));
+    }
+  return SSO_OK;
+}
+
 bool fused_used(const sso_problem* p) { return p->solver_used == SSO_SOLVER_FUSED; }
 
 // single: a solve of its own (sso_solve, the adjoint), whose standard FP64 products read only
@@ -1360,6 +1481,12 @@ int sso_batch_create(hipStream_t stream, sso_batch** out) {
   return SSO_OK;
 }
 
+int sso_solve_ready(const sso_problem* p, int32_t* ready) {
+  if (!p || !ready || !p->in_batch) return SSO_EINVAL;
+  *ready = p->direct && p->direct_steps == 0 && plan_pending(p) ? 0 : 1;
+  return SSO_OK;
+}
+
 int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) try {
   if (!b || (n > 0 && !ps) || n < 0 || n_iter < 0 || b->pending) return SSO_EINVAL;
   for (int i = 0; i < n; ++i) {
@@ -1368,67 +1495,15 @@ int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) tr
     for (int k = 0; k < i; ++k)
       if (ps[k] == p) return SSO_EINVAL;   // a problem listed twice would advance twice
   }
-  BatchLists lists;
-  for (auto& v : b->idx) v.clear();
-  b->direct.clear();
-  std::vector<DirectJob> jobs, more;
-  std::vector<int> at_more;
-  // a problem whose plan is still in the making is left for a later launch
-  b->idle = n_iter > 0;
-  for (int i = 0; i < n && n_iter > 0; ++i) {
-    sso_problem* p = ps[i];
-    if (!p->direct || p->direct_done) continue;
-    AllocScope ac(&p->bytes, &p->mem);
-    if (p->direct_steps == 0) {
-      if (plan_pending(p)) continue;
-      const int st = direct_attach(p);
-      if (st != SSO_OK) return st;
-      if (!p->direct) {                // not for this structure
-        const int sb = back_to_pcg(p);
-        if (sb != SSO_OK) return sb;
-        continue;
-      }
-    }
-    const bool factor = p->direct_steps == 0;
-    DirectJob j{&p->shared->plan, p->da,
-                residual_job(p->m, p->pat, p->K, p->u, p->f, factor ? nullptr : p->da.sol, p->w,
-                             p->da.flag),
-                factor};
-    j.a.rhs = factor ? p->f : p->w.r;
-    j.a.sol = factor ? p->u : p->da.sol;
-    if (j.factor) {
-      jobs.push_back(j);
-      b->direct.push_back(i);
-    } else {
-      more.push_back(j);
-      at_more.push_back(i);
-    }
-  }
-  jobs.insert(jobs.end(), more.begin(), more.end());
-  b->direct.insert(b->direct.end(), at_more.begin(), at_more.end());
-  for (int i = 0; i < n; ++i) {
-    sso_problem* p = ps[i];
-    if (p->direct || stopped(p)) continue;   // the direct solver's, or finished at an earlier poll
-    b->idle = false;
-    if (mixed(p) && fused(p)) {
-      lists.fused32.push_back(p->ms.fdesc);
-      b->idx[3].push_back(i);
-    } else if (mixed(p)) {
-      lists.standard32.push_back(p->ms.sdesc);
-      b->idx[2].push_back(i);
-    } else if (fused(p)) {
-      lists.fused.push_back(p->fdesc);
-      b->idx[1].push_back(i);
-    } else if (one_wg(p)) {
-      PcgDesc<double> d = p->desc;
-      d.n_wg = 1;
-      lists.wg.push_back(d);
-      b->idx[4].push_back(i);
-    } else {
-      lists.standard.push_back(p->desc);
-      b->idx[0].push_back(i);
-    }
-  }
+  b->listed.assign(ps, ps + n);
+  b->n_iter = n_iter;
+  b->steps.assign(n, 0);
+  std::vector<DirectJob> jobs;
+  std::vector<int> all, turned;
+  const int st = direct_jobs(b, false, jobs, turned);
+  if (st != SSO_OK) return st;
+  for (int i = 0; i < n; ++i) all.push_back(i);
+  BatchLists lists = pcg_lists(b, all);
   // a timing sample: every prof_every-th launch that holds FP64 standard problems and no other
   // kind on the batch stream (one-workgroup problems run on their own stream beside them)
   b->armed = 0;
@@ -1441,11 +1516,7 @@ int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) tr
   }
   b->bw.time_span = b->armed;
   TRY_HIP(pcg_batch_launch(lists, n_iter, b->bw, b->s));
-  if (!jobs.empty()) {
-    b->idle = false;
-    TRY_HIP(direct_batch_launch(jobs, b->db, b->s));
-  }
-  b->listed.assign(ps, ps + n);
+  if (!jobs.empty()) TRY_HIP(direct_batch_launch(jobs, b->db, b->s));
   for (int i = 0; i < n; ++i) ps[i]->batch_pending = true;
   b->pending = true;
   return SSO_OK;
@@ -1459,64 +1530,27 @@ int sso_batch_wait(sso_batch* b, sso_problem* const* ps, int n, int32_t* done) t
     if (ps[i] != b->listed[i]) return SSO_EINVAL;
   b->pending = false;
   for (int i = 0; i < n; ++i) ps[i]->batch_pending = false;
-  TRY_HIP(pcg_batch_wait(b->bw));
-  if (b->idle) {
-    // every problem that is not done waits for its plan: until the first of them is there
-    std::unique_lock<std::mutex> lock(plan_mutex);
-    plan_cv.wait(lock, [&] {
-      bool pending = false;
-      for (int i = 0; i < n; ++i) {
-        if (stopped(ps[i])) continue;
-        if (!plan_pending(ps[i])) return true;
-        pending = true;
-      }
-      return !pending;
-    });
+  int st = pcg_collect(b);
+  if (st != SSO_OK) return st;
+  // the direct solver's further steps, each of which hangs on the residual of the one before, up to
+  // the iterations asked for; a plan still in the making is waited for once nothing else is left
+  std::vector<int> turned;                 // to PCG: their iterations are still to be run
+  std::vector<DirectJob> jobs;
+  for (;;) {
+    st = direct_collect(b, turned);
+    if (st == SSO_OK) st = direct_jobs(b, false, jobs, turned);
+    if (st == SSO_OK && jobs.empty()) st = direct_jobs(b, true, jobs, turned);
+    if (st != SSO_OK) return st;
+    if (jobs.empty()) break;
+    TRY_HIP(direct_batch_launch(jobs, b->db, b->s));
   }
-  if (!b->direct.empty()) {
-    TRY_HIP(direct_batch_wait(b->db, b->s));
-    for (size_t k = 0; k < b->direct.size(); ++k) {
-      sso_problem* p = ps[b->direct[k]];
-      const double* r = b->db.out.data() + 3 * k;
-      const DirectNext next = direct_next(p, r[0], r[1], r[2] != 0.0);
-      p->direct_done = next == DIRECT_MET || next == DIRECT_STUCK;
-      if (next == DIRECT_FAILED) {
-        AllocScope ac(&p->bytes, &p->mem);
-        const int st = back_to_pcg(p);
-        if (st != SSO_OK) return st;
-      }
-    }
-    b->direct.clear();
+  if (!turned.empty()) {
+    const BatchLists lists = pcg_lists(b, turned);
+    b->bw.time_span = 0;
+    TRY_HIP(pcg_batch_launch(lists, b->n_iter, b->bw, b->s));
+    st = pcg_collect(b);
+    if (st != SSO_OK) return st;
   }
-  size_t k0 = 0;
-  for (const auto& v : b->idx)
-    for (int i : v) *ps[i]->w.h_st = b->bw.h_states[k0++];
-  if (b->armed > 0) {
-    // each problem's iterations inside the timed span: how far its next iteration index moved
-    // (an iteration that finds the problem stopped does no work and does not move it), at most
-    // the span; bytes per iteration with all of K counted, and as the launch's product read K
-    const int span = b->armed;
-    b->armed = 0;
-    float ms = 0.0f;
-    TRY_HIP(hipEventElapsedTime(&ms, b->bw.ev_t0, b->bw.ev_t1));
-    b->prof_us += 1000.0 * (double)ms;
-    b->prof_iters += span;
-    const bool sym = b->bw.standard.sym;
-    for (size_t k = 0; k < b->idx[0].size(); ++k) {
-      const sso_problem* p = ps[b->idx[0][k]];
-      int d = p->w.h_st->jn - b->jn0[k];
-      d = d < 0 ? 0 : (d > span ? span : d);
-      b->prof_bytes += d * pcg_bytes_per_iteration(p->m.n_nodes, p->pat.n_blocks, false, false);
-      b->prof_bytes_read += d * pcg_bytes_per_iteration(p->m.n_nodes, p->pat.n_blocks, false, sym);
-    }
-  }
-  // mixed precision: a stopped inner solve is refined in FP64 and the next one started
-  for (const std::vector<int>* v : {&b->idx[2], &b->idx[3]})
-    for (int i : *v) {
-      sso_problem* p = ps[i];
-      TRY_HIP(mixed_step(p->m, p->pat, p->K, p->K32, p->Dinv32, fused(p) ? p->B32 : nullptr, p->f,
-                         p->u, mixed_params(p), p->w, p->s, p->ms));
-    }
   if (done)
     for (int i = 0; i < n; ++i) done[i] = stopped(ps[i]) ? 1 : 0;
   return SSO_OK;

@@ -474,8 +474,11 @@ class BatchedServer:
                 # not yet finished, or, below, joining at the next launch)
                 peak_inflight = max(peak_inflight, len(active) + len(finishing))
                 t0 = time.perf_counter()
-                if active:
-                    batch.launch([a[0] for a in active], self.chunk)
+                # a launch waits for the elimination plans of the problems in it: those still in
+                # the making are left for a later one, unless there is nothing else to launch
+                launched = [a for a in active if a[0].solve_ready()] or active[:1]
+                if launched:
+                    batch.launch([a[0] for a in launched], self.chunk)
                     fresh = 0
                 # while the chunk runs: finish what stopped at the last poll, admit arrivals
                 t1 = time.perf_counter()
@@ -487,16 +490,13 @@ class BatchedServer:
                 t3 = time.perf_counter()
                 phase["finish"] += t2 - t1
                 phase["admit"] += t3 - t2
-                if active:
-                    done = batch.wait([a[0] for a in active])
-                    still = []
-                    for flag, item in zip(done, active):
+                if launched:
+                    done = batch.wait([a[0] for a in launched])
+                    for flag, item in zip(done, launched):
                         if flag:
+                            active.remove(item)
                             item[0].set_stream(aux)
                             finishing.append(item)
-                        else:
-                            still.append(item)
-                    active = still
                     phase["iterate"] += (t1 - t0) + (time.perf_counter() - t3)
                 elif not joining and not finishing and nxt < len(reqs):
                     time.sleep(max(0.0, reqs[nxt].arrival - clock()))

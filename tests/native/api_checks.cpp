@@ -130,6 +130,8 @@ static sso_options options(int solver = SSO_SOLVER_AUTO, int precision = SSO_PRE
 
 static sso_problem* create(const Structure& s, const sso_options& o, hipStream_t stream = nullptr) {
   sso_problem* p = nullptr;
+  // memory anew, and so zeroed: the pattern that no kernel builds is then one without blocks
+  CHECK(sso_pool_trim(fake::state().device, 0) == SSO_OK);
   CHECK(sso_problem_create(&s.m, &o, stream, &p) == SSO_OK && p);
   return p;
 }
@@ -211,11 +213,103 @@ static void mixed_recurrences_named_anew() {
   }
 }
 
+// One call with iterations enough brings a begun solve to its end, whatever it takes: a plan still in
+// the making, refinement, a factorisation that fails.
+static void one_call_ends_a_solve() {
+  struct {
+    std::vector<double> rr;    // after each step
+    bool singular;
+    int substitutions;         // forward sweeps of the lowest level
+    int solver;
+  } cases[] = {
+      {{1e-18}, false, 1, SSO_SOLVER_AUTO},                     // met at once
+      {{1e-10, 1e-18}, false, 2, SSO_SOLVER_AUTO},              // one refinement
+      {{1e-4, 1e-8, 1e-12, 1e-15, 1e-18}, false, 5, SSO_SOLVER_AUTO},
+      {{1e-10, 0.9e-10, 0.9e-10, 0.0}, false, 2, SSO_SOLVER_AUTO},   // stuck: PCG corrects
+      {{1.0}, true, 1, SSO_SOLVER_STANDARD},                    // a pivot too small: PCG
+  };
+  for (int precision : {SSO_PREC_FP64, SSO_PREC_MIXED})
+    for (int nodes : {400, 20000})         // the larger plan is not there when the call is made
+      for (const auto& c : cases) {
+        begin_check();
+        Structure s(nodes);
+        sso_problem* p = create(s, options(SSO_SOLVER_AUTO, precision));
+        script.rr = c.rr;
+        script.singular = c.singular;
+        CHECK(sso_solve_begin(p) == SSO_OK);
+        sso_batch* b = nullptr;
+        CHECK(sso_batch_create(nullptr, &b) == SSO_OK);
+        int32_t done = 0;
+        CHECK(sso_batch_iterate(b, &p, 1, 1000, &done) == SSO_OK && done == 1);
+        CHECK(launches("k_front_first") > 0);
+        sso_stats st;
+        CHECK(sso_solve_end(p, s.u, &st) == SSO_OK && st.solver == c.solver);
+        CHECK(launches("k_correct_many") == c.substitutions - 1);
+        sso_batch_destroy(b);
+        sso_problem_destroy(p);
+      }
+}
+
+// A call gives each problem the iterations asked for and no more: one is one step.
+static void iterations_are_steps() {
+  begin_check();
+  Structure s(400);
+  sso_problem* p = create(s, options());
+  script.rr = {1e-4, 1e-8, 1e-12, 1e-18};
+  CHECK(sso_solve_begin(p) == SSO_OK);
+  sso_batch* b = nullptr;
+  CHECK(sso_batch_create(nullptr, &b) == SSO_OK);
+  int32_t done = 1;
+  for (int k = 0; k < 2; ++k) {
+    CHECK(sso_batch_iterate(b, &p, 1, 1, &done) == SSO_OK && done == 0);
+    CHECK(launches("k_correct_many") == k);
+  }
+  CHECK(sso_batch_iterate(b, &p, 1, 2, &done) == SSO_OK && done == 1);
+  CHECK(launches("k_correct_many") == 3);
+  CHECK(sso_batch_iterate(b, &p, 1, 2, &done) == SSO_OK && done == 1);
+  CHECK(launches("k_correct_many") == 3);
+  CHECK(sso_solve_end(p, s.u, nullptr) == SSO_OK);
+  sso_batch_destroy(b);
+  sso_problem_destroy(p);
+}
+
+// Several problems: those whose plans are there are launched at once, the others follow within the
+// call; problems that iterate by PCG are in the first launch.
+static void a_call_with_several() {
+  begin_check();
+  Structure large(30000), small(300), other(300);
+  sso_options o = options();
+  sso_problem* ps[3] = {create(large, o), create(small, o), nullptr};
+  o.solver = SSO_SOLVER_STANDARD;
+  ps[2] = create(other, o);
+  for (sso_problem* p : ps) CHECK(sso_solve_begin(p) == SSO_OK);
+  int32_t ready[3] = {2, 2, 2}, done[3] = {0, 0, 0};
+  for (int i = 0; i < 3; ++i)
+    CHECK(sso_solve_ready(ps[i], &ready[i]) == SSO_OK && (ready[i] == 0 || ready[i] == 1));
+  CHECK(ready[2] == 1);
+  sso_batch* b = nullptr;
+  CHECK(sso_batch_create(nullptr, &b) == SSO_OK);
+  CHECK(sso_batch_iterate(b, ps, 3, 1000, done) == SSO_OK && done[0] && done[1] && done[2]);
+  for (int i = 0; i < 3; ++i) {
+    sso_stats st;
+    CHECK(sso_solve_ready(ps[i], &ready[i]) == SSO_OK && ready[i] == 1);
+    CHECK(sso_solve_end(ps[i], nullptr, &st) == SSO_OK);
+    CHECK(st.solver == (i == 2 ? SSO_SOLVER_STANDARD : SSO_SOLVER_AUTO));
+    CHECK(sso_solve_ready(ps[i], &ready[i]) == SSO_EINVAL);      // no longer begun
+  }
+  CHECK(sso_solve_ready(nullptr, ready) == SSO_EINVAL);
+  sso_batch_destroy(b);
+  for (sso_problem* p : ps) sso_problem_destroy(p);
+}
+
 int main(int argc, char** argv) {
   fake::state().kernel = kernel;
   const std::map<std::string, void (*)()> checks = {
       {"ended_before_a_launch", ended_before_a_launch},
       {"mixed_recurrences_named_anew", mixed_recurrences_named_anew},
+      {"one_call_ends_a_solve", one_call_ends_a_solve},
+      {"iterations_are_steps", iterations_are_steps},
+      {"a_call_with_several", a_call_with_several},
   };
   for (const auto& c : checks)
     if (argc < 2 || c.first == argv[1]) c.second();
