@@ -89,6 +89,7 @@ struct sso_problem {
   int32_t* col = nullptr;
   int32_t* perm = nullptr;
   int32_t* seg = nullptr;
+  bool scalar_view = false;     // built
   bool direct = false;          // the last solve chose the direct solver
   bool factored = false;        // its factor is that of the current K
   bool unchecked = false;       // the elements' errors are still to be looked at
@@ -1689,11 +1690,9 @@ int sso_size_objective(sso_problem* p, double eps1, double u_max, double t_min,
                        double* out_host, double* dg_dxyz, double* dg_dt, sso_stats* stats) {
   if (!size_args_ok(p, eps1, u_max, t_min, out_host, dg_dxyz)) return SSO_EINVAL;
   AllocScope ac(&p->bytes, &p->mem);
-  if (!p->xpart) {
-    TRY_HIP(dev_alloc(&p->xpart, 2 * SIZE_XWG, p->s));
-    TRY_HIP(dev_alloc(&p->gw, 14 * (int64_t)p->m.n_quads, p->s));
-    TRY_HIP(dev_alloc(&p->wv, p->m.n_quads, p->s));
-  }
+  if (!p->xpart) TRY_HIP(dev_alloc(&p->xpart, 2 * SIZE_XWG, p->s));
+  if (!p->gw) TRY_HIP(dev_alloc(&p->gw, 14 * (int64_t)p->m.n_quads, p->s));
+  if (!p->wv) TRY_HIP(dev_alloc(&p->wv, p->m.n_quads, p->s));
   return size_objective_impl(p, eps1, u_max, t_min, out_host, dg_dxyz, dg_dt, stats,
                              p->xpart, p->gw, p->wv);
 }
@@ -1742,13 +1741,14 @@ int sso_pattern(sso_problem* p, const int32_t** row_ptr, const int32_t** col,
   AllocScope ac(&p->bytes, &p->mem);
   const int64_t nz = 36 * p->pat.n_blocks;
   hipStream_t s = p->s;
-  if (!p->row_ptr) {
-    TRY_HIP(dev_alloc(&p->row_ptr, 6 * (int64_t)p->m.n_nodes + 1, s));
-    TRY_HIP(dev_alloc(&p->col, nz, s));
-    TRY_HIP(dev_alloc(&p->perm, p->n_coo, s));
-    TRY_HIP(dev_alloc(&p->seg, nz + 1, s));
+  if (!p->scalar_view) {
+    if (!p->row_ptr) TRY_HIP(dev_alloc(&p->row_ptr, 6 * (int64_t)p->m.n_nodes + 1, s));
+    if (!p->col) TRY_HIP(dev_alloc(&p->col, nz, s));
+    if (!p->perm) TRY_HIP(dev_alloc(&p->perm, p->n_coo, s));
+    if (!p->seg) TRY_HIP(dev_alloc(&p->seg, nz + 1, s));
     TRY_HIP(build_scalar_view(p->m, p->pat, p->row_ptr, p->col, p->perm, p->seg, p->s));
     TRY_HIP(hipStreamSynchronize(p->s));
+    p->scalar_view = true;
   }
   if (row_ptr) *row_ptr = p->row_ptr;
   if (col) *col = p->col;

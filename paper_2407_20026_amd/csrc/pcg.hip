@@ -2414,16 +2414,18 @@ hipError_t pcg_alloc(PcgWork& w, int64_t n_nodes, bool mixed, hipStream_t s) {
 }
 
 hipError_t pcg_alloc_mixed(PcgWork& w, hipStream_t s) {
-  if (w.r32) return hipSuccess;
-  hipError_t e;
-  if ((e = dev_alloc(&w.r32, w.n_dof , s)) != hipSuccess) return e;
-  if ((e = dev_alloc(&w.z32, w.n_dof , s)) != hipSuccess) return e;
-  // (z, p) pairs of the standard recurrences: two floats per DOF
-  if ((e = dev_alloc(&w.p32[0], 2 * w.n_dof, s)) != hipSuccess) return e;
-  if ((e = dev_alloc(&w.p32[1], 2 * w.n_dof, s)) != hipSuccess) return e;
-  if ((e = dev_alloc(&w.Ap32, w.n_dof , s)) != hipSuccess) return e;
-  if ((e = dev_alloc(&w.x32, w.n_dof , s)) != hipSuccess) return e;
-  if ((e = dev_alloc(&w.b32, w.n_dof , s)) != hipSuccess) return e;
+  struct {
+    float** p;
+    int64_t n;
+  } const all[] = {{&w.r32, w.n_dof}, {&w.z32, w.n_dof},
+                   // (z, p) pairs of the standard recurrences: two floats per DOF
+                   {&w.p32[0], 2 * w.n_dof}, {&w.p32[1], 2 * w.n_dof},
+                   {&w.Ap32, w.n_dof}, {&w.x32, w.n_dof}, {&w.b32, w.n_dof}};
+  for (const auto& a : all) {      // those that an earlier call could not get
+    if (*a.p) continue;
+    const hipError_t e = dev_alloc(a.p, a.n, s);
+    if (e != hipSuccess) return e;
+  }
   return hipSuccess;
 }
 
@@ -2799,15 +2801,17 @@ static hipError_t table_upload(LaunchTable<Desc>& t, const Desc* descs, int n, h
   if (n > t.cap_desc) {
     dev_free(t.d_desc, s);
     t.d_desc = nullptr;
-    t.cap_desc = 2 * n;
-    e = dev_alloc_scratch(reinterpret_cast<Desc**>(&t.d_desc), t.cap_desc, s);
+    t.cap_desc = 0;
+    e = dev_alloc_scratch(reinterpret_cast<Desc**>(&t.d_desc), 2 * n, s);
     if (e != hipSuccess) return e;
+    t.cap_desc = 2 * n;
   }
   if (t.total > t.cap_wg) {
     dev_free(t.d_wg, s);
     t.d_wg = nullptr;
+    t.cap_wg = 0;
+    if ((e = dev_alloc_scratch(&t.d_wg, 2 * t.total, s)) != hipSuccess) return e;
     t.cap_wg = 2 * t.total;
-    if ((e = dev_alloc_scratch(&t.d_wg, t.cap_wg, s)) != hipSuccess) return e;
   }
   if ((e = hipMemcpyAsync(t.d_desc, t.h_desc.data(), sizeof(Desc) * n, hipMemcpyHostToDevice,
                           s)) != hipSuccess)
@@ -2983,9 +2987,10 @@ hipError_t pcg_batch_launch(const BatchLists& L, int n_iter, BatchWork& bw, hipS
     dev_free(bw.d_stp, s);
     bw.d_states = nullptr;
     bw.d_stp = nullptr;
+    bw.cap_states = bw.cap_stp = 0;
+    if ((e = dev_alloc_scratch(&bw.d_states, 2 * nt, s)) != hipSuccess) return e;
+    if ((e = dev_alloc_scratch(&bw.d_stp, 2 * nt, s)) != hipSuccess) return e;
     bw.cap_states = bw.cap_stp = 2 * nt;
-    if ((e = dev_alloc_scratch(&bw.d_states, bw.cap_states, s)) != hipSuccess) return e;
-    if ((e = dev_alloc_scratch(&bw.d_stp, bw.cap_stp, s)) != hipSuccess) return e;
   }
   if ((e = hipMemcpyAsync(bw.d_stp, bw.h_stp.data(), sizeof(PcgState*) * nt,
                           hipMemcpyHostToDevice, s)) != hipSuccess)

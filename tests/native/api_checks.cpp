@@ -75,7 +75,15 @@ static void kernel(const fake::Launch& l) {
     if (const unsigned* w = l.arg<const unsigned*>(5)) out[3] = *w;
   } else if (is(l.name, "k_pcg_init")) {
     const PcgDesc<double>* d = l.arg<const PcgDesc<double>*>(0);
-    if (fake::valid(d, sizeof *d, l.stream, "descriptor")) *d->st = PcgState();
+    if (fake::valid(d, sizeof *d, l.stream, "descriptor")) {
+      for (const void* p : {(const void*)d->K, (const void*)d->Dinv, (const void*)d->b,
+                            (const void*)d->x, (const void*)d->r, (const void*)d->z,
+                            (const void*)d->p[0], (const void*)d->p[1], (const void*)d->Ap})
+        fake::valid(p, 4, l.stream, "operand of an iteration");
+      *d->st = PcgState();
+    }
+  } else if (is(l.name, "k_scalar_rows")) {
+    for (int i = 7; i < 10; ++i) fake::valid(l.arg<const void*>(i), 4, l.stream, "scalar view");
   } else if (is(l.name, "k_update_single")) {
     finish_state(l.arg<PcgState*>(7));
   } else if (is(l.name, "k_pcg_wg")) {
@@ -140,6 +148,7 @@ static void begin_check() {
   script = Script();
   fake::state().launches.clear();
   fake::state().fail = nullptr;
+  fake::state().busy.clear();
   fake::state().limit.clear();
   fake::state().device = 0;
 }
@@ -302,6 +311,114 @@ static void a_call_with_several() {
   for (sso_problem* p : ps) sso_problem_destroy(p);
 }
 
+// An allocation that fails in a call leaves nothing that the next call takes for complete.
+static void allocations_that_fail() {
+  const std::vector<std::function<int(sso_problem*, const Structure&)>> calls = {
+      [](sso_problem* p, const Structure& s) { return sso_solve(p, s.u, nullptr); },
+      [](sso_problem* p, const Structure& s) {
+        double out[3];
+        const int st = sso_solve(p, s.u, nullptr);
+        return st != SSO_OK ? st : sso_size_objective(p, 1.0, 1.0, 0.1, out, s.grad, nullptr, nullptr);
+      },
+      [](sso_problem* p, const Structure& s) {
+        const int st = sso_solve(p, s.u, nullptr);
+        return st != SSO_OK ? st : sso_adjoint(p, SSO_OBJ_LINEAR, s.load, s.grad, nullptr, nullptr, nullptr);
+      },
+      [](sso_problem* p, const Structure&) {
+        const int32_t *a, *b, *c, *d;
+        int64_t e, f;
+        return sso_pattern(p, &a, &b, &c, &d, &e, &f);
+      },
+      [](sso_problem* p, const Structure& s) {
+        sso_batch* b = nullptr;
+        int32_t done = 0;
+        int st = sso_batch_create(nullptr, &b);
+        for (int again = 0; again < 3; ++again) {     // the same launch tables, again after a failure
+          st = sso_solve_begin(p);
+          while (st == SSO_OK && !done) st = sso_batch_iterate(b, &p, 1, 8, &done);
+          if (st == SSO_OK) break;
+        }
+        sso_batch_destroy(b);
+        return st != SSO_OK ? st : sso_solve_end(p, s.u, nullptr);
+      },
+  };
+  for (size_t c = 0; c < calls.size(); ++c)
+    for (int solver = SSO_SOLVER_AUTO; solver <= SSO_SOLVER_WG; ++solver)
+      for (int precision : {SSO_PREC_FP64, SSO_PREC_MIXED}) {
+        if (solver == SSO_SOLVER_WG && precision == SSO_PREC_MIXED) continue;
+        for (int k = 0, failed = 1; failed && k < 200; ++k) {
+          begin_check();
+          Structure s(solver == SSO_SOLVER_WG ? 130 : 24000);   // buffers of their own
+          sso_options o = options(SSO_SOLVER_STANDARD), named = options(solver, precision);
+          o.max_it = named.max_it = 8;
+          sso_problem* p = create(s, o);
+          CHECK(sso_set_options(p, &named) == SSO_OK);   // what it needs is allocated by the call
+          int n = 0;
+          script.rr.assign(40, 1.0);       // far from met: inner solves and corrections run
+          fake::state().fail = [&](const char* what) {
+            return std::strcmp(what, "copy") && n++ >= k ? hipErrorOutOfMemory : hipSuccess;
+          };
+          const int st = calls[c](p, s);
+          fake::state().fail = nullptr;
+          failed = n > k;
+          if (!failed) CHECK(st == SSO_OK || st == SSO_ENOTCONV);
+          script = Script();
+          script.rr.assign(40, 1.0);
+          CHECK(calls[c](p, s) != SSO_EHIP);
+          sso_problem_destroy(p);
+          if (fake::state().faults) {
+            std::printf("call %zu solver %d precision %d allocation %d\n", c, solver, precision, k);
+            return;
+          }
+        }
+      }
+}
+
+// A launch that fails at any of its calls leaves nothing running, and the problems where a later
+// call takes them to their end; a correction is never added again.
+static void launches_that_fail() {
+  for (int steps : {1, 2}) {            // the failing launch factors, or refines
+    for (int k = 0, failed = 1; failed && k < 500; ++k) {
+      begin_check();
+      Structure s(400), t(300), w(100);
+      sso_options o = options();
+      sso_problem* ps[3] = {create(s, o), nullptr, nullptr};
+      o.solver = SSO_SOLVER_STANDARD;
+      ps[1] = create(t, o);
+      o.solver = SSO_SOLVER_WG;
+      ps[2] = create(w, o);
+      int32_t done[3] = {0, 0, 0}, ready = 0;
+      for (sso_problem* p : ps) CHECK(sso_solve_begin(p) == SSO_OK);
+      while (!ready) CHECK(sso_solve_ready(ps[0], &ready) == SSO_OK);
+      script.rr.assign(20, 1e-10);
+      sso_batch* b = nullptr;
+      CHECK(sso_batch_create(nullptr, &b) == SSO_OK);
+      if (steps == 2) CHECK(sso_batch_iterate(b, ps, 1, 1, done) == SSO_OK && !done[0]);
+      int calls = 0;
+      fake::state().fail = [&](const char*) { return calls++ >= k ? hipErrorOutOfMemory : hipSuccess; };
+      int st = sso_batch_launch(b, ps, 3, 1);
+      fake::state().fail = nullptr;
+      failed = calls > k;
+      if (failed && st != SSO_OK) {
+        for (const auto& q : fake::state().busy) CHECK(!q.second);
+      } else {
+        CHECK(st == SSO_OK);            // or it did without: PCG in place of the direct solver
+        CHECK(sso_batch_wait(b, ps, 3, done) == SSO_OK);
+      }
+      const int added = launches("k_correct_many"), factored = launches("k_front_first");
+      script = Script();                // the next residual is met
+      CHECK(sso_batch_iterate(b, ps, 3, 1000, done) == SSO_OK && done[0] && done[1] && done[2]);
+      // a correction that may have been added is not added again: x is solved for anew
+      if (failed && st != SSO_OK && steps == 2 && added > 0)
+        CHECK(launches("k_front_first") > factored && launches("k_correct_many") == added);
+      for (sso_problem* p : ps) CHECK(sso_solve_end(p, nullptr, nullptr) == SSO_OK);
+      sso_batch_destroy(b);
+      for (sso_problem* p : ps) sso_problem_destroy(p);
+      if (!failed) CHECK(k > 5);
+    }
+  }
+}
+
 int main(int argc, char** argv) {
   fake::state().kernel = kernel;
   const std::map<std::string, void (*)()> checks = {
@@ -310,6 +427,8 @@ int main(int argc, char** argv) {
       {"one_call_ends_a_solve", one_call_ends_a_solve},
       {"iterations_are_steps", iterations_are_steps},
       {"a_call_with_several", a_call_with_several},
+      {"allocations_that_fail", allocations_that_fail},
+      {"launches_that_fail", launches_that_fail},
   };
   for (const auto& c : checks)
     if (argc < 2 || c.first == argv[1]) c.second();

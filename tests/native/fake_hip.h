@@ -45,6 +45,8 @@ struct State {
   std::map<int, size_t> limit;                     // device -> bytes it has, none: no limit
   std::function<hipError_t(const char*)> fail;     // called first by calls that may be refused
   int allocations[8] = {};                         // by device
+  std::map<hipStream_t, bool> busy;                // launches since the host last waited
+  std::map<hipEvent_t, hipStream_t> recorded;
   int faults = 0;                                  // accesses outside of device memory
   std::vector<char> symbol = std::vector<char>(32 << 20);
 };
@@ -120,6 +122,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, 
   std::lock_guard<std::recursive_mutex> lock(st.mu);
   const std::string& name = st.names[f];
   ++st.launches[name];
+  st.busy[s] = true;
   if (st.kernel) st.kernel({name, grid, args, s});
   return hipSuccess;
 }
@@ -151,7 +154,12 @@ hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) {
   *d = fake::device_of(s);
   return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+  auto& st = fake::state();
+  std::lock_guard<std::recursive_mutex> lock(st.mu);
+  st.busy[s] = false;
+  return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
@@ -164,8 +172,19 @@ hipError_t hipEventDestroy(hipEvent_t e) {
   std::free(e);
   return hipSuccess;
 }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  auto& st = fake::state();
+  std::lock_guard<std::recursive_mutex> lock(st.mu);
+  const hipError_t r = fake::refused("record");
+  if (r == hipSuccess) st.recorded[e] = s;
+  return r;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) {
+  auto& st = fake::state();
+  std::lock_guard<std::recursive_mutex> lock(st.mu);
+  if (st.recorded.count(e)) st.busy[st.recorded[e]] = false;
+  return hipSuccess;
+}
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
   *ms = 0.0f;
   return hipSuccess;
