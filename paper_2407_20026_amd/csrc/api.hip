@@ -942,14 +942,19 @@ int begin_pcg(sso_problem* p) {
   return SSO_OK;
 }
 
-// A begun solve that the direct solver does not take, or could not finish.
+// A begun solve that the direct solver does not take, or could not finish.  Where that fails, the
+// problem is as no launch had taken it: it has no iteration that could go on.
 int back_to_pcg(sso_problem* p) {
   p->direct = false;
-  if (mixed(p)) {
-    const int st = mixed_operands(p);
-    if (st != SSO_OK) return st;
+  int st = mixed(p) ? mixed_operands(p) : SSO_OK;
+  if (st == SSO_OK) st = begin_pcg(p);
+  if (st != SSO_OK) {
+    p->direct = true;
+    p->factored = p->direct_done = false;
+    p->direct_steps = 0;
+    p->direct_rr = -1.0;
   }
-  return begin_pcg(p);
+  return st;
 }
 
 // ---- the two solvers' parts of a multi-problem launch ----------------------------------------
@@ -971,7 +976,10 @@ int direct_jobs(sso_batch* b, bool wait, std::vector<DirectJob>& jobs, std::vect
     if (factor) {
       if (!wait && plan_pending(p)) continue;
       const int st = direct_attach(p);
-      if (st != SSO_OK) return st;
+      if (st != SSO_OK) {
+        p->direct = true;              // still to be taken
+        return st;
+      }
       if (!p->direct) {                // not for this structure
         const int sb = back_to_pcg(p);
         if (sb != SSO_OK) return sb;
@@ -1079,6 +1087,24 @@ int pcg_collect(sso_batch* b) {
                          p->u, mixed_params(p), p->w, p->s, p->ms));
     }
   return SSO_OK;
+}
+
+// After a launch, or what follows one, that failed: nothing of it is left running, so that the
+// problems can go on or end.  Iterations go on from the states on the device; a direct solve starts
+// anew, since a correction that was added must not be added again.
+int abandon(sso_batch* b, int status) {
+  (void)hipStreamSynchronize(b->s);
+  if (b->bw.s_wg) (void)hipStreamSynchronize(b->bw.s_wg);
+  b->bw.pending_nt = -1;
+  b->armed = 0;
+  for (int i : b->direct) {
+    sso_problem* p = b->listed[i];
+    p->direct_steps = 0;
+    p->factored = false;
+    p->direct_rr = -1.0;
+  }
+  b->direct.clear();
+  return status;
 }
 
 bool fused_used(const sso_problem* p) { return p->solver_used == SSO_SOLVER_FUSED; }
@@ -1412,10 +1438,10 @@ int sso_solve_end(sso_problem* p, double* u_out, sso_stats* stats) {
   auto residual = [&] {   // into h_scal, once the stream gets there
     return launch_true_residual(p->m, p->pat, p->K, p->u, p->f, nullptr, p->w, p->h_scal, s);
   };
-  if (p->direct && p->direct_steps == 0) {
+  const bool untaken = p->direct && p->direct_steps == 0;
+  if (untaken) {
     // ended before a launch took it: u = 0, no factor, and perhaps no arrays to hold one; an
     // adjoint is solved by PCG, with its operands made here (some of those calls allocate nothing)
-    p->direct = false;
     if (mixed(p)) {
       const int st = mixed_operands(p);
       if (st != SSO_OK) return st;
@@ -1457,6 +1483,7 @@ int sso_solve_end(sso_problem* p, double* u_out, sso_stats* stats) {
     TRY_HIP(hipMemcpyAsync(u_out, p->u, sizeof(double) * 6 * (size_t)p->m.n_nodes,
                            hipMemcpyDeviceToDevice, s));
   TRY_HIP(hipStreamSynchronize(s));
+  if (untaken) p->direct = false;
   if (stats) {
     std::memset(stats, 0, sizeof(*stats));
     stats->iters = iters;
@@ -1502,7 +1529,10 @@ int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) tr
   std::vector<DirectJob> jobs;
   std::vector<int> all, turned;
   const int st = direct_jobs(b, false, jobs, turned);
-  if (st != SSO_OK) return st;
+  if (st != SSO_OK) {
+    b->direct.clear();       // none of the jobs was launched
+    return abandon(b, st);
+  }
   for (int i = 0; i < n; ++i) all.push_back(i);
   BatchLists lists = pcg_lists(b, all);
   // a timing sample: every prof_every-th launch that holds FP64 standard problems and no other
@@ -1516,13 +1546,16 @@ int sso_batch_launch(sso_batch* b, sso_problem* const* ps, int n, int n_iter) tr
     for (int i : b->idx[0]) b->jn0.push_back(ps[i]->w.h_st->jn);
   }
   b->bw.time_span = b->armed;
-  TRY_HIP(pcg_batch_launch(lists, n_iter, b->bw, b->s));
-  if (!jobs.empty()) TRY_HIP(direct_batch_launch(jobs, b->db, b->s));
+  // what the second part needs is there before the first is enqueued
+  hipError_t e = jobs.empty() ? hipSuccess : direct_batch_reserve((int)jobs.size(), b->db, b->s);
+  if (e == hipSuccess) e = pcg_batch_launch(lists, n_iter, b->bw, b->s);
+  if (e == hipSuccess && !jobs.empty()) e = direct_batch_launch(jobs, b->db, b->s);
+  if (e != hipSuccess) return abandon(b, map_hip(e));
   for (int i = 0; i < n; ++i) ps[i]->batch_pending = true;
   b->pending = true;
   return SSO_OK;
 } catch (...) {   // out of host memory for the lists
-  return SSO_ENOMEM;
+  return abandon(b, SSO_ENOMEM);
 }
 
 int sso_batch_wait(sso_batch* b, sso_problem* const* ps, int n, int32_t* done) try {
@@ -1532,7 +1565,7 @@ int sso_batch_wait(sso_batch* b, sso_problem* const* ps, int n, int32_t* done) t
   b->pending = false;
   for (int i = 0; i < n; ++i) ps[i]->batch_pending = false;
   int st = pcg_collect(b);
-  if (st != SSO_OK) return st;
+  if (st != SSO_OK) return abandon(b, st);
   // the direct solver's further steps, each of which hangs on the residual of the one before, up to
   // the iterations asked for; a plan still in the making is waited for once nothing else is left
   std::vector<int> turned;                 // to PCG: their iterations are still to be run
@@ -1541,22 +1574,23 @@ int sso_batch_wait(sso_batch* b, sso_problem* const* ps, int n, int32_t* done) t
     st = direct_collect(b, turned);
     if (st == SSO_OK) st = direct_jobs(b, false, jobs, turned);
     if (st == SSO_OK && jobs.empty()) st = direct_jobs(b, true, jobs, turned);
-    if (st != SSO_OK) return st;
+    if (st != SSO_OK) return abandon(b, st);
     if (jobs.empty()) break;
-    TRY_HIP(direct_batch_launch(jobs, b->db, b->s));
+    const hipError_t e = direct_batch_launch(jobs, b->db, b->s);
+    if (e != hipSuccess) return abandon(b, map_hip(e));
   }
   if (!turned.empty()) {
     const BatchLists lists = pcg_lists(b, turned);
     b->bw.time_span = 0;
-    TRY_HIP(pcg_batch_launch(lists, b->n_iter, b->bw, b->s));
-    st = pcg_collect(b);
-    if (st != SSO_OK) return st;
+    const hipError_t e = pcg_batch_launch(lists, b->n_iter, b->bw, b->s);
+    st = e == hipSuccess ? pcg_collect(b) : map_hip(e);
+    if (st != SSO_OK) return abandon(b, st);
   }
   if (done)
     for (int i = 0; i < n; ++i) done[i] = stopped(ps[i]) ? 1 : 0;
   return SSO_OK;
 } catch (...) {
-  return SSO_ENOMEM;
+  return abandon(b, SSO_ENOMEM);
 }
 
 int sso_batch_iterate(sso_batch* b, sso_problem* const* ps, int n, int n_iter, int32_t* done) {

@@ -1182,9 +1182,7 @@ hipError_t launch_direct_solve(const DirectPlan& pl, const DirectArgs& a, hipStr
   return substitute(Launch{&p, 1, &a, nullptr, s});
 }
 
-hipError_t direct_batch_launch(const std::vector<DirectJob>& jobs, DirectBatch& db,
-                               hipStream_t s) {
-  const int n = (int)jobs.size();
+hipError_t direct_batch_reserve(int n, DirectBatch& db, hipStream_t s) {
   if (n > db.cap) {   // nothing is pending: the last launch was waited for
     dev_free(db.d, s);
     dev_free(db.d_res, s);
@@ -1201,12 +1199,20 @@ hipError_t direct_batch_launch(const std::vector<DirectJob>& jobs, DirectBatch& 
   if (!db.ev) SSO_TRY(hipEventCreateWithFlags(&db.ev, hipEventDisableTiming));
   db.h.resize(n);
   db.h_res.resize(n);
-  std::vector<const DirectPlan*> plans(n);
+  db.plans.resize(n);
+  db.out.resize(3 * n);
+  return hipSuccess;
+}
+
+hipError_t direct_batch_launch(const std::vector<DirectJob>& jobs, DirectBatch& db,
+                               hipStream_t s) {
+  const int n = (int)jobs.size();
+  SSO_TRY(direct_batch_reserve(n, db, s));
   int nf = 0;
   for (int i = 0; i < n; ++i) {
     db.h[i] = jobs[i].a;
     db.h_res[i] = jobs[i].residual;
-    plans[i] = jobs[i].plan;
+    db.plans[i] = jobs[i].plan;
     if (jobs[i].factor) nf = i + 1;
   }
   SSO_TRY(hipMemcpyAsync(db.d, db.h.data(), sizeof(DirectArgs) * n, hipMemcpyHostToDevice, s));
@@ -1216,16 +1222,15 @@ hipError_t direct_batch_launch(const std::vector<DirectJob>& jobs, DirectBatch& 
     hipLaunchKernelGGL(k_direct_clear, dim3((unsigned)((nf + 63) / 64)), dim3(64), 0, s,
                        DirectArgs{}, db.d, nf);
     SSO_TRY(hipGetLastError());
-    SSO_TRY(factor(Launch{plans.data(), nf, nullptr, db.d, s}));
+    SSO_TRY(factor(Launch{db.plans.data(), nf, nullptr, db.d, s}));
   }
-  SSO_TRY(substitute(Launch{plans.data(), n, nullptr, db.d, s}));
+  SSO_TRY(substitute(Launch{db.plans.data(), n, nullptr, db.d, s}));
   SSO_TRY(launch_residuals(db.h_res, db.d_res, db.d_out, s));
   return hipEventRecord(db.ev, s);
 }
 
 hipError_t direct_batch_wait(DirectBatch& db, hipStream_t s) {
   SSO_TRY(hipEventSynchronize(db.ev));
-  db.out.resize(3 * db.h.size());
   SSO_TRY(hipMemcpyAsync(db.out.data(), db.d_out, sizeof(double) * db.out.size(),
                          hipMemcpyDeviceToHost, s));
   return hipStreamSynchronize(s);

@@ -526,6 +526,7 @@ struct DirectJob {
 struct DirectBatch {
   std::vector<DirectArgs> h;
   std::vector<ResidualJob> h_res;
+  std::vector<const DirectPlan*> plans;
   DirectArgs* d = nullptr;
   ResidualJob* d_res = nullptr;
   double* d_out = nullptr;   // [n][3]: rr, bb, flag
@@ -533,6 +534,8 @@ struct DirectBatch {
   int cap = 0;
   hipEvent_t ev = nullptr;
 };
+// What a launch of n jobs needs to allocate, ahead of it (nothing of the batch is pending).
+hipError_t direct_batch_reserve(int n, DirectBatch& db, hipStream_t s);
 // jobs: those that factor first.  direct_batch_wait waits for the results and fills db.out.
 hipError_t direct_batch_wait(DirectBatch& db, hipStream_t s);
 hipError_t direct_batch_launch(const std::vector<DirectJob>& jobs, DirectBatch& db, hipStream_t s);

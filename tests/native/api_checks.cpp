@@ -395,6 +395,7 @@ static void launches_that_fail() {
       CHECK(sso_batch_create(nullptr, &b) == SSO_OK);
       if (steps == 2) CHECK(sso_batch_iterate(b, ps, 1, 1, done) == SSO_OK && !done[0]);
       int calls = 0;
+      fake::state().busy.clear();
       fake::state().fail = [&](const char*) { return calls++ >= k ? hipErrorOutOfMemory : hipSuccess; };
       int st = sso_batch_launch(b, ps, 3, 1);
       fake::state().fail = nullptr;
