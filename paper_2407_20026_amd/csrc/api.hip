@@ -251,8 +251,25 @@ void pinned_give(double* p) {
     (void)hipHostFree(p);
 }
 
+// Makes a device current for as long as it lives.
+struct OnDevice {
+  int back = -1;
+  explicit OnDevice(int device) {
+    int cur = 0;
+    if (hipGetDevice(&cur) == hipSuccess && cur != device && hipSetDevice(device) == hipSuccess)
+      back = cur;
+  }
+  ~OnDevice() {
+    if (back >= 0) (void)hipSetDevice(back);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+};
+
 void free_problem(sso_problem* p) {
   if (!p) return;
+  // the null stream is the current device's, and this may run while any is (a garbage collector)
+  const OnDevice here(p->device);
   hipStream_t s = p->s;
   Mesh& m = p->m;
   for (void* q : {(void*)m.xyz, (void*)m.fixed, (void*)m.f_nodal, (void*)m.beam_nodes,

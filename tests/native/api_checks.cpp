@@ -420,10 +420,34 @@ static void launches_that_fail() {
   }
 }
 
+// The null stream is the current device's: a problem that ends while another device is current is
+// waited for on its own, and its memory goes to no other device's problems.
+static void ended_on_another_device() {
+  begin_check();
+  auto& hip = fake::state();
+  for (int pass = 0; pass < 2; ++pass)
+    for (int device : {1, 0}) {
+      hip.device = device;
+      Structure s(20000);
+      sso_options o = options(pass ? SSO_SOLVER_STANDARD : SSO_SOLVER_AUTO);
+      sso_problem* p = nullptr;          // from the memory that earlier problems left, zeroed
+      for (const auto& m : hip.device_memory) std::memset(m.first, 0, m.second.bytes);
+      CHECK(sso_problem_create(&s.m, &o, nullptr, &p) == SSO_OK);
+      hip.device = 1 - device;
+      hip.waited.clear();
+      sso_problem_destroy(p);
+      CHECK(hip.device == 1 - device);
+      CHECK(!hip.waited.empty());
+      for (int d : hip.waited) CHECK(d == device);
+    }
+  hip.device = 0;
+}
+
 int main(int argc, char** argv) {
   fake::state().kernel = kernel;
   const std::map<std::string, void (*)()> checks = {
       {"ended_before_a_launch", ended_before_a_launch},
+      {"ended_on_another_device", ended_on_another_device},
       {"mixed_recurrences_named_anew", mixed_recurrences_named_anew},
       {"one_call_ends_a_solve", one_call_ends_a_solve},
       {"iterations_are_steps", iterations_are_steps},

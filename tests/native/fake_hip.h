@@ -47,6 +47,7 @@ struct State {
   int allocations[8] = {};                         // by device
   std::map<hipStream_t, bool> busy;                // launches since the host last waited
   std::map<hipEvent_t, hipStream_t> recorded;
+  std::vector<int> waited;                         // devices of the streams waited for
   int faults = 0;                                  // accesses outside of device memory
   std::vector<char> symbol = std::vector<char>(32 << 20);
 };
@@ -158,6 +159,7 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
   auto& st = fake::state();
   std::lock_guard<std::recursive_mutex> lock(st.mu);
   st.busy[s] = false;
+  st.waited.push_back(fake::device_of(s));
   return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
