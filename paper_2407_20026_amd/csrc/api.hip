@@ -42,11 +42,13 @@ struct SharedPattern {
   std::thread builder;
   bool builder_started = false;          // set by the creating call
   std::atomic<bool> builder_done{false};
+  std::atomic<bool> unwanted{false};     // the last problem has ended: the builder may stop
   bool built = false;                    // the builder's result, read after joining it
   DirectPlan plan;
   DirectArgs tables{};                   // device tables, in the pattern's arena
   hipEvent_t uploaded = nullptr;         // orders other streams after the upload
   ~SharedPattern() {
+    unwanted = true;
     if (builder.joinable()) builder.join();
     if (uploaded) (void)hipEventDestroy(uploaded);
   }
@@ -289,6 +291,7 @@ void free_problem(sso_problem* p) {
   const bool idle = hipStreamSynchronize(s) == hipSuccess;
   if (p->shared) {
     if (p->shared->refs.fetch_sub(1) == 1) {   // the last problem of this topology
+      p->shared->unwanted = true;
       if (p->shared->builder.joinable()) p->shared->builder.join();
       free_pattern(p->shared->pat, s, idle);
       delete p->shared;
@@ -376,7 +379,7 @@ __global__ void k_same_topology(int64_t n, const int32_t* a, const int32_t* b, u
 void make_plan(SharedPattern* sh, double max_bytes) {
   try {
     sh->built = build_direct_plan((int)sh->brow.size() - 1, sh->brow.data(), sh->bcol.data(),
-                                  max_bytes, sh->plan);
+                                  max_bytes, sh->plan, &sh->unwanted);
   } catch (...) {   // out of host memory: PCG needs none of this
     sh->built = false;
   }

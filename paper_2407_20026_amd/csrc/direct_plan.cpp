@@ -64,6 +64,12 @@ struct Tree {                   // a front of the elimination: own nodes, then u
   }
 };
 
+// Ends the build where nobody waits for the plan any more.
+struct Stopped {};
+void go_on(const std::atomic<bool>* stop) {
+  if (stop && stop->load(std::memory_order_relaxed)) throw Stopped();
+}
+
 // Breadth-first distances from src (d: -1 everywhere on entry); queue: the nodes reached, in order.
 void bfs(const Part& g, int src, std::vector<int32_t>& d, std::vector<int32_t>& queue) {
   queue.clear();
@@ -86,11 +92,12 @@ void bfs(const Part& g, int src, std::vector<int32_t>& d, std::vector<int32_t>& 
 // that on a grid the corners come before the middles of its edges); ties go to the lower degree,
 // then to the lower number.  A node that a landmark does not reach counts as farther than any
 // other (a part may fall into a few pieces).
-void coordinates(Part& g) {
+void coordinates(Part& g, const std::atomic<bool>* stop) {
   const int n = g.n();
   std::vector<int32_t> dist[4], queue;
   queue.reserve(n);
   auto distances = [&](int src, std::vector<int32_t>& d) {
+    go_on(stop);
     d.assign(n, -1);
     bfs(g, src, d, queue);
     if ((int)queue.size() < n)
@@ -282,17 +289,18 @@ std::vector<Part> pieces(const Part& g, int few) {
   return out;
 }
 
-std::unique_ptr<Tree> dissect(Part g, int threads, int poor = 0);
+std::unique_ptr<Tree> dissect(Part g, int threads, const std::atomic<bool>* stop, int poor = 0);
 
 // Pieces that do not touch each other under fronts without own nodes: small ones together, up to
 // PIECE_NODES in a front, and always the two lowest trees under one, so that no more levels come on
 // top of the highest than their number makes necessary.
-std::unique_ptr<Tree> dissect_pieces(std::vector<Part> parts, int threads) {
+std::unique_ptr<Tree> dissect_pieces(std::vector<Part> parts, int threads,
+                                     const std::atomic<bool>* stop) {
   std::vector<std::unique_ptr<Tree>> trees;
   Tree* leaf = nullptr;
   for (Part& p : parts) {
     if (p.n() > PIECE_NODES) {
-      trees.push_back(dissect(std::move(p), threads));
+      trees.push_back(dissect(std::move(p), threads, stop));
       continue;
     }
     if (!leaf || (int)leaf->own.size() + p.n() > PIECE_NODES) {
@@ -321,15 +329,16 @@ std::unique_ptr<Tree> dissect_pieces(std::vector<Part> parts, int threads) {
 
 // threads: how many this call may use, itself included; poor: the cuts in a row before this one that
 // left nearly all of a part on one side
-std::unique_ptr<Tree> dissect(Part g, int threads, int poor) {
+std::unique_ptr<Tree> dissect(Part g, int threads, const std::atomic<bool>* stop, int poor) {
   const int n = g.n();
   if (n == 0) return nullptr;
+  go_on(stop);
   auto t = std::make_unique<Tree>();
   if (n <= LEAF_NODES) {
     t->own = std::move(g.id);
     return t;
   }
-  if (g.coord[0].empty()) coordinates(g);
+  if (g.coord[0].empty()) coordinates(g, stop);
   std::vector<int8_t> side(n);
   std::vector<int32_t> hist;
   double cost = 0.0;
@@ -348,7 +357,7 @@ std::unique_ptr<Tree> dissect(Part g, int threads, int poor) {
     std::vector<Part> parts = pieces(g, MAX_PIECES);
     if (!parts.empty()) {
       g = Part();
-      return dissect_pieces(std::move(parts), threads);
+      return dissect_pieces(std::move(parts), threads, stop);
     }
   }
   if (poor > MAX_POOR) {
@@ -367,7 +376,7 @@ std::unique_ptr<Tree> dissect(Part g, int threads, int poor) {
     std::exception_ptr err[2];
     auto half = [&](Part& part, int k, int th) {
       try {
-        t->child[k] = dissect(std::move(part), th, poor);
+        t->child[k] = dissect(std::move(part), th, stop, poor);
       } catch (...) {
         err[k] = std::current_exception();
       }
@@ -385,8 +394,8 @@ std::unique_ptr<Tree> dissect(Part g, int threads, int poor) {
     for (const std::exception_ptr& e : err)
       if (e) std::rethrow_exception(e);
   } else {
-    t->child[0] = dissect(std::move(left), 1, poor);
-    t->child[1] = dissect(std::move(right), 1, poor);
+    t->child[0] = dissect(std::move(left), 1, stop, poor);
+    t->child[1] = dissect(std::move(right), 1, stop, poor);
   }
   t->raise();
   return t;
@@ -414,7 +423,8 @@ struct Dissection {
     return (int)fronts.size() - 1;
   }
 
-  void run(int n, const int32_t* rp, const int32_t* col, int threads) {
+  void run(int n, const int32_t* rp, const int32_t* col, int threads,
+           const std::atomic<bool>* stop) {
     Part g;
     g.id.resize(n);
     g.rp.reserve(n + 1);
@@ -427,8 +437,8 @@ struct Dissection {
     }
     order.reserve(n);
     std::vector<Part> parts = pieces(g, 1);
-    flatten((parts.empty() ? dissect(std::move(g), threads)
-                           : dissect_pieces(std::move(parts), threads))
+    flatten((parts.empty() ? dissect(std::move(g), threads, stop)
+                           : dissect_pieces(std::move(parts), threads, stop))
                 .get());
   }
 };
@@ -475,11 +485,11 @@ inline int64_t even(int64_t v) { return (v + 1) & ~(int64_t)1; }
 }  // namespace
 
 bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_bytes,
-                       DirectPlan& plan) {
+                       DirectPlan& plan, const std::atomic<bool>* stop) try {
   plan = DirectPlan();
   plan.n_nodes = n;
   Dissection ds;
-  ds.run(n, rp, col, MAX_THREADS);
+  ds.run(n, rp, col, MAX_THREADS, stop);
   const int nf = (int)ds.fronts.size();
 
   // level by level, children's order within a level kept
@@ -508,6 +518,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
   std::vector<int32_t> stamp(n, -1);
   double bytes = 0.0;
   for (int f = 0; f < nf; ++f) {
+    go_on(stop);
     const Front0& F = ds.fronts[f];
     std::vector<int32_t>& b = bnd[f];
     auto add = [&](int v) {
@@ -547,6 +558,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
   for (int h = 0; h < nl; ++h) {
     int64_t work = 0, again = 0, w = 0;
     for (int i : by_level[h]) {
+      go_on(stop);
       const int f0 = order[i];
       const Front0& F = ds.fronts[f0];
       DirectFront& D = plan.fronts[i];
@@ -651,6 +663,7 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
     }
     open(STEP_PANEL);
     for (int i : by_level[h]) {
+      go_on(stop);
       DirectFront& D = plan.fronts[i];
       const int ns = D.ns6 / 6, cnt = ns + D.nb6 / 6;
       if (ns == 0) continue;
@@ -766,6 +779,9 @@ bool build_direct_plan(int n, const int32_t* rp, const int32_t* col, double max_
     close(STEP_BWD);
   }
   return true;
+} catch (const Stopped&) {
+  plan = DirectPlan();
+  return false;
 }
 
 int check_direct_plan(int n, const int32_t* rp, const int32_t* col, const DirectPlan& plan,

@@ -7,6 +7,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <vector>
 
 namespace sso {
@@ -150,9 +151,10 @@ struct DirectPlan {
 
 // Builds the plan for a block pattern (brow_ptr [n + 1], bcol, columns of a row ascending, the
 // pattern symmetric).  Returns false when its numeric arrays would take more than max_bytes or a
-// front has more than DIRECT_MAX_OWN own or DIRECT_MAX_BOUNDARY boundary DOFs.
+// front has more than DIRECT_MAX_OWN own or DIRECT_MAX_BOUNDARY boundary DOFs, and soon after *stop
+// (if given) is set.
 bool build_direct_plan(int n, const int32_t* brow_ptr, const int32_t* bcol, double max_bytes,
-                       DirectPlan& plan);
+                       DirectPlan& plan, const std::atomic<bool>* stop = nullptr);
 // 0 when every invariant of the plan holds, else the number of the first failed check, with a
 // message in msg.
 int check_direct_plan(int n, const int32_t* brow_ptr, const int32_t* bcol,

@@ -4,12 +4,15 @@
 // hold (check_direct_plan), and eliminating with it -- the work lists walked as the kernels walk
 // them, in plain loops over bounds-checked arrays -- solves a random symmetric positive definite
 // block system.
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
 #include <set>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "direct_plan.h"
@@ -300,8 +303,33 @@ static int run(const std::string& name, const Graph& g, bool numeric) {
   return 0;
 }
 
-int main() {
+// A build that nobody waits for any more ends early, without a plan.
+static int stopped() {
+  const Graph g = quads(260, 260);
+  std::vector<int32_t> rp{0}, col;
+  for (const auto& a : g.adj) {
+    col.insert(col.end(), a.begin(), a.end());
+    rp.push_back((int32_t)col.size());
+  }
   int bad = 0;
+  for (bool at_once : {true, false}) {
+    std::atomic<bool> stop{at_once};
+    DirectPlan pl;
+    bool built = true;
+    std::thread t([&] { built = build_direct_plan(g.n, rp.data(), col.data(), 1e12, pl, &stop); });
+    if (!at_once) std::this_thread::sleep_for(std::chrono::milliseconds(20));   // it takes longer
+    stop = true;
+    t.join();
+    if (built || !pl.fronts.empty() || !pl.items.empty()) {
+      std::printf("FAIL a build that was stopped gave a plan\n");
+      ++bad;
+    }
+  }
+  return bad;
+}
+
+int main() {
+  int bad = stopped();
   struct {
     const char* name;
     Graph g;
