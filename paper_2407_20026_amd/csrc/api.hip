@@ -906,6 +906,8 @@ int prepare(sso_problem* p, bool batch) {
   p->direct = p->factored = p->direct_done = false;
   p->direct_rr = -1.0;
   p->direct_steps = 0;
+  p->w.prof_us = 0.0;
+  p->w.prof_n = 0;
   if (may_be_direct(p)) {
     if (batch) {
       p->direct = true;     // attached by the first launch: its plan may still be in the making

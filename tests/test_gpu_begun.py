@@ -132,3 +132,17 @@ def test_iterations_are_refinement_steps():
         b.close()
     assert calls == sv["refine_steps"] == st["refine_steps"]
     assert p.last_status == status and torch.equal(u, v)
+
+
+def test_samples_are_of_the_last_solve():
+    """A direct solve has no iterations to time: no samples of an earlier solve are reported."""
+    import paper_2407_20026_amd as sso
+    print("[gpu] timing samples", flush=True)
+    with sso.Problem(meshgen.shell(20, seed=1),
+                     sso.Options(rtol=1e-9, solver=sso.SOLVER_STANDARD, profile_every=8)) as p:
+        _, st = p.solve()
+        assert st["spmv_samples"] > 0 and st["spmv_us"] > 0.0
+        p.set_options(sso.Options(rtol=1e-9, profile_every=8))
+        _, st = p.solve()
+        assert st["solver"] == sso.SOLVER_AUTO
+        assert st["spmv_samples"] == 0 and st["spmv_us"] == 0.0
