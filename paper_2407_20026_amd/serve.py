@@ -30,7 +30,8 @@ from dataclasses import dataclass, field, replace
 import numpy as np
 import torch
 
-from . import PREC_MIXED, SOLVER_AUTO, SOLVER_WG, Options, Problem
+from . import (PREC_MIXED, SOLVER_AUTO, SOLVER_FUSED, SOLVER_STANDARD, SOLVER_WG, Options,
+               Problem)
 
 
 # sso_solve's automatic choice of the single-reduction recurrences (which keep B = K M beside
@@ -60,15 +61,15 @@ def _arena_bound(bufs) -> int:
     return big + chunks * ARENA_CHUNK
 
 
-def footprint_bytes(mesh, mixed: bool | None = False) -> int:
+def footprint_bytes(mesh, mixed: bool | None = False, solver: int = SOLVER_AUTO) -> int:
     """Upper bound of the device memory one problem holds after its forward and adjoint
     (mesh copies, pattern, element list, K, packed preconditioner, the direct solver's arrays or
     B = K M of the single-reduction PCG, or the FP32 copies of mixed precision, solver vectors,
     gradients), in the chunks the library carves them from.  mixed=None: the precision is picked by the
-    library (AUTO), either bound.  Checked against the library's own count (sso_problem_bytes)
+    library (AUTO), either bound.  solver: a named one never allocates the direct solver's arrays.  Checked against the library's own count (sso_problem_bytes)
     in the serving tests."""
     if mixed is None:
-        return max(footprint_bytes(mesh, False), footprint_bytes(mesh, True))
+        return max(footprint_bytes(mesh, False, solver), footprint_bytes(mesh, True, solver))
     nn, nb, nq = mesh.n_nodes, mesh.n_beams, mesh.n_quads
     blocks = nn + 2 * nb + 12 * nq                  # diagonal + off-diagonal blocks (bound)
     padded = 12 * nn                                # padded block rows, 12 slots at most
@@ -81,15 +82,20 @@ def footprint_bytes(mesh, mixed: bool | None = False) -> int:
     bufs += [288 * blocks, 8 * dinv]                                               # K, Dinv
     bufs += [8 * ndof] * 14 + [8 * 6 * nb, 8 * 14 * nq]                            # vectors, grads
     bufs += [8 * 11 * 1024, 4096, 64]                                              # partials
-    # the direct solver's arrays, at most what the library lets them take (a structure that would
-    # fill more runs PCG), and its tables, some 200 bytes a node
-    direct = 288 * (math.log2(nn + 1) + 1) * (1.2 * nn + 2.3 * nb + 6.3 * nq) + (1 << 20)
-    if mixed:                       # or the FP32 copies of mixed precision's inner solves
+    if mixed:                       # the FP32 copies of mixed precision's inner solves
         bufs += [4 * ndof] * 11
-        direct = max(direct, 144 * max(blocks, padded) + 4 * dinv)
-    elif nn <= FUSED_MAX_NODES:     # or B = K M in FP64 (single-reduction recurrences)
-        direct = max(direct, 288 * max(blocks, padded))
-    bufs += [int(direct), 256 * nn]
+        pcg = [144 * max(blocks, padded), 4 * dinv]
+    elif solver == SOLVER_FUSED or (solver == SOLVER_AUTO and nn <= FUSED_MAX_NODES):
+        # B = K M in FP64 (single-reduction recurrences)
+        pcg = [288 * max(blocks, padded)]
+    else:
+        pcg = []
+    if solver == SOLVER_AUTO:
+        # the direct solver's arrays in their place, at most what the library lets them take (a
+        # structure that would fill more runs PCG), and its tables, some 200 bytes a node
+        direct = 288 * (math.log2(nn + 1) + 1) * (1.2 * nn + 2.3 * nb + 6.3 * nq) + (1 << 20)
+        pcg = [int(max(direct, sum(pcg))), 256 * nn]
+    bufs += pcg
     return int(1.05 * (_arena_bound(pattern) + _arena_bound(bufs))) + (1 << 20)
 
 
@@ -211,10 +217,13 @@ class Server:
         # FP64, mixed, or AUTO (the library picks per problem: either footprint)
         self.mixed = {0: False, 1: True}.get(self.options.precision)
 
+    def footprint(self, mesh) -> int:
+        return footprint_bytes(mesh, self.mixed, self.options.solver)
+
     def run(self, requests: list[Request]) -> ServeStats:
         reqs = sorted(requests, key=lambda r: r.arrival)
         for r in reqs:
-            if footprint_bytes(r.mesh, self.mixed) > self.budget:
+            if self.footprint(r.mesh) > self.budget:
                 raise ValueError(f"request {r.rid} can never be admitted: footprint above budget")
         cond = threading.Condition()
         waiting = collections.deque()
@@ -242,10 +251,9 @@ class Server:
                     while True:
                         if state["error"] is not None:
                             return
-                        if waiting and footprint_bytes(waiting[0].mesh, self.mixed) <= \
-                                state["free"]:
+                        if waiting and self.footprint(waiting[0].mesh) <= state["free"]:
                             req = waiting.popleft()
-                            need = footprint_bytes(req.mesh, self.mixed)
+                            need = self.footprint(req.mesh)
                             state["free"] -= need
                             state["inflight"] += 1
                             state["peak_inflight"] = max(state["peak_inflight"],
@@ -380,11 +388,22 @@ class BatchedServer:
             return self.options_wg
         return self.options
 
+    def admission(self, mesh) -> tuple[Options, int]:
+        """The options a request runs with and the memory it is charged.  One that only the direct
+        solver's arrays would put above the whole budget runs the recurrences that AUTO falls
+        back to."""
+        options = self.options_for(mesh)
+        need = footprint_bytes(mesh, self.mixed, options.solver)
+        if need > self.budget and options.solver == SOLVER_AUTO:
+            options = replace(options, solver=SOLVER_STANDARD)
+            need = footprint_bytes(mesh, self.mixed, options.solver)
+        return options, need
+
     def run(self, requests: list[Request]) -> ServeStats:
         from . import Batch
         reqs = sorted(requests, key=lambda r: r.arrival)
         for r in reqs:
-            if footprint_bytes(r.mesh, self.mixed) > self.budget:
+            if self.admission(r.mesh)[1] > self.budget:
                 raise ValueError(f"request {r.rid} can never be admitted: footprint above budget")
         it_stream = torch.cuda.Stream(device=self.device)
         aux = it_stream
@@ -419,15 +438,15 @@ class BatchedServer:
 
         def admit():
             nonlocal free
-            while waiting and len(active) + len(joining) < self.slots and \
-                    footprint_bytes(waiting[0].mesh, self.mixed) <= free:
+            while waiting and len(active) + len(joining) < self.slots:
+                options, need = self.admission(waiting[0].mesh)
+                if need > free:
+                    break
                 req = waiting.popleft()
-                need = footprint_bytes(req.mesh, self.mixed)
                 free -= need
                 key = topology_key(req.mesh) if self.share_patterns else None
                 like = next(iter(live[key]), None) if key in live else None
-                p = Problem(req.mesh, self.options_for(req.mesh), device=self.device, stream=aux,
-                            like=like)
+                p = Problem(req.mesh, options, device=self.device, stream=aux, like=like)
                 p.topology = key
                 if key is not None:
                     live[key].add(p)
