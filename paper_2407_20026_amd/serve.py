@@ -337,12 +337,15 @@ def streams_overlap(a, b, spin_cycles: int = 4_000_000):
     return overlap
 
 
-# Direct solves (SOLVER_AUTO) are one launch each, bound by the latency of its some 60 kernels: a
-# few requests in it take little longer than one.  A launch of fewer than COMPANY requests that has
-# not begun therefore waits for the next arrival if that is at most COMPANY_S away, about the time
-# of a launch.
+# Requests that come at a steady interval of at most COMPANY_S, about the time of a launch, are taken
+# up to COMPANY at a time: the next one is waited for until a quarter of the interval after it is due.
+# That halves the launches (240 small requests every 2 ms: 113 instead of 240, and of the GPU's time
+# with them) at the price of latency (p50 1.1 -> 3.8 ms; the served mix 5.8-7.3 -> 6.3-6.8); the
+# capacity is the same.  Requests at random are not held: they would wait as long and save less (small
+# ones at 500/s: p50 1.25 ms and 230 launches as it is, 1.96 and 189 held after every short interval).
 COMPANY = 4
 COMPANY_S = 2.5e-3
+STEADY = 0.05          # by how much the last two intervals may differ
 
 
 class BatchedServer:
@@ -430,11 +433,20 @@ class BatchedServer:
         free = self.budget
         peak_inflight = peak_bytes = 0
         nxt = fresh = 0      # fresh: requests of `active` that no launch has taken yet
+        seen = collections.deque(maxlen=3)   # the last arrivals
         t_start = time.perf_counter()
         phase = dict(admit=0.0, iterate=0.0, finish=0.0, idle=0.0)
 
         def clock():
             return time.perf_counter() - t_start
+
+        def next_due():
+            """Until when the next request is waited for, from the arrivals so far."""
+            if len(seen) < 3:
+                return 0.0
+            g0, g1 = seen[1] - seen[0], seen[2] - seen[1]
+            steady = g1 <= COMPANY_S and abs(g1 - g0) <= STEADY * g1
+            return seen[2] + 1.25 * g1 if steady else 0.0
 
         def admit():
             nonlocal free
@@ -470,6 +482,7 @@ class BatchedServer:
                 now = clock()
                 while nxt < len(reqs) and reqs[nxt].arrival <= now:
                     waiting.append(reqs[nxt])
+                    seen.append(reqs[nxt].arrival)
                     nxt += 1
                 fresh += len(joining)
                 for item in joining:
@@ -477,18 +490,14 @@ class BatchedServer:
                     active.append(item)
                 joining.clear()
                 if fresh == len(active) and 0 < fresh < min(COMPANY, self.slots) and \
-                        self.options.solver == SOLVER_AUTO and nxt < len(reqs) and \
-                        reqs[nxt].arrival - clock() <= COMPANY_S:
+                        self.options.solver == SOLVER_AUTO and clock() < next_due():
                     finish()
-                    time.sleep(max(0.0, reqs[nxt].arrival - clock()))
-                    while nxt < len(reqs) and reqs[nxt].arrival <= clock():
-                        waiting.append(reqs[nxt])
-                        nxt += 1
                     admit()
                     peak_inflight = max(peak_inflight, len(active) + len(joining))
                     peak_bytes = max(peak_bytes, self.budget - free)
-                    if joining:
-                        continue
+                    if not joining:
+                        time.sleep(1e-4)
+                    continue
                 # in flight: admitted and not finished (iterating, stopped at the last poll and
                 # not yet finished, or, below, joining at the next launch)
                 peak_inflight = max(peak_inflight, len(active) + len(finishing))
