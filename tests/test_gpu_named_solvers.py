@@ -1,0 +1,166 @@
+"""The recurrences by name.  Under the automatic choice most structures are solved directly, in FP64
+whatever the precision asked for; here the FP32 inner solves of mixed precision and the multi-problem
+launches run what the options name, shown by the iterations they count."""
+import os
+
+import numpy as np
+import pytest
+
+import meshgen
+import oracle
+from oracle import assembly
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+GOLDEN = os.path.join(os.path.dirname(__file__), "golden", "shell300_oracle.npz")
+
+CASES = {
+    "grid11": meshgen.grid_shell_11,
+    "shell8": lambda: meshgen.shell(8, L=8.0, seed=3),
+    "shell60": meshgen.shell_60,
+}
+
+
+@pytest.fixture(scope="module")
+def refs():
+    cache = {}
+
+    def get(name):
+        if name not in cache:
+            mesh = CASES[name]()
+            cache[name] = (mesh, oracle.analyze(mesh, "compliance", pat=assembly.pattern(mesh)))
+        return cache[name]
+    return get
+
+
+def _solver(name):
+    import paper_2407_20026_amd as sso
+    return {"standard": sso.SOLVER_STANDARD, "fused": sso.SOLVER_FUSED}[name]
+
+
+@pytest.mark.parametrize("solver", ["standard", "fused"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_fp32_inner_solves_reach_the_fp64_residual(refs, name, solver):
+    """The FP64 residual at 1e-10 by FP32 inner solves; u within 1e-6 and the gradient within 1e-5 of
+    the oracle, as that residual and these structures' condition numbers allow."""
+    import paper_2407_20026_amd as sso
+    mesh, r = refs(name)
+    print(f"[gpu] mixed {solver} {name}", flush=True)
+    o = sso.Options(precision=sso.PREC_MIXED, rtol=1e-10, refine_steps=30, solver=_solver(solver))
+    with sso.Problem(mesh, o) as p:
+        u, st = p.solve()
+        g = p.adjoint("compliance")
+    assert st["solver"] == _solver(solver) and st["iters"] > 0 and st["refine_steps"] > 0
+    assert st["rel_residual"] <= 1e-10
+    u = u.cpu().numpy().ravel()
+    assert np.linalg.norm(u - r["u"]) <= 1e-6 * np.linalg.norm(r["u"])
+    gx = g["dg_dxyz"].cpu().numpy()
+    assert np.abs(gx - r["grad_xyz"]).max() <= 1e-5 * np.abs(r["grad_xyz"]).max()
+
+
+def test_fp32_inner_solves_and_fp64_agree():
+    """Mixed precision by the standard recurrences against the direct solver: two solutions of the
+    same K at the same target, of different arithmetic."""
+    import paper_2407_20026_amd as sso
+    print("[gpu] mixed standard vs direct", flush=True)
+    mesh = meshgen.shell(20, seed=7)
+    out = []
+    for o in (sso.Options(rtol=1e-10),
+              sso.Options(rtol=1e-10, precision=sso.PREC_MIXED, solver=sso.SOLVER_STANDARD)):
+        with sso.Problem(mesh, o) as p:
+            u, st = p.solve()
+        assert (st["iters"] > 0) == (o.solver != sso.SOLVER_AUTO)
+        out.append(u)
+    assert not torch.equal(*out)
+    assert (out[0] - out[1]).norm() <= 1e-6 * out[0].norm()
+
+
+def test_capped_fp32_inner_solves_at_full_size():
+    """The 300 x 300 shell at 1e-10 by FP64 flexible CG around FP32 inner solves of at most 20
+    iterations: u within 1e-10 (2-norm) and every gradient entry within 1e-8 (of the largest) of
+    the oracle's reference, and AUTO precision at 1e-8, which takes FP32 inner solves at this
+    size."""
+    import paper_2407_20026_amd as sso
+    print("[gpu] 300x300: mixed standard, inner cap 20", flush=True)
+    mesh, ref = meshgen.shell_300(), np.load(GOLDEN)
+    with sso.Problem(mesh, sso.Options(precision=sso.PREC_MIXED, rtol=1e-10, max_it=400000,
+                                       refine_steps=20000, inner_max_it=20,
+                                       solver=sso.SOLVER_STANDARD)) as p:
+        u, st = p.solve()
+        c = p.objective("compliance")
+        g = p.adjoint("compliance")
+        assert st["iters"] > 0 and st["refine_steps"] > 10 and st["rel_residual"] <= 1e-10
+        p.set_options(sso.Options(precision=sso.PREC_AUTO, rtol=1e-8, max_it=400000,
+                                  solver=sso.SOLVER_STANDARD))
+        _, sa = p.solve()
+    assert sa["iters"] > 0 and sa["refine_steps"] > 0 and sa["rel_residual"] <= 1e-8
+    u = u.cpu().numpy().ravel()
+    assert np.linalg.norm(u - ref["u"]) <= 1e-10 * np.linalg.norm(ref["u"])
+    assert c == pytest.approx(float(ref["c"]), rel=1e-10)
+    for key, name in (("dg_dxyz", "grad_xyz"), ("dg_dt", "grad_t"), ("dg_dscale", "grad_scale")):
+        got = g[key].cpu().numpy()
+        assert np.abs(got - ref[name]).max() <= 1e-8 * np.abs(ref[name]).max(), name
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_served_by_the_standard_recurrences(precision):
+    """A served mix by name: every request iterates, in mixed precision by FP32 inner solves, and
+    agrees with the direct solver's result at the same target."""
+    import paper_2407_20026_amd as sso
+    from paper_2407_20026_amd.serve import BatchedServer, Request, errors_against
+    print(f"[gpu] served by name, {precision}", flush=True)
+    reqs = [Request(i, meshgen.served_request(i), 0.0) for i in (0, 4, 6, 10)]
+    mixed = precision == "mixed"
+    o = sso.Options(rtol=1e-10, max_it=400000, solver=sso.SOLVER_STANDARD, refine_steps=100,
+                    precision=sso.PREC_MIXED if mixed else sso.PREC_FP64)
+    named = BatchedServer(slots=4, options=o).run(reqs)
+    direct = BatchedServer(slots=4, options=sso.Options(rtol=1e-10)).run(reqs)
+    assert named.not_converged == direct.not_converged == 0
+    for r in named.results:
+        assert r.iters > 0 and (r.outer_steps > 0) == mixed
+    assert all(r.iters == 0 for r in direct.results)
+    for e in errors_against(named.results, direct.results):
+        assert e["g_rel"] <= 1e-9 and e["dg_dxyz_rel_inf"] <= 1e-7, e
+
+
+def test_direct_problems_in_a_batch_match_solves_alone():
+    """Direct solves in multi-problem launches -- of one topology and of several, with and without
+    refinement, beside problems that iterate -- to the bits of each solved alone."""
+    import paper_2407_20026_amd as sso
+    print("[gpu] direct batch against alone", flush=True)
+    made = [(meshgen.shell(14, seed=1), 1e-10, sso.SOLVER_AUTO, None),
+            (meshgen.shell(14, seed=2), 1e-10, sso.SOLVER_AUTO, 0),
+            (meshgen.arch_bridge(20, n_spans=40), 3e-13, sso.SOLVER_AUTO, None),
+            (meshgen.gridshell(21, seed=4), 1e-11, sso.SOLVER_AUTO, None),
+            (meshgen.shell(33, seed=5), 1e-12, sso.SOLVER_AUTO, None),
+            (meshgen.shell(12, seed=6), 1e-9, sso.SOLVER_STANDARD, None)]
+    alone = []
+    for mesh, rtol, solver, _ in made:
+        with sso.Problem(mesh, sso.Options(rtol=rtol, solver=solver)) as p:
+            u, st = p.solve()
+            assert st["solver"] == solver
+            alone.append((u, p.adjoint("compliance")["dg_dxyz"]))
+    for chunk in (1, 32):
+        stream = torch.cuda.Stream()
+        batch = sso.Batch(stream)
+        ps = []
+        try:
+            for mesh, rtol, solver, like in made:
+                ps.append(sso.Problem(mesh, sso.Options(rtol=rtol, solver=solver), stream=stream,
+                                      like=None if like is None else ps[like]))
+                ps[-1].solve_begin()
+            done = [False] * len(ps)
+            while not all(done):
+                done = batch.iterate(ps, chunk)
+            for p, (u, g) in zip(ps, alone):
+                v, st = p.solve_end()
+                assert st["solver"] == p.options.solver
+                h = p.adjoint("compliance")["dg_dxyz"]
+                stream.synchronize()
+                assert torch.equal(u, v) and torch.equal(g, h)
+        finally:
+            for p in reversed(ps):
+                p.close()
+            batch.close()
