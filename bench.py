@@ -4,21 +4,24 @@ Headline (the default): the mixed-size served stream.  2,000 forward + adjoint r
 grid-shell (n x n nodes, n ~ U{8..60}) or a quad shell (m x m elements, m ~ U{10..120}) with its
 own seed (``meshgen.served_request``), compliance, rtol 1e-8, served by continuous batching
 (``serve.BatchedServer``: admission by slots and device-memory footprint, all requests in flight
-iterating in shared multi-problem launches).  A "step" is one request.  The headline runs in
-mixed precision (FP32 inner PCG solves inside an FP64 flexible CG) with plain FP64 beside it:
+in shared multi-problem launches).  A "step" is one request.  The headline runs with the library's
+own choices (the direct solver in FP64 on these structures; ``dtype`` says what ran), with plain
+FP64 and with mixed precision by the standard recurrences (FP32 inner PCG solves inside an FP64
+flexible CG, named, since the automatic choice solves directly) beside it:
 
 * value (solves/s) and DOF/s: all requests queued at once (closed loop), wall time of the whole
   stream -- the throughput the server sustains on this mix of sizes;
 * p50/p99 latency (arrival to result): the same 2,000 requests arriving as a Poisson process at
-  0.8 times the smaller of the two precisions' closed-loop capacities;
+  0.8 times the smaller of the two first legs' closed-loop capacities;
 * per request, the error of the mixed result against the FP64 result (g, dg/dxyz, dg/dt).
 
 Inputs are resident in HBM before each request's timed work starts: a request's mesh is uploaded
 when it is admitted, which is part of serving it.
 
-Legs: the 300 x 300 shell (543,606 DOF) at rtol 1e-10 in FP64 and mixed precision, whose PCG
-iteration (k_spmv_dir_single + k_update_single, timed live with HIP events on the problem's stream) gives the
-roofline; the 60 x 60 shell; a linear objective (second PCG for the adjoint); the network batch
+Legs: the 300 x 300 shell (543,606 DOF) at rtol 1e-10, direct, by PCG in FP64 and by PCG in mixed
+precision; the roofline is that of the FP64 iteration (k_spmv_dir_single + k_update_single, timed
+live with HIP events on the problem's stream), which a named solver runs and the headline does not;
+the 60 x 60 shell; a linear objective (a second solution for the adjoint); the network batch
 (256 variants of the 80 x 80 shell through the MLP); the paper's arch-bridge rows; the measured
 HBM and FP64 ceilings; the oracle timed on the host on a sample of the stream's requests.
 Prints one JSON line.
@@ -83,8 +86,9 @@ def parse():
     ap.add_argument("--rtol", type=float, default=None,
                     help="relative residual target (default 1e-8; 1e-10 for shell300)")
     ap.add_argument("--precision", default=None, choices=["auto", "fp64", "mixed"],
-                    help="headline precision (default: auto for the stream -- FP32 inner "
-                         "solves where the problem's K outgrows the caches -- fp64 otherwise)")
+                    help="headline precision (default: auto for the stream, fp64 otherwise); "
+                         "mixed names the standard recurrences unless --solver does, since "
+                         "the automatic choice of solver would solve directly in FP64")
     ap.add_argument("--inner-max-it", type=int, default=0,
                     help="mixed precision: iteration cap of each FP32 inner solve (0 = none)")
     ap.add_argument("--refine-steps", type=int, default=20,
@@ -184,10 +188,27 @@ def cpu_baseline(meshes, objective, budget_s, what):
 PRECISIONS = {"auto": "PREC_AUTO", "fp64": "PREC_FP64", "mixed": "PREC_MIXED"}
 
 
+def _solver(sso, precision, args):
+    """The solver asked for; FP32 inner solves are run by name."""
+    named = {"auto": sso.SOLVER_AUTO, "standard": sso.SOLVER_STANDARD, "fused": sso.SOLVER_FUSED}
+    if precision == "mixed" and args.solver == "auto":
+        return sso.SOLVER_STANDARD
+    return named[args.solver]
+
+
 def _stream_options(sso, precision, rtol, args):
     return sso.Options(rtol=rtol, max_it=400000, precision=getattr(sso, PRECISIONS[precision]),
+                       solver=_solver(sso, precision, args),
                        inner_max_it=args.inner_max_it if precision == "mixed" else 0,
                        refine_steps=args.refine_steps)
+
+
+def _dtype(iters, outer):
+    """What ran, from each solve's PCG iterations and outer steps."""
+    iters, outer = np.asarray(iters), np.asarray(outer)
+    kinds = [("f64 (direct)", iters == 0), ("f64", (iters > 0) & (outer == 0)),
+             ("f32 inner PCG / f64 flexible CG", (iters > 0) & (outer > 0))]
+    return ", ".join(name for name, which in kinds if which.any())
 
 
 def _size_buckets(results, meshes):
@@ -262,7 +283,9 @@ def stream_headline(args):
                                "phase_s": {k: round(v, 3) for k, v in c.host_s.items()}},
                "not_converged": c.not_converged, "max_rel_residual": c.max_rel_residual,
                "iters_median": int(np.median([r.iters for r in c.results])),
-               "mixed_requests": int(sum(1 for r in c.results if r.outer_steps > 0))}
+               "mixed_requests": int(sum(1 for r in c.results
+                                         if r.outer_steps > 0 and r.iters > 0)),
+               "dtype": _dtype([r.iters for r in c.results], [r.outer_steps for r in c.results])}
         if c.iteration_timing and c.iteration_timing["iters"] > 0:
             out["closed_loop"]["iteration_timing"] = c.iteration_timing
         if prec in poisson:
@@ -285,9 +308,7 @@ def stream_headline(args):
         "ms_per_step": 1000.0 * c.wall_s / n,
         "p50_ms": q.p50_ms,
         "p99_ms": q.p99_ms,
-        "dtype": {"auto": "f64 (direct), f32 inner PCG where PCG solves above the size crossover",
-                  "fp64": "f64",
-                  "mixed": "f32 inner PCG / f64 flexible CG"}[head],
+        "dtype": leg(head)["dtype"],
         "config": {
             "workload": (f"served stream: {n} forward+adjoint requests (grid-shells n~U{{8..60}}, "
                          f"shells m~U{{10..120}}, per-request seeds 10^6+i), compliance, "
@@ -369,7 +390,9 @@ def problem_run(mesh, opts, steps, warmup, objective="compliance", with_grad=Tru
                       "fused single-reduction" if st["solver"] == sso.SOLVER_FUSED else
                       "standard",
             "n_blocks": n_blocks, "n_nodes": mesh.n_nodes,
-            "iteration": {"kernels": "k_cg1_iter1" if st["solver"] == sso.SOLVER_FUSED else
+            "dtype": _dtype(rec["iters"], rec["outer"]),
+            "iteration": None if st["solver"] == sso.SOLVER_AUTO else
+                         {"kernels": "k_cg1_iter1" if st["solver"] == sso.SOLVER_FUSED else
                           "k_spmv_dir_single<sym> + k_update_single" if st["sym_products"] else
                           "k_spmv_dir_single + k_update_single", "bytes": st["spmv_bytes"],
                           "avg_us": it_us, "samples": int(sum(rec["it_n"]))},
@@ -397,6 +420,8 @@ def algorithmic_iteration_bytes(n_nodes, n_blocks, precision, symmetric=False):
 
 def roofline_of(run, workload, precision, ceilings=None):
     it = run["iteration"]
+    if it is None:                 # solved directly: no iteration to time
+        return None
     sym_read = None
     if it["kernels"].startswith("k_spmv_dir"):
         # the unit of work is one PCG iteration on this K, counted by the scope table (all of K
@@ -452,9 +477,9 @@ def _public(run):
 
 
 def large_leg(args):
-    """The 300 x 300 shell at rtol 1e-10: FP64 (AUTO's choice at this size and tolerance), the
-    standard PCG recurrences beside it (whose iteration gives the roofline) and mixed precision
-    with AUTO's inner cap of 30 iterations, with the mixed result's error against the FP64 one."""
+    """The 300 x 300 shell at rtol 1e-10: the automatic choice (direct, FP64), the standard PCG
+    recurrences beside it (whose iteration gives the roofline) and, by the same recurrences, mixed
+    precision with inner solves of at most 30 iterations, its error against the first."""
     import paper_2407_20026_amd as sso
     mesh = meshgen.shell_300()
     out = {}
@@ -462,11 +487,12 @@ def large_leg(args):
     for prec in ("fp64", "fp64_pcg", "mixed"):
         opts = sso.Options(rtol=1e-10, max_it=400000, profile_every=args.profile_every,
                            precision=sso.PREC_MIXED if prec == "mixed" else sso.PREC_FP64,
-                           solver=sso.SOLVER_STANDARD if prec == "fp64_pcg" else sso.SOLVER_AUTO,
+                           solver=sso.SOLVER_AUTO if prec == "fp64" else sso.SOLVER_STANDARD,
                            refine_steps=20000, inner_max_it=30 if prec == "mixed" else 0)
         runs[prec] = problem_run(mesh, opts, steps=2, warmup=1)
-        log(f"300x300 shell {prec}: {runs[prec]['ms_per_step']:.1f} ms per forward + adjoint, "
-            f"iteration {runs[prec]['iteration']['avg_us']:.2f} us")
+        it = runs[prec]["iteration"]
+        log(f"300x300 shell {prec}: {runs[prec]['ms_per_step']:.1f} ms per forward + adjoint"
+            + (f", iteration {it['avg_us']:.2f} us" if it else ""))
         out[prec] = _public(runs[prec])
     u64, umx = runs["fp64"]["_u"], runs["mixed"]["_u"]
     g64, gmx = runs["fp64"]["_g"], runs["mixed"]["_g"]
@@ -477,11 +503,11 @@ def large_leg(args):
                                "dg_dxyz_rel_inf": rel_inf(gmx["dg_dxyz"], g64["dg_dxyz"]),
                                "dg_dt_rel_inf": rel_inf(gmx["dg_dt"], g64["dg_dt"])}
     out["workload"] = "300x300 continuous shell, 543,606 DOF, compliance, rtol 1e-10, seed 2"
-    out["mixed"]["precision"] = "mixed (inner solves capped at 30, as AUTO runs it)"
-    out["auto_precision"] = "fp64 (K of 234 MB, below the 256 MiB at which AUTO takes mixed " \
-                            "precision for rtol 1e-9 or tighter)"
-    if out["mixed"].get("outer_steps", 0) == 0:
-        raise RuntimeError("mixed precision ran no outer steps on the 300 x 300 shell")
+    out["mixed"]["precision"] = "mixed (standard recurrences, inner solves of at most 30)"
+    out["auto_precision"] = "fp64 (direct; by PCG too at this size and target: K of 234 MB is " \
+                            "below the 256 MiB at which AUTO takes FP32 inner solves)"
+    if out["mixed"]["outer_steps"] == 0 or out["mixed"]["pcg_iters"] == 0:
+        raise RuntimeError("mixed precision ran no FP32 inner solves on the 300 x 300 shell")
     return out, runs["fp64_pcg"]
 
 
@@ -696,16 +722,14 @@ def main():
         desc, gen = WORKLOADS[args.workload]
         mesh = gen()
         prec = getattr(sso, PRECISIONS[args.precision])
-        solver = {"auto": sso.SOLVER_AUTO, "standard": sso.SOLVER_STANDARD,
-                  "fused": sso.SOLVER_FUSED}[args.solver]
         opts = sso.Options(precision=prec, rtol=args.rtol, max_it=400000,
-                           profile_every=args.profile_every, solver=solver,
+                           profile_every=args.profile_every,
+                           solver=_solver(sso, args.precision, args),
                            refine_steps=args.refine_steps, inner_max_it=args.inner_max_it)
         run = problem_run(mesh, opts, args.steps, args.warmup, args.objective)
         out.update(value=run["solves_per_s"], dof_per_s=run["dof_per_s"],
                    ms_per_step=run["ms_per_step"], p50_ms=run["p50_ms"], p99_ms=run["p99_ms"],
-                   dtype={"fp64": "f64", "mixed": "f32 inner PCG / f64 flexible CG",
-                          "auto": "f64 (direct), f32 inner PCG where PCG solves above the size crossover"}[args.precision],
+                   dtype=run["dtype"],
                    config={"workload": desc, "n_dof": mesh.n_dof, "objective": args.objective,
                            "rtol": args.rtol, "precision": args.precision,
                            **{k: v for k, v in _public(run).items()
@@ -744,8 +768,12 @@ def main():
         out["shell60"]["roofline"] = roofline_of(run60, "shell60", "fp64", ceilings)
         out["shell60"]["roofline"]["note"] = ("9.4 MB of K: resident in the 256 MB Infinity "
                                               "Cache, not an HBM figure")
-    if roof_of is not None:
-        out["roofline"] = roofline_of(*roof_of, ceilings)
+    roof = roofline_of(*roof_of, ceilings) if roof_of is not None else None
+    if roof is not None:
+        out["roofline"] = roof
+        if args.workload == "stream":
+            roof["note"] = ("the PCG iteration of a named solver; the headline's direct solves do "
+                            "not run it")
     if run500 is not None:
         out["shell500_roofline"] = roofline_of(run500, "shell500", "fp64", ceilings)
         out["shell500_roofline"]["note"] = (
