@@ -90,11 +90,15 @@ enum { SSO_PREC_FP64 = 0, SSO_PREC_MIXED = 1, SSO_PREC_AUTO = 2 };
  * of K's size).  AUTO solves directly
  * (multifrontal elimination in FP64 in a nested dissection order, refined on the true residual
  * until rtol is met; no PCG iterations), single and begun solves alike, where the solver's arrays
- * stay within what a surface structure fills, some 2 KB per node and doubling of the node count.
- * Measured against the recurrences named below, one design step: 11 x 11 grid-shell 0.51 against
- * 3.2 ms, 60 x 60 shell 1.6 against 14 ms, 300 x 300 shell 19 against 480 ms; 16 served requests
- * of 8 to 60 a side 16 against 100 ms.  A structure that fills more, a K that is not positive
- * definite to working precision, or a target below what refinement reaches runs PCG:
+ * stay within what an open surface structure fills, some 2 KB per node and doubling of the node
+ * count (288 (log2(n + 1) + 1) (1.2 n + 2.3 n_beams + 6.3 n_quads) bytes and 1 MiB: closed surfaces
+ * lie on either side, members joined in space above).
+ * Measured against the recurrences named below, one design step: 11 x 11 grid-shell 0.39 against
+ * 3.2 ms, 60 x 60 shell 1.1 against 14 ms, 300 x 300 shell 10.9 against 480 ms; 16 served requests
+ * of 8 to 60 a side 15 against 100 ms.  precision, max_it, refine_steps, inner_rtol, inner_max_it
+ * and profile_every have no effect on a direct solve.  A target below what refinement reaches is
+ * left to corrections by PCG (up to max_it iterations); a K that is not positive definite to
+ * working precision runs the STANDARD recurrences from u = 0.  Where the arrays would take more:
  * sso_solve takes WG for FP64 problems resident in one workgroup's LDS
  * (at most 144 nodes; measured 3.07 against 4.39 ms on the 121-node grid-shell), FUSED up to
  * 8,192 nodes (latency-bound sizes; 13.4 against 20.2 ms on a 60 x 60 shell, equal on 90 x 90,
@@ -140,10 +144,12 @@ typedef struct {
                                  the updates of u stay FP64                                  */
   double rtol;                /* stop when ||f - K u||_2 <= rtol ||f||_2 (recursive residual;
                                  the reported residual is recomputed)                       */
-  int32_t max_it;             /* PCG iteration limit per solve                               */
-  int32_t refine_steps;       /* mixed precision: maximum outer (FP64) steps                 */
+  int32_t max_it;             /* PCG iteration limit per solve (no limit to a direct solve,
+                                 which takes seven substitutions at most)                    */
+  int32_t refine_steps;       /* mixed precision by PCG: maximum outer (FP64) steps          */
   int32_t profile_every;      /* 0 = off; n > 0: time every n-th PCG iteration with HIP
-                                 events on the problem's stream (stats.spmv_us)              */
+                                 events on the problem's stream (stats.spmv_us; a direct
+                                 solve has none)                                             */
   double inner_rtol;          /* mixed precision: relative tolerance of each FP32 inner PCG
                                  solve (0 = 1e-5)                                           */
   int32_t solver;             /* SSO_SOLVER_*: PCG recurrences (also of the FP32 inner solves) */
@@ -158,7 +164,7 @@ typedef struct {
                                  sums of K u in double-double (compensated) arithmetic       */
   double t_elem_us;           /* element stiffness + loads                                   */
   double t_asm_us;            /* assembly + masking + block-Jacobi                           */
-  double t_solve_us;          /* PCG                                                         */
+  double t_solve_us;          /* PCG, or factorisation and substitutions                     */
   double t_adj_us;            /* adjoint solve + element contraction + gather (sso_adjoint)  */
   double bytes_moved;         /* algorithmic HBM bytes of the PCG iterations                 */
   double spmv_us;             /* mean duration of one PCG iteration, from samples of 8
@@ -242,8 +248,9 @@ int sso_solve(sso_problem* p, double* u_out, sso_stats* stats);
  * picks STANDARD here: the faster form when many problems share the launches); sso_batch_iterate then advances many begun
  * problems together (mixed precision: including the FP64 outer steps between FP32 inner
  * solves); sso_solve_end finishes one (FP64 correction of the true residual, u_out as in
- * sso_solve, stats) once its iteration has stopped.  With the same precision and recurrence,
- * results are bitwise the same as sso_solve's. */
+ * sso_solve, stats) once its iteration has stopped; one that no launch took ends with u = 0 on the
+ * free DOFs and SSO_ENOTCONV, and its adjoints are solved by PCG.  With the same precision and
+ * recurrence, results are bitwise the same as sso_solve's. */
 int sso_solve_begin(sso_problem* p);
 int sso_solve_end(sso_problem* p, double* u_out, sso_stats* stats);
 /* *ready (host) = 0 while the next multi-problem launch of the begun problem would have to wait for

@@ -135,11 +135,13 @@ namespace {
 
 constexpr int MAX_DEVICES = 64;
 
-// Most device memory that the direct solver's numeric arrays may take: what the fill of a surface
-// structure (grid-shell or shell of any outline) or of a chain needs, which grows as n log n.  A
-// structure that fills more (members joined in space; a solid lattice of 20 x 20 x 20 nodes takes
-// three times this) also costs more operations than PCG's few hundred iterations there, and PCG
-// keeps it.  The serving loops' admission bounds a request's memory by the same formula.
+// Most device memory that the direct solver's numeric arrays may take: what the fill of an open
+// surface structure (grid-shell or shell of any outline) or of a chain needs, which grows as n log
+// n.  Members joined in space fill more (a solid lattice of 20 x 20 x 20 nodes three times this) and
+// also cost more operations than PCG's few hundred iterations there; PCG keeps them.  It is a bound
+// on memory, not on time: closed surfaces lie close to it on either side (a tube of 20 x 20 quads
+// takes 9.6 MB against 9.5 and a torus of 40 x 40 42.9 against 41.3, tubes of 40 and 100 a side are
+// taken).  The serving loops' admission bounds a request's memory by the same formula.
 double direct_max_bytes(const Mesh& m) {
   const double n = m.n_nodes;
   return 288.0 * (std::log2(n + 1.0) + 1.0) * (1.2 * n + 2.3 * m.n_beams + 6.3 * m.n_quads) +

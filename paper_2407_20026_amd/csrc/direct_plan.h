@@ -138,15 +138,6 @@ struct DirectPlan {
     return fact_len + work_len + again_len + w_len + u_len + v_len + 12 * (int64_t)n_nodes;
   }
   int levels() const { return (int)level_off.size(); }
-  // Keeps what the launches need once the other tables are on the device.
-  void drop_tables() {
-    fronts = {};
-    nodes = {};
-    maps = {};
-    entries = {};
-    tile_end = {};
-    items = {};
-  }
 };
 
 // Builds the plan for a block pattern (brow_ptr [n + 1], bcol, columns of a row ascending, the
