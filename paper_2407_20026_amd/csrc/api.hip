@@ -399,6 +399,24 @@ void start_plan(SharedPattern* sh, const Mesh& m) {
   }
 }
 
+// Enqueues the copy of the pattern to the host for a plan; left empty where host memory is short.
+int fetch_pattern(sso_problem* p) {
+  SharedPattern* sh = p->shared;
+  try {
+    sh->brow.resize(p->m.n_nodes + 1);
+    sh->bcol.resize(p->pat.n_blocks);
+  } catch (...) {
+    sh->brow = {};
+    sh->bcol = {};
+    return SSO_OK;
+  }
+  TRY_HIP(hipMemcpyAsync(sh->brow.data(), p->pat.brow_ptr, sizeof(int32_t) * sh->brow.size(),
+                         hipMemcpyDeviceToHost, p->s));
+  TRY_HIP(hipMemcpyAsync(sh->bcol.data(), p->pat.bcol, sizeof(int32_t) * sh->bcol.size(),
+                         hipMemcpyDeviceToHost, p->s));
+  return SSO_OK;
+}
+
 // scratch: buffers that only the creation uses, idle once it has synchronised the stream.
 int create_impl(const sso_mesh* mesh, const sso_options* opts, hipStream_t stream,
                 sso_problem* p, const sso_problem* like, Arena& scratch) {
@@ -482,17 +500,8 @@ int create_impl(const sso_mesh* mesh, const sso_options* opts, hipStream_t strea
     p->shared->pat = p->pat;
     if (p->opt.solver == SSO_SOLVER_AUTO) {
       // the pattern for the direct solver's plan (its build starts after the synchronisation below)
-      SharedPattern* sh = p->shared;
-      try {
-        sh->brow.resize(nn + 1);
-        sh->bcol.resize(p->pat.n_blocks);
-      } catch (...) {
-        return SSO_ENOMEM;
-      }
-      TRY_HIP(hipMemcpyAsync(sh->brow.data(), p->pat.brow_ptr, sizeof(int32_t) * sh->brow.size(),
-                             hipMemcpyDeviceToHost, s));
-      TRY_HIP(hipMemcpyAsync(sh->bcol.data(), p->pat.bcol, sizeof(int32_t) * sh->bcol.size(),
-                             hipMemcpyDeviceToHost, s));
+      const int st = fetch_pattern(p);
+      if (st != SSO_OK) return st;
     }
     if (debug_mode()) {
       const int st = debug_check_pattern(p);
@@ -515,7 +524,7 @@ int create_impl(const sso_mesh* mesh, const sso_options* opts, hipStream_t strea
   if (like) TRY_HIP(hipMemcpyAsync(p->h_err, p->d_err, sizeof(unsigned), hipMemcpyDeviceToHost, s));
   TRY_HIP(hipStreamSynchronize(s));
   if (like && *p->h_err) return SSO_EINVAL;
-  if (!like && p->opt.solver == SSO_SOLVER_AUTO) start_plan(p->shared, m);
+  if (!like && !p->shared->brow.empty()) start_plan(p->shared, m);
   return SSO_OK;
 }
 
@@ -647,18 +656,10 @@ int direct_tables(sso_problem* p, bool* ready) {
     if (sh->builder.joinable()) {
       sh->builder.join();
     } else {
-      try {
-        sh->brow.resize(p->m.n_nodes + 1);
-        sh->bcol.resize(p->pat.n_blocks);
-      } catch (...) {
-        return SSO_ENOMEM;
-      }
-      TRY_HIP(hipMemcpyAsync(sh->brow.data(), p->pat.brow_ptr, sizeof(int32_t) * sh->brow.size(),
-                             hipMemcpyDeviceToHost, s));
-      TRY_HIP(hipMemcpyAsync(sh->bcol.data(), p->pat.bcol, sizeof(int32_t) * sh->bcol.size(),
-                             hipMemcpyDeviceToHost, s));
+      const int st = fetch_pattern(p);
+      if (st != SSO_OK) return st;
       TRY_HIP(hipStreamSynchronize(s));
-      make_plan(sh, direct_max_bytes(p->m));
+      if (!sh->brow.empty()) make_plan(sh, direct_max_bytes(p->m));
     }
     if (sh->built && debug_mode()) {
       char msg[256];

@@ -7,7 +7,21 @@
 #include "hipsso.h"
 #include "sso_internal.h"
 
+#include <new>
+
 using namespace sso;
+
+// Host memory that may run short: requests of at least this many bytes are refused (0: none).  The
+// library's own go this way too.
+static std::atomic<size_t> refuse_from{0};
+void* operator new(size_t n) {
+  const size_t from = refuse_from;
+  if (from && n >= from) throw std::bad_alloc();
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 static int failures = 0;
 #define CHECK(c)                                                       \
@@ -443,6 +457,37 @@ static void ended_on_another_device() {
   hip.device = 0;
 }
 
+// Host memory that is too short for the elimination's plan leaves the problem to PCG.
+static void no_host_memory_for_a_plan() {
+  for (bool late : {false, true})        // the solver named at first, so that the solve plans
+    for (int begun : {0, 1}) {
+      begin_check();
+      Structure s(60000);
+      sso_options o = options(late ? SSO_SOLVER_STANDARD : SSO_SOLVER_AUTO);
+      CHECK(sso_pool_trim(0, 0) == SSO_OK);
+      refuse_from = 200000;              // the pattern's row pointers are 240 kB
+      sso_problem* p = nullptr;
+      CHECK(sso_problem_create(&s.m, &o, nullptr, &p) == SSO_OK && p);
+      o.solver = SSO_SOLVER_AUTO;
+      CHECK(sso_set_options(p, &o) == SSO_OK);
+      sso_stats st{};
+      if (begun) {
+        sso_batch* b = nullptr;
+        int32_t done = 0;
+        CHECK(sso_solve_begin(p) == SSO_OK);
+        CHECK(sso_batch_create(nullptr, &b) == SSO_OK);
+        CHECK(sso_batch_iterate(b, &p, 1, 8, &done) == SSO_OK && done);
+        sso_batch_destroy(b);
+        CHECK(sso_solve_end(p, s.u, &st) == SSO_OK);
+      } else {
+        CHECK(sso_solve(p, s.u, &st) == SSO_OK);
+      }
+      CHECK(st.solver == SSO_SOLVER_STANDARD && launches("k_front_") == 0);
+      refuse_from = 0;
+      sso_problem_destroy(p);
+    }
+}
+
 int main(int argc, char** argv) {
   fake::state().kernel = kernel;
   const std::map<std::string, void (*)()> checks = {
@@ -454,6 +499,7 @@ int main(int argc, char** argv) {
       {"a_call_with_several", a_call_with_several},
       {"allocations_that_fail", allocations_that_fail},
       {"launches_that_fail", launches_that_fail},
+      {"no_host_memory_for_a_plan", no_host_memory_for_a_plan},
   };
   for (const auto& c : checks)
     if (argc < 2 || c.first == argv[1]) c.second();
