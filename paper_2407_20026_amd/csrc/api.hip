@@ -737,6 +737,13 @@ int direct_attach(sso_problem* p) {
     const int64_t n = 6 * (int64_t)p->m.n_nodes;
     DirectArgs a = p->shared->tables;
     TRY_HIP(hipStreamWaitEvent(p->s, p->shared->uploaded, 0));
+    // An eighth of the device's memory stays for what comes later (a problem holds three to five times
+    // as much with these arrays as without: 112 and 36 MB for a 60 x 60 shell); one that would take of
+    // it runs PCG.  Looking costs 4 us.
+    size_t left = 0, total = 0;
+    const OnDevice here(p->device);
+    TRY_HIP(memory_left(p->device, &left, &total));
+    if (8.0 * (double)pl.values() + (double)(total / 8) > (double)left) return SSO_OK;
     double* d = nullptr;
     const hipError_t e = dev_alloc(&d, pl.values() + 2, p->s);   // one buffer, cut below
     if (e == hipErrorOutOfMemory) {
@@ -1291,6 +1298,27 @@ static ChunkCache* cache_of(hipStream_t s) {
   if (hipStreamGetDevice(s, &device) != hipSuccess || device < 0 || device >= MAX_DEVICES)
     return nullptr;
   return &chunk_caches[device];
+}
+
+hipError_t memory_left(int device, size_t* left, size_t* total) {
+  hipError_t e = hipMemGetInfo(left, total);
+  if (e != hipSuccess || device < 0 || device >= MAX_DEVICES) return e;
+  hipMemPool_t pool = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(pool_mutex);
+    pool = pools[device];
+  }
+  if (pool) {
+    uint64_t reserved = 0, used = 0;
+    e = hipMemPoolGetAttribute(pool, hipMemPoolAttrReservedMemCurrent, &reserved);
+    if (e == hipSuccess) e = hipMemPoolGetAttribute(pool, hipMemPoolAttrUsedMemCurrent, &used);
+    if (e != hipSuccess) return e;
+    if (reserved > used) *left += reserved - used;
+  }
+  ChunkCache& c = chunk_caches[device];
+  std::lock_guard<std::mutex> lock(c.mu);
+  *left += c.bytes;
+  return hipSuccess;
 }
 
 static void cache_flush(ChunkCache& c, hipStream_t s) {

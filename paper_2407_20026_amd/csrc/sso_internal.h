@@ -198,6 +198,8 @@ hipError_t pool_alloc(void** p, size_t bytes, hipStream_t s);
 
 // Carves `bytes` (rounded up to ARENA_ALIGN) on stream s; *held = bytes newly taken from the pool.
 hipError_t arena_alloc(Arena& a, size_t bytes, hipStream_t s, void** out, int64_t* held);
+// The device's memory, and what of it is free or idle in the library's pool and cache.
+hipError_t memory_left(int device, size_t* left, size_t* total);
 bool arena_owns(const Arena& a, const void* p);
 void arena_free(Arena& a, hipStream_t s);   // every chunk, stream-ordered on s
 // Every chunk to the device's cache of idle chunks: no work that uses them may be pending.

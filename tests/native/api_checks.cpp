@@ -488,6 +488,40 @@ static void no_host_memory_for_a_plan() {
     }
 }
 
+// The direct solver's arrays leave an eighth of the device's memory to those who come later: problems
+// that are created and kept go on by PCG from there, and their own later calls find memory.
+static void memory_left_for_others() {
+  begin_check();
+  CHECK(sso_pool_trim(0, 0) == SSO_OK);
+  Structure s(20000);
+  size_t left = 0, total = 0;
+  fake::state().limit[0] = (size_t)640 << 20;
+  std::vector<sso_problem*> ps;
+  int direct = 0;
+  for (int k = 0; k < 12; ++k) {
+    sso_stats st{};
+    sso_problem* p = create(s, options());
+    if (!p) break;
+    ps.push_back(p);
+    CHECK(sso_solve(p, s.u, &st) == SSO_OK);
+    direct += st.solver == SSO_SOLVER_AUTO;
+    hipMemGetInfo(&left, &total);
+    if (st.solver == SSO_SOLVER_AUTO) CHECK(left >= total / 8);
+    double out[3];
+    CHECK(sso_size_objective(p, 1.0, 1.0, 0.1, out, s.grad, nullptr, nullptr) == SSO_OK);
+  }
+  CHECK(ps.size() == 12 && direct >= 1 && direct < 12);
+  for (sso_problem* p : ps) sso_problem_destroy(p);
+  // memory that ended problems left counts as free
+  sso_stats st{};
+  sso_problem* p = nullptr;
+  for (const auto& m : fake::state().device_memory) std::memset(m.first, 0, m.second.bytes);
+  sso_options o = options();
+  CHECK(sso_problem_create(&s.m, &o, nullptr, &p) == SSO_OK);
+  CHECK(sso_solve(p, s.u, &st) == SSO_OK && st.solver == SSO_SOLVER_AUTO);
+  sso_problem_destroy(p);
+}
+
 int main(int argc, char** argv) {
   fake::state().kernel = kernel;
   const std::map<std::string, void (*)()> checks = {
@@ -499,6 +533,7 @@ int main(int argc, char** argv) {
       {"a_call_with_several", a_call_with_several},
       {"allocations_that_fail", allocations_that_fail},
       {"launches_that_fail", launches_that_fail},
+      {"memory_left_for_others", memory_left_for_others},
       {"no_host_memory_for_a_plan", no_host_memory_for_a_plan},
   };
   for (const auto& c : checks)

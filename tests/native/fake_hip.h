@@ -224,6 +224,20 @@ hipError_t hipMallocFromPoolAsync(void** p, size_t bytes, hipMemPool_t pool, hip
   ++st.allocations[device];
   return hipSuccess;
 }
+hipError_t hipMemGetInfo(size_t* left, size_t* total) {
+  auto& st = fake::state();
+  std::lock_guard<std::recursive_mutex> lock(st.mu);
+  size_t held = 0;
+  for (const auto& b : st.device_memory)
+    if (b.second.device == st.device) held += b.second.bytes;
+  *total = st.limit.count(st.device) ? st.limit[st.device] : (size_t)288 << 30;
+  *left = *total - held;
+  return hipSuccess;
+}
+hipError_t hipMemPoolGetAttribute(hipMemPool_t, hipMemPoolAttr, void* v) {   // nothing idle is kept
+  *static_cast<uint64_t*>(v) = 0;
+  return hipSuccess;
+}
 hipError_t hipFreeAsync(void* p, hipStream_t) {
   auto& st = fake::state();
   std::lock_guard<std::recursive_mutex> lock(st.mu);

@@ -33,7 +33,8 @@ def program():
 @pytest.mark.parametrize("check", [
     "ended_before_a_launch", "mixed_recurrences_named_anew", "one_call_ends_a_solve",
     "iterations_are_steps", "a_call_with_several", "allocations_that_fail",
-    "launches_that_fail", "ended_on_another_device", "no_host_memory_for_a_plan"])
+    "launches_that_fail", "ended_on_another_device", "no_host_memory_for_a_plan",
+    "memory_left_for_others"])
 def test_host_code(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=120)
     print(r.stdout[-4000:], r.stderr[-2000:])
