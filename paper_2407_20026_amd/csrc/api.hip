@@ -787,9 +787,12 @@ DirectNext direct_next(sso_problem* p, double rr, double bb, unsigned flag) {
   p->factored = true;
   // A first solution that meets the target by less than FIRST takes one more step, after which u is
   // accurate to the last bits.  Its residual lies in smooth modes, where an iteration's is in rough
-  // ones: over 130 grid-shells of 8 to 60 nodes a side, shells of 10 to 100 and arches, u was up to 0.9
-  // times as far off as PCG's at the same target with a first residual of up to a quarter of it, and
-  // up to 36 times (an 11 x 11 grid-shell) between 0.3 and a half.
+  // ones, and with a first residual between 0.3 and a half of the target u was up to 36 times as far
+  // off as PCG's at the same target (an 11 x 11 grid-shell).  With the quarter, over 300 structures,
+  // u and the gradient are closer than PCG's on shells and arches (0.03 to 0.9 times) and about as
+  // close on grid-shells (up to 1.6 times in u, 1.8 in a linear objective's gradient, 3.5 once).
+  // 0.03 would bring all below 0.25 and take 15 to 35 % longer on arches and small shells, which do
+  // not need it (arch 444 -> 607 us, 16 x 16 shell 445 -> 565).
   constexpr double FIRST = 0.25;
   if (rn <= (step == 1 ? FIRST : 1.0) * p->opt.rtol * bn) return DIRECT_MET;
   if (step == MAX_STEPS || (prev >= 0.0 && rn > 0.5 * prev)) return DIRECT_STUCK;
